@@ -65,11 +65,13 @@ void launch_gather_vt(const T* vt, int64_t row_stride, int64_t col0, int64_t S, 
 void launch_gemm_f32(const float* A, int64_t lda, const float* W, int64_t ldw, int64_t M, int64_t N,
                      int64_t K, int epi, const EpiArgs& e, hipStream_t st);
 // ---- attn_f32.hip ----------------------------------------------------------------------------
-// q [h][*][d] rows q_row0.., k [h][*][d] rows k_row0.. (L rows), vt [h][d][*] cols k_row0.. ;
-// out[s, head*d + c], row stride ldo
+// q [h][*][d], k [h][*][d] rows k_row0.. (L rows), vt [h][d][*] cols k_row0.. ; out[s, head*d + c], row stride ldo.
+// k rows and vt columns must be readable from k_row0 & ~3 up to (k_row0 & ~3) + roundup(L + 3, 32); vt, its rows and ldo
+// in 16-byte steps.  scratch: scratch_floats floats for the partial results of work that is cut into key ranges
+// (0: never cut).
 void launch_attn_f32(const float* q, int64_t q_head_stride, const float* k, int64_t k_head_stride,
                      int64_t k_row0, const float* vt, int64_t vt_row_stride, int64_t S, int64_t L,
-                     int h, int d, float* out, int64_t ldo, hipStream_t st);
+                     int h, int d, float* out, int64_t ldo, float* scratch, size_t scratch_floats, hipStream_t st);
 
 // out[f, :] = pool[index[f], :], frame_bytes % 16 == 0, all pointers 16-byte aligned
 void launch_gather_frames(const void* pool, int pool_frames, int64_t frame_bytes, const int32_t* index,

@@ -78,7 +78,7 @@ struct dp_stage {
   float *tau, *e1, *e2, *e0, *mtab, *mod;
   float2 *rope_f, *rope_y, *rope_x; RopeTables rt;
   void* tap_attn; float *tap_xself, *tap_xcross;
-  float* attn_scratch;
+  float* attn_scratch; size_t attn_scratch_floats;   // partial results of attention over cut key ranges
   // DP_BF16 with dim % 256 == 0: the q/k/v and cross-q projections write per head from their GEMM epilogues
   // (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
   float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi; bool launch_ok = true;
@@ -202,7 +202,9 @@ static size_t carve(dp_stage* s, void* base) {
     m.tvt = cv.take(s->Ltpad * D * E);
   }
   const size_t zero_end = cv.off;      // everything up to here is zero-filled at init
-  s->attn_scratch = bf ? (float*)cv.take(attn_bf16_scratch_bytes(c.head_dim)) : nullptr;
+  // the fp32 path borrows the FFN's intermediate buffer, which nothing uses while attention runs
+  s->attn_scratch = bf ? (float*)cv.take(attn_bf16_scratch_bytes(c.head_dim)) : (float*)s->mid;
+  s->attn_scratch_floats = bf ? attn_bf16_scratch_bytes(c.head_dim) / 4 : (size_t)(s->Spad * F);
   if (bf) {
     for (int64_t l = 0; l < L; ++l) {
       LayerMem& m = s->lm[(size_t)l];
@@ -246,9 +248,10 @@ template <> struct Path<float> {
     return true;
   }
   static void attn(const void* q, int64_t qhs, const void* k, int64_t khs, int64_t row0, const void* vt,
-                   int64_t vrs, int64_t S, int64_t L, int h, int d, void* out, int64_t ldo, float* /*scratch*/,
-                   const AttnQNorm* /*qn*/, hipStream_t st) {
-    launch_attn_f32((const float*)q, qhs, (const float*)k, khs, row0, (const float*)vt, vrs, S, L, h, d, (float*)out, ldo, st);
+                   int64_t vrs, int64_t S, int64_t L, int h, int d, void* out, int64_t ldo, float* scratch,
+                   size_t scratch_floats, const AttnQNorm* /*qn*/, hipStream_t st) {
+    launch_attn_f32((const float*)q, qhs, (const float*)k, khs, row0, (const float*)vt, vrs, S, L, h, d, (float*)out, ldo,
+                    scratch, scratch_floats, st);
   }
 };
 template <> struct Path<bf16_t> {
@@ -259,7 +262,7 @@ template <> struct Path<bf16_t> {
   }
   static void attn(const void* q, int64_t qhs, const void* k, int64_t khs, int64_t row0, const void* vt,
                    int64_t vrs, int64_t S, int64_t L, int h, int d, void* out, int64_t ldo, float* scratch,
-                   const AttnQNorm* qn, hipStream_t st) {
+                   size_t /*scratch_floats: fixed, see attn_bf16_scratch_bytes*/, const AttnQNorm* qn, hipStream_t st) {
     launch_attn_bf16((const bf16_t*)q, qhs, (const bf16_t*)k, khs, row0, (const bf16_t*)vt, vrs, S, L, h, d, (bf16_t*)out, ldo, scratch, qn, st);
   }
 };
@@ -463,7 +466,7 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     }
     PROF(DP_PROF_SELF_ATTN,
          Path<T>::attn(s->qbuf, s->Spad * d, m.kbuf, kv_hs, key0, m.vtbuf, s->Lpad, S,
-                       s->cache_len + S, h, d, s->attn_o, D, s->attn_scratch, s->heads_epi ? &qn : nullptr, st));
+                       s->cache_len + S, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, s->heads_epi ? &qn : nullptr, st));
     if (s->tap_attn && l == c.n_layers - 1) launch_copy2d<T>((const T*)s->attn_o, 0, (T*)s->tap_attn, 0, 1, S * D, st);
     PROF(DP_PROF_OPROJ_GEMM, Path<T>::gemm(s->attn_o, D, w.wo, m.wo_t, S, D, D, EPI_RESID, epi_resid(s->xres, D, w.bo, g1), st));
     if (s->tap_xself && l == c.n_layers - 1) launch_copy2d<float>(s->xres, 0, s->tap_xself, 0, 1, S * D, st);
@@ -479,14 +482,14 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
       qn.np = ha.ssq_np;
       s->cross_np = ha.ssq_np;
       PROF(DP_PROF_CROSS_ATTN,
-           Path<T>::attn(s->qbuf, s->Spad * d, m.tkq, s->Ltpad * d, 0, m.tvt, s->Ltpad, S, c.text_len, h, d, s->attn_o, D, s->attn_scratch, &qn, st));
+           Path<T>::attn(s->qbuf, s->Spad * d, m.tkq, s->Ltpad * d, 0, m.tvt, s->Ltpad, S, c.text_len, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, &qn, st));
     } else {
       PROF(DP_PROF_CROSS_Q_GEMM, Path<T>::gemm(s->hbuf, D, w.cwq, m.cwq_t, S, D, D, EPI_STORE, epi_store(s->raw, D, w.cbq), st));
       PROF(DP_PROF_NORM_ROPE,
            const NormRopeJob<T> cq{0, m.cgq, Path<T>::q_scale(d), (T*)s->qbuf, s->Spad * d, 0, 0};
            launch_norm_rope<T>((const T*)s->raw, D, S, h, d, c.eps, &cq, 1, nullptr, 0, 1, 1, st));
       PROF(DP_PROF_CROSS_ATTN,
-           Path<T>::attn(s->qbuf, s->Spad * d, m.tk, s->Ltpad * d, 0, m.tvt, s->Ltpad, S, c.text_len, h, d, s->attn_o, D, s->attn_scratch, nullptr, st));
+           Path<T>::attn(s->qbuf, s->Spad * d, m.tk, s->Ltpad * d, 0, m.tvt, s->Ltpad, S, c.text_len, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, nullptr, st));
     }
     PROF(DP_PROF_CROSS_O_GEMM, Path<T>::gemm(s->attn_o, D, w.cwo, m.cwo_t, S, D, D, EPI_RESID, epi_resid(s->xres, D, w.cbo, nullptr), st));
     if (s->tap_xcross && l == c.n_layers - 1) launch_copy2d<float>(s->xres, 0, s->tap_xcross, 0, 1, S * D, st);
