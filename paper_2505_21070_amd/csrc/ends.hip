@@ -133,7 +133,7 @@ template <typename T>
 static void gemm(dp_ends* s, const void* A, int64_t lda, const void* W, const void* wt, int64_t M, int64_t N, int64_t K,
                  int epi, const EpiArgs& e, hipStream_t st) {
   if constexpr (sizeof(T) == 2) launch_gemm_bf16((const bf16_t*)A, lda, (const bf16_t*)wt, K, M, N, K, epi, e, st);
-  else launch_gemm_f32((const float*)A, lda, (const float*)W, N, M, N, K, epi, e, st);
+  else launch_gemm_f32((const float*)A, lda, GemmF32W{{(const float*)W}, {(const float*)e.bias}, 1}, N, M, N, K, epi, e, st);
   (void)s;
 }
 

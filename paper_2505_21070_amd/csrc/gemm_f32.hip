@@ -1,79 +1,209 @@
-// fp32 GEMM for the DP_F32 path: C = A[M,K] * W[K,N] with a fused epilogue.  Plain FMA arithmetic
-// (no matrix cores) so that results stay within fp32 rounding of the reference.
-// 64x64 tile per 256-thread block, 4x4 outputs per thread, K stepped by 16 through LDS, the next step's
-// operands prefetched into registers.
+// fp32 GEMM for the DP_F32 path: C = A[M,K] * W[K,N] with a fused epilogue, on the fp32 matrix instructions
+// (v_mfma_f32_32x32x2_f32: fp32 operands, fp32 accumulation, nothing rounded below fp32).
+//
+// Bound: the fp32 matrix rate, 64 cycles an MFMA, 157 TFLOP/s over the chip (the vector unit has half of that without
+// its packed forms, and lost more of it to LDS reads: 45 TFLOP/s).  An MFMA sums two k; a lane group lg of a wavefront
+// takes k = 8j + 4lg + t for the t-th of four MFMAs, so that the A operand of four is one 16-byte LDS read of a row and
+// the W operand one 4-byte read each.  k-tiles of 32 go through registers into one of two LDS buffers, the next tile's
+// loads in flight while this one is multiplied.  Rows of As are 36 floats and rows of Ws BN + 8 apart: 16 rows x 16 bytes
+// and the two lane groups' rows (4 apart) then fall on different banks.
+// 1560 x 1536 x 1536: 154 -> 88 us; 1560 x 8960 x 1536: 631 -> 391; 1560 x 1536 x 8960: 868 -> 462 (600 blocks: three on
+// some CUs, two on the others); q | k | v of 1560 x 1536: 492 in three launches -> 223 in one.
 #include "kernels.h"
 
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int64_t lda,
-                                                  const float* __restrict__ W, int64_t ldw, int64_t M,
-                                                  int64_t N, int64_t K, EpiArgs e) {
-  __shared__ float As[16][64 + 4];   // [k][m]
-  __shared__ float Ws[16][64 + 4];   // [k][n]
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;        // thread owns rows ty*4.., cols tx*4..
-  const int64_t m0 = (int64_t)blockIdx.x * 64, n0 = (int64_t)blockIdx.y * 64;   // rows on x: no 65535-block limit
-  float acc[4][4] = {};
-  // the next k-step's operands travel from global memory into registers while this one is multiplied
-  float ra[4], rw[4];
-  auto fetch = [&](int64_t k0) {
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// VEC: rows of A and W are read (and start) in 16-byte steps.  WGM x WGN wavefronts of (BM / WGM) x (BN / WGN) outputs.
+template <int BM, int BN, int WGM, int WGN, int EPI, bool VEC>
+__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int64_t lda, GemmF32W w, int64_t ldw,
+                                                  int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int tiles,
+                                                  EpiArgs e) {
+  static_assert(WGM * WGN == 4, "four wavefronts");
+  constexpr int BK = 32, AS = BK + 4, WS = BN + 8, PF = 2;
+  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
+  constexpr int IA = BM * BK / 4 / 256, IW = BK * BN / 4 / 256;    // 16-byte pieces per thread and tile
+  __shared__ __align__(16) float As[2][BM * AS];
+  __shared__ __align__(16) float Ws[2][BK * WS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lg = lane >> 5;
+  const int wm = wave / WGN, wn = wave % WGN;
+  // each XCD takes a contiguous run of tiles, walked in bands of 8 tile rows so that the run is near square and its
+  // panels of A and W are shared in that XCD's L2
+  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (pid >= tiles) return;
+  const int tn_all = tiles_n * w.n;                                // w.n matrices side by side
+  const int band = pid / (8 * tn_all), in_band = pid % (8 * tn_all);
+  const int band_rows = tiles_m - band * 8 < 8 ? tiles_m - band * 8 : 8;
+  const int tn = in_band / band_rows, sec = tn / tiles_n;
+  const int64_t m0 = (int64_t)(band * 8 + in_band % band_rows) * BM, n0 = (int64_t)(tn % tiles_n) * BN;
+  const float* __restrict__ W = w.w[sec];
+  const float* __restrict__ bias = w.bias[sec];
+
+  float4 ra[PF][IA], rw[PF][IW];
+  // VEC: rows and columns beyond M and N read the last ones (what they produce is not stored), so only a k-tile that
+  // reaches beyond K needs a look at its elements
+  const float *pa[IA], *pw[IW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {                // A tile: 64 rows x 16 k; W tile: 16 k x 64 columns
-      const int idx = tid + i * 256;             // 0..1023
-      const int64_t m = m0 + (idx >> 4), ka = k0 + (idx & 15);
-      ra[i] = (m < M && ka < K) ? A[m * lda + ka] : 0.f;
-      const int64_t kw = k0 + (idx >> 6), n = n0 + (idx & 63);
-      rw[i] = (kw < K && n < N) ? W[kw * ldw + n] : 0.f;
+  for (int i = 0; i < IA; ++i) {
+    const int idx = tid + i * 256;
+    const int64_t m = m0 + idx / (BK / 4);
+    pa[i] = A + (m < M ? m : M - 1) * lda + idx % (BK / 4) * 4;
+  }
+#pragma unroll
+  for (int i = 0; i < IW; ++i) {
+    const int idx = tid + i * 256;
+    const int64_t n = n0 + idx % (BN / 4) * 4;
+    pw[i] = W + (int64_t)(idx / (BN / 4)) * ldw + (!VEC || n < N ? n : N - 4);
+  }
+  auto fetch = [&](int64_t k0, int z) __attribute__((always_inline)) {
+    if (VEC && k0 + BK <= K) {
+#pragma unroll
+      for (int i = 0; i < IA; ++i) ra[z][i] = *(const float4*)(pa[i] + k0);
+#pragma unroll
+      for (int i = 0; i < IW; ++i) rw[z][i] = *(const float4*)(pw[i] + k0 * ldw);
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int64_t k = k0 + (tid + i * 256) % (BK / 4) * 4;
+      ra[z][i].x = k < K ? pa[i][k0] : 0.f;
+      ra[z][i].y = k + 1 < K ? pa[i][k0 + 1] : 0.f;
+      ra[z][i].z = k + 2 < K ? pa[i][k0 + 2] : 0.f;
+      ra[z][i].w = k + 3 < K ? pa[i][k0 + 3] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < IW; ++i) {
+      const int idx = tid + i * 256;
+      const bool ok = k0 + idx / (BN / 4) < K;
+      const int64_t n = n0 + idx % (BN / 4) * 4;
+      const float* p = pw[i] + k0 * ldw;
+      rw[z][i].x = ok && (VEC || n < N) ? p[0] : 0.f;
+      rw[z][i].y = ok && (VEC || n + 1 < N) ? p[1] : 0.f;
+      rw[z][i].z = ok && (VEC || n + 2 < N) ? p[2] : 0.f;
+      rw[z][i].w = ok && (VEC || n + 3 < N) ? p[3] : 0.f;
     }
   };
-  fetch(0);
-  for (int64_t k0 = 0; k0 < K; k0 += 16) {
+  auto stash = [&](int b, int z) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < IA; ++i) {
       const int idx = tid + i * 256;
-      As[idx & 15][idx >> 4] = ra[i];
-      Ws[idx >> 6][idx & 63] = rw[i];
+      *(float4*)&As[b][idx / (BK / 4) * AS + idx % (BK / 4) * 4] = ra[z][i];
     }
-    __syncthreads();
-    if (k0 + 16 < K) fetch(k0 + 16);
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Ws[kk][tx * 4 + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    for (int i = 0; i < IW; ++i) {
+      const int idx = tid + i * 256;
+      *(float4*)&Ws[b][idx / (BN / 4) * WS + idx % (BN / 4) * 4] = rw[z][i];
     }
-    __syncthreads();
-  }
-  const float* bias = (const float*)e.bias;
+  };
+
+  f32x16 acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t m = m0 + ty * 4 + i;
-    if (m >= M) continue;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int64_t n = n0 + tx * 4 + j;
-      if (n >= N) continue;
-      float v = acc[i][j] + (bias ? bias[n] : 0.f);
-      if (EPI == EPI_GELU) v = gelu_tanh_f(v);
-      if (EPI == EPI_RESID) {
-        float* r = e.resid + m * e.ldr + n;
-        *r = *r + (e.gate ? e.gate[n] : 1.f) * v;
-      } else {
-        ((float*)e.out)[m * e.ldo + n] = v;
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  // k-tiles travel PF ahead of the one being multiplied: a tile's MFMAs take 1024 cycles of a SIMD, a load from beyond
+  // L2 several times that (one ahead: 488 us where two take 462 at 1560 x 1536 x 8960; three: 497)
+  const int KT = (int)((K + BK - 1) / BK);
+#pragma unroll
+  for (int z = 0; z < PF; ++z)
+    if (z < KT) fetch((int64_t)z * BK, z);
+  stash(0, 0);
+  if (PF < KT) fetch((int64_t)PF * BK, 0);
+  __syncthreads();
+  auto step = [&](int kt, int z) __attribute__((always_inline)) {
+    const int b = kt & 1;
+    // half a k-tile's operands are requested together, the second half's behind the first half's first MFMAs: left to
+    // itself the compiler reads each operand right in front of the MFMA that waits for it
+    float4 a[BK / 8][TM];
+    float bw[BK / 8][TN][4];
+    auto read = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[j][i] = *(const float4*)&As[b][(wm * TM * 32 + i * 32 + lr) * AS + j * 8 + lg * 4];
+#pragma unroll
+      for (int c = 0; c < TN; ++c)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) bw[j][c][t] = Ws[b][(j * 8 + lg * 4 + t) * WS + wn * TN * 32 + c * 32 + lr];
+    };
+    read(0);
+    read(1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < BK / 8; ++j) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int c = 0; c < TN; ++c) {
+            const float av = t == 0 ? a[j][i].x : t == 1 ? a[j][i].y : t == 2 ? a[j][i].z : a[j][i].w;
+            acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bw[j][c][t], acc[i][c], 0, 0, 0);
+          }
+      if (j + 2 < BK / 8) read(j + 2);
+      if (j == 0 && kt + 1 < KT) {                   // the next tile's registers are set (z + 1) % PF
+        stash(b ^ 1, (z + 1) % PF);
+        if (kt + 1 + PF < KT) fetch((int64_t)(kt + 1 + PF) * BK, (z + 1) % PF);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    __syncthreads();
+  };
+  for (int kt = 0; kt < KT; kt += PF) {
+#pragma unroll
+    for (int z = 0; z < PF; ++z)
+      if (kt + z < KT) step(kt + z, z);
+  }
+
+  // accumulator register r of lane group lg: row (r / 4) * 8 + lg * 4 + r % 4, column lr: 32 lanes write 128 bytes of a row
+#pragma unroll
+  for (int c = 0; c < TN; ++c) {
+    const int64_t n = n0 + wn * TN * 32 + c * 32 + lr;
+    if (n >= N) continue;
+    const float bv = bias ? bias[n] : 0.f, gv = EPI == EPI_RESID && e.gate ? e.gate[n] : 1.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t m = m0 + wm * TM * 32 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3);
+        if (m >= M) continue;
+        float v = acc[i][c][r] + bv;
+        if (EPI == EPI_GELU) v = gelu_tanh_f(v);
+        if (EPI == EPI_RESID) {
+          float* x = e.resid + m * e.ldr + n;
+          v = *x + gv * v;
+          *x = v;
+          if (e.out) ((float*)e.out)[m * e.ldo + n] = v;
+        } else {
+          ((float*)e.out)[m * e.ldo + (int64_t)sec * N + n] = v;
+        }
+      }
   }
 }
 
-void launch_gemm_f32(const float* A, int64_t lda, const float* W, int64_t ldw, int64_t M, int64_t N,
+template <int BM, int BN, int WGM, int WGN>
+static void launch_cfg(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                       int epi, const EpiArgs& e, bool vec, hipStream_t st) {
+  const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN), tiles = tm * tn * w.n;
+  const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
+#define GEMM_F32(E, V) k_gemm_f32<BM, BN, WGM, WGN, E, V><<<grid, 256, 0, st>>>(A, lda, w, ldw, M, N, K, tm, tn, tiles, e)
+  if (epi == EPI_STORE) { if (vec) GEMM_F32(EPI_STORE, true); else GEMM_F32(EPI_STORE, false); }
+  else if (epi == EPI_GELU) { if (vec) GEMM_F32(EPI_GELU, true); else GEMM_F32(EPI_GELU, false); }
+  else { if (vec) GEMM_F32(EPI_RESID, true); else GEMM_F32(EPI_RESID, false); }
+#undef GEMM_F32
+}
+
+void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw, int64_t M, int64_t N,
                      int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
   if (M <= 0 || N <= 0) return;
-  dim3 grid((unsigned)((M + 63) / 64), (unsigned)((N + 63) / 64));     // N <= 6 * 8192, so grid.y stays small
-  if (epi == EPI_STORE) k_gemm_f32<EPI_STORE><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, e);
-  else if (epi == EPI_GELU) k_gemm_f32<EPI_GELU><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, e);
-  else k_gemm_f32<EPI_RESID><<<grid, 256, 0, st>>>(A, lda, W, ldw, M, N, K, e);
+  bool vec = K % 4 == 0 && N % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)A & 15) == 0;
+  for (int i = 0; i < w.n; ++i) vec = vec && ((uintptr_t)w.w[i] & 15) == 0;
+  // 64 x 64 tiles, up to four blocks to a CU, unless 128 x 128 ones (two to a CU, half the operand bytes per flop) make at
+  // least two full rounds: 1560 x 8960 x 1536 (912 of them) 391 against 413 us, 1560 x 1536 x 8960 (156) 462 against 639;
+  // 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s where 64 x 64 tiles stay at 110
+  const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128) * w.n;
+  if (t128 >= 1024)
+    launch_cfg<128, 128, 2, 2>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+  else launch_cfg<64, 64, 2, 2>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
 }

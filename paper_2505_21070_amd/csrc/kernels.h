@@ -61,8 +61,11 @@ template <typename T>
 void launch_gather_vt(const T* vt, int64_t row_stride, int64_t col0, int64_t S, int h, int d,
                       float* dst, hipStream_t st);
 
-// ---- gemm_f32.hip : C = A[M,K] * W[K,N] (+ epilogue), all row-major, fp32 FMA ---------------
-void launch_gemm_f32(const float* A, int64_t lda, const float* W, int64_t ldw, int64_t M, int64_t N,
+// ---- gemm_f32.hip : C = A[M,K] * W[K,N] (+ epilogue), all row-major, fp32 MFMA ---------------
+// One launch multiplies by w.n matrices of equal shape; with EPI_STORE matrix i's result goes to columns [i * N, (i + 1) * N)
+// of e.out (the other epilogues take one).  The biases are w.bias (null: none); e.bias is not looked at.
+struct GemmF32W { const float* w[3]; const float* bias[3]; int n; };
+void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw, int64_t M, int64_t N,
                      int64_t K, int epi, const EpiArgs& e, hipStream_t st);
 // ---- attn_f32.hip ----------------------------------------------------------------------------
 // q [h][*][d], k [h][*][d] rows k_row0.. (L rows), vt [h][d][*] cols k_row0.. ; out[s, head*d + c], row stride ldo.

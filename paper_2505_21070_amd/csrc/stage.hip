@@ -244,7 +244,7 @@ template <> struct Path<float> {
   // y = x[M,K] * W[K,N] (+epilogue); `wt` unused
   static bool gemm(const void* A, int64_t lda, const void* W, const void* /*wt*/, int64_t M, int64_t N,
                    int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
-    launch_gemm_f32((const float*)A, lda, (const float*)W, N, M, N, K, epi, e, st);
+    launch_gemm_f32((const float*)A, lda, GemmF32W{{(const float*)W}, {(const float*)e.bias}, 1}, N, M, N, K, epi, e, st);
     return true;
   }
   static void attn(const void* q, int64_t qhs, const void* k, int64_t khs, int64_t row0, const void* vt,
@@ -453,10 +453,10 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
         PROF(DP_PROF_QKV_GEMM,
              Path<T>::gemm(s->hbuf, D, nullptr, m.wqkv_t, S, 3 * D, D, EPI_STORE, epi_store(s->raw, 3 * D, m.bqkv), st));
       } else {
+        const GemmF32W qkv{{(const float*)w.wq, (const float*)w.wk, (const float*)w.wv},
+                           {(const float*)w.bq, (const float*)w.bk, (const float*)w.bv}, 3};
         PROF(DP_PROF_QKV_GEMM,
-             Path<T>::gemm(s->hbuf, D, w.wq, nullptr, S, D, D, EPI_STORE, epi_store(s->raw, 3 * D, w.bq), st);
-             Path<T>::gemm(s->hbuf, D, w.wk, nullptr, S, D, D, EPI_STORE, epi_store((T*)s->raw + D, 3 * D, w.bk), st);
-             Path<T>::gemm(s->hbuf, D, w.wv, nullptr, S, D, D, EPI_STORE, epi_store((T*)s->raw + 2 * D, 3 * D, w.bv), st));
+             launch_gemm_f32((const float*)s->hbuf, D, qkv, D, S, D, D, EPI_STORE, epi_store(s->raw, 3 * D, nullptr), st));
       }
       PROF(DP_PROF_NORM_ROPE,
            const NormRopeJob<T> qk[2] = {{0, m.gq, Path<T>::q_scale(d), (T*)s->qbuf, s->Spad * d, 0, 1},
