@@ -28,10 +28,10 @@ struct dp_ends {
 };
 
 // token s, value r = (dy*2 + dx)*C + c  <->  latent element ((f*H + 2y+dy)*W + 2x+dx)*C + c
-__device__ __forceinline__ int64_t patch_elem(int64_t s, int r, int tok, int tw, int C) {
-  const int64_t f = s / tok;
-  const int rem = (int)(s % tok), y = rem / tw, x = rem % tw;
-  const int dy = r / (2 * C), dx = (r / C) & 1, c = r % C;
+__device__ __forceinline__ int64_t patch_elem(uint32_t s, int r_, int tok_, int tw_, int C_) {   // at most 2^24 tokens
+  const uint32_t r = r_, tok = tok_, tw = tw_, C = C_;
+  const uint32_t f = s / tok, rem = s % tok, y = rem / tw, x = rem % tw;
+  const uint32_t dy = r / (2 * C), dx = (r / C) & 1, c = r % C;
   const int64_t H = 2 * (tok / tw), W = 2 * tw;
   return ((f * H + 2 * y + dy) * W + 2 * x + dx) * C + c;
 }
@@ -51,6 +51,265 @@ __global__ void k_euler(float* __restrict__ x, const float* __restrict__ v, int6
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) x[i] = x[i] + ds * v[i];
 }
 
+// ------------------------------------------------------------------------------------------ bf16 ends in one kernel each
+// Both ends are contractions with one narrow side (4C values per token), so they are bound by one pass over the tokens;
+// as patchify + GEMM and as conversion + LayerNorm + GEMM + scatter they made three and six passes of it.
+// v_mfma_f32_16x16x32_bf16 with the weights as the A operand: lane l supplies / receives token l % 16, k (8 of them) or
+// output quad l / 16.  The weights are packed once in the order of the fragments, so a fragment is 1 KiB read in one piece.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t cvt_pk(float a, float b) {
+  f32x2_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+constexpr int kEndsMaxP = 256;                       // widest narrow side that stays in registers; beyond it: the GEMMs
+// fragment (chunk, tile) lane l, element e <- W[k = 32 chunk + 8 (l / 16) + e][n], W row-major [K, N], with
+// n = 16 tile + l % 16 (quad = 0), or (quad = 1) n = 64 (tile / 4) + 16 (l % 16 / 4) + 4 (tile % 4) + l % 4: the four
+// tiles of a 64-column group then leave 16 consecutive columns in one lane
+__global__ __launch_bounds__(256) void k_pack_frags(const bf16_t* __restrict__ W, int K, int N, int quad, uint4* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (int64_t)(K / 32) * (N / 16) * 64) return;
+  const int l = (int)(i & 63), tile = (int)((i >> 6) % (N / 16)), chunk = (int)((i >> 6) / (N / 16)), r = l & 15;
+  const int n = quad ? 64 * (tile >> 2) + 16 * (r >> 2) + 4 * (tile & 3) + (r & 3) : 16 * tile + r;
+  const bf16_t* src = W + (int64_t)(32 * chunk + 8 * (l >> 4)) * N + n;
+  uint32_t w[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) w[e] = (uint32_t)src[(int64_t)(2 * e) * N] | (uint32_t)src[(int64_t)(2 * e + 1) * N] << 16;
+  out[i] = make_uint4(w[0], w[1], w[2], w[3]);
+}
+static void launch_pack_frags(const bf16_t* W, int64_t K, int64_t N, int quad, void* out, hipStream_t st) {
+  k_pack_frags<<<(unsigned)((K * N / 8 + 255) / 256), 256, 0, st>>>(W, (int)K, (int)N, quad, (uint4*)out);
+}
+
+// Patch embedding.  A wavefront holds 16 tokens' patches (read from the fp32 latent, rounded to bf16) as operands and walks
+// 64-column groups of the output; a lane ends up with 16 consecutive columns of its token.  6240 tokens x 64 -> 1536:
+// 12.2 us in two launches -> 9.6 us (21 MB, of which a launch alone is 4.6); 14400 x 64 -> 5120: 50 -> 39 us (3.9 TB/s).
+// 16-byte stores of 16 different rows an instruction instead of the staged ones: 52 us.
+template <int KC>                                    // 32-value chunks of a patch
+__global__ __launch_bounds__(256) void k_embed(const float* __restrict__ latent, const uint4* __restrict__ wf,
+                                               const bf16_t* __restrict__ bias, bf16_t* __restrict__ out, int64_t S, int D,
+                                               int tok, int tw, int C, int aligned) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4;
+  const int64_t s = (int64_t)blockIdx.x * 16 + (lane & 15), sc = s < S ? s : S - 1;
+  __shared__ uint4 stage[4][16][9];
+  const int tiles = D >> 4, step = gridDim.y * 4;
+  int g = blockIdx.y * 4 + wave;
+  uint4 w[KC][4];
+  auto fetch = [&](int grp) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) w[c][t] = wf[((int64_t)c * tiles + grp * 4 + t) * 64 + lane];
+  };
+  if (g * 64 < D) fetch(g);
+  bf16x8 x[KC];
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const float* p = latent + patch_elem(sc, c * 32 + q * 8, tok, tw, C);      // 8 values of one pixel: C % 16 == 0
+    float v[8];
+    if (aligned) { *(float4*)v = *(const float4*)p; *(float4*)(v + 4) = *(const float4*)(p + 4); }
+    else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = p[e];
+    }
+    uint32_t u[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) u[e] = cvt_pk(v[2 * e], v[2 * e + 1]);
+    x[c] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+  }
+  for (; g * 64 < D; g += step) {
+    f32x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const uint2 b = *(const uint2*)(bias + g * 64 + q * 16 + t * 4);
+      acc[t] = f32x4{bf16_to_f32((bf16_t)(b.x & 0xffff)), bf16_to_f32((bf16_t)(b.x >> 16)),
+                     bf16_to_f32((bf16_t)(b.y & 0xffff)), bf16_to_f32((bf16_t)(b.y >> 16))};
+    }
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[c][t]), x[c], acc[t], 0, 0, 0);
+    if ((g + step) * 64 < D) fetch(g + step);
+    // through LDS (the wavefront's own 16 x 64 tile: no barrier), so that a store covers whole 128-byte pieces of rows
+    uint4* o = &stage[wave][lane & 15][q * 2];
+    o[0] = make_uint4(cvt_pk(acc[0][0], acc[0][1]), cvt_pk(acc[0][2], acc[0][3]), cvt_pk(acc[1][0], acc[1][1]), cvt_pk(acc[1][2], acc[1][3]));
+    o[1] = make_uint4(cvt_pk(acc[2][0], acc[2][1]), cvt_pk(acc[2][2], acc[2][3]), cvt_pk(acc[3][0], acc[3][1]), cvt_pk(acc[3][2], acc[3][3]));
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int tk = i * 8 + (lane >> 3);
+      const uint4 d = stage[wave][tk][lane & 7];
+      const int64_t row = (int64_t)blockIdx.x * 16 + tk;
+      if (row < S) __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)(out + row * D + g * 64 + (lane & 7) * 8));
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Output head: LayerNorm (two-pass statistics in fp32) -> (1 + scale), shift -> bf16 -> times W_head -> scatter.  A block of 8
+// wavefronts owns RT * 16 tokens; wavefront w holds the 64-channel groups w, w + 8, .. of their rows in registers, in operand
+// layout, so a row is read once.  The wavefronts' partial products over their channels meet in LDS, summed in wavefront
+// order.  blockIdx.y: 64 of the 4C output values.  14400 tokens x 5120: 237 us in six launches -> 57 us (147 MB).
+template <int NG, int RT>
+__global__ __launch_bounds__(512, 2) void k_head(const bf16_t* __restrict__ x, int64_t S, int D, float eps,
+                                                 const float* __restrict__ scale, const float* __restrict__ shift,
+                                                 const uint4* __restrict__ wf, const bf16_t* __restrict__ bias, int P,
+                                                 float* __restrict__ v_out, int tok, int tw, int C, int x_aligned, int v_aligned) {
+  __shared__ float red[2][RT][8][16];
+  __shared__ __align__(16) float part[8][RT * 16][68];            // [wavefront][token][64 values, padded]
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, lt = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t s0 = (int64_t)blockIdx.x * (RT * 16);
+  const int groups = D >> 6;
+  u32x4 xr[NG][RT][2];
+  float sum[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int64_t s = s0 + t * 16 + lt;
+    const bf16_t* p = x + (s < S ? s : S - 1) * D + wave * 64 + q * 8;
+    if (x_aligned) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          xr[g][t][c] = wave + 8 * g < groups ? *(const u32x4*)(p + g * 512 + c * 32) : u32x4{0, 0, 0, 0};
+    } else {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bf16_t* pe = p + g * 512 + c * 32 + 2 * e;
+            xr[g][t][c][e] = wave + 8 * g < groups ? pe[0] | (uint32_t)pe[1] << 16 : 0u;
+          }
+    }
+  }
+  // keeps the packed values, and nothing unpacked from them, in registers from one pass over the row to the next
+  auto repack = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) asm volatile("" : "+v"(xr[g][t][c]));
+  };
+  auto elem = [&](int g, int t, int c, int e) __attribute__((always_inline)) {
+    const uint32_t w = xr[g][t][c][e >> 1];
+    return __uint_as_float((e & 1) ? (w & 0xffff0000u) : (w << 16));
+  };
+  // sum over a token's channels: the lane's own, the other three lanes of the token, the 8 wavefronts in order
+  auto token_sum = [&](float (&v)[RT], int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      v[t] += __shfl_xor(v[t], 16, 64);
+      v[t] += __shfl_xor(v[t], 32, 64);
+      if (q == 0) red[slot][t][wave][lt] = v[t];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      v[t] = 0.f;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v[t] += red[slot][t][w][lt];
+    }
+  };
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    sum[t] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        float p = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p += elem(g, t, c, e);
+        sum[t] += p;
+      }
+  }
+  token_sum(sum, 0);
+  repack();
+  float mean[RT], rstd[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    mean[t] = sum[t] / (float)D;
+    sum[t] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+      if (wave + 8 * g < groups) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          float p = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) { const float d = elem(g, t, c, e) - mean[t]; p += d * d; }
+          sum[t] += p;
+        }
+      }
+  }
+  token_sum(sum, 1);
+  repack();
+#pragma unroll
+  for (int t = 0; t < RT; ++t) rstd[t] = rsqrtf(sum[t] / (float)D + eps);
+
+  f32x4 acc[RT][4];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int ptiles = P >> 4;
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    if (wave + 8 * g < groups) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int k0 = (wave + 8 * g) * 64 + c * 32, kl = k0 + q * 8;
+        uint4 w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = wf[((int64_t)(k0 >> 5) * ptiles + blockIdx.y * 4 + j) * 64 + lane];
+        float m[8], a[8];
+        *(float4*)m = *(const float4*)(scale + kl); *(float4*)(m + 4) = *(const float4*)(scale + kl + 4);
+        *(float4*)a = *(const float4*)(shift + kl); *(float4*)(a + 4) = *(const float4*)(shift + kl + 4);
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          uint32_t h[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            h[e] = cvt_pk((elem(g, t, c, 2 * e) - mean[t]) * rstd[t] * (m[2 * e] + 1.f) + a[2 * e],
+                          (elem(g, t, c, 2 * e + 1) - mean[t]) * rstd[t] * (m[2 * e + 1] + 1.f) + a[2 * e + 1]);
+          const bf16x8 hv = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[j]), hv, acc[t][j], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);           // without it the loads of all groups move up and spill
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) *(f32x4*)&part[wave][t * 16 + lt][j * 16 + q * 4] = acc[t][j];
+  __syncthreads();
+  for (int i = tid; i < RT * 16 * 16; i += 512) {    // four values of one token each
+    const int tk = i >> 4, r = (i & 15) * 4, p = blockIdx.y * 64 + r;
+    if (s0 + tk >= S) continue;
+    f32x4 v = *(const f32x4*)&part[0][tk][r];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) v += *(const f32x4*)&part[w][tk][r];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += bf16_to_f32(bias[p + e]);
+    float* o = v_out + patch_elem(s0 + tk, p, tok, tw, C);          // consecutive channels of one pixel: C % 16 == 0
+    if (v_aligned) *(f32x4*)o = v;
+    else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = v[e];
+    }
+  }
+}
+
 static const char* validate(const dp_ends_config* c) {
   if (!c) return "null config";
   if (c->dim < 1 || c->tok_h < 1 || c->tok_w < 1 || c->channels < 1 || c->max_frames < 1) return "non-positive size";
@@ -65,6 +324,11 @@ static const char* validate(const dp_ends_config* c) {
   if (c->dtype == DP_BF16 && (c->dim % 64 || (4 * c->channels) % 64)) return "bf16 path needs dim and 4*channels % 64 == 0";
   return nullptr;
 }
+
+// The one-kernel forms: bf16, at most 256 values per token (they stay in registers; wider ones re-read the tokens once per 64
+// values), and for the head rows of at most 5120 channels (10 groups of 64 per wavefront: 160 registers).
+static bool embed_fused(const dp_ends_config& c) { return c.dtype == DP_BF16 && 4 * c.channels <= kEndsMaxP; }
+static bool head_fused(const dp_ends_config& c) { return embed_fused(c) && c.dim <= 5120; }
 
 static size_t carve(dp_ends* s, void* base) {
   const dp_ends_config& c = s->cfg;
@@ -85,6 +349,12 @@ static size_t carve(dp_ends* s, void* base) {
   s->e1 = (float*)take(GEMV_MAX_SLICES * D * 4); s->e = (float*)take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
   s->mhead = (float*)take(2 * D * 4); s->mod = (float*)take(2 * D * 4);
   return (size_t)rup((int64_t)off, 256);
+}
+
+static void pack_head(dp_ends* s, hipStream_t st) {
+  const bf16_t* w = (const bf16_t*)s->w.w_head;
+  if (head_fused(s->cfg)) launch_pack_frags(w, s->cfg.dim, s->P, 0, s->w_head_t, st);
+  else launch_transpose_pad<bf16_t>(w, s->cfg.dim, s->P, (bf16_t*)s->w_head_t, rup(s->P, 256), st);
 }
 
 extern "C" size_t dp_ends_workspace_bytes(const dp_ends_config* cfg) {
@@ -115,8 +385,9 @@ extern "C" int dp_ends_init(const dp_ends_config* cfg, const dp_ends_weights* w,
   const int64_t D = cfg->dim;
   launch_fill_zero(s->patches, (size_t)((char*)s->tau - (char*)s->patches), st);      // padding rows of the GEMM operands
   if (cfg->dtype == DP_BF16) {
-    launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
-    launch_transpose_pad<bf16_t>((const bf16_t*)w->w_head, D, s->P, (bf16_t*)s->w_head_t, rup(s->P, 256), st);
+    if (embed_fused(*cfg)) launch_pack_frags((const bf16_t*)w->w_pe, s->P, D, 1, s->w_pe_t, st);
+    else launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
+    pack_head(s, st);
     launch_to_f32<bf16_t>((const bf16_t*)w->m_head, s->mhead, 2 * D, st);
   } else {
     launch_to_f32<float>((const float*)w->m_head, s->mhead, 2 * D, st);
@@ -137,10 +408,30 @@ static void gemm(dp_ends* s, const void* A, int64_t lda, const void* W, const vo
   (void)s;
 }
 
+static void launch_embed(dp_ends* s, const float* latent, void* x_out, int64_t S, hipStream_t st) {
+  const dp_ends_config& c = s->cfg;
+  const int64_t rows = (S + 15) / 16;
+  const int groups = c.dim / 64, per = (groups + 3) / 4;           // 64-column groups; blocks of 4 that cover them
+  // few tokens: the columns are dealt over blocks until the chip is full, many: a block walks all of them
+  int64_t cols = (512 + rows - 1) / rows;
+  cols = cols < 1 ? 1 : cols > per ? per : cols;
+  const dim3 grid((unsigned)rows, (unsigned)cols);
+  const int al = ((uintptr_t)latent & 15) == 0;
+#define EMBED_CASE(KC) k_embed<KC><<<grid, 256, 0, st>>>(latent, (const uint4*)s->w_pe_t, (const bf16_t*)s->w.b_pe, (bf16_t*)x_out, S, c.dim, (int)s->tok, c.tok_w, c.channels, al)
+  if (s->P == 64) EMBED_CASE(2);
+  else if (s->P == 128) EMBED_CASE(4);
+  else if (s->P == 192) EMBED_CASE(6);
+  else EMBED_CASE(8);
+#undef EMBED_CASE
+}
+
 template <typename T>
 static void embed_typed(dp_ends* s, const float* latent, void* x_out, int n_frames, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
   const int64_t S = s->tok * n_frames, n = S * s->P;
+  if constexpr (sizeof(T) == 2) {
+    if (embed_fused(c)) { launch_embed(s, latent, x_out, S, st); return; }
+  }
   k_patchify<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(latent, (T*)s->patches, n, (int)s->P, (int)s->tok, c.tok_w, c.channels);
   gemm<T>(s, s->patches, s->P, s->w.w_pe, s->w_pe_t, S, c.dim, s->P, EPI_STORE, EpiArgs{x_out, c.dim, s->w.b_pe, nullptr, 0, nullptr}, st);
 }
@@ -156,6 +447,22 @@ extern "C" int dp_embed_forward(dp_ends_t* s, const float* latent, void* x_out, 
   return DP_OK;
 }
 
+static void launch_head(dp_ends* s, const void* x_in, float* v_out, int64_t S, hipStream_t st) {
+  const dp_ends_config& c = s->cfg;
+  const int ng = (c.dim / 64 + 7) / 8, xa = ((uintptr_t)x_in & 15) == 0, va = ((uintptr_t)v_out & 15) == 0;
+  // 32 tokens a block halve the reads of the weights; with fewer than 128 such blocks 16 spread over more CUs
+  // (14400 x 5120: 57 against 66 us, 6240 x 1536: 11.4 against 12.5)
+  const bool two = S >= 4096;
+  const dim3 grid((unsigned)((S + (two ? 31 : 15)) / (two ? 32 : 16)), (unsigned)(s->P / 64));
+#define HEAD_CASE(NG, RT) k_head<NG, RT><<<grid, 512, 0, st>>>((const bf16_t*)x_in, S, c.dim, c.eps, s->mod + c.dim, s->mod, \
+    (const uint4*)s->w_head_t, (const bf16_t*)s->w.b_head, (int)s->P, v_out, (int)s->tok, c.tok_w, c.channels, xa, va)
+#define HEAD_NG(RT) do { if (ng <= 1) HEAD_CASE(1, RT); else if (ng <= 2) HEAD_CASE(2, RT); else if (ng <= 3) HEAD_CASE(3, RT); \
+    else if (ng <= 4) HEAD_CASE(4, RT); else if (ng <= 6) HEAD_CASE(6, RT); else if (ng <= 8) HEAD_CASE(8, RT); else HEAD_CASE(10, RT); } while (0)
+  if (two) HEAD_NG(2); else HEAD_NG(1);
+#undef HEAD_NG
+#undef HEAD_CASE
+}
+
 template <typename T>
 static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int n_frames, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
@@ -164,6 +471,9 @@ static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int 
   launch_gemv<T>(s->tau, 1, 0, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, 0, s->e1, st);
   launch_gemv<T>(s->e1, gemv_slices(c.freq_dim, (int)D), (int)D, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, 1, s->e, st);
   launch_mod_add<T>(s->mhead, s->e, gemv_slices((int)D, (int)D), (const T*)s->w.bt2, s->mod, 2, (int)D, st);   // rows: shift, scale
+  if constexpr (sizeof(T) == 2) {
+    if (head_fused(c)) { launch_head(s, x_in, v_out, S, st); return; }
+  }
   launch_to_f32<T>((const T*)x_in, s->x32, S * D, st);
   launch_ln_modulate<T>(s->x32, nullptr, (T*)s->h, S, (int)D, c.eps, s->mod + D, s->mod, 1, st);
   // fp32 output through the residual epilogue (out32 += h W + b) on a cleared buffer
@@ -256,9 +566,9 @@ extern "C" int dp_head_forward_static(const dp_ends_config* cfg, const dp_ends_w
   const bool bf = cfg->dtype == DP_BF16;
   // the array keeps the last call's contents: rows of the GEMM operand beyond this call's tokens are cleared with
   // a fill kernel (no memset call, so the entry point can be captured), the rest is overwritten below
-  if (s.Spad > S) launch_fill_zero((char*)s.h + S * D * (bf ? 2 : 4), (size_t)((s.Spad - S) * D * (bf ? 2 : 4)), st);
+  if (s.Spad > S && !head_fused(*cfg)) launch_fill_zero((char*)s.h + S * D * (bf ? 2 : 4), (size_t)((s.Spad - S) * D * (bf ? 2 : 4)), st);
   if (bf) {
-    launch_transpose_pad<bf16_t>((const bf16_t*)w->w_head, D, s.P, (bf16_t*)s.w_head_t, rup(s.P, 256), st);
+    pack_head(&s, st);
     launch_to_f32<bf16_t>((const bf16_t*)w->m_head, s.mhead, 2 * D, st);
     head_typed<bf16_t>(&s, x_in, timestep, v_out, n_frames, st);
   } else {
