@@ -275,27 +275,6 @@ void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float e
 template void launch_norm_rope<float>(const float*, int64_t, int64_t, int, int, float, const NormRopeJob<float>*, int, const RopeTables*, int, int, int, hipStream_t);
 template void launch_norm_rope<bf16_t>(const bf16_t*, int64_t, int64_t, int, int, float, const NormRopeJob<bf16_t>*, int, const RopeTables*, int, int, int, hipStream_t);
 
-// ---------------------------------------------------------------- per-token rotation table of one block
-// cs[s][i] = (cos, sin) of channel pair i at token s = (frame0 + s / (tok_h * tok_w), y, x), gathered from the
-// three per-axis tables
-__global__ void k_rope_tokens(RopeTables rt, int frame0, int tok_h, int tok_w, int64_t S, float2* __restrict__ cs) {
-  const int half = rt.c_f + rt.c_h + rt.c_w;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= S * half) return;
-  const int64_t s = i / half; const int pi = (int)(i % half);
-  const int tok = tok_h * tok_w, rem = (int)(s % tok);
-  const int f = frame0 + (int)(s / tok), y = rem / tok_w, x = rem % tok_w;
-  float2 v;
-  if (pi < rt.c_f) v = rt.f[(int64_t)f * rt.c_f + pi];
-  else if (pi < rt.c_f + rt.c_h) v = rt.y[y * rt.c_h + (pi - rt.c_f)];
-  else v = rt.x[x * rt.c_w + (pi - rt.c_f - rt.c_h)];
-  cs[i] = v;
-}
-void launch_rope_tokens(const RopeTables& rt, int frame0, int tok_h, int tok_w, int64_t S, float2* cs, hipStream_t st) {
-  if (S <= 0) return;
-  k_rope_tokens<<<cdiv(S * (rt.c_f + rt.c_h + rt.c_w), 256), 256, 0, st>>>(rt, frame0, tok_h, tok_w, S, cs);
-}
-
 // ---------------------------------------------------------------- deferred RMSNorm of head-major bf16 rows
 // k[head][row0 + s][:] *= rsqrt(sum_i ssq[i * stride + s] * inv_dim + eps) for every head: the row scale of an
 // RMSNorm whose gains and rotation a GEMM epilogue has applied already.  One wavefront per token.
@@ -452,94 +431,153 @@ template void launch_transpose_pad<float>(const float*, int64_t, int64_t, float*
 template void launch_transpose_pad<bf16_t>(const bf16_t*, int64_t, int64_t, bf16_t*, int64_t, hipStream_t);
 
 // ---------------------------------------------------------------- timestep modulation vector
-__global__ void k_sinusoid(float t, int freq_dim, float* out) {
-  const int half = freq_dim >> 1;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= half) return;
-  const double w = pow(10000.0, -(double)i / (double)half);
-  const double a = (double)t * w;
-  out[i] = (float)cos(a);
-  out[half + i] = (float)sin(a);
+// Matrix-vector products of the timestep MLP, bound by one read of W.  A block owns 64 * CPL output columns and one of
+// gridDim.y slices of the K rows; a wavefront instruction reads one row's piece of them (256 bytes at CPL = 2 in bf16),
+// up to 16 rows in flight per wavefront, and the 16 wavefronts' sums meet in LDS.  (Lanes of a wavefront on different rows,
+// 16 bytes each, took 108 us where this takes 82: every row is another page.)  A sliced product leaves partial results
+// that its consumer adds up in slice order together with the bias; a whole one can add its result to the L rows of a table.
+// 5120 x 30720: 315 MB in 82 us = 3.8 TB/s, what a read-only pass reaches here; more rows in flight do not change it.
+// The chain (features, three products, table, rotation table) is three launches: 128-wide model 28 -> 13 us, 1536-wide
+// 39 -> 32 us under the profiler, which counts a launch as 4.6 us; 1 us each otherwise.
+template <typename T> struct GemvArgs {
+  GemvIn in;
+  const T *xbias, *W, *ybias;
+  int K, N;
+  float* y;
+  const float* mtab; float* mod; int L;
+  int cols;                    // blocks along N; further ones build the rotation table
+};
+// cs[s][i] = (cos, sin) of channel pair i at token s = (frame0 + s / (tok_h * tok_w), y, x), gathered from the per-axis tables
+__device__ __forceinline__ void rope_token(const RopeTokens& r, int64_t i) {
+  const uint32_t half = r.rt.c_f + r.rt.c_h + r.rt.c_w, s = (uint32_t)(i / half), pi = (uint32_t)(i % half);
+  const uint32_t tok = (uint32_t)r.tok_h * r.tok_w, rem = s % tok, f = r.frame0 + s / tok, y = rem / r.tok_w, x = rem % r.tok_w;
+  const uint32_t cf = r.rt.c_f, ch = r.rt.c_h, cw = r.rt.c_w;
+  r.cs[i] = pi < cf ? r.rt.f[(int64_t)f * cf + pi] : pi < cf + ch ? r.rt.y[y * ch + (pi - cf)] : r.rt.x[x * cw + (pi - cf - ch)];
 }
-void launch_sinusoid(float t, int freq_dim, float* out, hipStream_t st) {
-  k_sinusoid<<<cdiv(freq_dim / 2, 64), 64, 0, st>>>(t, freq_dim, out);
-}
-
-// Matrix-vector products of the timestep MLP.  A block owns 64 output columns and one of gridDim.y slices of the
-// K rows; its 16 wavefronts each take every 16th row of the slice (coalesced 64-column reads) and the partial
-// sums meet in LDS.  The block writes its slice's partial result y[slice][n] without bias: whoever consumes the
-// vector adds the slices up in index order (so the result does not depend on timing) together with the bias.
-// The input is such a sliced vector itself: x[k] = act(sum_p x[p][k] + xbias[k]).
-template <typename T>
-__global__ __launch_bounds__(1024) void k_gemv(const float* __restrict__ x, int x_parts, int x_stride,
-                                               const T* __restrict__ xbias, int K, const T* __restrict__ W, int N,
-                                               int silu_in, float* __restrict__ y) {
-  extern __shared__ float xs[];            // this slice's activations, then 16 x 64 partial sums
-  const int KS = gridDim.y, ks = blockIdx.y;
-  const int k0 = (int)((int64_t)K * ks / KS), Kb = (int)((int64_t)K * (ks + 1) / KS) - k0;
-  float* red = xs + Kb;
-  for (int k = threadIdx.x; k < Kb; k += 1024) {
-    float v = xbias ? Elem<T>::ld(xbias + k0 + k) : 0.f;
-    for (int p = 0; p < x_parts; ++p) v += x[(int64_t)p * x_stride + k0 + k];
-    xs[k] = silu_in ? v / (1.0f + expf(-v)) : v;
+// SINUS: the input is the sinusoidal features of a.in.t (a kernel of its own: their double-precision code would cost every
+// product registers and scratch memory).  CPL == 2: bf16, rows of W in 4-byte steps.
+template <typename T, int CPL, bool SINUS>
+__global__ __launch_bounds__(1024) void k_gemv(GemvArgs<T> a, RopeTokens rope) {
+  constexpr int KC = 8192, U = SINUS ? 8 : 16;
+  __shared__ float xs[KC];
+  __shared__ float red[16][64 * CPL];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (SINUS && (int)blockIdx.x >= a.cols) {
+    const int64_t i = (int64_t)((int)blockIdx.x - a.cols) * 1024 + tid;
+    if (i < rope.S * (rope.rt.c_f + rope.rt.c_h + rope.rt.c_w)) rope_token(rope, i);
+    return;
   }
-  __syncthreads();
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n = blockIdx.x * 64 + tx;
-  const T* Wb = W + (int64_t)k0 * N;
-  float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-  if (n < N) {
-    int k = ty;
-    for (; k + 48 < Kb; k += 64) {
-      a0 += xs[k] * Elem<T>::ld(Wb + (int64_t)k * N + n);
-      a1 += xs[k + 16] * Elem<T>::ld(Wb + (int64_t)(k + 16) * N + n);
-      a2 += xs[k + 32] * Elem<T>::ld(Wb + (int64_t)(k + 32) * N + n);
-      a3 += xs[k + 48] * Elem<T>::ld(Wb + (int64_t)(k + 48) * N + n);
-    }
-    for (; k < Kb; k += 16) a0 += xs[k] * Elem<T>::ld(Wb + (int64_t)k * N + n);
-  }
-  red[ty * 64 + tx] = (a0 + a1) + (a2 + a3);
-  __syncthreads();
-  if (ty == 0 && n < N) {
-    float sum = 0.f;
+  const int ks = blockIdx.y, k0 = (int)((int64_t)a.K * ks / gridDim.y), Kb = (int)((int64_t)a.K * (ks + 1) / gridDim.y) - k0;
+  const int n0 = (int)blockIdx.x * 64 * CPL, n = n0 + lane * CPL;
+  const T* const wn = a.W + (n < a.N ? n : 0);
+  float acc[CPL];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sum += red[i * 64 + tx];
-    y[(int64_t)ks * N + n] = sum;
+  for (int v = 0; v < CPL; ++v) acc[v] = 0.f;
+  for (int c0 = 0; c0 < Kb; c0 += KC) {
+    const int kc = Kb - c0 < KC ? Kb - c0 : KC;
+    if (c0) __syncthreads();
+    const T* w = wn + (int64_t)(k0 + c0) * a.N;
+    // rows wave, wave + 16, ..: groups of U, the next group requested before this one is used (past the end: the last row
+    // again, not added)
+    using Piece = std::conditional_t<CPL == 2, uint32_t, T>;
+    Piece d[2][U];
+    auto fetch = [&](int k, int z) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) d[z][u] = *(const Piece*)(w + (int64_t)(k + u * 16 < kc ? k + u * 16 : kc - 1) * a.N);
+    };
+    auto add = [&](int k, int z) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k + u * 16 < kc) {
+          const float x = xs[k + u * 16];
+          if constexpr (CPL == 2) {
+            acc[0] += x * __uint_as_float(d[z][u] << 16);
+            acc[1] += x * __uint_as_float(d[z][u] & 0xffff0000u);
+          } else {
+            acc[0] += x * Elem<T>::ld(&d[z][u]);
+          }
+        }
+    };
+    if (wave < kc) fetch(wave, 0);                     // travels while the activations are made
+    for (int k = tid; k < kc; k += 1024) {
+      const int kk = k0 + c0 + k;
+      if constexpr (SINUS) {
+        const int half = a.K >> 1, i = kk < half ? kk : kk - half;
+        const double ang = (double)a.in.t * pow(10000.0, -(double)i / (double)half);
+        xs[k] = kk < half ? (float)cos(ang) : (float)sin(ang);
+      } else {
+        float v = Elem<T>::ld(a.xbias + kk);
+        for (int p = 0; p < a.in.parts; ++p) v += a.in.x[(int64_t)p * a.K + kk];
+        xs[k] = v / (1.0f + expf(-v));                 // SiLU
+      }
+    }
+    __syncthreads();
+    for (int k = wave; k < kc; k += 32 * U) {
+      if (k + 16 * U < kc) fetch(k + 16 * U, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      add(k, 0);
+      if (k + 32 * U < kc) fetch(k + 32 * U, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (k + 16 * U < kc) add(k + 16 * U, 1);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < CPL; ++v) red[wave][lane * CPL + v] = acc[v];
+  __syncthreads();
+  if (tid < 64 * CPL && n0 + tid < a.N) {
+    float y = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) y += red[i][tid];
+    if (a.y) a.y[(int64_t)ks * a.N + n0 + tid] = y;
+    if (a.L > 0) {
+      y += Elem<T>::ld(a.ybias + n0 + tid);
+      for (int l = 0; l < a.L; ++l) a.mod[(int64_t)l * a.N + n0 + tid] = a.mtab[(int64_t)l * a.N + n0 + tid] + y;
+    }
   }
 }
-int gemv_slices(int K, int N) {
-  int ks = (256 + cdiv(N, 64) - 1) / cdiv(N, 64);     // enough blocks for the 256 CUs
-  if (ks > GEMV_MAX_SLICES) ks = GEMV_MAX_SLICES;
-  while (ks > 1 && K / ks < 64) --ks;
-  return ks < 1 ? 1 : ks;
+// mod[l, i] = mtab[l, i] + sum_p e[p][i] + bias[i]: a sliced vector added to every row of a table
+template <typename T>
+__global__ __launch_bounds__(256) void k_mod_add(const float* __restrict__ e, int parts, GemvTable<T> t, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float v = 0.f;
+  for (int p = 0; p < parts; ++p) v += e[(int64_t)p * n + i];
+  v += Elem<T>::ld(t.bias + i);
+  for (int l = 0; l < t.L; ++l) t.mod[(int64_t)l * n + i] = t.mtab[(int64_t)l * n + i] + v;
 }
 template <typename T>
-void launch_gemv(const float* x, int x_parts, int x_stride, const T* xbias, int K, const T* W, int N, int silu_in,
-                 float* y, hipStream_t st) {
-  const int ks = gemv_slices(K, N);
-  k_gemv<T><<<dim3(cdiv(N, 64), ks), 1024, (size_t)(cdiv(K, ks) + 1 + 1024) * sizeof(float), st>>>(
-      x, x_parts, x_stride, xbias, K, W, N, silu_in, y);
+int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, float* y, const GemvTable<T>* table,
+                const RopeTokens* rope, hipStream_t st) {
+  // A product that ends in a table stays whole unless its columns make less than half a round of blocks that each have many
+  // rows to read (5120 x 5120: 38 us whole, 21 sliced with a launch more; 1536 x 1536: 13 and 11 under the
+  // profiler, which counts the launch as 4.6 us).
+  const bool whole = table && (!y || cdiv(N, 64) >= 128 || K <= 2048);
+  // two columns per lane unless a whole product would then leave CUs without a block
+  const bool wide = sizeof(T) == 2 && N % 2 == 0 && ((uintptr_t)W & 3) == 0 && (!whole || cdiv(N, 128) >= 192);
+  const int cols = cdiv(N, wide ? 128 : 64);
+  int slices = 1;
+  if (!whole && in.x) {                                // enough blocks for the 256 CUs, at least 64 rows each
+    slices = cdiv(256, cols);
+    if (slices > GEMV_MAX_SLICES) slices = GEMV_MAX_SLICES;
+    while (slices > 1 && K / slices < 64) --slices;
+  }
+  GemvArgs<T> a{in, xbias, W, table ? table->bias : nullptr, K, N, whole ? nullptr : y, table ? table->mtab : nullptr,
+                table ? table->mod : nullptr, whole ? table->L : 0, cols};
+  const RopeTokens r = rope ? *rope : RopeTokens{};
+  const int64_t extra = rope ? (rope->S * (rope->rt.c_f + rope->rt.c_h + rope->rt.c_w) + 1023) / 1024 : 0;
+  const dim3 grid((unsigned)(cols + extra), (unsigned)slices);
+#define GEMV_CASE(C, SIN) k_gemv<T, C, SIN><<<grid, 1024, 0, st>>>(a, r)
+  if constexpr (sizeof(T) == 2) {
+    if (wide && in.x) GEMV_CASE(2, false);
+    else if (wide) GEMV_CASE(2, true);
+  }
+  if (!wide) { if (in.x) GEMV_CASE(1, false); else GEMV_CASE(1, true); }
+#undef GEMV_CASE
+  if (table && !whole) k_mod_add<T><<<cdiv(N, 256), 256, 0, st>>>(y, slices, *table, N);
+  return slices;
 }
-template void launch_gemv<float>(const float*, int, int, const float*, int, const float*, int, int, float*, hipStream_t);
-template void launch_gemv<bf16_t>(const float*, int, int, const bf16_t*, int, const bf16_t*, int, int, float*, hipStream_t);
-
-// mod[l, i] = mtab[l, i] + sum_p e[p][i] + bias[i]: a sliced vector (see k_gemv) added to every row of a table
-template <typename T>
-__global__ void k_mod_add(const float* __restrict__ mtab, const float* __restrict__ e, int parts,
-                          const T* __restrict__ bias, float* __restrict__ mod, int L, int n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)L * n) return;
-  const int c = (int)(i % n);
-  float v = bias ? Elem<T>::ld(bias + c) : 0.f;
-  for (int p = 0; p < parts; ++p) v += e[(int64_t)p * n + c];
-  mod[i] = mtab[i] + v;
-}
-template <typename T>
-void launch_mod_add(const float* mtab, const float* e, int parts, const T* bias, float* mod, int L, int n, hipStream_t st) {
-  k_mod_add<T><<<cdiv((int64_t)L * n, 256), 256, 0, st>>>(mtab, e, parts, bias, mod, L, n);
-}
-template void launch_mod_add<float>(const float*, const float*, int, const float*, float*, int, int, hipStream_t);
-template void launch_mod_add<bf16_t>(const float*, const float*, int, const bf16_t*, float*, int, int, hipStream_t);
+template int launch_gemv<float>(const GemvIn&, const float*, int, const float*, int, float*, const GemvTable<float>*, const RopeTokens*, hipStream_t);
+template int launch_gemv<bf16_t>(const GemvIn&, const bf16_t*, int, const bf16_t*, int, float*, const GemvTable<bf16_t>*, const RopeTokens*, hipStream_t);
 
 // cos/sin of pos * theta^(-i/pairs), angles in double
 __global__ void k_rope_table(float2* tab, int n_pos, int pairs, float theta) {

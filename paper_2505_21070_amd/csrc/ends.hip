@@ -24,7 +24,7 @@ struct dp_ends {
   dp_ends_weights w{};
   int64_t tok, Smax, Spad, P;                  // P = 4 * channels values per token
   void *patches, *h, *w_pe_t, *w_head_t;       // storage type
-  float *x32, *out32, *tau, *e1, *e, *mhead, *mod;
+  float *x32, *out32, *e1, *e, *mhead, *mod;
 };
 
 // token s, value r = (dy*2 + dx)*C + c  <->  latent element ((f*H + 2y+dy)*W + 2x+dx)*C + c
@@ -345,7 +345,6 @@ static size_t carve(dp_ends* s, void* base) {
   s->out32 = (float*)take(s->Spad * s->P * 4);
   s->w_pe_t = take(rup(D, 256) * s->P * E);
   s->w_head_t = take(rup(s->P, 256) * D * E);
-  s->tau = (float*)take(c.freq_dim * 4);
   s->e1 = (float*)take(GEMV_MAX_SLICES * D * 4); s->e = (float*)take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
   s->mhead = (float*)take(2 * D * 4); s->mod = (float*)take(2 * D * 4);
   return (size_t)rup((int64_t)off, 256);
@@ -383,7 +382,7 @@ extern "C" int dp_ends_init(const dp_ends_config* cfg, const dp_ends_weights* w,
   hipStream_t st = (hipStream_t)hip_stream;
   (void)hipGetLastError();
   const int64_t D = cfg->dim;
-  launch_fill_zero(s->patches, (size_t)((char*)s->tau - (char*)s->patches), st);      // padding rows of the GEMM operands
+  launch_fill_zero(s->patches, (size_t)((char*)s->e1 - (char*)s->patches), st);      // padding rows of the GEMM operands
   if (cfg->dtype == DP_BF16) {
     if (embed_fused(*cfg)) launch_pack_frags((const bf16_t*)w->w_pe, s->P, D, 1, s->w_pe_t, st);
     else launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
@@ -467,10 +466,10 @@ template <typename T>
 static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int n_frames, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
   const int64_t D = c.dim, S = s->tok * n_frames, n = S * s->P;
-  launch_sinusoid(t, c.freq_dim, s->tau, st);
-  launch_gemv<T>(s->tau, 1, 0, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, 0, s->e1, st);
-  launch_gemv<T>(s->e1, gemv_slices(c.freq_dim, (int)D), (int)D, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, 1, s->e, st);
-  launch_mod_add<T>(s->mhead, s->e, gemv_slices((int)D, (int)D), (const T*)s->w.bt2, s->mod, 2, (int)D, st);   // rows: shift, scale
+  // mod rows: shift, scale
+  const GemvTable<T> table{(const T*)s->w.bt2, s->mhead, s->mod, 2};
+  const int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, nullptr, st);
+  launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e, &table, nullptr, st);
   if constexpr (sizeof(T) == 2) {
     if (head_fused(c)) { launch_head(s, x_in, v_out, S, st); return; }
   }
@@ -536,8 +535,7 @@ static size_t carve_head(dp_ends* s, void* base, int n_frames) {
   s->x32 = (float*)take(s->Spad * D * 4);
   s->out32 = (float*)take(s->Spad * s->P * 4);
   s->w_head_t = take(rup(s->P, 256) * D * E);
-  s->tau = (float*)take(c.freq_dim * 4);
-  s->e1 = (float*)take(GEMV_MAX_SLICES * D * 4); s->e = (float*)take(GEMV_MAX_SLICES * D * 4);
+  s->e1 = (float*)take(GEMV_MAX_SLICES * D * 4); s->e = (float*)take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
   s->mhead = (float*)take(2 * D * 4); s->mod = (float*)take(2 * D * 4);
   return (size_t)rup((int64_t)off, 256);
 }
@@ -553,7 +551,7 @@ extern "C" int dp_head_forward_static(const dp_ends_config* cfg, const dp_ends_w
   if (!(timestep == timestep)) return dp_set_error(DP_EINVAL, "dp_head_forward_static: timestep is NaN");
   dp_ends s;                                            // host struct on the stack: nothing is allocated
   s.cfg = *cfg; s.w = *w;
-  if (carve_head(&s, nullptr, n_frames) > kHeadScratchBytes)
+  if (carve_head(&s, nullptr, n_frames) + (size_t)rup(4 * (int64_t)cfg->freq_dim, 256) > kHeadScratchBytes)   // the documented limit
     return dp_set_error(DP_ENOMEM, "dp_head_forward_static: this many tokens need more than the 64 MiB of static scratch; "
                                    "call it per frame or use dp_head_forward with a workspace");
   void* base = nullptr;

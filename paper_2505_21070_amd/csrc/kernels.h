@@ -21,8 +21,8 @@ template <typename T> struct NormRopeJob {
 template <typename T>
 void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float eps, const NormRopeJob<T>* jobs,
                       int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st);
-// cs[s][i] = rotation (cos, sin) of channel pair i < head_dim / 2 at token s of a block that starts at frame0
-void launch_rope_tokens(const RopeTables& rt, int frame0, int tok_h, int tok_w, int64_t S, float2* cs, hipStream_t st);
+// cs[s][i] = rotation (cos, sin) of channel pair i < head_dim / 2 at token s < S of a block that starts at frame0
+struct RopeTokens { RopeTables rt; int frame0, tok_h, tok_w; int64_t S; float2* cs; };
 // k[head][row0 + s][:] *= rsqrt(sum_i ssq[i * stride + s] / (h * d) + eps), bf16 rows of d elements, in place
 void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* ssq,
                             int np, int64_t stride, float eps, hipStream_t st);
@@ -38,18 +38,17 @@ void launch_copy2d(const T* src, int64_t src_stride, T* dst, int64_t dst_stride,
 template <typename T>
 void launch_transpose_pad(const T* in, int64_t K, int64_t N, T* out, int64_t Npad, hipStream_t st);
 
-void launch_sinusoid(float t, int freq_dim, float* out, hipStream_t st);
-// Timestep-MLP matrix-vector product over sliced vectors.  A sliced vector is `parts` partial vectors
-// (stride apart) whose sum, plus a bias, is the value.  y receives gemv_slices(K, N) <= GEMV_MAX_SLICES partial
-// results [slice][N] of sum_k act(x[k]) * W[k, n], x[k] = sum_p x[p][k] + xbias[k]; act = SiLU when silu_in.
+// Timestep-MLP product of act(x) with W [K, N].  The input is the K sinusoidal features of timestep t (x == null, no
+// activation) or a sliced vector: x[k] = SiLU(sum over `parts` rows of x[parts][K] + xbias[k]).  Without a table y receives
+// the product's own slices [returned count <= GEMV_MAX_SLICES][N], without a bias (its consumer adds them up); with one
+// the whole result goes to mod[l, n] = mtab[l, n] + (result + bias)[n] for l < L (y, if given, may serve as scratch).  rope != null (with sinusoidal
+// input only): the launch builds that rotation table next to it.
 constexpr int GEMV_MAX_SLICES = 8;
-int gemv_slices(int K, int N);
+struct GemvIn { const float* x; int parts; float t; };
+template <typename T> struct GemvTable { const T* bias; const float* mtab; float* mod; int L; };
 template <typename T>
-void launch_gemv(const float* x, int x_parts, int x_stride, const T* xbias, int K, const T* W, int N, int silu_in,
-                 float* y, hipStream_t st);
-// mod[l, i] = mtab[l, i] + sum_p e[p][i] + bias[i]
-template <typename T>
-void launch_mod_add(const float* mtab, const float* e, int parts, const T* bias, float* mod, int L, int n, hipStream_t st);
+int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, float* y, const GemvTable<T>* table,
+                const RopeTokens* rope, hipStream_t st);
 void launch_rope_table(float2* tab, int n_pos, int pairs, float theta, hipStream_t st);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // dst[s, head*d + c] (fp32) = src[head][row0 + s][c]

@@ -75,7 +75,7 @@ struct dp_stage {
   // shared activations
   float* xres; void* hbuf; void* raw; void* qbuf; void* attn_o; void* mid;
   void* textpad; void* ctx; void* ctx_mid; void* wtmp;
-  float *tau, *e1, *e2, *e0, *mtab, *mod;
+  float *e1, *e2, *mtab, *mod;
   float2 *rope_f, *rope_y, *rope_x; RopeTables rt;
   void* tap_attn; float *tap_xself, *tap_xcross;
   float* attn_scratch; size_t attn_scratch_floats;   // partial results of attention over cut key ranges
@@ -174,9 +174,7 @@ static size_t carve(dp_stage* s, void* base) {
   s->qssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
   s->kssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
   s->rope_tok = s->heads_epi ? (float2*)cv.take(s->Smax * (c.head_dim / 2) * 8) : nullptr;
-  s->tau = (float*)cv.take(c.freq_dim * 4);
   s->e1 = (float*)cv.take(GEMV_MAX_SLICES * D * 4); s->e2 = (float*)cv.take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
-  s->e0 = (float*)cv.take(GEMV_MAX_SLICES * 6 * D * 4);
   s->mtab = (float*)cv.take(L * 6 * D * 4);
   s->mod = (float*)cv.take(L * 6 * D * 4);
   const int half = c.head_dim / 2, c_sp = c.head_dim / 6, c_f = half - 2 * c_sp;
@@ -412,13 +410,14 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
   // bf16 storage: the first LayerNorm reads x_in itself and leaves its fp32 copy in the residual stream, and
   // the last GEMM writes x_out next to its residual update, so neither end needs a conversion pass
   if (!bf) PROF(DP_PROF_CONVERT, launch_to_f32<T>((const T*)x_in, s->xres, S * D, st));
-  // adaLN modulation: sinusoidal features -> two-layer MLP (SiLU) -> SiLU -> 6*dim head, plus each layer's table
+  // adaLN modulation: sinusoidal features -> two-layer MLP (SiLU) -> SiLU -> 6*dim head, plus each layer's table; the first
+  // launch also builds the block's rotation table
   PROF(DP_PROF_MODULATION,
-       launch_sinusoid(t, c.freq_dim, s->tau, st);
-       launch_gemv<T>(s->tau, 1, 0, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, 0, s->e1, st);
-       launch_gemv<T>(s->e1, gemv_slices(c.freq_dim, (int)D), (int)D, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, 1, s->e2, st);
-       launch_gemv<T>(s->e2, gemv_slices((int)D, (int)D), (int)D, (const T*)s->w.bt2, (int)D, (const T*)s->w.wm, (int)(6 * D), 1, s->e0, st);
-       launch_mod_add<T>(s->mtab, s->e0, gemv_slices((int)D, (int)(6 * D)), (const T*)s->w.bm, s->mod, c.n_layers, (int)(6 * D), st));
+       const RopeTokens rope{s->rt, frame0, c.tok_h, c.tok_w, S, s->rope_tok};
+       const GemvTable<T> table{(const T*)s->w.bm, s->mtab, s->mod, c.n_layers};
+       int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, s->heads_epi ? &rope : nullptr, st);
+       parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e2, nullptr, nullptr, st);
+       launch_gemv<T>(GemvIn{s->e2, parts, 0.f}, (const T*)s->w.bt2, (int)D, (const T*)s->w.wm, (int)(6 * D), nullptr, &table, nullptr, st));
   const int64_t kv_hs = s->Lpad * d;        // head stride of kbuf
   // where this block's keys go: directly before the cached range if it fits there, else directly after it
   // (dp_cache_update left the cache where one side has room for a maximal block)
@@ -428,7 +427,6 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     else { blk0 = s->cache0 + s->cache_len; key0 = s->cache0; }
   }
   s->blk0 = blk0;
-  if (s->heads_epi) PROF(DP_PROF_NORM_ROPE, launch_rope_tokens(s->rt, frame0, c.tok_h, c.tok_w, S, s->rope_tok, st));
   for (int l = 0; l < c.n_layers; ++l) {
     const dp_layer_weights& w = s->lw[(size_t)l]; LayerMem& m = s->lm[(size_t)l];
     const float* md = s->mod + (int64_t)l * 6 * D;
