@@ -49,6 +49,12 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F&& f) {
 template <int C> __device__ __forceinline__ void lds_wait() {
   if constexpr (C < 15) __builtin_amdgcn_s_waitcnt(0xC07F | (C << 8));
 }
+// wait until at most C of this wavefront's vector-memory loads are outstanding (direct global -> LDS loads among them;
+// they complete in order)
+template <int C> __device__ __forceinline__ void vm_wait() {
+  static_assert(C < 64, "vmcnt has six bits");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (C & 15) | ((C >> 4) << 14));
+}
 // 16 bytes at LDS byte address addr + OFF through inline assembly: the compiler neither moves it nor waits for
 // it; the caller does (lds_wait) before the first use of the result
 template <int OFF> __device__ __forceinline__ u32x4 lds_read16_raw(uint32_t addr) {

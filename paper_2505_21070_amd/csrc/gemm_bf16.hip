@@ -52,7 +52,8 @@ template <int NM, int NR> constexpr int reads_before(int n, int first) {
   for (int k = 0; k < NR; ++k) c += first + k * (NM - first) / NR < n ? 1 : 0;
   return c;
 }
-template <int BM, int BN, int WGM, int WGN, int EPI>
+// ST = 2: the large-tile loop below.  ST > 2: small tiles with a ring of ST stages.
+template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
 __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
                                                              const bf16_t* __restrict__ Bt, int64_t ldb,
                                                              int64_t M, int64_t N, int64_t K, int tiles_n,
@@ -170,6 +171,51 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   // issued together right behind the barrier they fill the vector-memory queue, and a wavefront that waits
   // there to issue a load cannot issue the MFMAs behind it either.
   constexpr int NL = IA + IB, NS = (NM - NB) + NM;
+  if constexpr (ST > 2) {
+    // Ring of ST stages.  A small tile's k-tile is multiplied in a fraction of the time its loads travel, and a small
+    // problem has no second block to fill the gap, so ST - 1 k-tiles are in flight: tile kt is waited for by its place
+    // in the queue of vector loads (they arrive in order), not by an empty queue.  Behind the barrier every wavefront
+    // has tile kt, and all are done with tile kt - 1, whose stage the next loads go to.
+    static_assert(!A_RAGGED, "every wavefront issues the same loads");
+    static_assert(4 * NR <= 16, "one k-tile's fragment reads are counted in lgkmcnt");
+#pragma unroll
+    for (int z = 0; z < ST - 1; ++z)
+#pragma unroll
+      for (int q = 0; q < NL; ++q) load_part(z, z, q);
+    bf16x8 fr[4][NR];
+    int stage = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      const int behind = KT - 1 - kt;                    // tiles behind this one that are (or were) still to come
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<ST - 1>([&](auto r_) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_)::value;           // tiles in flight behind tile kt: min(ST - 2, behind)
+        if (r == ST - 2 ? behind >= r : behind == r) vm_wait<r * NL>();
+      });
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      const int nxt = stage == 0 ? ST - 1 : stage - 1;   // (kt + ST - 1) % ST
+#pragma unroll
+      for (int q = 0; q < NL; ++q) load_part(kt + ST - 1, nxt, q);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t base = (uint32_t)stage * STAGE * 16;
+      static_for<4 * NR>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int ks = decltype(i_)::value / NR, f = decltype(i_)::value % NR;
+        fr[ks][f] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fbase[f] + (base + (swz ^ (uint32_t)(ks * 32)))));
+      });
+      static_for<4>([&](auto ks_) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_)::value;
+        lds_wait<(3 - ks) * NR>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[ks][1 + j], fr[ks][i == 0 ? 0 : TN + i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      stage = stage + 1 == ST ? 0 : stage + 1;
+    }
+  } else {
 #pragma unroll
   for (int q = 0; q < NL; ++q) load_part(0, 0, q);
   tile_barrier();
@@ -209,6 +255,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
       });
     }
   }
+  }
   lds_wait<0>();
 
   // Epilogue.  The MFMAs ran with the weight rows as the A operand, so a lane holds the output row
@@ -217,6 +264,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   // consecutive lanes on consecutive addresses.  LDS rows are XOR-swizzled with the row index so that
   // neither the column-wise writes nor the row-wise reads conflict on banks.
   constexpr int NW = WGM * WGN;
+  constexpr int XM = BN / 4 < 32 ? BN / 4 - 1 : 31;      // row bits in the XOR: a row of 8-byte units has BN / 4 of them
   const bf16_t* bias = (const bf16_t*)e.bias;
   if constexpr (EPI == EPI_HEADS) {
     // Sections of `dim` columns, each stored per attention head (see HeadsArgs).  A plain section gets, per
@@ -246,7 +294,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
             uint2 pk;
             pk.x = cvt_pk_bf16(acc[i][j][q * 4 + 0] + bvr, acc[i][j][q * 4 + 1] + bvr);
             pk.y = cvt_pk_bf16(acc[i][j][q * 4 + 2] + bvr, acc[i][j][q * 4 + 3] + bvr);
-            l8[row * UPR + ((nl >> 2) ^ (row & 31))] = pk;
+            l8[row * UPR + ((nl >> 2) ^ (row & XM))] = pk;
           }
       }
     } else {
@@ -276,7 +324,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
             uint2 pk;
             pk.x = cvt_pk_bf16(v[0], v[1]);
             pk.y = cvt_pk_bf16(v[2], v[3]);
-            l8[row * UPR + ((nl >> 2) ^ (row & 31))] = pk;
+            l8[row * UPR + ((nl >> 2) ^ (row & XM))] = pk;
           }
         }
 #pragma unroll
@@ -331,7 +379,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
           const int row = wave * (BM / NW) + (it0 + g) * RP2 + lane / HC;
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
-            d[g][k] = smem[row * CPR + (((c8 >> 3) + k * HC) ^ ((row & 31) >> 1))];
+            d[g][k] = smem[row * CPR + (((c8 >> 3) + k * HC) ^ ((row & XM) >> 1))];
             if (row & 1) d[g][k] = make_uint4(d[g][k].z, d[g][k].w, d[g][k].x, d[g][k].y);
           }
           if (rotate && m0 + row < M) {
@@ -413,7 +461,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
               uint2 pk;
               pk.x = cvt_pk_bf16(v[0], v[1]);
               pk.y = cvt_pk_bf16(v[2], v[3]);
-              l8[row * UPR + ((nl >> 2) ^ (row & 31))] = pk;
+              l8[row * UPR + ((nl >> 2) ^ (row & XM))] = pk;
             }
           }
       }
@@ -423,9 +471,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
         const int row = wave * (RP / NW) + it * RPI + lane / CPR, p = lane % CPR;
         uint4 d = smem[row * CPR + p];
         // the chunk read holds units 2p and 2p+1 of the swizzled row, i.e. the two halves of logical
-        // chunk p ^ ((row & 31) >> 1), exchanged when the row index is odd
+        // chunk p ^ ((row & XM) >> 1), exchanged when the row index is odd
         if (row & 1) d = make_uint4(d.z, d.w, d.x, d.y);
-        const int64_t m = m0 + pass * RP + row, n = n0 + (p ^ ((row & 31) >> 1)) * 8;
+        const int64_t m = m0 + pass * RP + row, n = n0 + (p ^ ((row & XM) >> 1)) * 8;
         // streamed out once; non-temporal so that the output does not displace the operand panels the other
         // tiles still re-read from the caches (measured at the 14400 x 13824 x 5120 GELU shape: -3 %)
         if (m < M && n < N) __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)e.out + m * e.ldo + n));
@@ -515,32 +563,50 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI>
+template <int BM, int BN, int WGM, int WGN, int EPI, int ST = 2>
 static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, const EpiArgs& e, hipStream_t st) {
   constexpr int NT = WGM * WGN * 64;
-  constexpr size_t lds = (size_t)(BM + BN) * 128 * 2;
+  constexpr size_t lds = (size_t)(BM + BN) * 128 * ST;
   const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
   static std::atomic<uint64_t> done;
-  allow_dynamic_lds((const void*)k_gemm_bf16<BM, BN, WGM, WGN, EPI>, (int)lds, done);
+  allow_dynamic_lds((const void*)k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST>, (int)lds, done);
   HeadsArgs ha{};
   if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / BN; ha = *e.heads; }
   dim3 grid((unsigned)((tm * tn + 7) / 8 * 8));
-  k_gemm_bf16<BM, BN, WGM, WGN, EPI><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, e, ha);
+  k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, e, ha);
 }
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, int ST = 2>
 static void launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
-  if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU>(A, lda, Wt, ldw, M, N, K, e, st);
-  else launch_one<BM, BN, WGM, WGN, EPI_RESID>(A, lda, Wt, ldw, M, N, K, e, st);
+  if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE, ST>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU, ST>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID, ST>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if constexpr (ST > 2) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st);
 }
 
-// EPI_HEADS.  Sections must be whole tiles wide (dim % 256 == 0, or dim % 128 == 0 for problems small enough
-// for 128x128 tiles) and a transposed section needs a square tile, 8 | M and 8 | row0.
+// Which tile family a problem takes.  A 256-row tile keeps a CU busy by itself but a small problem has too few of them; small
+// tiles run as a ring of loads (see ST above), 64 x 64 ones up to three to a CU, 128 x 128 ones one.  Lines, measured at
+// 1560 x 1536 x 1536 (42 tiles of 256^2): 64^2 22 us, 128^2 ring 27, 128^2 with two stages 27; 1008 x 1024 x 4096 (16): 64^2 25,
+// 128^2 ring 51, two stages 63; 1008 x 4096 x 1024 (64): 128^2 ring 18, 64^2 20, 256^2 30; 1560 x 4608 x 1536 (126): 256^2 43,
+// 128^2 ring 47, 64^2 48; 1560 x 8960 x 1536 (245): 256^2 51, 64^2 79.
+enum { TILE_64 = 0, TILE_128 = 1, TILE_BIG = 2 };
+static int tile_family(int64_t M, int64_t N) {
+  if (((M + 63) / 64) * ((N + 63) / 64) <= 768) return TILE_64;        // three blocks per CU: one round
+  if (((M + 127) / 128) * ((N + 127) / 128) <= 256) return TILE_128;   // one block per CU: one round
+  return TILE_BIG;
+}
+static void launch_small(int family, const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                         int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
+  if (family == TILE_128) launch_cfg<128, 128, 2, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
+  // 64 KB of LDS (two blocks per CU) where two suffice, 48 KB where a third has to fit
+  else if (((M + 63) / 64) * ((N + 63) / 64) <= 512) launch_cfg<64, 64, 2, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
+  else launch_cfg<64, 64, 2, 2, 3>(A, lda, Wt, ldw, M, N, K, epi, e, st);
+}
+
+// EPI_HEADS.  Sections must be whole tiles wide and a transposed section needs a square tile, 8 | M and 8 | row0.
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
-  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  const int bn = t256 < 64 ? 128 : 256;
+  const int family = tile_family(M, N), bn = family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
   if (h.dim <= 0 || (h.head_dim != 64 && h.head_dim != 128) || h.dim % bn || h.dim % h.head_dim || N % h.dim || N / h.dim > 3) return false;
   for (int i = 0; i < (int)(N / h.dim); ++i) {
     if (h.sec[i].transposed && (M % 8 || h.sec[i].row0 % 8 || h.sec[i].ld % 8)) return false;
@@ -548,10 +614,9 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   }
   return true;
 }
-static void launch_gemm_bf16_heads(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                                   int64_t K, const EpiArgs& e, hipStream_t st) {
+static void launch_big_heads(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                             int64_t K, const EpiArgs& e, hipStream_t st) {
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  if (t256 < 64) { launch_one<128, 128, 2, 2, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st); return; }
   bool any_t = false;
   for (int i = 0; i < (int)(N / e.heads->dim); ++i) any_t = any_t || e.heads->sec[i].transposed;
   // the 160-row tile cannot exchange its operands; it pays where it fills the one round better (see below)
@@ -567,22 +632,20 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
                       int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
   if (M <= 0 || N <= 0) return true;
   if (K < 64 || K % 64) return false;          // whole k-tiles of 64 (the callers validate their widths)
-  if (epi == EPI_HEADS) {
-    if (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads)) return false;
-    launch_gemm_bf16_heads(A, lda, Wt, ldw, M, N, K, e, st);
-    return true;
-  }
+  if (epi == EPI_HEADS && (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads))) return false;
+  const int family = tile_family(M, N);
+  if (family != TILE_BIG) { launch_small(family, A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
+  if (epi == EPI_HEADS) { launch_big_heads(A, lda, Wt, ldw, M, N, K, e, st); return true; }
   // One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.
   // 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration comes out lower:
   // 192x256 (0.88 of a 256x256 tile), 160x256 (0.80; 1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6
   // tiles fill one round where 33 x 6 leave 58 CUs idle) and 320x256 (1.25, fewer operand bytes per flop).
   // The 160-, 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where
-  // that stays inside the 256-row padding the caller guarantees.  Tiny problems take 128x128 tiles.
+  // that stays inside the 256-row padding the caller guarantees.
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t192 = ((M + 191) / 192) * ((N + 255) / 256);
   const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
   const int64_t t320 = ((M + 319) / 320) * ((N + 255) / 256);
-  if (t256 < 64) { launch_cfg<128, 128, 2, 2>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
   const int64_t mpad = (M + 255) / 256 * 256;
   const double cost256 = (double)((t256 + 255) / 256);
   const double cost192 = (M + 191) / 192 * 192 <= mpad ? 0.88 * (double)((t192 + 255) / 256) : 1e30;

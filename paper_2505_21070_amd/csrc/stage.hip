@@ -170,7 +170,7 @@ static size_t carve(dp_stage* s, void* base) {
   const bool own = bf && c.weight_layout == DP_WEIGHTS_IN_OUT;   // the library keeps [out, in] copies of the matrices
   s->wtmp = own ? cv.take(rup(D, 256) * kmax * E) : nullptr;
   s->heads_epi = bf && D % 256 == 0;
-  s->ssq_np = (int)(D / 128);                         // most partial sums per row any tile shape produces
+  s->ssq_np = (int)(D / 64);                          // most partial sums per row any tile shape produces
   s->qssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
   s->kssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
   s->rope_tok = s->heads_epi ? (float2*)cv.take(s->Smax * (c.head_dim / 2) * 8) : nullptr;
