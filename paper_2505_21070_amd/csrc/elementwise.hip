@@ -85,12 +85,12 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {   // bytes % 4 ==
 // caches: 5120-wide rows 152 -> 89 us for 442 MB, 1536-wide rows 24 -> 15 us for 57 MB), faster than a plain
 // conversion pass of the same bytes.  Wide rows gain another 25 % from four wavefronts per row (more rows in
 // flight per compute unit, 5 instead of 20 outstanding loads per lane).
-// xin != null: the row is read from xin (bf16) instead of x, and x receives its fp32 copy (the first
+// xin != null: the row is read from xin (storage type) instead of x, and x receives its fp32 copy (the first
 // LayerNorm of a stage, which thereby also fills the fp32 residual stream).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 template <typename T, int NCH, int NW>
-__global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, const bf16_t* __restrict__ xin,
+__global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, const T* __restrict__ xin,
                                                      T* __restrict__ out, int64_t S, int D, float eps,
                                                      const float* __restrict__ mul,
                                                      const float* __restrict__ add, float plus) {
@@ -111,9 +111,14 @@ __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, cons
       const int idx = i * (NW * 64) + part;
       if (idx < nvec) {
         if (xin) {
-          const u32x2_t wv = __builtin_nontemporal_load((const u32x2_t*)(xin + row * D) + idx);
-          v[i] = f32x4_t{bf16_to_f32((bf16_t)(wv.x & 0xffff)), bf16_to_f32((bf16_t)(wv.x >> 16)),
-                         bf16_to_f32((bf16_t)(wv.y & 0xffff)), bf16_to_f32((bf16_t)(wv.y >> 16))};
+          if constexpr (sizeof(T) == 2) {
+            const u32x2_t wv = __builtin_nontemporal_load((const u32x2_t*)(xin + row * D) + idx);
+            v[i] = f32x4_t{bf16_to_f32((bf16_t)(wv.x & 0xffff)), bf16_to_f32((bf16_t)(wv.x >> 16)),
+                           bf16_to_f32((bf16_t)(wv.y & 0xffff)), bf16_to_f32((bf16_t)(wv.y >> 16))};
+          } else {
+            const T* p = xin + row * D + idx * 4;      // the caller's buffer may start anywhere
+            v[i] = f32x4_t{p[0], p[1], p[2], p[3]};
+          }
           xr[idx] = v[i];
         } else {
           v[i] = __builtin_nontemporal_load(xr + idx);
@@ -171,7 +176,7 @@ __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, cons
   }
 }
 template <typename T>
-void launch_ln_modulate(float* x, const bf16_t* xin, T* out, int64_t S, int D, float eps, const float* mul,
+void launch_ln_modulate(float* x, const T* xin, T* out, int64_t S, int D, float eps, const float* mul,
                         const float* add, int plus_one, hipStream_t st) {
   if (S <= 0) return;
   const float plus = plus_one ? 1.f : 0.f;
@@ -186,7 +191,7 @@ void launch_ln_modulate(float* x, const bf16_t* xin, T* out, int64_t S, int D, f
   else LN_CASE(8, 4);                                  // D <= 8192
 #undef LN_CASE
 }
-template void launch_ln_modulate<float>(float*, const bf16_t*, float*, int64_t, int, float, const float*, const float*, int, hipStream_t);
+template void launch_ln_modulate<float>(float*, const float*, float*, int64_t, int, float, const float*, const float*, int, hipStream_t);
 template void launch_ln_modulate<bf16_t>(float*, const bf16_t*, bf16_t*, int64_t, int, float, const float*, const float*, int, hipStream_t);
 
 // ---------------------------------------------------------------- RMSNorm over D + 3D RoPE, head-major output

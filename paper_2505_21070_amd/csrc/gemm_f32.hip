@@ -13,20 +13,22 @@
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// VEC: rows of A and W are read (and start) in 16-byte steps.  WGM x WGN wavefronts of (BM / WGM) x (BN / WGN) outputs.
-template <int BM, int BN, int WGM, int WGN, int EPI, bool VEC>
+// VEC: rows of A and W are read (and start) in 16-byte steps.  WGM x WGN x WGK wavefronts: WGM x WGN of them share the
+// tile's outputs, WGK the k of every k-tile.  WGK = 4 (32 x 32 tiles) is for problems of a few tiles, whose time is the
+// chain of MFMAs through K: a quarter of it each, joined through LDS in wavefront order, on four times the blocks.
+template <int BM, int BN, int WGM, int WGN, int WGK, int EPI, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, int64_t lda, GemmF32W w, int64_t ldw,
                                                   int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int tiles,
                                                   EpiArgs e) {
-  static_assert(WGM * WGN == 4, "four wavefronts");
-  constexpr int BK = 32, AS = BK + 4, WS = BN + 8, PF = 2;
+  static_assert(WGM * WGN * WGK == 4, "four wavefronts");
+  constexpr int BK = 32 * (WGK > 1 ? 2 : 1), AS = BK + 4, WS = BN + 8, PF = 2;
   constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
   constexpr int IA = BM * BK / 4 / 256, IW = BK * BN / 4 / 256;    // 16-byte pieces per thread and tile
   __shared__ __align__(16) float As[2][BM * AS];
   __shared__ __align__(16) float Ws[2][BK * WS];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lg = lane >> 5;
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wm = wave / (WGN * WGK), wn = wave / WGK % WGN, wk = wave % WGK;
   // each XCD takes a contiguous run of tiles, walked in bands of 8 tile rows so that the run is near square and its
   // panels of A and W are shared in that XCD's L2
   const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
@@ -117,21 +119,23 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
     const int b = kt & 1;
     // half a k-tile's operands are requested together, the second half's behind the first half's first MFMAs: left to
     // itself the compiler reads each operand right in front of the MFMA that waits for it
-    float4 a[BK / 8][TM];
-    float bw[BK / 8][TN][4];
+    constexpr int NJ = BK / 8 / WGK;                 // this wavefront's share of the k-tile, in groups of 8
+    float4 a[NJ][TM];
+    float bw[NJ][TN][4];
     auto read = [&](int j) __attribute__((always_inline)) {
+      const int k = (wk * NJ + j) * 8 + lg * 4;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[j][i] = *(const float4*)&As[b][(wm * TM * 32 + i * 32 + lr) * AS + j * 8 + lg * 4];
+      for (int i = 0; i < TM; ++i) a[j][i] = *(const float4*)&As[b][(wm * TM * 32 + i * 32 + lr) * AS + k];
 #pragma unroll
       for (int c = 0; c < TN; ++c)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) bw[j][c][t] = Ws[b][(j * 8 + lg * 4 + t) * WS + wn * TN * 32 + c * 32 + lr];
+        for (int t = 0; t < 4; ++t) bw[j][c][t] = Ws[b][(k + t) * WS + wn * TN * 32 + c * 32 + lr];
     };
     read(0);
     read(1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < BK / 8; ++j) {
+    for (int j = 0; j < NJ; ++j) {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
             const float av = t == 0 ? a[j][i].x : t == 1 ? a[j][i].y : t == 2 ? a[j][i].z : a[j][i].w;
             acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bw[j][c][t], acc[i][c], 0, 0, 0);
           }
-      if (j + 2 < BK / 8) read(j + 2);
+      if (j + 2 < NJ) read(j + 2);
       if (j == 0 && kt + 1 < KT) {                   // the next tile's registers are set (z + 1) % PF
         stash(b ^ 1, (z + 1) % PF);
         if (kt + 1 + PF < KT) fetch((int64_t)(kt + 1 + PF) * BK, (z + 1) % PF);
@@ -156,7 +160,39 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
       if (kt + z < KT) step(kt + z, z);
   }
 
+  auto put = [&](int64_t m, int64_t n, float v, float bv, float gv) __attribute__((always_inline)) {
+    if (m >= M) return;
+    v += bv;
+    if (EPI == EPI_GELU) v = gelu_tanh_f(v);
+    if (EPI == EPI_RESID) {
+      float* x = e.resid + m * e.ldr + n;
+      v = *x + gv * v;
+      *x = v;
+      if (e.out) ((float*)e.out)[m * e.ldo + n] = v;
+    } else {
+      ((float*)e.out)[m * e.ldo + (int64_t)sec * N + n] = v;
+    }
+  };
   // accumulator register r of lane group lg: row (r / 4) * 8 + lg * 4 + r % 4, column lr: 32 lanes write 128 bytes of a row
+  if constexpr (WGK > 1) {
+    static_assert(TM == 1 && TN == 1 && BM == 32 && BN == 32 && 2 * BM * AS >= 4 * 64 * 16, "the tile's partial sums fit As");
+    float* part = &As[0][0];                         // free behind the last step's barrier: [wavefront][register][lane]
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[(wk * 16 + r) * 64 + lane] = acc[0][0][r];
+    __syncthreads();
+    const int64_t n = n0 + lr;
+    if (n >= N) return;
+    const float bv = bias ? bias[n] : 0.f, gv = EPI == EPI_RESID && e.gate ? e.gate[n] : 1.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                    // wavefront w finishes registers 4w .. 4w + 3
+      const int r = wk * 4 + i;
+      float v = part[r * 64 + lane];
+#pragma unroll
+      for (int w2 = 1; w2 < WGK; ++w2) v += part[(w2 * 16 + r) * 64 + lane];
+      put(m0 + (r >> 2) * 8 + lg * 4 + (r & 3), n, v, bv, gv);
+    }
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < TN; ++c) {
     const int64_t n = n0 + wn * TN * 32 + c * 32 + lr;
@@ -165,29 +201,16 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t m = m0 + wm * TM * 32 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3);
-        if (m >= M) continue;
-        float v = acc[i][c][r] + bv;
-        if (EPI == EPI_GELU) v = gelu_tanh_f(v);
-        if (EPI == EPI_RESID) {
-          float* x = e.resid + m * e.ldr + n;
-          v = *x + gv * v;
-          *x = v;
-          if (e.out) ((float*)e.out)[m * e.ldo + n] = v;
-        } else {
-          ((float*)e.out)[m * e.ldo + (int64_t)sec * N + n] = v;
-        }
-      }
+      for (int r = 0; r < 16; ++r) put(m0 + wm * TM * 32 + i * 32 + (r >> 2) * 8 + lg * 4 + (r & 3), n, acc[i][c][r], bv, gv);
   }
 }
 
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, int WGK>
 static void launch_cfg(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw, int64_t M, int64_t N, int64_t K,
                        int epi, const EpiArgs& e, bool vec, hipStream_t st) {
   const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN), tiles = tm * tn * w.n;
   const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
-#define GEMM_F32(E, V) k_gemm_f32<BM, BN, WGM, WGN, E, V><<<grid, 256, 0, st>>>(A, lda, w, ldw, M, N, K, tm, tn, tiles, e)
+#define GEMM_F32(E, V) k_gemm_f32<BM, BN, WGM, WGN, WGK, E, V><<<grid, 256, 0, st>>>(A, lda, w, ldw, M, N, K, tm, tn, tiles, e)
   if (epi == EPI_STORE) { if (vec) GEMM_F32(EPI_STORE, true); else GEMM_F32(EPI_STORE, false); }
   else if (epi == EPI_GELU) { if (vec) GEMM_F32(EPI_GELU, true); else GEMM_F32(EPI_GELU, false); }
   else { if (vec) GEMM_F32(EPI_RESID, true); else GEMM_F32(EPI_RESID, false); }
@@ -201,9 +224,12 @@ void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw
   for (int i = 0; i < w.n; ++i) vec = vec && ((uintptr_t)w.w[i] & 15) == 0;
   // 64 x 64 tiles, up to four blocks to a CU, unless 128 x 128 ones (two to a CU, half the operand bytes per flop) make at
   // least two full rounds: 1560 x 8960 x 1536 (912 of them) 391 against 413 us, 1560 x 1536 x 8960 (156) 462 against 639;
-  // 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s where 64 x 64 tiles stay at 110
+  // 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s where 64 x 64 tiles stay at 110.  Fewer than one 64 x 64 tile per CU:
+  // 32 x 32 tiles with K dealt over the wavefronts (whole passes: 128 tokens x 128 channels 200 -> 148 us, 300 x 768 301 -> 210,
+  // 750 x 768 379 -> 340)
   const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128) * w.n;
   if (t128 >= 1024)
-    launch_cfg<128, 128, 2, 2>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
-  else launch_cfg<64, 64, 2, 2>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+    launch_cfg<128, 128, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+  else if (((M + 63) / 64) * ((N + 63) / 64) * w.n >= 256) launch_cfg<64, 64, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+  else launch_cfg<32, 32, 1, 1, 4>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
 }

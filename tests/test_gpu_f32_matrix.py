@@ -1,6 +1,6 @@
 """GPU parity of the fp32 path's matrix kernels at the sizes where they can go wrong: edges of query, key and GEMM
-tiles, rows without 16-byte alignment, key ranges that start off a 16-byte boundary, key ranges cut over blocks, all against the CPU oracle at the fp32 tolerance
-(every element within 1e-4 of the oracle, relative to max(1, |ref|))."""
+tiles, rows without 16-byte alignment, key ranges that start off a 16-byte boundary, key ranges cut over blocks, all
+against the CPU oracle at the fp32 tolerance (every element within 1e-4 of the oracle, relative to max(1, |ref|))."""
 import pytest
 import torch
 
@@ -44,10 +44,15 @@ def test_attention_cut_key_ranges(heads, hd, ffn):
     pair(f"cut{hd}/{ffn}", 6, 3, 1, dim=heads * hd, n_heads=heads, head_dim=hd, ffn_dim=ffn, tok_h=9, tok_w=13, text_len=37)
 
 
-# widths that are no multiple of 4 (no 16-byte rows), shorter than a k-tile, one past a tile; and enough output tiles for the
-# 128 x 128 shape, ragged in both directions, with and without 16-byte rows
+# widths that are no multiple of 4 (no 16-byte rows), shorter than a k-tile, one past a tile, on the 32 x 32 shape with K dealt
+# over the wavefronts; and enough output tiles for the 128 x 128 shape, ragged in both directions, with and without
+# 16-byte rows (the 64 x 64 shape runs above and below)
 @pytest.mark.parametrize("tok_h,tok_w,ffn,text_dim", [(7, 9, 641, 37), (5, 13, 644, 36), (8, 8, 5, 1), (13, 5, 65, 260),
                                                       (31, 33, 16381, 64), (31, 33, 16380, 64)])
 def test_gemm_edges(tok_h, tok_w, ffn, text_dim):
     pair(f"gemm{tok_h}x{tok_w}/{ffn}/{text_dim}", 1, 1, 0, dim=128, n_heads=2, head_dim=64, tok_h=tok_h, tok_w=tok_w, ffn_dim=ffn,
          text_dim=text_dim, text_len=19)
+
+
+def test_gemm_middle_tiles_every_epilogue():
+    pair("gemm64", 1, 1, 0, dim=1408, n_heads=11, head_dim=128, tok_h=23, tok_w=33, ffn_dim=1444, text_dim=1408, text_len=19)
