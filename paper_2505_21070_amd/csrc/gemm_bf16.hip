@@ -52,7 +52,8 @@ template <int NM, int NR> constexpr int reads_before(int n, int first) {
   for (int k = 0; k < NR; ++k) c += first + k * (NM - first) / NR < n ? 1 : 0;
   return c;
 }
-// ST = 2: the large-tile loop below.  ST > 2: small tiles with a ring of ST stages.
+// ST: LDS stages.  Tiles of more than 128 rows run the pinned loop below (two stages, or three where they fit), smaller ones
+// a ring of ST > 2.
 template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
 __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
                                                              const bf16_t* __restrict__ Bt, int64_t ldb,
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   // issued together right behind the barrier they fill the vector-memory queue, and a wavefront that waits
   // there to issue a load cannot issue the MFMAs behind it either.
   constexpr int NL = IA + IB, NS = (NM - NB) + NM;
-  if constexpr (ST > 2) {
+  if constexpr (ST > 2 && BM <= 128) {
     // Ring of ST stages.  A small tile's k-tile is multiplied in a fraction of the time its loads travel, and a small
     // problem has no second block to fill the gap, so ST - 1 k-tiles are in flight: tile kt is waited for by its place
     // in the queue of vector loads (they arrive in order), not by an empty queue.  Behind the barrier every wavefront
@@ -216,17 +217,38 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
       stage = stage + 1 == ST ? 0 : stage + 1;
     }
   } else {
+  // Barrier behind which tile `next` (its loads the oldest in flight) is in LDS for everyone and the stage read before it is
+  // free.  With three stages the loads of the tile after it stay in flight: a wavefront waits for all but its own share of
+  // that tile (the last wavefronts' share is shorter where the A tile does not divide).
+  auto next_tile = [&](bool more) __attribute__((always_inline)) {
+    if constexpr (ST == 2) {
+      tile_barrier();
+    } else {
+      lds_wait<0>();
+      if (!more) vm_wait<0>();
+      else if (!A_RAGGED || (wave + 1) * IA * 64 <= BM * 8) vm_wait<NL>();
+      else if (wave * IA * 64 >= BM * 8) vm_wait<IB>();
+      else vm_wait<IB + (BM * 8 / 64) % IA>();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  static_assert(!A_RAGGED || BM * 8 % 64 == 0, "whole wavefront instructions");
 #pragma unroll
-  for (int q = 0; q < NL; ++q) load_part(0, 0, q);
-  tile_barrier();
+  for (int z = 0; z < ST - 1; ++z)
+#pragma unroll
+    for (int q = 0; q < NL; ++q) load_part(z, z, q);
+  next_tile(KT > 1);
   static_for<NL>([&](auto q_) __attribute__((always_inline)) {
     constexpr int q = decltype(q_)::value;
-    if constexpr (q * NS / NL < NM - NB) load_part(1, 1, q);           // the part that k-step 3 would have issued
+    if constexpr (q * NS / NL < NM - NB) load_part(ST - 1, ST - 1, q);           // the part that k-step 3 would have issued
   });
 #pragma unroll
   for (int f = 0; f < NR; ++f) read_frag(0, 0, f, 0);
+  int s_cur = 0, s_nxt = 1, s_prev = ST - 1;             // stages of tiles kt, kt + 1 and kt - 1
   for (int kt = 0; kt < KT; ++kt) {
-    const uint32_t cur = (uint32_t)(kt & 1) * STAGE * 16, nxt = (uint32_t)((kt + 1) & 1) * STAGE * 16;
+    const uint32_t cur = (uint32_t)s_cur * STAGE * 16, nxt = (uint32_t)s_nxt * STAGE * 16;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       static_for<NM>([&](auto n_) __attribute__((always_inline)) {
@@ -237,7 +259,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
           if constexpr (need > prev) lds_wait<NR - 1 - need + reads_before<NM, NR>(n, 0)>();
         } else {
           if constexpr (n < NB) { if constexpr (need > prev) lds_wait<NR - 1 - need>(); }
-          if constexpr (n == NB) tile_barrier();           // every read of this k-tile has landed (lgkmcnt(0) precedes it)
+          if constexpr (n == NB) next_tile(kt + 2 < KT);   // every read of this k-tile has landed (lgkmcnt(0) precedes it)
         }
         __builtin_amdgcn_sched_barrier(0);               // the MFMA stays behind the wait for its fragments
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
@@ -248,12 +270,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
         });
         static_for<NL>([&](auto q_) __attribute__((always_inline)) {
           constexpr int q = decltype(q_)::value, slot = q * NS / NL;       // MFMAs after the barrier
-          if (ks == 3) { if constexpr (n >= NB && slot == n - NB) load_part(kt + 2, kt & 1, q); }
-          else if (ks == 0) { if constexpr (slot == (NM - NB) + n) load_part(kt + 1, (kt + 1) & 1, q); }
+          if (ks == 3) { if constexpr (n >= NB && slot == n - NB) load_part(kt + ST, s_cur, q); }
+          else if (ks == 0) { if constexpr (slot == (NM - NB) + n) load_part(kt + ST - 1, s_prev, q); }
         });
         __builtin_amdgcn_sched_barrier(0);               // keeps the MFMAs, reads, loads and waits in this order
       });
     }
+    s_prev = s_cur; s_cur = s_nxt; s_nxt = s_nxt + 1 == ST ? 0 : s_nxt + 1;
   }
   }
   lds_wait<0>();
@@ -274,7 +297,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
     // across lanes.  A transposed section is C^T already.
     constexpr int UPR = BN / 4, CPR = BN / 8, RPI = 64 / CPR;
     static_assert(BM * BN * 2 <= (BM + BN) * 256, "EPI_HEADS stages the whole tile at once");
-    __shared__ float red[BM * WGN];                      // [row][wavefront column]: sums of squares
+    // [row][wavefront column]: sums of squares; behind the staged tile where three stages leave no static LDS
+    constexpr bool RED_DYN = ST == 3 && BM > 128;
+    __shared__ float red_static[RED_DYN ? 1 : BM * WGN];
+    float* const red = RED_DYN ? (float*)smem + BM * BN / 2 : red_static;
+    static_assert(!RED_DYN || BM * BN * 2 + BM * WGN * 4 <= (BM + BN) * 128 * ST, "the sums fit behind the tile");
     const HeadSection sc = ha.sec[sec];
     const int64_t nsec = n0 - (int64_t)sec * ha.dim;     // first column of this tile inside its section
     const int hshift = ha.head_dim == 128 ? 7 : 6, hmask = ha.head_dim - 1;
@@ -582,7 +609,7 @@ static void launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t l
   if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID, ST>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if constexpr (ST > 2) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if constexpr (ST > 2 && BM <= 128) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st);
 }
 
 // Which tile family a problem takes.  A 256-row tile keeps a CU busy by itself but a small problem has too few of them; small
@@ -623,7 +650,7 @@ static void launch_big_heads(const bf16_t* A, int64_t lda, const bf16_t* Wt, int
   const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
   const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
   if (!any_t && fits160 && 0.80 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256))
-    launch_one<160, 256, 1, 8, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
+    launch_one<160, 256, 1, 8, EPI_HEADS, 3>(A, lda, Wt, ldw, M, N, K, e, st);
   else
     launch_one<256, 256, 2, 4, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
 }
@@ -655,7 +682,7 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
   // on a tie the taller tile wins: fewer operand bytes per flop
   if (best == cost320) { launch_cfg<320, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
   if (best == cost256) { launch_cfg<256, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
-  if (best == cost160) { launch_cfg<160, 256, 1, 8>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
+  if (best == cost160) { launch_cfg<160, 256, 1, 8, 3>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
   launch_cfg<192, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
   return true;
 }
