@@ -80,8 +80,9 @@ __device__ __forceinline__ float gelu_tanh_f(float v) {
 }
 __device__ __forceinline__ float silu_f(float v) { return v / (1.0f + __expf(-v)); }
 
-// GEMM epilogue selector (shared by the fp32 and the bf16 GEMM kernels; EPI_HEADS is bf16 only)
-enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_HEADS = 3 };
+// GEMM epilogue selector (shared by the fp32 and the bf16 GEMM kernels; EPI_HEADS is bf16 only).  EPI_PART is internal to
+// the bf16 GEMM: one K range's plain fp32 sums, for a launch that adds the ranges up.
+enum { EPI_STORE = 0, EPI_GELU = 1, EPI_RESID = 2, EPI_HEADS = 3, EPI_PART = 4 };
 
 struct RopeTables {            // cos/sin pairs: tab[pos][pair] = (cos, sin)
   const float2* f; const float2* y; const float2* x;
@@ -118,4 +119,6 @@ struct EpiArgs {
   int64_t ldr;
   const float* gate;    // EPI_RESID: fp32 [N] or null (= 1)
   HeadsArgs* heads;        // EPI_HEADS: host pointer, copied into the launch; its ssq_np is filled in
+  float* scratch;          // EPI_RESID (bf16 GEMM): memory for partial sums over cut K ranges, or null to never cut
+  size_t scratch_floats;
 };

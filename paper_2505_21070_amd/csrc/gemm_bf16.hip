@@ -58,7 +58,7 @@ template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
 __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
                                                              const bf16_t* __restrict__ Bt, int64_t ldb,
                                                              int64_t M, int64_t N, int64_t K, int tiles_n,
-                                                             int tiles, EpiArgs e, HeadsArgs ha) {
+                                                             int tiles, int parts, EpiArgs e, HeadsArgs ha) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -75,15 +75,16 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   // of work ids (row-major tiles, so neighbours share the A row-panel and walk the B panels together).
   // The grid is padded to a multiple of 8; the padding blocks have nothing to do.
   const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  if (pid >= tiles) return;
-  const int tile = pid;
+  if (pid >= tiles * parts) return;
+  const int part = EPI == EPI_PART ? pid / tiles : 0, tile = EPI == EPI_PART ? pid % tiles : pid;   // K range, output tile
   // tiles are walked in bands of 4 tile rows, column by column inside a band: the ~32 blocks an XCD runs
   // at a time then cover about 4 x 8 tiles and share 4 A panels and 8 B panels instead of 1 and 32
   const int tiles_m = tiles / tiles_n;
   const int band = tile / (4 * tiles_n), in_band = tile % (4 * tiles_n);
   const int band_rows = tiles_m - band * 4 < 4 ? tiles_m - band * 4 : 4;
   const int64_t m0 = (int64_t)(band * 4 + in_band % band_rows) * BM, n0 = (int64_t)(in_band / band_rows) * BN;
-  const int KT = (int)(K / 64);
+  const int kt0 = EPI == EPI_PART ? (int)((K / 64) * part / parts) : 0;
+  const int KT = EPI == EPI_PART ? (int)((K / 64) * (part + 1) / parts) - kt0 : (int)(K / 64);
 
   // EPI_HEADS: a tile of a section that is stored channel-major is computed with the operands exchanged
   // (square tiles only), so that its accumulators, staging tile and row stores are those of C^T
@@ -93,8 +94,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
     sec = (int)(n0 / ha.dim);
     if constexpr (BM == BN) swapped = ha.sec[sec].transposed != 0;
   }
-  const bf16_t* const pa = swapped ? Bt + n0 * ldb : A + m0 * lda;
-  const bf16_t* const pb = swapped ? A + m0 * lda : Bt + n0 * ldb;
+  const bf16_t* const pa = (swapped ? Bt + n0 * ldb : A + m0 * lda) + kt0 * 64;
+  const bf16_t* const pb = (swapped ? A + m0 * lda : Bt + n0 * ldb) + kt0 * 64;
   const int64_t lpa = swapped ? ldb : lda, lpb = swapped ? lda : ldb;
   // slot p of a tile holds chunk (p & 7) ^ ((row >> 1) & 7) of row p >> 3; one wavefront instruction
   // fills slots [base, base + 64), lane l the slot base + l
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
         }
       }
     }
-  } else if constexpr (EPI != EPI_RESID) {
+  } else if constexpr (EPI != EPI_RESID && EPI != EPI_PART) {
     constexpr int UPR = BN / 4;                          // 8-byte units (4 bf16) per LDS row
     constexpr int CPR = BN / 8, RPI = 64 / CPR;          // 16-byte chunks per row, rows per wavefront read
     // the whole tile at once if it fits the two operand buffers, else one wavefront row (WM rows) per pass
@@ -507,7 +508,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
       }
     }
   } else {
-    // residual stream: x[m, n] += gate[n] * (acc + bias[n]) in fp32.  Passes over the wavefront rows of the
+    // residual stream: x[m, n] += gate[n] * (acc + bias[n]) in fp32 (EPI_PART: this range's x[m, n] = acc).  Passes over the wavefront rows of the
     // block tile and, inside one, over groups of GI 32-row accumulator tiles: as many as fit in LDS as floats
     constexpr int CPR = BN / 4, RPI = 64 / CPR;          // 16-byte chunks (4 floats) per row
     constexpr int GI_FIT = (BM + BN) * 256 / (32 * BN * 4), GI = GI_FIT < TM ? GI_FIT : TM;
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
           if (r < gi * 32) {
             const int row = r + lane / CPR, p = lane % CPR;
             const int64_t m = m0 + pass * WM + i0 * 32 + row, n = n0 + (p ^ (row & 15)) * 4;
-            if (m < M && n < N) xpre[it] = *(const float4*)(e.resid + m * e.ldr + n);
+            if (EPI == EPI_RESID && m < M && n < N) xpre[it] = *(const float4*)(e.resid + m * e.ldr + n);
           }
         }
         __syncthreads();
@@ -540,7 +541,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
               const int nl = wn * WN + j * 32 + q * 8 + lg * 4;
               float bv[4] = {0.f, 0.f, 0.f, 0.f};
               float4 gv = make_float4(1.f, 1.f, 1.f, 1.f);
-              if (n0 + nl < N) {
+              if (EPI == EPI_RESID && n0 + nl < N) {
                 if (bias) {
                   const uint2 b4 = *(const uint2*)(bias + n0 + nl);
                   bv[0] = bf16_to_f32((bf16_t)(b4.x & 0xffff)); bv[1] = bf16_to_f32((bf16_t)(b4.x >> 16));
@@ -573,6 +574,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
             const float4 v = l16[row * CPR + p];
             const int64_t m = m0 + pass * WM + i0 * 32 + row, n = n0 + (p ^ (row & 15)) * 4;
             if (m < M && n < N) {
+              if constexpr (EPI == EPI_PART) {
+                *(float4*)(e.resid + (int64_t)part * M * e.ldr + m * e.ldr + n) = v;
+                continue;
+              }
               float4 xv = xpre[it];
               xv.x += v.x; xv.y += v.y; xv.z += v.z; xv.w += v.w;
               *(float4*)(e.resid + m * e.ldr + n) = xv;
@@ -592,7 +597,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
 
 template <int BM, int BN, int WGM, int WGN, int EPI, int ST = 2>
 static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                       int64_t K, const EpiArgs& e, hipStream_t st) {
+                       int64_t K, const EpiArgs& e, hipStream_t st, int parts = 1) {
   constexpr int NT = WGM * WGN * 64;
   constexpr size_t lds = (size_t)(BM + BN) * 128 * ST;
   const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
@@ -600,8 +605,8 @@ static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t l
   allow_dynamic_lds((const void*)k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST>, (int)lds, done);
   HeadsArgs ha{};
   if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / BN; ha = *e.heads; }
-  dim3 grid((unsigned)((tm * tn + 7) / 8 * 8));
-  k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, e, ha);
+  dim3 grid((unsigned)((tm * tn * parts + 7) / 8 * 8));
+  k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
 }
 template <int BM, int BN, int WGM, int WGN, int ST = 2>
 static void launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
@@ -655,12 +660,78 @@ static void launch_big_heads(const bf16_t* A, int64_t lda, const bf16_t* Wt, int
     launch_one<256, 256, 2, 4, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
 }
 
+// x[m, n] += gate[n] * (bias[n] + sum over the K ranges, in range order), and its rounded copy
+__global__ __launch_bounds__(256) void k_add_parts(const float* __restrict__ part, int parts, int64_t M, int64_t N, EpiArgs e) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i >= M * N) return;
+  const int64_t m = i / N, n = i % N;
+  float4 s = *(const float4*)(part + i);
+  for (int p = 1; p < parts; ++p) {
+    const float4 v = *(const float4*)(part + (int64_t)p * M * N + i);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  if (e.bias) {
+    const uint2 b = *(const uint2*)((const bf16_t*)e.bias + n);
+    s.x += bf16_to_f32((bf16_t)(b.x & 0xffff)); s.y += bf16_to_f32((bf16_t)(b.x >> 16));
+    s.z += bf16_to_f32((bf16_t)(b.y & 0xffff)); s.w += bf16_to_f32((bf16_t)(b.y >> 16));
+  }
+  float4 x = *(const float4*)(e.resid + m * e.ldr + n);
+  const float4 g = e.gate ? *(const float4*)(e.gate + n) : make_float4(1.f, 1.f, 1.f, 1.f);
+  x.x += g.x * s.x; x.y += g.y * s.y; x.z += g.z * s.z; x.w += g.w * s.w;
+  *(float4*)(e.resid + m * e.ldr + n) = x;
+  if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x.x, x.y), cvt_pk_bf16(x.z, x.w));
+}
+size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
+  const size_t most = (size_t)256 * 256 * 256 * 4, need = (size_t)(8 * M * N * 4);      // one round of 256 x 256 tiles
+  return need < most ? need : most;
+}
+// Cutting K.  A long K over few tiles leaves most CUs idle, and small tiles in the hundreds move several times the bytes of
+// large ones through the caches.  Tiles whose K is cut over blocks until about one round of CUs is full do neither, for the
+// price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile 1.3
+// (256 x 256), 1.25 (160 x 256, three stages), 0.27 per block on the CU (64 x 64), 8 (4) for a block's ends, 3 for the
+// second launch, partials at 4 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU, 0.72 for 128 x 128, 1.3 per round
+// of 256 x 256.
+enum { CUT_256 = 0, CUT_160 = 1, CUT_64 = 2 };
+static int split_parts(int64_t M, int64_t N, int64_t K, const EpiArgs& e, int* tile) {
+  if (!e.scratch || N % 4 || e.ldr % 4) return 1;
+  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t160 = ((M + 159) / 160) * ((N + 255) / 256);
+  const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), KT = K / 64;
+  const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
+  const int family = tile_family(M, N);
+  double best = family == TILE_BIG ? 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8
+              : family == TILE_128 ? 0.72 * (double)KT + 5 : 0.24 * (double)(KT * ((t64 + 255) / 256)) + 5;
+  best *= 0.9;                                         // not for a few per cent
+  int parts = 1;
+  for (int p = 2; p <= 8; ++p) {
+    if ((size_t)(p * M * N) > e.scratch_floats) break;
+    const double extra = 3 + (double)(M * N) * 4 * (2 * p + 2.5) / 4e6, kt = (double)((KT + p - 1) / p);
+    const double cost[3] = {t256 * p <= 256 && KT / p >= 8 ? 1.3 * kt + 8 + extra : 1e30,
+                            fits160 && t160 * p <= 256 && KT / p >= 8 ? 1.25 * kt + 8 + extra : 1e30,
+                            t64 * p <= 512 && KT / p >= 4 ? 0.27 * kt * (double)((t64 * p + 255) / 256) + 4 + extra : 1e30};
+    for (int w = 0; w < 3; ++w)
+      if (cost[w] < best) { best = cost[w]; parts = p; *tile = w; }
+  }
+  return parts;
+}
+
 bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                       int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
   if (M <= 0 || N <= 0) return true;
   if (K < 64 || K % 64) return false;          // whole k-tiles of 64 (the callers validate their widths)
   if (epi == EPI_HEADS && (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads))) return false;
   const int family = tile_family(M, N);
+  if (epi == EPI_RESID) {
+    int tile = CUT_256;
+    const int parts = split_parts(M, N, K, e, &tile);
+    if (parts > 1) {
+      const EpiArgs p{nullptr, 0, nullptr, e.scratch, N, nullptr, nullptr, nullptr, 0};
+      if (tile == CUT_64) launch_one<64, 64, 2, 2, EPI_PART, 4>(A, lda, Wt, ldw, M, N, K, p, st, parts);
+      else if (tile == CUT_160) launch_one<160, 256, 1, 8, EPI_PART, 3>(A, lda, Wt, ldw, M, N, K, p, st, parts);
+      else launch_one<256, 256, 2, 4, EPI_PART>(A, lda, Wt, ldw, M, N, K, p, st, parts);
+      k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, parts, M, N, e);
+      return true;
+    }
+  }
   if (family != TILE_BIG) { launch_small(family, A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
   if (epi == EPI_HEADS) { launch_big_heads(A, lda, Wt, ldw, M, N, K, e, st); return true; }
   // One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.

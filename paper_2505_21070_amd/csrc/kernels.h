@@ -93,6 +93,9 @@ inline void allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_
 // A must be readable for roundup(M, 256) rows, Wt for roundup(N, 256) rows; K % 64 == 0.
 bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M,
                       int64_t N, int64_t K, int epi, const EpiArgs& e, hipStream_t st);
+// EPI_RESID may cut K into ranges whose partial sums go through e.scratch (a second launch adds them up, in range order);
+// what a problem of up to M rows can make use of:
+size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N);
 // whether launch_gemm_bf16(.., EPI_HEADS, ..) can take this problem; if not it launches nothing and returns false
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h);
 // ---- attn_bf16.hip : flash attention on MFMA, head_dim 64 or 128 ------------------------------

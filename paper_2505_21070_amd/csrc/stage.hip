@@ -78,7 +78,8 @@ struct dp_stage {
   float *e1, *e2, *mtab, *mod;
   float2 *rope_f, *rope_y, *rope_x; RopeTables rt;
   void* tap_attn; float *tap_xself, *tap_xcross;
-  float* attn_scratch; size_t attn_scratch_floats;   // partial results of attention over cut key ranges
+  float* attn_scratch; size_t attn_scratch_floats;   // partial results of attention over cut key ranges and of
+                                                       // the residual GEMMs over cut K ranges
   // DP_BF16 with dim % 256 == 0: the q/k/v and cross-q projections write per head from their GEMM epilogues
   // (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
   float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi; bool launch_ok = true;
@@ -201,8 +202,9 @@ static size_t carve(dp_stage* s, void* base) {
   }
   const size_t zero_end = cv.off;      // everything up to here is zero-filled at init
   // the fp32 path borrows the FFN's intermediate buffer, which nothing uses while attention runs
-  s->attn_scratch = bf ? (float*)cv.take(attn_bf16_scratch_bytes(c.head_dim)) : (float*)s->mid;
-  s->attn_scratch_floats = bf ? attn_bf16_scratch_bytes(c.head_dim) / 4 : (size_t)(s->Spad * F);
+  const size_t sa = attn_bf16_scratch_bytes(c.head_dim), sg = gemm_bf16_scratch_bytes(s->Spad, D), sb = sa > sg ? sa : sg;
+  s->attn_scratch = bf ? (float*)cv.take(sb) : (float*)s->mid;
+  s->attn_scratch_floats = bf ? sb / 4 : (size_t)(s->Spad * F);
   if (bf) {
     for (int64_t l = 0; l < L; ++l) {
       LayerMem& m = s->lm[(size_t)l];
@@ -266,8 +268,8 @@ template <> struct Path<bf16_t> {
 };
 
 static EpiArgs epi_store(void* out, int64_t ldo, const void* bias) { return EpiArgs{out, ldo, bias, nullptr, 0, nullptr}; }
-static EpiArgs epi_resid(float* resid, int64_t ldr, const void* bias, const float* gate) {
-  return EpiArgs{nullptr, 0, bias, resid, ldr, gate};
+static EpiArgs epi_resid(dp_stage* s, const void* bias, const float* gate) {
+  return EpiArgs{nullptr, 0, bias, s->xres, s->cfg.dim, gate, nullptr, s->attn_scratch, s->attn_scratch_floats};
 }
 
 // ------------------------------------------------------------------------------------------ init
@@ -465,7 +467,7 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
          Path<T>::attn(s->qbuf, s->Spad * d, m.kbuf, kv_hs, key0, m.vtbuf, s->Lpad, S,
                        s->cache_len + S, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, s->heads_epi ? &qn : nullptr, st));
     if (s->tap_attn && l == c.n_layers - 1) launch_copy2d<T>((const T*)s->attn_o, 0, (T*)s->tap_attn, 0, 1, S * D, st);
-    PROF(DP_PROF_OPROJ_GEMM, Path<T>::gemm(s->attn_o, D, w.wo, m.wo_t, S, D, D, EPI_RESID, epi_resid(s->xres, D, w.bo, g1), st));
+    PROF(DP_PROF_OPROJ_GEMM, Path<T>::gemm(s->attn_o, D, w.wo, m.wo_t, S, D, D, EPI_RESID, epi_resid(s, w.bo, g1), st));
     if (s->tap_xself && l == c.n_layers - 1) launch_copy2d<float>(s->xres, 0, s->tap_xself, 0, 1, S * D, st);
     // --- cross-attention to the text tokens
     PROF(DP_PROF_LN, launch_ln_modulate<T>(s->xres, nullptr, (T*)s->hbuf, S, (int)D, c.eps, m.ln3g, m.ln3b, 0, st));
@@ -488,12 +490,12 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
       PROF(DP_PROF_CROSS_ATTN,
            Path<T>::attn(s->qbuf, s->Spad * d, m.tk, s->Ltpad * d, 0, m.tvt, s->Ltpad, S, c.text_len, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, nullptr, st));
     }
-    PROF(DP_PROF_CROSS_O_GEMM, Path<T>::gemm(s->attn_o, D, w.cwo, m.cwo_t, S, D, D, EPI_RESID, epi_resid(s->xres, D, w.cbo, nullptr), st));
+    PROF(DP_PROF_CROSS_O_GEMM, Path<T>::gemm(s->attn_o, D, w.cwo, m.cwo_t, S, D, D, EPI_RESID, epi_resid(s, w.cbo, nullptr), st));
     if (s->tap_xcross && l == c.n_layers - 1) launch_copy2d<float>(s->xres, 0, s->tap_xcross, 0, 1, S * D, st);
     // --- FFN
     PROF(DP_PROF_LN, launch_ln_modulate<T>(s->xres, nullptr, (T*)s->hbuf, S, (int)D, c.eps, sc2, sh2, 1, st));
     PROF(DP_PROF_FFN1_GEMM, Path<T>::gemm(s->hbuf, D, w.w1, m.w1_t, S, F, D, EPI_GELU, epi_store(s->mid, F, w.b1), st));
-    EpiArgs e2 = epi_resid(s->xres, D, w.b2, g2);
+    EpiArgs e2 = epi_resid(s, w.b2, g2);
     if (l == c.n_layers - 1) { e2.out = x_out; e2.ldo = D; }
     PROF(DP_PROF_FFN2_GEMM, Path<T>::gemm(s->mid, F, w.w2, m.w2_t, S, D, F, EPI_RESID, e2, st));
   }
