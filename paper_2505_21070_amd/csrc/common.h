@@ -68,17 +68,10 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-
 __device__ __forceinline__ float gelu_tanh_f(float v) {
   const float c = 0.7978845608028654f;
   return 0.5f * v * (1.0f + tanhf(c * (v + 0.044715f * v * v * v)));
 }
-__device__ __forceinline__ float silu_f(float v) { return v / (1.0f + __expf(-v)); }
 
 // GEMM epilogue selector (shared by the fp32 and the bf16 GEMM kernels; EPI_HEADS is bf16 only).  EPI_PART is internal to
 // the bf16 GEMM: one K range's plain fp32 sums, for a launch that adds the ranges up.

@@ -53,7 +53,6 @@ template <typename T> void launch_from_f32(const float* in, T* out, int64_t n, h
 }
 template void launch_to_f32<float>(const float*, float*, int64_t, hipStream_t);
 template void launch_to_f32<bf16_t>(const bf16_t*, float*, int64_t, hipStream_t);
-template void launch_from_f32<float>(const float*, float*, int64_t, hipStream_t);
 template void launch_from_f32<bf16_t>(const float*, bf16_t*, int64_t, hipStream_t);
 
 __global__ void k_mul_f32(const float* __restrict__ a, const float* __restrict__ b, float* __restrict__ out, int64_t n) {
