@@ -3,7 +3,8 @@
 //
 // Block tile BM x BN x 64, WGM x WGN wavefronts, each owning a (BM/WGM) x (BN/WGN) sub-tile built from
 // v_mfma_f32_32x32x16_bf16.  k-tiles go HBM -> LDS directly (no staging registers, no LDS stores) into
-// two buffers: k-tile kt+1 is in flight while k-tile kt is multiplied.  Operand fragments are
+// two buffers: k-tile kt+1 is in flight while k-tile kt is multiplied (160-row tiles have three and two in
+// flight; problems of few tiles take small tiles and a ring of loads, see the ST > 2 loop and tile_family).  Operand fragments are
 // double-buffered in registers: those of k-step ks+1 are read from LDS while the MFMAs of k-step ks run.
 // The issue order of the main loop is pinned (see there): the two wavefronts of a SIMD are served oldest
 // first rather than interleaved, so each has to keep the matrix pipe busy on its own; tile loads go out
