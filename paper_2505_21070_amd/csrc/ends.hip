@@ -407,6 +407,14 @@ static void gemm(dp_ends* s, const void* A, int64_t lda, const void* W, const vo
   (void)s;
 }
 
+// Both one-kernel forms store results while other blocks still load their input.  The entry points take an output that shares
+// memory with its input, so such a call's input is copied into scratch first (the general paths read all of it before
+// they store anything).
+static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+  return pa < pb + b_bytes && pb < pa + a_bytes;
+}
+
 static void launch_embed(dp_ends* s, const float* latent, void* x_out, int64_t S, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
   const int64_t rows = (S + 15) / 16;
@@ -429,7 +437,15 @@ static void embed_typed(dp_ends* s, const float* latent, void* x_out, int n_fram
   const dp_ends_config& c = s->cfg;
   const int64_t S = s->tok * n_frames, n = S * s->P;
   if constexpr (sizeof(T) == 2) {
-    if (embed_fused(c)) { launch_embed(s, latent, x_out, S, st); return; }
+    if (embed_fused(c)) {
+      if (overlap(latent, (size_t)n * 4, x_out, (size_t)(S * c.dim) * 2)) {
+        const int64_t row = (int64_t)2 * c.tok_w * c.channels;        // values per pixel row
+        launch_copy2d<float>(latent, row, s->out32, row, n / row, row, st);
+        latent = s->out32;
+      }
+      launch_embed(s, latent, x_out, S, st);
+      return;
+    }
   }
   k_patchify<T><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(latent, (T*)s->patches, n, (int)s->P, (int)s->tok, c.tok_w, c.channels);
   gemm<T>(s, s->patches, s->P, s->w.w_pe, s->w_pe_t, S, c.dim, s->P, EPI_STORE, EpiArgs{x_out, c.dim, s->w.b_pe, nullptr, 0, nullptr}, st);
@@ -471,7 +487,14 @@ static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int 
   const int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, nullptr, st);
   launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e, &table, nullptr, st);
   if constexpr (sizeof(T) == 2) {
-    if (head_fused(c)) { launch_head(s, x_in, v_out, S, st); return; }
+    if (head_fused(c)) {
+      if (overlap(x_in, (size_t)(S * D) * 2, v_out, (size_t)n * 4)) {
+        launch_copy2d<bf16_t>((const bf16_t*)x_in, D, (bf16_t*)s->h, D, S, D, st);
+        x_in = s->h;
+      }
+      launch_head(s, x_in, v_out, S, st);
+      return;
+    }
   }
   launch_to_f32<T>((const T*)x_in, s->x32, S * D, st);
   launch_ln_modulate<T>(s->x32, nullptr, (T*)s->h, S, (int)D, c.eps, s->mod + D, s->mod, 1, st);

@@ -1,7 +1,7 @@
 """The one-kernel patch embedding and output head at the edges of their ranges, against the CPU oracle: token counts that
 are no multiple of a block's 16 or 32 tokens, channel groups that do not divide by the eight wavefronts, one to four
 fragments of values per token and the first width beyond them (which takes the GEMMs, as does a head wider than 5120),
-and buffers that start off a 16-byte boundary."""
+buffers that start off a 16-byte boundary, and outputs that overlap their input."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +47,39 @@ def test_buffers_off_a_16_byte_boundary():
     out = shifted(torch.full_like(ref, float("nan")))
     B.head_forward_static(cfg, g._keep, 16, x, 437.0, 3, out)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_output_may_overlap_the_input(dtype):
+    """An output that shares memory with the input: same values as with buffers of their own.  65536 tokens are several
+    times what is resident at once, so a kernel that stores while others still have input to load gives other values."""
+    from paper_2505_21070_amd import binding as B
+    dim, side, frames, channels = 64, 64, 16, 16
+    cfg = synth.stage_config("tiny_bf16", dim=dim, tok_h=side, tok_w=side, dtype=dtype)
+    w = {"stage": synth.make_weights(dict(cfg, n_layers=0), seed=43)["stage"]}
+    g, _ = make_ends(cfg, w, channels, frames, seed=43)
+    gen = torch.Generator().manual_seed(44)
+    lat, x = synth.make_latent(cfg, frames, channels, gen).cuda(), to_dev(synth.make_block(cfg, frames, gen), cfg)
+    stream = torch.cuda.current_stream().cuda_stream
+    want_x, want_v = g.embed(lat), g.head(x, 437.0, frames)
+    room = max(lat.numel() * 4, x.numel() * x.element_size())
+
+    def place(t, offset):                            # t's values inside a buffer of three times the room
+        buf = torch.zeros(3 * room, dtype=torch.uint8, device="cuda")
+        at = buf[offset:offset + t.numel() * t.element_size()].view(t.dtype)
+        at.copy_(t.reshape(-1))
+        return buf, at.view(t.shape)
+
+    for off in (-room // 2, -256, 0, 256, room // 2):       # of the output against the input
+        buf, src = place(lat, room)
+        out = buf[room + off:room + off + want_x.numel() * want_x.element_size()].view(want_x.dtype).view(want_x.shape)
+        B._check(B._lib.dp_embed_forward(g._h, src.data_ptr(), out.data_ptr(), frames, stream), "overlap")
+        assert torch.equal(out, want_x), f"embed, output {off} bytes from the latent"
+        for static in (False, True):
+            buf, src = place(x, room)
+            out = buf[room + off:room + off + want_v.numel() * 4].view(torch.float32).view(want_v.shape)
+            if static:
+                B.head_forward_static(cfg, g._keep, channels, src, 437.0, frames, out)
+            else:
+                B._check(B._lib.dp_head_forward(g._h, src.data_ptr(), 437.0, out.data_ptr(), frames, stream), "overlap")
+            assert torch.equal(out, want_v), f"head (static {static}), output {off} bytes from the tokens"
