@@ -23,7 +23,7 @@ struct dp_ends {
   dp_ends_config cfg{};
   dp_ends_weights w{};
   int64_t tok, Smax, Spad, P;                  // P = 4 * channels values per token
-  void *patches, *h, *w_pe_t, *w_head_t;       // storage type
+  void *patches, *h, *w_pe_t, *w_pe_f, *w_head_t;   // storage type; w_pe_f: in the order of k_embed's fragments
   float *x32, *out32, *e1, *e, *mhead, *mod;
 };
 
@@ -327,8 +327,19 @@ static const char* validate(const dp_ends_config* c) {
 
 // The one-kernel forms: bf16, at most 256 values per token (they stay in registers; wider ones re-read the tokens once per 64
 // values), and for the head rows of at most 5120 channels (10 groups of 64 per wavefront: 160 registers).
-static bool embed_fused(const dp_ends_config& c) { return c.dtype == DP_BF16 && 4 * c.channels <= kEndsMaxP; }
-static bool head_fused(const dp_ends_config& c) { return embed_fused(c) && c.dim <= 5120; }
+// k_embed reads all weights once per 16 tokens, 4C / 16 times the bytes it stores.  With 4C = 64, or weights of at most
+// 256 KB, that stays below the separate patchify pass and GEMM at every token count; beyond, only while the tokens are
+// few enough for both to be bound by their launches.  One kernel / patchify + GEMM in us: 4C = 64: 1560 x 5120 9.0 / 11.0,
+// 14400 x 5120 38.0 / 48.4; 4C = 128: 18720 x 1024 19.2 / 26.5, 2340 x 3072 10.6 / 11.0, 6240 x 5120 30.5 / 27.5;
+// 4C = 256: 18720 x 512 23.2 / 31.2, 780 x 3072 11.3 / 11.7, 1560 x 3072 14.7 / 12.3, 14400 x 5120 100.9 / 82.6.
+static bool embed_frags(const dp_ends_config& c) { return c.dtype == DP_BF16 && 4 * c.channels <= kEndsMaxP; }
+static bool embed_gemm(const dp_ends_config& c) {
+  return !embed_frags(c) || (c.channels > 16 && (int64_t)c.dim * 4 * c.channels > (1 << 17));
+}
+static bool embed_fused(const dp_ends_config& c, int64_t S) {
+  return embed_frags(c) && (!embed_gemm(c) || S * c.dim * 4 * c.channels <= ((int64_t)640 << 20));
+}
+static bool head_fused(const dp_ends_config& c) { return embed_frags(c) && c.dim <= 5120; }
 
 static size_t carve(dp_ends* s, void* base) {
   const dp_ends_config& c = s->cfg;
@@ -343,7 +354,8 @@ static size_t carve(dp_ends* s, void* base) {
   s->h = take(s->Spad * D * E);
   s->x32 = (float*)take(s->Spad * D * 4);
   s->out32 = (float*)take(s->Spad * s->P * 4);
-  s->w_pe_t = take(rup(D, 256) * s->P * E);
+  s->w_pe_t = embed_gemm(c) ? take(rup(D, 256) * s->P * E) : nullptr;
+  s->w_pe_f = embed_frags(c) ? take(D * s->P * E) : nullptr;
   s->w_head_t = take(rup(s->P, 256) * D * E);
   s->e1 = (float*)take(GEMV_MAX_SLICES * D * 4); s->e = (float*)take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
   s->mhead = (float*)take(2 * D * 4); s->mod = (float*)take(2 * D * 4);
@@ -384,8 +396,8 @@ extern "C" int dp_ends_init(const dp_ends_config* cfg, const dp_ends_weights* w,
   const int64_t D = cfg->dim;
   launch_fill_zero(s->patches, (size_t)((char*)s->e1 - (char*)s->patches), st);      // padding rows of the GEMM operands
   if (cfg->dtype == DP_BF16) {
-    if (embed_fused(*cfg)) launch_pack_frags((const bf16_t*)w->w_pe, s->P, D, 1, s->w_pe_t, st);
-    else launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
+    if (embed_frags(*cfg)) launch_pack_frags((const bf16_t*)w->w_pe, s->P, D, 1, s->w_pe_f, st);
+    if (embed_gemm(*cfg)) launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
     pack_head(s, st);
     launch_to_f32<bf16_t>((const bf16_t*)w->m_head, s->mhead, 2 * D, st);
   } else {
@@ -419,12 +431,14 @@ static void launch_embed(dp_ends* s, const float* latent, void* x_out, int64_t S
   const dp_ends_config& c = s->cfg;
   const int64_t rows = (S + 15) / 16;
   const int groups = c.dim / 64, per = (groups + 3) / 4;           // 64-column groups; blocks of 4 that cover them
-  // few tokens: the columns are dealt over blocks until the chip is full, many: a block walks all of them
+  // few tokens: the columns are dealt over blocks until there are 512 of them (two per CU), many: a block walks all of them.
+  // Against dealing them by whole rounds of the blocks that are resident: 4096 x 5120 11.9 / 12.9 us, 6240 x 5120 19.7 / 17.9,
+  // 14400 x 5120 38.0 / 40.0, the same where both are at the launch's 9 us (6240 x 1536 and all smaller ones).
   int64_t cols = (512 + rows - 1) / rows;
   cols = cols < 1 ? 1 : cols > per ? per : cols;
   const dim3 grid((unsigned)rows, (unsigned)cols);
   const int al = ((uintptr_t)latent & 15) == 0;
-#define EMBED_CASE(KC) k_embed<KC><<<grid, 256, 0, st>>>(latent, (const uint4*)s->w_pe_t, (const bf16_t*)s->w.b_pe, (bf16_t*)x_out, S, c.dim, (int)s->tok, c.tok_w, c.channels, al)
+#define EMBED_CASE(KC) k_embed<KC><<<grid, 256, 0, st>>>(latent, (const uint4*)s->w_pe_f, (const bf16_t*)s->w.b_pe, (bf16_t*)x_out, S, c.dim, (int)s->tok, c.tok_w, c.channels, al)
   if (s->P == 64) EMBED_CASE(2);
   else if (s->P == 128) EMBED_CASE(4);
   else if (s->P == 192) EMBED_CASE(6);
@@ -437,7 +451,7 @@ static void embed_typed(dp_ends* s, const float* latent, void* x_out, int n_fram
   const dp_ends_config& c = s->cfg;
   const int64_t S = s->tok * n_frames, n = S * s->P;
   if constexpr (sizeof(T) == 2) {
-    if (embed_fused(c)) {
+    if (embed_fused(c, S)) {
       if (overlap(latent, (size_t)n * 4, x_out, (size_t)(S * c.dim) * 2)) {
         const int64_t row = (int64_t)2 * c.tok_w * c.channels;        // values per pixel row
         launch_copy2d<float>(latent, row, s->out32, row, n / row, row, st);
@@ -553,7 +567,7 @@ static size_t carve_head(dp_ends* s, void* base, int n_frames) {
   s->P = 4 * (int64_t)c.channels;
   char* b = (char*)base; size_t off = 0;
   auto take = [&](size_t bytes) { off = (size_t)rup((int64_t)off, 256); void* p = b ? b + off : nullptr; off += bytes; return p; };
-  s->patches = nullptr; s->w_pe_t = nullptr;
+  s->patches = nullptr; s->w_pe_t = nullptr; s->w_pe_f = nullptr;
   s->h = take(s->Spad * D * E);
   s->x32 = (float*)take(s->Spad * D * 4);
   s->out32 = (float*)take(s->Spad * s->P * 4);
