@@ -459,9 +459,12 @@ __device__ __forceinline__ void rope_token(const RopeTokens& r, int64_t i) {
   r.cs[i] = pi < cf ? r.rt.f[(int64_t)f * cf + pi] : pi < cf + ch ? r.rt.y[y * ch + (pi - cf)] : r.rt.x[x * cw + (pi - cf - ch)];
 }
 // SINUS: the input is the sinusoidal features of a.in.t (a kernel of its own: their double-precision code would cost every
-// product registers and scratch memory).  CPL == 2: bf16, rows of W in 4-byte steps.
+// product registers and scratch memory).  CPL == 2: bf16, rows of W in 4-byte steps.  At most 64 registers, so that a CU
+// holds two blocks: with 72 it held one, and a grid of a few more blocks than CUs took two rounds (fp32 5120 x 30720, 480
+// blocks: the chain 157 -> 148 us; bf16 6144 x 36864, 288 blocks: 161 -> 145; fp32 8192 x 49152, three whole rounds:
+// 351 -> 359).
 template <typename T, int CPL, bool SINUS>
-__global__ __launch_bounds__(1024) void k_gemv(GemvArgs<T> a, RopeTokens rope) {
+__global__ __launch_bounds__(1024, SINUS ? 4 : 8) void k_gemv(GemvArgs<T> a, RopeTokens rope) {
   constexpr int KC = 8192, U = SINUS ? 8 : 16;
   __shared__ float xs[KC];
   __shared__ float red[16][64 * CPL];
@@ -554,10 +557,14 @@ int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, floa
                 const RopeTokens* rope, hipStream_t st) {
   // A product that ends in a table stays whole unless its columns make less than half a round of blocks that each have many
   // rows to read (5120 x 5120: 38 us whole, 21 sliced with a launch more; 1536 x 1536: 13 and 11 under the
-  // profiler, which counts the launch as 4.6 us).
+  // profiler, which counts the launch as 4.6 us).  A caller that gives no y wants it whole: the stage's, 6 * dim
+  // columns, of which a whole one at dim 1536 takes 17.5 us where two slices took 10.0 and the launch that adds them up
+  // 4.9 (the whole chain 27.3 us both ways, 1024 wide 21.9 against 24.5, 512 wide 18.4 against 21.7).
   const bool whole = table && (!y || cdiv(N, 64) >= 128 || K <= 2048);
-  // two columns per lane unless a whole product would then leave CUs without a block
-  const bool wide = sizeof(T) == 2 && N % 2 == 0 && ((uintptr_t)W & 3) == 0 && (!whole || cdiv(N, 128) >= 192);
+  // two columns per lane, unless a whole product still has a CU for each block at one column (chains at dim 2816, 264
+  // blocks of 64 columns or 132 of 128: 57.8 and 38.4 us, 44.1 as six launches; 3584: 76.5, 57.8 and 71.4; one column up
+  // to dim 2688)
+  const bool wide = sizeof(T) == 2 && N % 2 == 0 && ((uintptr_t)W & 3) == 0 && (!whole || cdiv(N, 64) > 256);
   const int cols = cdiv(N, wide ? 128 : 64);
   int slices = 1;
   if (!whole && in.x) {                                // enough blocks for the 256 CUs, at least 64 rows each

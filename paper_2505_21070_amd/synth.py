@@ -57,6 +57,9 @@ CONFIGS = {
                          tok_h=8, tok_w=8, block_frames=2, cache_frames=1, dtype="bf16"),
     "dim2176_bf16": dict(n_layers=1, dim=2176, n_heads=17, head_dim=128, ffn_dim=640, text_len=24, text_dim=2176,
                          tok_h=8, tok_w=8, block_frames=2, cache_frames=1, dtype="bf16"),
+    # the narrowest model whose modulation product takes two columns per lane (more 64-column blocks than CUs)
+    "dim2752_bf16": dict(n_layers=1, dim=2752, n_heads=43, head_dim=64, ffn_dim=640, text_len=24, text_dim=2752,
+                         tok_h=8, tok_w=8, block_frames=2, cache_frames=1, dtype="bf16"),
     # Wan-1.3B-shaped stage: 4 of 30 layers, 4 frames x 30x52 tokens + 2 cached frames
     "wan1p3b_stage": dict(n_layers=4, dim=1536, n_heads=12, head_dim=128, ffn_dim=8960, text_len=512,
                           text_dim=4096, tok_h=30, tok_w=52, block_frames=4, cache_frames=2, dtype="bf16"),
