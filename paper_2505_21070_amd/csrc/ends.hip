@@ -328,16 +328,16 @@ static const char* validate(const dp_ends_config* c) {
 // The one-kernel forms: bf16, at most 256 values per token (they stay in registers; wider ones re-read the tokens once per 64
 // values), and for the head rows of at most 5120 channels (10 groups of 64 per wavefront: 160 registers).
 // k_embed reads all weights once per 16 tokens, 4C / 16 times the bytes it stores.  With 4C = 64, or weights of at most
-// 256 KB, that stays below the separate patchify pass and GEMM at every token count; beyond, only while the tokens are
-// few enough for both to be bound by their launches.  One kernel / patchify + GEMM in us: 4C = 64: 1560 x 5120 9.0 / 11.0,
-// 14400 x 5120 38.0 / 48.4; 4C = 128: 18720 x 1024 19.2 / 26.5, 2340 x 3072 10.6 / 11.0, 6240 x 5120 30.5 / 27.5;
-// 4C = 256: 18720 x 512 23.2 / 31.2, 780 x 3072 11.3 / 11.7, 1560 x 3072 14.7 / 12.3, 14400 x 5120 100.9 / 82.6.
+// 384 KB (512 KB with 4C = 128), that stays below the separate patchify pass and GEMM; beyond, only while the tokens are
+// few.  One kernel / patchify + GEMM in us: 4C = 64: 1560 x 5120 9.0 / 11.0, 14400 x 5120 38.0 / 48.4; 4C = 128: 6240 x 2048
+// 16.2 / 15.9 (that and 6240 x 1536 are behind by 2 %, no other), 18720 x 2048 32.2 / 38.3, 1560 x 4096 9.8 / 10.9, 6240 x 5120
+// 30.5 / 27.5; 4C = 256: 18720 x 768 28.7 / 34.7, 780 x 5120 10.3 / 11.8, 1560 x 3072 12.6 / 12.3, 14400 x 5120 100.7 / 82.6.
 static bool embed_frags(const dp_ends_config& c) { return c.dtype == DP_BF16 && 4 * c.channels <= kEndsMaxP; }
 static bool embed_gemm(const dp_ends_config& c) {
-  return !embed_frags(c) || (c.channels > 16 && (int64_t)c.dim * 4 * c.channels > (1 << 17));
+  return !embed_frags(c) || (c.channels > 16 && (int64_t)c.dim * 4 * c.channels > ((c.channels == 32 ? 256 : 192) << 10));
 }
 static bool embed_fused(const dp_ends_config& c, int64_t S) {
-  return embed_frags(c) && (!embed_gemm(c) || S * c.dim * 4 * c.channels <= ((int64_t)640 << 20));
+  return embed_frags(c) && (!embed_gemm(c) || S * c.dim * 4 * c.channels <= ((int64_t)1 << 30));
 }
 static bool head_fused(const dp_ends_config& c) { return embed_frags(c) && c.dim <= 5120; }
 
@@ -431,11 +431,22 @@ static void launch_embed(dp_ends* s, const float* latent, void* x_out, int64_t S
   const dp_ends_config& c = s->cfg;
   const int64_t rows = (S + 15) / 16;
   const int groups = c.dim / 64, per = (groups + 3) / 4;           // 64-column groups; blocks of 4 that cover them
-  // few tokens: the columns are dealt over blocks until there are 512 of them (two per CU), many: a block walks all of them.
-  // Against dealing them by whole rounds of the blocks that are resident: 4096 x 5120 11.9 / 12.9 us, 6240 x 5120 19.7 / 17.9,
-  // 14400 x 5120 38.0 / 40.0, the same where both are at the launch's 9 us (6240 x 1536 and all smaller ones).
-  int64_t cols = (512 + rows - 1) / rows;
-  cols = cols < 1 ? 1 : cols > per ? per : cols;
+  // few tokens: the columns are dealt over blocks, many: a block walks all of them.  4C <= 128, five and three blocks to a CU:
+  // until there are 512 blocks (by whole rounds of resident blocks, 4C = 64: 4096 x 5120 12.9 instead of 11.9 us, 14400 x 5120
+  // 40.0 instead of 38.0, 6240 x 5120 17.9 instead of 19.7; 4C = 128: 14400 x 1024 18.8 instead of 16.3).  Wider ones, two
+  // to a CU, so that whole rounds of them take least, a round being the column groups a block walks and about 1.5 more
+  // (4C = 256: 6240 x 768 12.6 us, 15.3 the other way; 1560 x 3072 12.6 and 14.7).
+  int64_t cols = 1;
+  if (s->P <= 128) {
+    cols = (512 + rows - 1) / rows;
+    cols = cols > per ? per : cols;
+  } else {
+    double best = 1e30;
+    for (int k = 1; k <= per; ++k) {
+      const double cost = (double)((rows * k + 511) / 512) * ((double)((groups + 4 * k - 1) / (4 * k)) + 1.5);
+      if (cost < best) { best = cost; cols = k; }
+    }
+  }
   const dim3 grid((unsigned)rows, (unsigned)cols);
   const int al = ((uintptr_t)latent & 15) == 0;
 #define EMBED_CASE(KC) k_embed<KC><<<grid, 256, 0, st>>>(latent, (const uint4*)s->w_pe_f, (const bf16_t*)s->w.b_pe, (bf16_t*)x_out, S, c.dim, (int)s->tok, c.tok_w, c.channels, al)

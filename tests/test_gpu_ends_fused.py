@@ -24,7 +24,7 @@ def setup(dim, channels, tok_h, tok_w, frames):
 
 @pytest.mark.parametrize("dim,channels,tok_h,tok_w,frames", [
     (64, 16, 1, 1, 1), (320, 16, 3, 5, 3), (576, 32, 7, 9, 2), (128, 48, 5, 7, 1), (1024, 64, 4, 5, 1), (128, 80, 3, 11, 1),
-    (2560, 64, 20, 50, 1), (2560, 64, 20, 52, 1), (512, 64, 20, 51, 6),
+    (2560, 64, 20, 80, 1), (2560, 64, 20, 82, 1), (768, 64, 20, 51, 6),
     (2176, 16, 3, 5, 1), (3136, 16, 3, 6, 1), (5120, 16, 3, 7, 1), (5184, 16, 2, 3, 1), (128, 16, 64, 65, 1), (128, 16, 63, 65, 1)])
 def test_embed_and_head_edges(dim, channels, tok_h, tok_w, frames):
     cfg, _, g, o, lat, tokens = setup(dim, channels, tok_h, tok_w, frames)
