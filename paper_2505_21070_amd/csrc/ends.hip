@@ -350,9 +350,10 @@ static size_t carve(dp_ends* s, void* base) {
   s->P = 4 * (int64_t)c.channels;
   char* b = (char*)base; size_t off = 0;
   auto take = [&](size_t bytes) { off = (size_t)rup((int64_t)off, 256); void* p = b ? b + off : nullptr; off += bytes; return p; };
-  s->patches = take(s->Spad * s->P * E);
+  // the one-kernel forms need none of this but a copy of an input that their output overlaps (head: h, embedding: out32)
+  s->patches = embed_gemm(c) ? take(s->Spad * s->P * E) : nullptr;
   s->h = take(s->Spad * D * E);
-  s->x32 = (float*)take(s->Spad * D * 4);
+  s->x32 = head_fused(c) ? nullptr : (float*)take(s->Spad * D * 4);
   s->out32 = (float*)take(s->Spad * s->P * 4);
   s->w_pe_t = embed_gemm(c) ? take(rup(D, 256) * s->P * E) : nullptr;
   s->w_pe_f = embed_frags(c) ? take(D * s->P * E) : nullptr;
@@ -394,7 +395,9 @@ extern "C" int dp_ends_init(const dp_ends_config* cfg, const dp_ends_weights* w,
   hipStream_t st = (hipStream_t)hip_stream;
   (void)hipGetLastError();
   const int64_t D = cfg->dim;
-  launch_fill_zero(s->patches, (size_t)((char*)s->e1 - (char*)s->patches), st);      // padding rows of the GEMM operands
+  // padding rows of the GEMM operands; k_embed and k_head read no such rows
+  if (embed_gemm(*cfg)) launch_fill_zero(s->patches, (size_t)(s->Spad * s->P) * (cfg->dtype == DP_BF16 ? 2 : 4), st);
+  if (!head_fused(*cfg)) launch_fill_zero(s->h, (size_t)((char*)s->e1 - (char*)s->h), st);
   if (cfg->dtype == DP_BF16) {
     if (embed_frags(*cfg)) launch_pack_frags((const bf16_t*)w->w_pe, s->P, D, 1, s->w_pe_f, st);
     if (embed_gemm(*cfg)) launch_transpose_pad<bf16_t>((const bf16_t*)w->w_pe, s->P, D, (bf16_t*)s->w_pe_t, rup(D, 256), st);
@@ -545,9 +548,10 @@ extern "C" int dp_head_forward(dp_ends_t* s, const void* x_in, float timestep, f
 // ------------------------------------------------------------------------------------------ no allocation
 // dp_head_forward for callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses
 // that forbid it): no handle and no workspace.  Everything dp_head_forward keeps in the caller's workspace (the
-// timestep-MLP vectors, the fp32 copy of the tokens, the normalised tokens, the fp32 result before the scatter,
-// the repacked head matrix) lives in one file-scope device array instead.  Each GPU the library runs on holds its
-// own copy of the array at its own address, looked up once per device; host code only ever uses that address.
+// timestep-MLP vectors, the repacked head matrix; where the head takes the GEMM the fp32 copy of the tokens, the
+// normalised tokens and the fp32 result before the scatter) lives in one file-scope device array instead.  Each GPU the
+// library runs on holds its own copy of the array at its own address, looked up once per device; host code only ever
+// uses that address.
 constexpr size_t kHeadScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kHeadScratchBytes];
 static std::mutex g_scratch_mu;
@@ -568,7 +572,8 @@ static int head_scratch(void** out) {
   return DP_OK;
 }
 
-// the head's share of carve(), sized for the frames of this call
+// the head's share of carve(), sized for the frames of this call.  The GEMM's buffers are laid out in either case: they
+// are the documented size limit, and h takes the copy of an overlapped input.
 static size_t carve_head(dp_ends* s, void* base, int n_frames) {
   const dp_ends_config& c = s->cfg;
   const int64_t E = c.dtype == DP_BF16 ? 2 : 4, D = c.dim;

@@ -226,3 +226,13 @@ def test_noise_assignment_random_parameter_sweep_matches_oracle(B):
         num_c = 2 * int(rng.integers(0, num_b + 1))
         words = synth.shuffle_words((nb - 1) * max(num_b - 1, 0) + 2 * num_b + 2, 1000 + i)
         assert B.noise_assign(nb, num_b, num_c, words) == noise_assignment(nb, num_b, num_c, words), (nb, num_b, num_c)
+
+
+def test_ends_workspace_holds_only_what_its_kernels_use(B):
+    """bf16 at the 14B shape: both ends are one kernel each, so beside packed weights and vectors the workspace holds a copy of
+    an input that may be overlapped (tokens in bf16, latent in fp32) and no fp32 copy of the tokens or patch matrix."""
+    S, D, P = 14592, 5120, 64                                # 4 x 45 x 80 tokens, padded to 256
+    need = lambda dim, channels, dtype: B._lib.dp_ends_workspace_bytes(C.byref(B.EndsConfig(dim, 45, 80, channels, 4, dtype, 256, 1e-6)))
+    assert S * (2 * D + 4 * P) < need(D, 16, B.DP_BF16) < S * (2 * D + 4 * P) + (8 << 20)
+    assert need(D, 16, B.DP_F32) > S * (8 * D + 8 * P)       # the general path keeps its buffers
+    assert need(5184, 16, B.DP_BF16) > S * (6 * 5184 + 4 * P)
