@@ -609,13 +609,18 @@ static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t l
   dim3 grid((unsigned)((tm * tn * parts + 7) / 8 * 8));
   k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
 }
-template <int BM, int BN, int WGM, int WGN, int ST = 2>
-static void launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                       int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
+// false: this tile shape has no such epilogue (the rules below never ask for it)
+template <int BM, int BN, int WGM, int WGN, int ST>
+static bool launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                       int64_t K, int epi, const EpiArgs& e, hipStream_t st, int parts) {
+  constexpr bool HEADS = BM <= 160 || BM == 256, PART = ST == 4 ? BM == 64 : BM == 160 || BM == 256;
   if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID, ST>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if constexpr (ST > 2 && BM <= 128) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_HEADS && HEADS) { if constexpr (HEADS) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st); }
+  else if (epi == EPI_PART && PART) { if constexpr (PART) launch_one<BM, BN, WGM, WGN, EPI_PART, ST>(A, lda, Wt, ldw, M, N, K, e, st, parts); }
+  else return false;
+  return true;
 }
 
 // Which tile family a problem takes.  A 256-row tile keeps a CU busy by itself but a small problem has too few of them; small
@@ -629,12 +634,11 @@ static int tile_family(int64_t M, int64_t N) {
   if (((M + 127) / 128) * ((N + 127) / 128) <= 256) return TILE_128;   // one block per CU: one round
   return TILE_BIG;
 }
-static void launch_small(int family, const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                         int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
-  if (family == TILE_128) launch_cfg<128, 128, 2, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
+// Tile shape, LDS stages and K ranges of a problem: what the rules below decide and launch_gemm_bf16 runs
+static GemmRoute small_tile(int family, int64_t M, int64_t N) {
+  if (family == TILE_128) return {128, 128, 4, 1};
   // 64 KB of LDS (two blocks per CU) where two suffice, 48 KB where a third has to fit
-  else if (((M + 63) / 64) * ((N + 63) / 64) <= 512) launch_cfg<64, 64, 2, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
-  else launch_cfg<64, 64, 2, 2, 3>(A, lda, Wt, ldw, M, N, K, epi, e, st);
+  return {64, 64, ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 4 : 3, 1};
 }
 
 // EPI_HEADS.  Sections must be whole tiles wide and a transposed section needs a square tile, 8 | M and 8 | row0.
@@ -647,18 +651,13 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   }
   return true;
 }
-static void launch_big_heads(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                             int64_t K, const EpiArgs& e, hipStream_t st) {
+static GemmRoute big_heads_tile(int64_t M, int64_t N, bool any_transposed) {
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  bool any_t = false;
-  for (int i = 0; i < (int)(N / e.heads->dim); ++i) any_t = any_t || e.heads->sec[i].transposed;
   // the 160-row tile cannot exchange its operands; it pays where it fills the one round better (see below)
   const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
   const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
-  if (!any_t && fits160 && 0.80 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256))
-    launch_one<160, 256, 1, 8, EPI_HEADS, 3>(A, lda, Wt, ldw, M, N, K, e, st);
-  else
-    launch_one<256, 256, 2, 4, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
+  if (!any_transposed && fits160 && 0.80 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256)) return {160, 256, 3, 1};
+  return {256, 256, 2, 1};
 }
 
 // x[m, n] += gate[n] * (bias[n] + sum over the K ranges, in range order), and its rounded copy
@@ -692,9 +691,9 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // (256 x 256), 1.25 (160 x 256, three stages), 0.27 per block on the CU (64 x 64), 8 (4) for a block's ends, 3 for the
 // second launch, partials at 4 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU, 0.72 for 128 x 128, 1.3 per round
 // of 256 x 256.
-enum { CUT_256 = 0, CUT_160 = 1, CUT_64 = 2 };
-static int split_parts(int64_t M, int64_t N, int64_t K, const EpiArgs& e, int* tile) {
-  if (!e.scratch || N % 4 || e.ldr % 4) return 1;
+static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats) {
+  GemmRoute r{0, 0, 0, 1};                             // parts == 1: not cut
+  if (N % 4) return r;
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t160 = ((M + 159) / 160) * ((N + 255) / 256);
   const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), KT = K / 64;
   const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
@@ -702,45 +701,26 @@ static int split_parts(int64_t M, int64_t N, int64_t K, const EpiArgs& e, int* t
   double best = family == TILE_BIG ? 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8
               : family == TILE_128 ? 0.72 * (double)KT + 5 : 0.24 * (double)(KT * ((t64 + 255) / 256)) + 5;
   best *= 0.9;                                         // not for a few per cent
-  int parts = 1;
   for (int p = 2; p <= 8; ++p) {
-    if ((size_t)(p * M * N) > e.scratch_floats) break;
+    if ((size_t)(p * M * N) > scratch_floats) break;
     const double extra = 3 + (double)(M * N) * 4 * (2 * p + 2.5) / 4e6, kt = (double)((KT + p - 1) / p);
     const double cost[3] = {t256 * p <= 256 && KT / p >= 8 ? 1.3 * kt + 8 + extra : 1e30,
                             fits160 && t160 * p <= 256 && KT / p >= 8 ? 1.25 * kt + 8 + extra : 1e30,
                             t64 * p <= 512 && KT / p >= 4 ? 0.27 * kt * (double)((t64 * p + 255) / 256) + 4 + extra : 1e30};
+    const GemmRoute tile[3] = {{256, 256, 2, p}, {160, 256, 3, p}, {64, 64, 4, p}};
     for (int w = 0; w < 3; ++w)
-      if (cost[w] < best) { best = cost[w]; parts = p; *tile = w; }
+      if (cost[w] < best) { best = cost[w]; r = tile[w]; }
   }
-  return parts;
+  return r;
 }
 
-bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
-                      int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
-  if (M <= 0 || N <= 0) return true;
-  if (K < 64 || K % 64) return false;          // whole k-tiles of 64 (the callers validate their widths)
-  if (epi == EPI_HEADS && (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads))) return false;
-  const int family = tile_family(M, N);
-  if (epi == EPI_RESID) {
-    int tile = CUT_256;
-    const int parts = split_parts(M, N, K, e, &tile);
-    if (parts > 1) {
-      const EpiArgs p{nullptr, 0, nullptr, e.scratch, N, nullptr, nullptr, nullptr, 0};
-      if (tile == CUT_64) launch_one<64, 64, 2, 2, EPI_PART, 4>(A, lda, Wt, ldw, M, N, K, p, st, parts);
-      else if (tile == CUT_160) launch_one<160, 256, 1, 8, EPI_PART, 3>(A, lda, Wt, ldw, M, N, K, p, st, parts);
-      else launch_one<256, 256, 2, 4, EPI_PART>(A, lda, Wt, ldw, M, N, K, p, st, parts);
-      k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, parts, M, N, e);
-      return true;
-    }
-  }
-  if (family != TILE_BIG) { launch_small(family, A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
-  if (epi == EPI_HEADS) { launch_big_heads(A, lda, Wt, ldw, M, N, K, e, st); return true; }
-  // One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.
-  // 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration comes out lower:
-  // 192x256 (0.88 of a 256x256 tile), 160x256 (0.80; 1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6
-  // tiles fill one round where 33 x 6 leave 58 CUs idle) and 320x256 (1.25, fewer operand bytes per flop).
-  // The 160-, 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where
-  // that stays inside the 256-row padding the caller guarantees.
+// One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.
+// 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration comes out lower:
+// 192x256 (0.88 of a 256x256 tile), 160x256 (0.80; 1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6
+// tiles fill one round where 33 x 6 leave 58 CUs idle) and 320x256 (1.25, fewer operand bytes per flop).
+// The 160-, 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where
+// that stays inside the 256-row padding the caller guarantees.
+static GemmRoute big_tile(int64_t M, int64_t N) {
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
   const int64_t t192 = ((M + 191) / 192) * ((N + 255) / 256);
   const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
@@ -752,9 +732,53 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
   const double cost320 = (M + 319) / 320 * 320 <= mpad ? 1.25 * (double)((t320 + 255) / 256) : 1e30;
   const double best = fmin(fmin(cost256, cost192), fmin(cost160, cost320));
   // on a tie the taller tile wins: fewer operand bytes per flop
-  if (best == cost320) { launch_cfg<320, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
-  if (best == cost256) { launch_cfg<256, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
-  if (best == cost160) { launch_cfg<160, 256, 1, 8, 3>(A, lda, Wt, ldw, M, N, K, epi, e, st); return true; }
-  launch_cfg<192, 256, 2, 4>(A, lda, Wt, ldw, M, N, K, epi, e, st);
-  return true;
+  if (best == cost320) return {320, 256, 2, 1};
+  if (best == cost256) return {256, 256, 2, 1};
+  if (best == cost160) return {160, 256, 3, 1};
+  return {192, 256, 2, 1};
+}
+
+GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, bool any_transposed, size_t scratch_floats) {
+  if (epi == EPI_RESID) {
+    const GemmRoute r = cut_tile(M, N, K, scratch_floats);
+    if (r.parts > 1) return r;
+  }
+  const int family = tile_family(M, N);
+  if (family != TILE_BIG) return small_tile(family, M, N);
+  return epi == EPI_HEADS ? big_heads_tile(M, N, any_transposed) : big_tile(M, N);
+}
+// for the parity tests, which state the kernel that each of their products is meant to reach
+extern "C" void dp_gemm_bf16_route(int64_t M, int64_t N, int64_t K, int32_t epi, int32_t any_transposed, int64_t scratch_floats,
+                                   int32_t* bm_bn_stages_parts) {
+  const GemmRoute r = gemm_bf16_route(M, N, K, epi, any_transposed != 0, (size_t)scratch_floats);
+  const int32_t v[4] = {r.bm, r.bn, r.stages, r.parts};
+  for (int i = 0; i < 4; ++i) bm_bn_stages_parts[i] = v[i];
+}
+
+bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                      int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
+  if (M <= 0 || N <= 0) return true;
+  if (K < 64 || K % 64) return false;          // whole k-tiles of 64 (the callers validate their widths)
+  bool any_t = false;
+  if (epi == EPI_HEADS) {
+    if (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads)) return false;
+    for (int i = 0; i < (int)(N / e.heads->dim); ++i) any_t = any_t || e.heads->sec[i].transposed;
+  }
+  const GemmRoute r = gemm_bf16_route(M, N, K, epi, any_t, e.scratch && e.ldr % 4 == 0 ? e.scratch_floats : 0);
+  const EpiArgs part{nullptr, 0, nullptr, e.scratch, N, nullptr, nullptr, nullptr, 0};
+  const EpiArgs& ea = r.parts > 1 ? part : e;
+  const int ep = r.parts > 1 ? (int)EPI_PART : epi;
+  bool ok = false;
+#define GEMM_TILE(BM, BN, WGM, WGN, ST) \
+  if (r.bm == BM && r.stages == ST) ok = launch_cfg<BM, BN, WGM, WGN, ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
+  GEMM_TILE(64, 64, 2, 2, 4);
+  else GEMM_TILE(64, 64, 2, 2, 3);
+  else GEMM_TILE(128, 128, 2, 2, 4);
+  else GEMM_TILE(160, 256, 1, 8, 3);
+  else GEMM_TILE(192, 256, 2, 4, 2);
+  else GEMM_TILE(256, 256, 2, 4, 2);
+  else GEMM_TILE(320, 256, 2, 4, 2);
+#undef GEMM_TILE
+  if (r.parts > 1) k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, r.parts, M, N, e);
+  return ok;
 }

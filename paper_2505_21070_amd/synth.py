@@ -42,14 +42,15 @@ CONFIGS = {
     "wide128_bf16": dict(n_layers=1, dim=768, n_heads=6, head_dim=128, ffn_dim=1024, text_len=48, text_dim=768,
                          tok_h=16, tok_w=16, block_frames=8, cache_frames=2, dtype="bf16"),
     # dim % 256 != 0, so q|k|v and the cross-attention query take the plain store epilogue and the separate
-    # norm / rotation / transpose kernels, at row counts that make the GEMM choose its other tile shapes for
-    # every epilogue: 4032 rows -> 192 x 256 tiles, 4096 rows -> 256 x 256, 4160 rows with dim 1408 -> 320 x 256
-    # (q|k|v) and 160 x 256 (the rest)
-    "tile192_bf16": dict(n_layers=1, dim=896, n_heads=7, head_dim=128, ffn_dim=1024, text_len=40, text_dim=896,
+    # norm / rotation / transpose kernels, at row counts that make the GEMM choose its large tile shapes:
+    # 4032 rows of 1152 -> 192 x 256 tiles, 4096 rows -> 256 x 256 (more than 256 tiles of 128 x 128 in every
+    # product, K too short to be cut); 4160 rows of 1408 -> 160 x 256, with 320 x 256 for q|k|v and the FFN's first
+    # product (tests/test_gemm_routes.py holds them to it)
+    "tile192_bf16": dict(n_layers=1, dim=1152, n_heads=9, head_dim=128, ffn_dim=1152, text_len=40, text_dim=1152,
                          tok_h=14, tok_w=36, block_frames=8, cache_frames=2, dtype="bf16"),
-    "tile256_bf16": dict(n_layers=1, dim=896, n_heads=7, head_dim=128, ffn_dim=1024, text_len=40, text_dim=896,
+    "tile256_bf16": dict(n_layers=1, dim=1152, n_heads=9, head_dim=128, ffn_dim=1152, text_len=40, text_dim=1152,
                          tok_h=16, tok_w=32, block_frames=8, cache_frames=2, dtype="bf16"),
-    "tile320_bf16": dict(n_layers=1, dim=1408, n_heads=11, head_dim=128, ffn_dim=1024, text_len=40, text_dim=1408,
+    "tile320_bf16": dict(n_layers=1, dim=1408, n_heads=11, head_dim=128, ffn_dim=3904, text_len=40, text_dim=1408,
                          tok_h=20, tok_w=26, block_frames=8, cache_frames=2, dtype="bf16"),
     # few tokens, wide models: the widest register variants of the row kernels (LayerNorm, deferred key scale,
     # norm + rotation); 6144 takes the per-head GEMM epilogue, 2176 = 17 x 128 the separate kernels

@@ -56,3 +56,28 @@ def test_gemm_edges(tok_h, tok_w, ffn, text_dim):
 
 def test_gemm_middle_tiles_every_epilogue():
     pair("gemm64", 1, 1, 0, dim=1408, n_heads=11, head_dim=128, tok_h=23, tok_w=33, ffn_dim=1444, text_dim=1408, text_len=19)
+
+
+@pytest.mark.parametrize("heads,hd", [(2, 64), (2, 128)])
+@pytest.mark.parametrize("tok_h,tok_w,kept", [(7, 9, 0), (7, 9, 1), (3, 11, 1), (3, 11, 2)])
+def test_non_finite_keys_beside_the_live_range(heads, hd, tok_h, tok_w, kept):
+    """Frames of the last block that are not cached leave NaN keys and values in front of and behind the live range, inside
+    its first 16-byte piece and its last key tile.  None of it may reach the result: the same bits as after a
+    neighbour of finite values."""
+    cfg, w, text, _ = synth.make_case("small_f32", seed=33, strong_gate=True, n_blocks=0, n_layers=1, dim=heads * hd, n_heads=heads,
+                                      head_dim=hd, tok_h=tok_h, tok_w=tok_w)
+    tok, gen = tok_h * tok_w, torch.Generator().manual_seed(34)
+    xa, xb = synth.make_block(cfg, 3, gen), synth.make_block(cfg, 1, gen)
+    outs = []
+    for bad in (False, True):
+        if bad:
+            other = torch.ones(3 * tok, dtype=torch.bool)
+            other[kept * tok:(kept + 1) * tok] = False
+            xa = torch.where(other[:, None], torch.full_like(xa, float("nan")), xa)
+        g = gpu_stage(cfg, w, text, max_block_frames=3, max_cache_frames=1, debug_taps=1, max_abs_frames=64)
+        g.forward(to_dev(xa, cfg), 3, 3, 625.0)
+        g.cache_update(kept, 1)
+        y = g.forward(to_dev(xb, cfg), 1, 0, 500.0)
+        assert torch.isfinite(y).all()
+        outs.append((y.clone(), g.peek("attn")))
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])

@@ -12,6 +12,19 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("name", ["tiny", "tiny_bf16", "wide128_bf16"])
 def test_captured_forward_replays_bit_exact(name):
+    replay(name)
+
+
+def test_captured_forward_with_cut_k_replays_bit_exact(monkeypatch):
+    """The FFN's second product cut into K ranges: partial sums in scratch, added up by a second launch."""
+    from test_gemm_routes import products
+    monkeypatch.setitem(synth.CONFIGS, "cut", dict(synth.CONFIGS["tiny_bf16"], dim=256, n_heads=2, head_dim=128, ffn_dim=2048, text_dim=256,
+                                                   tok_h=2, tok_w=4, block_frames=2))
+    assert products(synth.CONFIGS["cut"])["ffn2"][0] == "cut"
+    replay("cut")
+
+
+def replay(name):
     cfg, w, text, blocks = synth.make_case(name, seed=3, strong_gate=True)
     nf, nc = cfg["block_frames"], cfg["cache_frames"]
     g = gpu_stage(cfg, w, text)
