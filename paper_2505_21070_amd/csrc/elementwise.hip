@@ -435,19 +435,22 @@ template void launch_transpose_pad<float>(const float*, int64_t, int64_t, float*
 template void launch_transpose_pad<bf16_t>(const bf16_t*, int64_t, int64_t, bf16_t*, int64_t, hipStream_t);
 
 // ---------------------------------------------------------------- timestep modulation vector
-// Matrix-vector products of the timestep MLP, bound by one read of W.  A block owns 64 * CPL output columns and one of
-// gridDim.y slices of the K rows; a wavefront instruction reads one row's piece of them (256 bytes at CPL = 2 in bf16),
-// up to 16 rows in flight per wavefront, and the 16 wavefronts' sums meet in LDS.  (Lanes of a wavefront on different rows,
-// 16 bytes each, took 108 us where this takes 82: every row is another page.)  A sliced product leaves partial results
-// that its consumer adds up in slice order together with the bias; a whole one can add its result to the L rows of a table.
+// Matrix-vector products of the timestep MLP, bound by one read of W.  A block owns 64 * CPL output columns; a wavefront
+// instruction reads one row's piece of them (256 bytes at CPL = 2 in bf16), up to 16 rows in flight per wavefront, and the
+// 16 wavefronts' sums meet in LDS.  (Lanes of a wavefront on different rows, 16 bytes each, took 108 us where this takes
+// 82: every row is another page.)
+// The sum over K: slices of the rows (launch_gemv); in a slice wavefront w takes rows w, w + 16, .. into four chains in turn
+// (one chain per wavefront is 1.4 times as far from 64 bits at K = 5120), (0 + 1) + (2 + 3), the wavefronts in order; bias +
+// slices in order.  A product is either sliced over blocks, partial results left for the consumer to add up, or whole: a
+// block takes all slices of its columns and adds its result to the L rows of a table.
 // 5120 x 30720: 315 MB in 82 us = 3.8 TB/s, what a read-only pass reaches here; more rows in flight do not change it.
 // The chain (features, three products, table, rotation table) is three launches: 128-wide model 28 -> 13 us, 1536-wide
 // 39 -> 32 us under the profiler, which counts a launch as 4.6 us; 1 us each otherwise.
 template <typename T> struct GemvArgs {
   GemvIn in;
   const T *xbias, *W, *ybias;
-  int K, N;
-  float* y;
+  int K, N, slices;
+  float* y;                    // [slices][N], or null: whole
   const float* mtab; float* mod; int L;
   int cols;                    // blocks along N; further ones build the rotation table
 };
@@ -465,125 +468,163 @@ __device__ __forceinline__ void rope_token(const RopeTokens& r, int64_t i) {
 // 351 -> 359).
 template <typename T, int CPL, bool SINUS>
 __global__ __launch_bounds__(1024, SINUS ? 4 : 8) void k_gemv(GemvArgs<T> a, RopeTokens rope) {
-  constexpr int KC = 8192, U = SINUS ? 8 : 16;
+  constexpr int KC = 8192, U = SINUS ? 4 : 16, MS = CPL == 1 && !SINUS ? GEMV_MAX_SLICES : 1;   // MS: most slices a block takes
   __shared__ float xs[KC];
-  __shared__ float red[16][64 * CPL];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ float red[MS][16][64 * CPL];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (SINUS && (int)blockIdx.x >= a.cols) {
-    const int64_t i = (int64_t)((int)blockIdx.x - a.cols) * 1024 + tid;
+    const int64_t i = ((int64_t)((int)blockIdx.x - a.cols) * gridDim.y + blockIdx.y) * 1024 + tid;
     if (i < rope.S * (rope.rt.c_f + rope.rt.c_h + rope.rt.c_w)) rope_token(rope, i);
     return;
   }
-  const int ks = blockIdx.y, k0 = (int)((int64_t)a.K * ks / gridDim.y), Kb = (int)((int64_t)a.K * (ks + 1) / gridDim.y) - k0;
+  const int s0 = a.y ? (int)blockIdx.y : 0, ns = a.y ? 1 : MS < a.slices ? MS : a.slices;     // this block's slices
+  auto bound = [&](int s) __attribute__((always_inline)) { return (int)((int64_t)a.K * (s0 + s) / a.slices); };
   const int n0 = (int)blockIdx.x * 64 * CPL, n = n0 + lane * CPL;
   const T* const wn = a.W + (n < a.N ? n : 0);
-  float acc[CPL];
+  float acc[4][CPL];
 #pragma unroll
-  for (int v = 0; v < CPL; ++v) acc[v] = 0.f;
-  for (int c0 = 0; c0 < Kb; c0 += KC) {
-    const int kc = Kb - c0 < KC ? Kb - c0 : KC;
-    if (c0) __syncthreads();
-    const T* w = wn + (int64_t)(k0 + c0) * a.N;
-    // rows wave, wave + 16, ..: groups of U, the next group requested before this one is used (past the end: the last row
-    // again, not added)
+  for (int c = 0; c < 4; ++c)
+#pragma unroll
+    for (int v = 0; v < CPL; ++v) acc[c][v] = 0.f;
+  auto flush = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < CPL; ++v) {
+      red[s][wave][lane * CPL + v] = (acc[0][v] + acc[1][v]) + (acc[2][v] + acc[3][v]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c][v] = 0.f;
+    }
+  };
+  const int lo = bound(0), hi = bound(ns);
+  for (int w0 = lo; w0 < hi; w0 += KC) {               // several windows only in one slice: K <= KC otherwise
+    const int w1 = hi - w0 < KC ? hi : w0 + KC;
+    if (w0 > lo) __syncthreads();
+    // rows k, k + 16, .. of this wavefront, up to row e of the slice: groups of U, the next group requested before this one
+    // is used (past the end: the last row again, not added)
     using Piece = std::conditional_t<CPL == 2, uint32_t, T>;
     Piece d[2][U];
-    auto fetch = [&](int k, int z) __attribute__((always_inline)) {
+    auto fetch = [&](int k, int e, int z) __attribute__((always_inline)) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) d[z][u] = *(const Piece*)(w + (int64_t)(k + u * 16 < kc ? k + u * 16 : kc - 1) * a.N);
+      for (int u = 0; u < U; ++u) d[z][u] = *(const Piece*)(wn + (int64_t)(k + u * 16 < e ? k + u * 16 : e - 1) * a.N);
     };
-    auto add = [&](int k, int z) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (k + u * 16 < kc) {
-          const float x = xs[k + u * 16];
-          if constexpr (CPL == 2) {
-            acc[0] += x * __uint_as_float(d[z][u] << 16);
-            acc[1] += x * __uint_as_float(d[z][u] & 0xffff0000u);
-          } else {
-            acc[0] += x * Elem<T>::ld(&d[z][u]);
-          }
+    auto add = [&](int k, int e, int z) __attribute__((always_inline)) {
+      auto one = [&](int u, int c) __attribute__((always_inline)) {
+        const float x = xs[k - w0 + u * 16];
+        if constexpr (CPL == 2) {
+          acc[c][0] += x * __uint_as_float(d[z][u] << 16);
+          acc[c][1] += x * __uint_as_float(d[z][u] & 0xffff0000u);
+        } else {
+          acc[c][0] += x * Elem<T>::ld(&d[z][u]);
         }
+      };
+      if (k + (U - 1) * 16 < e) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) one(u, u & 3);
+      } else {                                         // rows of an incomplete last four all go to the first chain
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (k + (u | 3) * 16 < e) one(u, u & 3);
+          else if (k + u * 16 < e) one(u, 0);
+        }
+      }
     };
-    if (wave < kc) fetch(wave, 0);                     // travels while the activations are made
-    for (int k = tid; k < kc; k += 1024) {
-      const int kk = k0 + c0 + k;
+    int s = 0, k = w0 + wave, e = ns > 1 ? bound(1) : w1;
+    fetch(k, e, 0);                                    // travels while the activations are made
+    for (int i = tid; i < w1 - w0; i += 1024) {
+      const int kk = w0 + i;
       if constexpr (SINUS) {
-        const int half = a.K >> 1, i = kk < half ? kk : kk - half;
-        const double ang = (double)a.in.t * pow(10000.0, -(double)i / (double)half);
-        xs[k] = kk < half ? (float)cos(ang) : (float)sin(ang);
+        const int half = a.K >> 1, j = kk < half ? kk : kk - half;
+        const double ang = (double)a.in.t * pow(10000.0, -(double)j / (double)half);
+        xs[i] = kk < half ? (float)cos(ang) : (float)sin(ang);
       } else {
         float v = Elem<T>::ld(a.xbias + kk);
-        for (int p = 0; p < a.in.parts; ++p) v += a.in.x[(int64_t)p * a.K + kk];
-        xs[k] = v / (1.0f + expf(-v));                 // SiLU
+        const float* const xp = a.in.x + kk;
+        for (int p0 = 0; p0 < a.in.parts; p0 += 4) {   // four parts requested together
+          float part[4];
+#pragma unroll
+          for (int p = 0; p < 4; ++p) part[p] = xp[(int64_t)(p0 + p < a.in.parts ? p0 + p : p0) * a.K];
+#pragma unroll
+          for (int p = 0; p < 4; ++p)
+            if (p0 + p < a.in.parts) v += part[p];
+        }
+        xs[i] = v / (1.0f + expf(-v));                 // SiLU
       }
     }
     __syncthreads();
-    for (int k = wave; k < kc; k += 32 * U) {
-      if (k + 16 * U < kc) fetch(k + 16 * U, 1);
+    // one group, with the next one (of this slice or the next) on its way; false behind the window's last
+    auto step = [&](int z) __attribute__((always_inline)) {
+      int s2 = s, k2 = k + 16 * U, e2 = e;
+      if (k2 >= e) {
+        ++s2;
+        k2 = e + wave;
+        e2 = s2 < ns ? bound(s2 + 1) : e;
+      }
+      const bool more = s2 < ns;
+      if (more) fetch(k2, e2, z ^ 1);
       __builtin_amdgcn_sched_barrier(0);
-      add(k, 0);
-      if (k + 32 * U < kc) fetch(k + 32 * U, 0);
+      add(k, e, z);
       __builtin_amdgcn_sched_barrier(0);
-      if (k + 16 * U < kc) add(k + 16 * U, 1);
-    }
+      if (more && s2 != s) flush(s);
+      s = s2; k = k2; e = e2;
+      return more;
+    };
+    while (step(0) && step(1)) {}
   }
-#pragma unroll
-  for (int v = 0; v < CPL; ++v) red[wave][lane * CPL + v] = acc[v];
+  flush(ns - 1);
   __syncthreads();
   if (tid < 64 * CPL && n0 + tid < a.N) {
-    float y = 0.f;
+    float y = a.y ? 0.f : Elem<T>::ld(a.ybias + n0 + tid);
+    for (int s = 0; s < ns; ++s) {
+      float sum = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) y += red[i][tid];
-    if (a.y) a.y[(int64_t)ks * a.N + n0 + tid] = y;
-    if (a.L > 0) {
-      y += Elem<T>::ld(a.ybias + n0 + tid);
-      for (int l = 0; l < a.L; ++l) a.mod[(int64_t)l * a.N + n0 + tid] = a.mtab[(int64_t)l * a.N + n0 + tid] + y;
+      for (int i = 0; i < 16; ++i) sum += red[s][i][tid];
+      y += sum;
     }
+    if (a.y) a.y[(int64_t)s0 * a.N + n0 + tid] = y;
+    else
+      for (int l = 0; l < a.L; ++l) a.mod[(int64_t)l * a.N + n0 + tid] = a.mtab[(int64_t)l * a.N + n0 + tid] + y;
   }
 }
-// mod[l, i] = mtab[l, i] + sum_p e[p][i] + bias[i]: a sliced vector added to every row of a table
+// mod[l, i] = mtab[l, i] + (bias[i] + sum_p e[p][i]): a sliced vector added to every row of a table
 template <typename T>
 __global__ __launch_bounds__(256) void k_mod_add(const float* __restrict__ e, int parts, GemvTable<T> t, int n) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
-  float v = 0.f;
+  float v = Elem<T>::ld(t.bias + i);
   for (int p = 0; p < parts; ++p) v += e[(int64_t)p * n + i];
-  v += Elem<T>::ld(t.bias + i);
   for (int l = 0; l < t.L; ++l) t.mod[(int64_t)l * n + i] = t.mtab[(int64_t)l * n + i] + v;
+}
+// enough blocks of 64 columns for the 256 CUs, at least 64 rows each
+static int gemv_slices(int K, int N) {
+  int ks = cdiv(256, cdiv(N, 64));
+  if (ks > GEMV_MAX_SLICES) ks = GEMV_MAX_SLICES;
+  while (ks > 1 && K / ks < 64) --ks;
+  return ks;
 }
 template <typename T>
 int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, float* y, const GemvTable<T>* table,
                 const RopeTokens* rope, hipStream_t st) {
   // A product that ends in a table stays whole unless its columns make less than half a round of blocks that each have many
   // rows to read (5120 x 5120: 38 us whole, 21 sliced with a launch more; 1536 x 1536: 13 and 11 under the
-  // profiler, which counts the launch as 4.6 us).  A caller that gives no y wants it whole: the stage's, 6 * dim
-  // columns, of which a whole one at dim 1536 takes 17.5 us where two slices took 10.0 and the launch that adds them up
-  // 4.9 (the whole chain 27.3 us both ways, 1024 wide 21.9 against 24.5, 512 wide 18.4 against 21.7).
+  // profiler, which counts the launch as 4.6 us).  A caller that gives no y wants it whole: the stage's, 6 * dim columns
+  // (the whole chain / as six launches, us: dim 512 16.5 / 21.8, 1152 24.9 / 24.9, 1536 23.0 / 26.8, 5120 87 / 100).
   const bool whole = table && (!y || cdiv(N, 64) >= 128 || K <= 2048);
-  // two columns per lane, unless a whole product still has a CU for each block at one column (chains at dim 2816, 264
-  // blocks of 64 columns or 132 of 128: 57.8 and 38.4 us, 44.1 as six launches; 3584: 76.5, 57.8 and 71.4; one column up
-  // to dim 2688)
-  const bool wide = sizeof(T) == 2 && N % 2 == 0 && ((uintptr_t)W & 3) == 0 && (!whole || cdiv(N, 64) > 256);
+  // short slices cost a whole product a load latency each (chain at dim 512 24.7 us with six of them, 16.5 with one)
+  int slices = gemv_slices(K, N);
+  if (whole && K / slices < 384) slices = 1;
+  // two columns per lane where one would make more blocks than CUs: stage chains at dim 2816, 264 blocks of 64 columns or
+  // 132 of 128: 57.8 and 38.4 us, 44.1 as six launches; head at 1560 x 2560, 280 or 140: 27.0 and 25.8 us.  (The features'
+  // product, a few columns and rows, stays at one; a whole product with so many columns has one slice.)
+  const bool wide = sizeof(T) == 2 && in.x && N % 2 == 0 && ((uintptr_t)W & 3) == 0 && cdiv(N, 64) * (whole ? 1 : slices) > 256;
   const int cols = cdiv(N, wide ? 128 : 64);
-  int slices = 1;
-  if (!whole && in.x) {                                // enough blocks for the 256 CUs, at least 64 rows each
-    slices = cdiv(256, cols);
-    if (slices > GEMV_MAX_SLICES) slices = GEMV_MAX_SLICES;
-    while (slices > 1 && K / slices < 64) --slices;
-  }
-  GemvArgs<T> a{in, xbias, W, table ? table->bias : nullptr, K, N, whole ? nullptr : y, table ? table->mtab : nullptr,
-                table ? table->mod : nullptr, whole ? table->L : 0, cols};
+  GemvArgs<T> a{in, xbias, W, table ? table->bias : nullptr, K, N, slices, whole ? nullptr : y, table ? table->mtab : nullptr,
+                table ? table->mod : nullptr, table ? table->L : 0, cols};
   const RopeTokens r = rope ? *rope : RopeTokens{};
-  const int64_t extra = rope ? (rope->S * (rope->rt.c_f + rope->rt.c_h + rope->rt.c_w) + 1023) / 1024 : 0;
-  const dim3 grid((unsigned)(cols + extra), (unsigned)slices);
-#define GEMV_CASE(C, SIN) k_gemv<T, C, SIN><<<grid, 1024, 0, st>>>(a, r)
-  if constexpr (sizeof(T) == 2) {
-    if (wide && in.x) GEMV_CASE(2, false);
-    else if (wide) GEMV_CASE(2, true);
-  }
-  if (!wide) { if (in.x) GEMV_CASE(1, false); else GEMV_CASE(1, true); }
-#undef GEMV_CASE
+  const int per = 1024 * (whole ? 1 : slices);
+  const int64_t extra = rope ? (rope->S * (rope->rt.c_f + rope->rt.c_h + rope->rt.c_w) + per - 1) / per : 0;
+  const dim3 grid((unsigned)(cols + extra), (unsigned)(whole ? 1 : slices));
+  if (!in.x) k_gemv<T, 1, true><<<grid, 1024, 0, st>>>(a, r);
+  else if (!wide) k_gemv<T, 1, false><<<grid, 1024, 0, st>>>(a, r);
+  else if constexpr (sizeof(T) == 2) k_gemv<T, 2, false><<<grid, 1024, 0, st>>>(a, r);
   if (table && !whole) k_mod_add<T><<<cdiv(N, 256), 256, 0, st>>>(y, slices, *table, N);
   return slices;
 }
