@@ -651,12 +651,17 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   }
   return true;
 }
+// Duration of a block of the other large tiles over one of 256 x 256, from whole rounds of blocks at K = 1536 ... 13824, each
+// tile forced in turn: 160 rows (three LDS stages) 0.69 ... 0.74, 192 rows 0.81 ... 0.88, 320 rows 1.15 ... 1.25.  Where they
+// decide (us): 7800 x 5120 x 13824 160 rows in 4 rounds 1027, 256 rows in 3 1074; 9000 x 5632 x 1024 5 rounds 135, 4 143;
+// 7200 x 6720 x 3008 320 rows in 3 rounds 298, 160 rows in 5 307; 6240 x 13824 x 5120 320 rows in 5 761, 256 rows in 6 773.
+constexpr double kTile160 = 0.72, kTile192 = 0.88, kTile320 = 1.19;
 static GemmRoute big_heads_tile(int64_t M, int64_t N, bool any_transposed) {
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
   // the 160-row tile cannot exchange its operands; it pays where it fills the one round better (see below)
   const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
   const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
-  if (!any_transposed && fits160 && 0.80 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256)) return {160, 256, 3, 1};
+  if (!any_transposed && fits160 && kTile160 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256)) return {160, 256, 3, 1};
   return {256, 256, 2, 1};
 }
 
@@ -688,9 +693,12 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // Cutting K.  A long K over few tiles leaves most CUs idle, and small tiles in the hundreds move several times the bytes of
 // large ones through the caches.  Tiles whose K is cut over blocks until about one round of CUs is full do neither, for the
 // price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile 1.3
-// (256 x 256), 1.25 (160 x 256, three stages), 0.27 per block on the CU (64 x 64), 8 (4) for a block's ends, 3 for the
-// second launch, partials at 4 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU, 0.72 for 128 x 128, 1.3 per round
-// of 256 x 256.
+// (256 x 256), 1.25 (160 x 256 on a nearly full chip), 0.27 per block on the CU (64 x 64), 8 (4) for a block's ends, 3 for
+// the second launch, partials at 4 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU, 0.72 for 128 x 128, and 1.3 per
+// round of 256 x 256 also where another large tile would run: the estimate of a cut problem is high by about as much (its
+// partial results stay in the caches).  Cut / the fastest uncut large tile in us: 776 x 5120 x 5120 69 / 88 (160 rows),
+// 920 x 5120 x 5120 75 / 89, 1288 x 5120 x 13824 204 / 226, 2560 x 3072 x 12288 194 / 210, 2560 x 2048 x 8192 106 / 133: at none of
+// 45 sizes (128 ... 3072 rows, 768 ... 5120 columns) was an uncut large tile faster.
 static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats) {
   GemmRoute r{0, 0, 0, 1};                             // parts == 1: not cut
   if (N % 4) return r;
@@ -715,9 +723,9 @@ static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats
 }
 
 // One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.
-// 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration comes out lower:
-// 192x256 (0.88 of a 256x256 tile), 160x256 (0.80; 1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6
-// tiles fill one round where 33 x 6 leave 58 CUs idle) and 320x256 (1.25, fewer operand bytes per flop).
+// 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration (above) comes out lower:
+// 192x256, 160x256 (1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6 tiles fill one round where 33 x 6 leave
+// 58 CUs idle) and 320x256 (fewer operand bytes per flop).
 // The 160-, 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where
 // that stays inside the 256-row padding the caller guarantees.
 static GemmRoute big_tile(int64_t M, int64_t N) {
@@ -727,9 +735,9 @@ static GemmRoute big_tile(int64_t M, int64_t N) {
   const int64_t t320 = ((M + 319) / 320) * ((N + 255) / 256);
   const int64_t mpad = (M + 255) / 256 * 256;
   const double cost256 = (double)((t256 + 255) / 256);
-  const double cost192 = (M + 191) / 192 * 192 <= mpad ? 0.88 * (double)((t192 + 255) / 256) : 1e30;
-  const double cost160 = (M + 159) / 160 * 160 <= mpad ? 0.80 * (double)((t160 + 255) / 256) : 1e30;
-  const double cost320 = (M + 319) / 320 * 320 <= mpad ? 1.25 * (double)((t320 + 255) / 256) : 1e30;
+  const double cost192 = (M + 191) / 192 * 192 <= mpad ? kTile192 * (double)((t192 + 255) / 256) : 1e30;
+  const double cost160 = (M + 159) / 160 * 160 <= mpad ? kTile160 * (double)((t160 + 255) / 256) : 1e30;
+  const double cost320 = (M + 319) / 320 * 320 <= mpad ? kTile320 * (double)((t320 + 255) / 256) : 1e30;
   const double best = fmin(fmin(cost256, cost192), fmin(cost160, cost320));
   // on a tie the taller tile wins: fewer operand bytes per flop
   if (best == cost320) return {320, 256, 2, 1};

@@ -4,9 +4,9 @@
 // Bound: the fp32 matrix rate, 64 cycles an MFMA, 157 TFLOP/s over the chip (the vector unit has half of that without
 // its packed forms, and lost more of it to LDS reads: 45 TFLOP/s).  An MFMA sums two k; a lane group lg of a wavefront
 // takes k = 8j + 4lg + t for the t-th of four MFMAs, so that the A operand of four is one 16-byte LDS read of a row and
-// the W operand one 4-byte read each.  k-tiles of 32 go through registers into one of two LDS buffers, the next tile's
-// loads in flight while this one is multiplied.  Rows of As are 36 floats and rows of Ws BN + 8 apart: 16 rows x 16 bytes
-// and the two lane groups' rows (4 apart) then fall on different banks.
+// the W operand one 4-byte read each.  k-tiles (32 deep, 64 where the wavefronts share out K) go through registers into one
+// of two LDS buffers, the loads of the next two in flight while one is multiplied.  Rows of As are the k-tile + 4 floats
+// and rows of Ws BN + 8 apart: 16 rows x 16 bytes and the two lane groups' rows (4 apart) then fall on different banks.
 // 1560 x 1536 x 1536: 154 -> 88 us; 1560 x 8960 x 1536: 631 -> 391; 1560 x 1536 x 8960: 868 -> 462 (600 blocks: three on
 // some CUs, two on the others); q | k | v of 1560 x 1536: 492 in three launches -> 223 in one.
 #include "kernels.h"
@@ -223,8 +223,8 @@ void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw
   bool vec = K % 4 == 0 && N % 4 == 0 && lda % 4 == 0 && ldw % 4 == 0 && ((uintptr_t)A & 15) == 0;
   for (int i = 0; i < w.n; ++i) vec = vec && ((uintptr_t)w.w[i] & 15) == 0;
   // 64 x 64 tiles, up to four blocks to a CU, unless 128 x 128 ones (two to a CU, half the operand bytes per flop) make at
-  // least two full rounds: 1560 x 8960 x 1536 (912 of them) 391 against 413 us, 1560 x 1536 x 8960 (156) 462 against 639;
-  // 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s where 64 x 64 tiles stay at 110.  Fewer than one 64 x 64 tile per CU:
+  // least two full rounds.  64 x 64 against 128 x 128: 1560 x 8960 x 1536 (910 of the large ones) 391 against 413 us, 1560 x 1536
+  // x 8960 (156) 462 against 639; 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s on 128 x 128 where 64 x 64 stay at 110.  Fewer than one 64 x 64 tile per CU:
   // 32 x 32 tiles with K dealt over the wavefronts (whole passes: 128 tokens x 128 channels 200 -> 148 us, 300 x 768 301 -> 210,
   // 750 x 768 379 -> 340)
   const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128) * w.n;
