@@ -493,9 +493,11 @@ extern "C" int dp_embed_forward(dp_ends_t* s, const float* latent, void* x_out, 
 static void launch_head(dp_ends* s, const void* x_in, float* v_out, int64_t S, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
   const int ng = (c.dim / 64 + 7) / 8, xa = ((uintptr_t)x_in & 15) == 0, va = ((uintptr_t)v_out & 15) == 0;
-  // 32 tokens a block halve the reads of the weights; with fewer than 128 such blocks 16 spread over more CUs
-  // (14400 x 5120: 57 against 66 us, 6240 x 1536: 11.4 against 12.5)
-  const bool two = S >= 4096;
+  // 32 tokens a block halve the reads of the weights, 16 spread few tokens over more CUs: up to 4095, or one round of 16-token
+  // blocks.  16 / 32 tokens a block in us (the whole call): 4096 x 1536 23.7 / 25.2, 4590 x 1536 26.0 / 25.2, 4096 x 4096 37.1 / 39.4,
+  // 4590 x 4096 43.3 / 39.4, 14400 x 5120 85.6 / 76.7; four times the blocks with 64 latent channels: 4096 x 1536 35.4 / 34.2,
+  // 3072 x 1536 30.4 / 33.9.  (9360 tokens are 293 blocks of 32: 34.9 us at 1536, 30.6 with 16.)
+  const bool two = S >= 4096 && (S + 15) / 16 * (s->P / 64) > 256;
   const dim3 grid((unsigned)((S + (two ? 31 : 15)) / (two ? 32 : 16)), (unsigned)(s->P / 64));
 #define HEAD_CASE(NG, RT) k_head<NG, RT><<<grid, 512, 0, st>>>((const bf16_t*)x_in, S, c.dim, c.eps, s->mod + c.dim, s->mod, \
     (const uint4*)s->w_head_t, (const bf16_t*)s->w.b_head, (int)s->P, v_out, (int)s->tok, c.tok_w, c.channels, xa, va)
