@@ -436,16 +436,16 @@ template void launch_transpose_pad<bf16_t>(const bf16_t*, int64_t, int64_t, bf16
 
 // ---------------------------------------------------------------- timestep modulation vector
 // Matrix-vector products of the timestep MLP, bound by one read of W.  A block owns 64 * CPL output columns; a wavefront
-// instruction reads one row's piece of them (256 bytes at CPL = 2 in bf16), up to 16 rows in flight per wavefront, and the
-// 16 wavefronts' sums meet in LDS.  (Lanes of a wavefront on different rows, 16 bytes each, took 108 us where this takes
+// instruction reads one row's piece of them (256 bytes at CPL = 2 in bf16), 16 to 32 rows in flight per wavefront, and the
+// 16 wavefronts' sums meet in LDS.  (Lanes of a wavefront on different rows, 16 bytes each, took 108 us where this took
 // 82: every row is another page.)
 // The sum over K: slices of the rows (launch_gemv); in a slice wavefront w takes rows w, w + 16, .. into four chains in turn
 // (one chain per wavefront is 1.4 times as far from 64 bits at K = 5120), (0 + 1) + (2 + 3), the wavefronts in order; bias +
 // slices in order.  A product is either sliced over blocks, partial results left for the consumer to add up, or whole: a
 // block takes all slices of its columns and adds its result to the L rows of a table.
-// 5120 x 30720: 315 MB in 82 us = 3.8 TB/s, what a read-only pass reaches here; more rows in flight do not change it.
+// 5120 x 30720: 315 MB in 78 us = 4.0 TB/s, what a read-only pass reaches here; more rows in flight do not change it.
 // The chain (features, three products, table, rotation table) is three launches: 128-wide model 28 -> 13 us, 1536-wide
-// 39 -> 32 us under the profiler, which counts a launch as 4.6 us; 1 us each otherwise.
+// 39 -> 29 us under the profiler, which counts a launch as 4.6 us; 1 us each otherwise.
 template <typename T> struct GemvArgs {
   GemvIn in;
   const T *xbias, *W, *ybias;

@@ -654,8 +654,8 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
 // Duration of a block of the other large tiles over one of 256 x 256, from whole rounds of blocks at K = 1536 ... 13824, each
 // tile forced in turn: 160 rows (three LDS stages) 0.69 ... 0.74, 192 rows 0.81 ... 0.88, 320 rows 1.15 ... 1.25.  Where they
 // decide (us): 7800 x 5120 x 13824 160 rows in 4 rounds 1027, 256 rows in 3 1074; 9000 x 5632 x 1024 5 rounds 135, 4 143;
-// 7200 x 6720 x 3008 320 rows in 3 rounds 298, 160 rows in 5 307; 6240 x 13824 x 5120 320 rows in 5 761, 256 rows in 6 773.
-constexpr double kTile160 = 0.72, kTile192 = 0.88, kTile320 = 1.19;
+// 7200 x 6720 x 3008 320 rows in 3 rounds 298, 160 rows in 5 307; 18720 x 8960 x 1536 256 rows in 11 512, 320 rows in 9 516.
+constexpr double kTile160 = 0.74, kTile192 = 0.88, kTile320 = 1.23;
 static GemmRoute big_heads_tile(int64_t M, int64_t N, bool any_transposed) {
   const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
   // the 160-row tile cannot exchange its operands; it pays where it fills the one round better (see below)
