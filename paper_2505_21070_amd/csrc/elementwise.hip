@@ -608,9 +608,10 @@ int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, floa
   // profiler, which counts the launch as 4.6 us).  A caller that gives no y wants it whole: the stage's, 6 * dim columns
   // (the whole chain / as six launches, us: dim 512 16.5 / 21.8, 1152 24.9 / 24.9, 1536 23.0 / 26.8, 5120 87 / 100).
   const bool whole = table && (!y || cdiv(N, 64) >= 128 || K <= 2048);
-  // short slices cost a whole product a load latency each (chain at dim 512 24.7 us with six of them, 16.5 with one)
+  // short slices cost a whole product a load latency each (chain at dim 512 24.7 us with six of them, 16.5 with one); the
+  // kernel's limits for several in one block are K <= 8192 and no features to make
   int slices = gemv_slices(K, N);
-  if (whole && K / slices < 384) slices = 1;
+  if (whole && (K / slices < 384 || K > 8192 || !in.x)) slices = 1;
   // two columns per lane where one would make more blocks than CUs: stage chains at dim 2816, 264 blocks of 64 columns or
   // 132 of 128: 57.8 and 38.4 us, 44.1 as six launches; head at 1560 x 2560, 280 or 140: 27.0 and 25.8 us.  (The features'
   // product, a few columns and rows, stays at one; a whole product with so many columns has one slice.)
