@@ -3,8 +3,8 @@
 //
 // Block tile BM x BN x 64, WGM x WGN wavefronts, each owning a (BM/WGM) x (BN/WGN) sub-tile built from
 // v_mfma_f32_32x32x16_bf16.  k-tiles go HBM -> LDS directly (no staging registers, no LDS stores) into
-// two buffers: k-tile kt+1 is in flight while k-tile kt is multiplied (160-row tiles have three and two in
-// flight; problems of few tiles take small tiles and a ring of loads, see the ST > 2 loop and tile_family).  Operand fragments are
+// two buffers: k-tile kt+1 is in flight while k-tile kt is multiplied (problems of few tiles take small tiles and a
+// ring of loads, see the ST > 2 loop; mid-size tiles run in turns, see k_gemm_turns; which takes what: tile_family, big_tile).  Operand fragments are
 // double-buffered in registers: those of k-step ks+1 are read from LDS while the MFMAs of k-step ks run.
 // The issue order of the main loop is pinned (see there): the two wavefronts of a SIMD are served oldest
 // first rather than interleaved, so each has to keep the matrix pipe busy on its own; tile loads go out
@@ -19,6 +19,7 @@
 #include "kernels.h"
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
@@ -53,242 +54,24 @@ template <int NM, int NR> constexpr int reads_before(int n, int first) {
   for (int k = 0; k < NR; ++k) c += first + k * (NM - first) / NR < n ? 1 : 0;
   return c;
 }
-// ST: LDS stages.  Tiles of more than 128 rows run the pinned loop below (two stages, or three where they fit), smaller ones
-// a ring of ST > 2.
-template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
-__global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
-                                                             const bf16_t* __restrict__ Bt, int64_t ldb,
-                                                             int64_t M, int64_t N, int64_t K, int tiles_n,
-                                                             int tiles, int parts, EpiArgs e, HeadsArgs ha) {
-  constexpr int NT = WGM * WGN * 64;
-  constexpr int WM = BM / WGM, WN = BN / WGN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int IA = (BM * 8 + NT - 1) / NT, IB = BN * 8 / NT;   // wavefront load instructions per k-tile (64 chunks each)
-  constexpr bool A_RAGGED = BM * 8 % NT != 0;                  // the last wavefronts' share of the A tile is shorter
-  constexpr int STAGE = (BM + BN) * 8;                   // 16-byte chunks per LDS buffer
-  static_assert(BM * 8 % 64 == 0 && BN * 8 % NT == 0, "tile/thread mismatch");
-  extern __shared__ uint4 smem[];
+// Accumulators of v_mfma_f32_MF x MF: lane l holds column l % MF and, per register quad q, the four consecutive rows
+// q * 8 + (l / MF) * 4 + (0..3)
+template <int MF> struct Mfma;
+template <> struct Mfma<32> { typedef f32x16 acc; };
+template <> struct Mfma<16> { typedef f32x4 acc; };
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
-  // Blocks are dealt round-robin over the 8 XCDs, each with its own L2: give every XCD a contiguous run
-  // of work ids (row-major tiles, so neighbours share the A row-panel and walk the B panels together).
-  // The grid is padded to a multiple of 8; the padding blocks have nothing to do.
-  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-  if (pid >= tiles * parts) return;
-  const int part = EPI == EPI_PART ? pid / tiles : 0, tile = EPI == EPI_PART ? pid % tiles : pid;   // K range, output tile
-  // tiles are walked in bands of 4 tile rows, column by column inside a band: the ~32 blocks an XCD runs
-  // at a time then cover about 4 x 8 tiles and share 4 A panels and 8 B panels instead of 1 and 32
-  const int tiles_m = tiles / tiles_n;
-  const int band = tile / (4 * tiles_n), in_band = tile % (4 * tiles_n);
-  const int band_rows = tiles_m - band * 4 < 4 ? tiles_m - band * 4 : 4;
-  const int64_t m0 = (int64_t)(band * 4 + in_band % band_rows) * BM, n0 = (int64_t)(in_band / band_rows) * BN;
-  const int kt0 = EPI == EPI_PART ? (int)((K / 64) * part / parts) : 0;
-  const int KT = EPI == EPI_PART ? (int)((K / 64) * (part + 1) / parts) - kt0 : (int)(K / 64);
-
-  // EPI_HEADS: a tile of a section that is stored channel-major is computed with the operands exchanged
-  // (square tiles only), so that its accumulators, staging tile and row stores are those of C^T
-  int sec = 0;
-  bool swapped = false;
-  if constexpr (EPI == EPI_HEADS) {
-    sec = (int)(n0 / ha.dim);
-    if constexpr (BM == BN) swapped = ha.sec[sec].transposed != 0;
-  }
-  const bf16_t* const pa = (swapped ? Bt + n0 * ldb : A + m0 * lda) + kt0 * 64;
-  const bf16_t* const pb = (swapped ? A + m0 * lda : Bt + n0 * ldb) + kt0 * 64;
-  const int64_t lpa = swapped ? ldb : lda, lpb = swapped ? lda : ldb;
-  // slot p of a tile holds chunk (p & 7) ^ ((row >> 1) & 7) of row p >> 3; one wavefront instruction
-  // fills slots [base, base + 64), lane l the slot base + l
-  const bf16_t* gA[IA]; const bf16_t* gB[IB];
-#pragma unroll
-  for (int i = 0; i < IA; ++i) {
-    const int p = (wave * IA + i) * 64 + lane, row = p >> 3, ch = (p & 7) ^ ((row >> 1) & 7);
-    gA[i] = pa + row * lpa + ch * 8;
-  }
-#pragma unroll
-  for (int i = 0; i < IB; ++i) {
-    const int p = (wave * IB + i) * 64 + lane, row = p >> 3, ch = (p & 7) ^ ((row >> 1) & 7);
-    gB[i] = pb + row * lpb + ch * 8;
-  }
-  // load instruction q < IA + IB of this wavefront's share of k-tile kt into stage bufi
-  auto load_part = [&](int kt, int bufi, int q) __attribute__((always_inline)) {
-    if (kt >= KT) return;
-    const int t = kt * 64;
-    uint4* base = smem + bufi * STAGE;
-    if (q < IA) {
-      if (!A_RAGGED || (wave * IA + q) * 64 < BM * 8)
-        __builtin_amdgcn_global_load_lds((glb_void_t*)(gA[q] + t), (lds_void_t*)(base + (wave * IA + q) * 64), 16, 0, 0);
-    } else {
-      __builtin_amdgcn_global_load_lds((glb_void_t*)(gB[q - IA] + t), (lds_void_t*)(base + BM * 8 + (wave * IB + q - IA) * 64), 16, 0, 0);
-    }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int lr = lane & 31, lg = lane >> 5;
-  int arow[TM], brow[TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) arow[i] = wm * WM + i * 32 + lr;
-#pragma unroll
-  for (int j = 0; j < TN; ++j) brow[j] = wn * WN + j * 32 + lr;
-
-  // Software pipeline.  k-tile kt+1 is in flight while k-tile kt is multiplied; the fragments of k-step
-  // ks+1 are read while the MFMAs of k-step ks run, one read behind each of the first MFMAs, in the order in
-  // which the next step's MFMAs first need them.  The LDS reads are issued through inline assembly and
-  // waited for with explicit counts: the compiler would wait for all outstanding reads before the first
-  // MFMA of a step (the last of them only two MFMAs old), which stalls a wavefront whenever the other
-  // wavefront of its SIMD is not there to fill the gap; here an MFMA waits only for the fragments it
-  // needs, issued most of a k-step earlier.  LDS returns reads in order, so "at most c reads outstanding"
-  // means every read but the c newest has landed.
-  constexpr int NM = TM * TN, NR = TM + TN;              // MFMAs and fragment reads per k-step
-  constexpr int NB = NM >= 8 ? 2 : 1;                    // MFMAs of the last k-step issued before the barrier
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
-  static_assert(WM % 16 == 0 && WN % 16 == 0, "every fragment row of a lane has the same swizzle");
-  // chunk (ks * 2 + lg) ^ s of a row, s = (row >> 1) & 7 = (lr >> 1) & 7 for all of this lane's fragment rows,
-  // is at byte (ks * 32) ^ swz of the row
-  const uint32_t swz = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
-  uint32_t fbase[NR];                                    // fragment f: LDS byte offset of this lane's row in stage 0
-#pragma unroll
-  for (int f = 0; f < NR; ++f) {
-    const bool is_a = f == 0 || f > TN;
-    const int row = is_a ? arow[f == 0 ? 0 : f - TN] : brow[f - 1];
-    fbase[f] = lds0 + (uint32_t)((is_a ? 0 : BM * 8) + row * 8) * 16;
-  }
-  bf16x8 af[2][TM], bfr[2][TN];
-  // fragment f of k-step ks of the stage at byte offset `stage` into register buffer `to`
-  auto read_frag = [&](uint32_t stage, int ks, int f, int to) __attribute__((always_inline)) {
-    const u32x4 v = lds_read16_raw<0>(fbase[f] + (stage + (swz ^ (uint32_t)(ks * 32))));
-    if (f == 0) af[to][0] = __builtin_bit_cast(bf16x8, v);
-    else if (f <= TN) bfr[to][f - 1] = __builtin_bit_cast(bf16x8, v);
-    else af[to][f - TN] = __builtin_bit_cast(bf16x8, v);
-  };
-  // The NL load instructions of a k-tile are spread, one behind an MFMA, over the NS MFMAs that follow the
-  // barrier which frees their stage (the rest of the last k-step and the first k-step of the next k-tile):
-  // issued together right behind the barrier they fill the vector-memory queue, and a wavefront that waits
-  // there to issue a load cannot issue the MFMAs behind it either.
-  constexpr int NL = IA + IB, NS = (NM - NB) + NM;
-  if constexpr (ST > 2 && BM <= 128) {
-    // Ring of ST stages.  A small tile's k-tile is multiplied in a fraction of the time its loads travel, and a small
-    // problem has no second block to fill the gap, so ST - 1 k-tiles are in flight: tile kt is waited for by its place
-    // in the queue of vector loads (they arrive in order), not by an empty queue.  Behind the barrier every wavefront
-    // has tile kt, and all are done with tile kt - 1, whose stage the next loads go to.
-    static_assert(!A_RAGGED, "every wavefront issues the same loads");
-    static_assert(4 * NR <= 16, "one k-tile's fragment reads are counted in lgkmcnt");
-#pragma unroll
-    for (int z = 0; z < ST - 1; ++z)
-#pragma unroll
-      for (int q = 0; q < NL; ++q) load_part(z, z, q);
-    bf16x8 fr[4][NR];
-    int stage = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-      const int behind = KT - 1 - kt;                    // tiles behind this one that are (or were) still to come
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<ST - 1>([&](auto r_) __attribute__((always_inline)) {
-        constexpr int r = decltype(r_)::value;           // tiles in flight behind tile kt: min(ST - 2, behind)
-        if (r == ST - 2 ? behind >= r : behind == r) vm_wait<r * NL>();
-      });
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      const int nxt = stage == 0 ? ST - 1 : stage - 1;   // (kt + ST - 1) % ST
-#pragma unroll
-      for (int q = 0; q < NL; ++q) load_part(kt + ST - 1, nxt, q);
-      __builtin_amdgcn_sched_barrier(0);
-      const uint32_t base = (uint32_t)stage * STAGE * 16;
-      static_for<4 * NR>([&](auto i_) __attribute__((always_inline)) {
-        constexpr int ks = decltype(i_)::value / NR, f = decltype(i_)::value % NR;
-        fr[ks][f] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fbase[f] + (base + (swz ^ (uint32_t)(ks * 32)))));
-      });
-      static_for<4>([&](auto ks_) __attribute__((always_inline)) {
-        constexpr int ks = decltype(ks_)::value;
-        lds_wait<(3 - ks) * NR>();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[ks][1 + j], fr[ks][i == 0 ? 0 : TN + i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      stage = stage + 1 == ST ? 0 : stage + 1;
-    }
-  } else {
-  // Barrier behind which tile `next` (its loads the oldest in flight) is in LDS for everyone and the stage read before it is
-  // free.  With three stages the loads of the tile after it stay in flight: a wavefront waits for all but its own share of
-  // that tile (the last wavefronts' share is shorter where the A tile does not divide).
-  auto next_tile = [&](bool more) __attribute__((always_inline)) {
-    if constexpr (ST == 2) {
-      tile_barrier();
-    } else {
-      lds_wait<0>();
-      if (!more) vm_wait<0>();
-      else if (!A_RAGGED || (wave + 1) * IA * 64 <= BM * 8) vm_wait<NL>();
-      else if (wave * IA * 64 >= BM * 8) vm_wait<IB>();
-      else vm_wait<IB + (BM * 8 / 64) % IA>();
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  static_assert(!A_RAGGED || BM * 8 % 64 == 0, "whole wavefront instructions");
-#pragma unroll
-  for (int z = 0; z < ST - 1; ++z)
-#pragma unroll
-    for (int q = 0; q < NL; ++q) load_part(z, z, q);
-  next_tile(KT > 1);
-  static_for<NL>([&](auto q_) __attribute__((always_inline)) {
-    constexpr int q = decltype(q_)::value;
-    if constexpr (q * NS / NL < NM - NB) load_part(ST - 1, ST - 1, q);           // the part that k-step 3 would have issued
-  });
-#pragma unroll
-  for (int f = 0; f < NR; ++f) read_frag(0, 0, f, 0);
-  int s_cur = 0, s_nxt = 1, s_prev = ST - 1;             // stages of tiles kt, kt + 1 and kt - 1
-  for (int kt = 0; kt < KT; ++kt) {
-    const uint32_t cur = (uint32_t)s_cur * STAGE * 16, nxt = (uint32_t)s_nxt * STAGE * 16;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      static_for<NM>([&](auto n_) __attribute__((always_inline)) {
-        constexpr int n = decltype(n_)::value, i = n / TN, j = n % TN;
-        constexpr int need = frag_need<TN>(n), prev = n == 0 ? -1 : frag_need_upto<TN>(n - 1);
-        if (ks < 3) {
-          // reads of step ks+1 issued so far in this step: those with k * NM / NR < n
-          if constexpr (need > prev) lds_wait<NR - 1 - need + reads_before<NM, NR>(n, 0)>();
-        } else {
-          if constexpr (n < NB) { if constexpr (need > prev) lds_wait<NR - 1 - need>(); }
-          if constexpr (n == NB) next_tile(kt + 2 < KT);   // every read of this k-tile has landed (lgkmcnt(0) precedes it)
-        }
-        __builtin_amdgcn_sched_barrier(0);               // the MFMA stays behind the wait for its fragments
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
-        static_for<NR>([&](auto k_) __attribute__((always_inline)) {
-          constexpr int k = decltype(k_)::value;
-          if (ks < 3) { if constexpr (k * NM / NR == n) read_frag(cur, ks + 1, k, (ks + 1) & 1); }
-          else { if constexpr (n >= NB && NB + k * (NM - NB) / NR == n) read_frag(nxt, 0, k, 0); }
-        });
-        static_for<NL>([&](auto q_) __attribute__((always_inline)) {
-          constexpr int q = decltype(q_)::value, slot = q * NS / NL;       // MFMAs after the barrier
-          if (ks == 3) { if constexpr (n >= NB && slot == n - NB) load_part(kt + ST, s_cur, q); }
-          else if (ks == 0) { if constexpr (slot == (NM - NB) + n) load_part(kt + ST - 1, s_prev, q); }
-        });
-        __builtin_amdgcn_sched_barrier(0);               // keeps the MFMAs, reads, loads and waits in this order
-      });
-    }
-    s_prev = s_cur; s_cur = s_nxt; s_nxt = s_nxt + 1 == ST ? 0 : s_nxt + 1;
-  }
-  }
-  lds_wait<0>();
-
-  // Epilogue.  The MFMAs ran with the weight rows as the A operand, so a lane holds the output row
+// A block's epilogue over its BM x BN tile; LB: bytes of LDS (free by now) that it may stage through.
+template <int MF, int BM, int BN, int WGM, int WGN, int TM, int TN, int EPI, int LB>
+__device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN], uint4* smem, int64_t m0, int64_t n0, int64_t M,
+                                            int64_t N, int part, int sec, bool swapped, const EpiArgs& e, const HeadsArgs& ha) {
+  // The MFMAs ran with the weight rows as the A operand, so a lane holds the output row
   // m = .. + lr and, per register quad q, the four consecutive columns n = .. + q*8 + lg*4 + (0..3).
   // The tile goes through LDS (free now) so that global memory sees whole rows: 16 bytes per lane,
   // consecutive lanes on consecutive addresses.  LDS rows are XOR-swizzled with the row index so that
   // neither the column-wise writes nor the row-wise reads conflict on banks.
-  constexpr int NW = WGM * WGN;
+  constexpr int NW = WGM * WGN, NT = NW * 64, WM = BM / WGM, WN = BN / WGN, Q = MF == 32 ? 4 : 1;   // register quads of an accumulator tile
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & (MF - 1), lg = lane / MF;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WGN, wn = wave % WGN;
   constexpr int XM = BN / 4 < 32 ? BN / 4 - 1 : 31;      // row bits in the XOR: a row of 8-byte units has BN / 4 of them
   const bf16_t* bias = (const bf16_t*)e.bias;
   if constexpr (EPI == EPI_HEADS) {
@@ -298,28 +81,54 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
     // a lane holds 8 consecutive channels of one row, so that the table and gain reads are contiguous
     // across lanes.  A transposed section is C^T already.
     constexpr int UPR = BN / 4, CPR = BN / 8, RPI = 64 / CPR;
-    static_assert(BM * BN * 2 <= (BM + BN) * 256, "EPI_HEADS stages the whole tile at once");
-    // [row][wavefront column]: sums of squares; behind the staged tile where three stages leave no static LDS
-    constexpr bool RED_DYN = ST == 3 && BM > 128;
+    static_assert(BM * BN * 2 <= LB, "EPI_HEADS stages the whole tile at once");
+    // [row][wavefront column]: sums of squares; behind the staged tile where there is room
+    constexpr bool RED_DYN = BM * BN * 2 + BM * WGN * 4 <= LB;
     __shared__ float red_static[RED_DYN ? 1 : BM * WGN];
     float* const red = RED_DYN ? (float*)smem + BM * BN / 2 : red_static;
-    static_assert(!RED_DYN || BM * BN * 2 + BM * WGN * 4 <= (BM + BN) * 128 * ST, "the sums fit behind the tile");
     const HeadSection sc = ha.sec[sec];
     const int64_t nsec = n0 - (int64_t)sec * ha.dim;     // first column of this tile inside its section
     const int hshift = ha.head_dim == 128 ? 7 : 6, hmask = ha.head_dim - 1;
     uint2* l8 = (uint2*)smem;
     __syncthreads();
+    if constexpr (MF == 16) {
+      if (swapped) {
+        // C^T: a lane holds channel wn * WN + j * 16 + lr and, per quad, four consecutive output rows; staged as BN rows of BM
+        constexpr int TU = BM / 4, TX = TU % 32 == 0 ? 31 : 7;           // 8-byte units of a row, row bits in the XOR
+        static_assert(TU % 8 == 0, "the XOR stays inside a row");
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int row = wn * WN + j * 16 + lr;
+          const float bvr = bias && n0 + row < N ? bf16_to_f32(bias[n0 + row]) : 0.f;
+#pragma unroll
+          for (int i = 0; i < TM; ++i) {
+            const uint2 pk = make_uint2(cvt_pk_bf16(acc[i][j][0] + bvr, acc[i][j][1] + bvr), cvt_pk_bf16(acc[i][j][2] + bvr, acc[i][j][3] + bvr));
+            l8[row * TU + (((wm * WM + i * 16) / 4 + lg) ^ (row & TX))] = pk;
+          }
+        }
+        __syncthreads();
+        for (int c = tid; c < BN * (BM / 8); c += NT) {
+          const int row = c / (BM / 8), p = c % (BM / 8);
+          uint4 d = smem[c];
+          if (row & 1) d = make_uint4(d.z, d.w, d.x, d.y);
+          const int64_t m = m0 + (p ^ ((row & TX) >> 1)) * 8;
+          if (n0 + row < N && m < M)
+            __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)sc.dst + (nsec + row) * sc.ld + sc.row0 + m));
+        }
+        return;
+      }
+    }
     if (swapped) {
       // lane: channel row (weight row) nsec + wm*WM + i*32 + lr; register quad: 4 consecutive output rows m
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row = wm * WM + i * 32 + lr;
+        const int row = wm * WM + i * MF + lr;
         const float bvr = bias && n0 + row < N ? bf16_to_f32(bias[n0 + row]) : 0.f;
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int nl = wn * WN + j * 32 + q * 8 + lg * 4;
+          for (int q = 0; q < Q; ++q) {
+            const int nl = wn * WN + j * MF + q * 8 + lg * 4;
             uint2 pk;
             pk.x = cvt_pk_bf16(acc[i][j][q * 4 + 0] + bvr, acc[i][j][q * 4 + 1] + bvr);
             pk.y = cvt_pk_bf16(acc[i][j][q * 4 + 2] + bvr, acc[i][j][q * 4 + 3] + bvr);
@@ -333,8 +142,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int nl = wn * WN + j * 32 + q * 8 + lg * 4;
+        for (int q = 0; q < Q; ++q) {
+          const int nl = wn * WN + j * MF + q * 8 + lg * 4;
           float bv[4] = {0.f, 0.f, 0.f, 0.f};
           if (bias && n0 + nl < N) {
             const uint2 b4 = *(const uint2*)(bias + n0 + nl);
@@ -343,7 +152,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
           }
 #pragma unroll
           for (int i = 0; i < TM; ++i) {
-            const int row = wm * WM + i * 32 + lr;
+            const int row = wm * WM + i * MF + lr;
             float v[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -358,8 +167,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
         }
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const float tot = ss[i] + __shfl_xor(ss[i], 32, 64);
-        if (lg == 0) red[(wm * WM + i * 32 + lr) * WGN + wn] = tot;
+        float tot = ss[i];
+        if constexpr (MF == 16) tot += __shfl_xor(tot, 16, 64);
+        tot += __shfl_xor(tot, 32, 64);
+        if (lg == 0) red[(wm * WM + i * MF + lr) * WGN + wn] = tot;
       }
     }
     __syncthreads();
@@ -461,7 +272,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
     constexpr int UPR = BN / 4;                          // 8-byte units (4 bf16) per LDS row
     constexpr int CPR = BN / 8, RPI = 64 / CPR;          // 16-byte chunks per row, rows per wavefront read
     // the whole tile at once if it fits the two operand buffers, else one wavefront row (WM rows) per pass
-    constexpr int SP = (BM * BN * 2 <= (BM + BN) * 256) ? 1 : WGM, RP = BM / SP;
+    constexpr int SP = BM * BN * 2 <= LB ? 1 : WGM, RP = BM / SP;
     uint2* l8 = (uint2*)smem;
 #pragma unroll
     for (int pass = 0; pass < SP; ++pass) {
@@ -470,8 +281,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int nl = wn * WN + j * 32 + q * 8 + lg * 4;
+          for (int q = 0; q < Q; ++q) {
+            const int nl = wn * WN + j * MF + q * 8 + lg * 4;
             float bv[4] = {0.f, 0.f, 0.f, 0.f};
             if (bias && n0 + nl < N) {
               const uint2 b4 = *(const uint2*)(bias + n0 + nl);
@@ -480,7 +291,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
             }
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
-              const int row = (SP == 1 ? wm * WM : 0) + i * 32 + lr;      // row inside this pass
+              const int row = (SP == 1 ? wm * WM : 0) + i * MF + lr;      // row inside this pass
               float v[4];
 #pragma unroll
               for (int t = 0; t < 4; ++t) {
@@ -509,10 +320,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
       }
     }
   } else {
+    static_assert(MF == 32, "the other accumulators' is in k_gemm_turns");
     // residual stream: x[m, n] += gate[n] * (acc + bias[n]) in fp32 (EPI_PART: this range's x[m, n] = acc).  Passes over the wavefront rows of the
     // block tile and, inside one, over groups of GI 32-row accumulator tiles: as many as fit in LDS as floats
     constexpr int CPR = BN / 4, RPI = 64 / CPR;          // 16-byte chunks (4 floats) per row
-    constexpr int GI_FIT = (BM + BN) * 256 / (32 * BN * 4), GI = GI_FIT < TM ? GI_FIT : TM;
+    constexpr int GI_FIT = LB / (32 * BN * 4), GI = GI_FIT < TM ? GI_FIT : TM;
     static_assert(GI >= 1, "one 32-row tile of fp32 results must fit the operand buffers");
     float4* l16 = (float4*)smem;
 #pragma unroll
@@ -538,8 +350,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
 #pragma unroll
           for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int nl = wn * WN + j * 32 + q * 8 + lg * 4;
+            for (int q = 0; q < Q; ++q) {
+              const int nl = wn * WN + j * MF + q * 8 + lg * 4;
               float bv[4] = {0.f, 0.f, 0.f, 0.f};
               float4 gv = make_float4(1.f, 1.f, 1.f, 1.f);
               if (EPI == EPI_RESID && n0 + nl < N) {
@@ -553,7 +365,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
 #pragma unroll
               for (int ii = 0; ii < GI; ++ii) {
                 if (i0 + ii < TM) {
-                  const int row = ii * 32 + lr;
+                  const int row = ii * MF + lr;
                   float4 v;
                   v.x = gv.x * (acc[i0 + ii][j][q * 4 + 0] + bv[0]);
                   v.y = gv.y * (acc[i0 + ii][j][q * 4 + 1] + bv[1]);
@@ -596,6 +408,467 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   }
 }
 
+// ST: LDS stages.  Tiles of more than 128 rows run the pinned loop below (two stages), smaller ones a ring of ST > 2.
+template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
+__global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
+                                                             const bf16_t* __restrict__ Bt, int64_t ldb,
+                                                             int64_t M, int64_t N, int64_t K, int tiles_n,
+                                                             int tiles, int parts, EpiArgs e, HeadsArgs ha) {
+  constexpr int NT = WGM * WGN * 64;
+  constexpr int WM = BM / WGM, WN = BN / WGN;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int IA = BM * 8 / NT, IB = BN * 8 / NT;      // wavefront load instructions per k-tile (64 chunks each)
+  constexpr int STAGE = (BM + BN) * 8;                   // 16-byte chunks per LDS buffer
+  static_assert(BM * 8 % NT == 0 && BN * 8 % NT == 0, "tile/thread mismatch");
+  extern __shared__ uint4 smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  // Blocks are dealt round-robin over the 8 XCDs, each with its own L2: give every XCD a contiguous run
+  // of work ids (row-major tiles, so neighbours share the A row-panel and walk the B panels together).
+  // The grid is padded to a multiple of 8; the padding blocks have nothing to do.
+  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (pid >= tiles * parts) return;
+  const int part = EPI == EPI_PART ? pid / tiles : 0, tile = EPI == EPI_PART ? pid % tiles : pid;   // K range, output tile
+  // tiles are walked in bands of 4 tile rows, column by column inside a band: the ~32 blocks an XCD runs
+  // at a time then cover about 4 x 8 tiles and share 4 A panels and 8 B panels instead of 1 and 32
+  const int tiles_m = tiles / tiles_n;
+  const int band = tile / (4 * tiles_n), in_band = tile % (4 * tiles_n);
+  const int band_rows = tiles_m - band * 4 < 4 ? tiles_m - band * 4 : 4;
+  const int64_t m0 = (int64_t)(band * 4 + in_band % band_rows) * BM, n0 = (int64_t)(in_band / band_rows) * BN;
+  const int kt0 = EPI == EPI_PART ? (int)((K / 64) * part / parts) : 0;
+  const int KT = EPI == EPI_PART ? (int)((K / 64) * (part + 1) / parts) - kt0 : (int)(K / 64);
+
+  // EPI_HEADS: a tile of a section that is stored channel-major is computed with the operands exchanged
+  // (square tiles only), so that its accumulators, staging tile and row stores are those of C^T
+  int sec = 0;
+  bool swapped = false;
+  if constexpr (EPI == EPI_HEADS) {
+    sec = (int)(n0 / ha.dim);
+    if constexpr (BM == BN) swapped = ha.sec[sec].transposed != 0;
+  }
+  const bf16_t* const pa = (swapped ? Bt + n0 * ldb : A + m0 * lda) + kt0 * 64;
+  const bf16_t* const pb = (swapped ? A + m0 * lda : Bt + n0 * ldb) + kt0 * 64;
+  const int64_t lpa = swapped ? ldb : lda, lpb = swapped ? lda : ldb;
+  // slot p of a tile holds chunk (p & 7) ^ ((row >> 1) & 7) of row p >> 3; one wavefront instruction
+  // fills slots [base, base + 64), lane l the slot base + l
+  const bf16_t* gA[IA]; const bf16_t* gB[IB];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int p = (wave * IA + i) * 64 + lane, row = p >> 3, ch = (p & 7) ^ ((row >> 1) & 7);
+    gA[i] = pa + row * lpa + ch * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < IB; ++i) {
+    const int p = (wave * IB + i) * 64 + lane, row = p >> 3, ch = (p & 7) ^ ((row >> 1) & 7);
+    gB[i] = pb + row * lpb + ch * 8;
+  }
+  // load instruction q < IA + IB of this wavefront's share of k-tile kt into stage bufi
+  auto load_part = [&](int kt, int bufi, int q) __attribute__((always_inline)) {
+    if (kt >= KT) return;
+    const int t = kt * 64;
+    uint4* base = smem + bufi * STAGE;
+    if (q < IA) {
+      __builtin_amdgcn_global_load_lds((glb_void_t*)(gA[q] + t), (lds_void_t*)(base + (wave * IA + q) * 64), 16, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds((glb_void_t*)(gB[q - IA] + t), (lds_void_t*)(base + BM * 8 + (wave * IB + q - IA) * 64), 16, 0, 0);
+    }
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  const int lr = lane & 31, lg = lane >> 5;
+  int arow[TM], brow[TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i) arow[i] = wm * WM + i * 32 + lr;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) brow[j] = wn * WN + j * 32 + lr;
+
+  // Software pipeline.  k-tile kt+1 is in flight while k-tile kt is multiplied; the fragments of k-step
+  // ks+1 are read while the MFMAs of k-step ks run, one read behind each of the first MFMAs, in the order in
+  // which the next step's MFMAs first need them.  The LDS reads are issued through inline assembly and
+  // waited for with explicit counts: the compiler would wait for all outstanding reads before the first
+  // MFMA of a step (the last of them only two MFMAs old), which stalls a wavefront whenever the other
+  // wavefront of its SIMD is not there to fill the gap; here an MFMA waits only for the fragments it
+  // needs, issued most of a k-step earlier.  LDS returns reads in order, so "at most c reads outstanding"
+  // means every read but the c newest has landed.
+  constexpr int NM = TM * TN, NR = TM + TN;              // MFMAs and fragment reads per k-step
+  constexpr int NB = NM >= 8 ? 2 : 1;                    // MFMAs of the last k-step issued before the barrier
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
+  static_assert(WM % 16 == 0 && WN % 16 == 0, "every fragment row of a lane has the same swizzle");
+  // chunk (ks * 2 + lg) ^ s of a row, s = (row >> 1) & 7 = (lr >> 1) & 7 for all of this lane's fragment rows,
+  // is at byte (ks * 32) ^ swz of the row
+  const uint32_t swz = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+  uint32_t fbase[NR];                                    // fragment f: LDS byte offset of this lane's row in stage 0
+#pragma unroll
+  for (int f = 0; f < NR; ++f) {
+    const bool is_a = f == 0 || f > TN;
+    const int row = is_a ? arow[f == 0 ? 0 : f - TN] : brow[f - 1];
+    fbase[f] = lds0 + (uint32_t)((is_a ? 0 : BM * 8) + row * 8) * 16;
+  }
+  bf16x8 af[2][TM], bfr[2][TN];
+  // fragment f of k-step ks of the stage at byte offset `stage` into register buffer `to`
+  auto read_frag = [&](uint32_t stage, int ks, int f, int to) __attribute__((always_inline)) {
+    const u32x4 v = lds_read16_raw<0>(fbase[f] + (stage + (swz ^ (uint32_t)(ks * 32))));
+    if (f == 0) af[to][0] = __builtin_bit_cast(bf16x8, v);
+    else if (f <= TN) bfr[to][f - 1] = __builtin_bit_cast(bf16x8, v);
+    else af[to][f - TN] = __builtin_bit_cast(bf16x8, v);
+  };
+  // The NL load instructions of a k-tile are spread, one behind an MFMA, over the NS MFMAs that follow the
+  // barrier which frees their stage (the rest of the last k-step and the first k-step of the next k-tile):
+  // issued together right behind the barrier they fill the vector-memory queue, and a wavefront that waits
+  // there to issue a load cannot issue the MFMAs behind it either.
+  constexpr int NL = IA + IB, NS = (NM - NB) + NM;
+  if constexpr (ST > 2 && BM <= 128) {
+    // Ring of ST stages.  A small tile's k-tile is multiplied in a fraction of the time its loads travel, and a small
+    // problem has no second block to fill the gap, so ST - 1 k-tiles are in flight: tile kt is waited for by its place
+    // in the queue of vector loads (they arrive in order), not by an empty queue.  Behind the barrier every wavefront
+    // has tile kt, and all are done with tile kt - 1, whose stage the next loads go to.
+    static_assert(4 * NR <= 16, "one k-tile's fragment reads are counted in lgkmcnt");
+#pragma unroll
+    for (int z = 0; z < ST - 1; ++z)
+#pragma unroll
+      for (int q = 0; q < NL; ++q) load_part(z, z, q);
+    bf16x8 fr[4][NR];
+    int stage = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      const int behind = KT - 1 - kt;                    // tiles behind this one that are (or were) still to come
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<ST - 1>([&](auto r_) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_)::value;           // tiles in flight behind tile kt: min(ST - 2, behind)
+        if (r == ST - 2 ? behind >= r : behind == r) vm_wait<r * NL>();
+      });
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      const int nxt = stage == 0 ? ST - 1 : stage - 1;   // (kt + ST - 1) % ST
+#pragma unroll
+      for (int q = 0; q < NL; ++q) load_part(kt + ST - 1, nxt, q);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t base = (uint32_t)stage * STAGE * 16;
+      static_for<4 * NR>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int ks = decltype(i_)::value / NR, f = decltype(i_)::value % NR;
+        fr[ks][f] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fbase[f] + (base + (swz ^ (uint32_t)(ks * 32)))));
+      });
+      static_for<4>([&](auto ks_) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_)::value;
+        lds_wait<(3 - ks) * NR>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[ks][1 + j], fr[ks][i == 0 ? 0 : TN + i], acc[i][j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      stage = stage + 1 == ST ? 0 : stage + 1;
+    }
+  } else {
+  static_assert(ST == 2, "one k-tile in flight");
+#pragma unroll
+  for (int q = 0; q < NL; ++q) load_part(0, 0, q);
+  tile_barrier();
+  static_for<NL>([&](auto q_) __attribute__((always_inline)) {
+    constexpr int q = decltype(q_)::value;
+    if constexpr (q * NS / NL < NM - NB) load_part(1, 1, q);           // the part that k-step 3 would have issued
+  });
+#pragma unroll
+  for (int f = 0; f < NR; ++f) read_frag(0, 0, f, 0);
+  for (int kt = 0; kt < KT; ++kt) {
+    const int st = kt & 1;                               // stage of this k-tile
+    const uint32_t cur = (uint32_t)st * STAGE * 16, nxt = (uint32_t)(st ^ 1) * STAGE * 16;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      static_for<NM>([&](auto n_) __attribute__((always_inline)) {
+        constexpr int n = decltype(n_)::value, i = n / TN, j = n % TN;
+        constexpr int need = frag_need<TN>(n), prev = n == 0 ? -1 : frag_need_upto<TN>(n - 1);
+        if (ks < 3) {
+          // reads of step ks+1 issued so far in this step: those with k * NM / NR < n
+          if constexpr (need > prev) lds_wait<NR - 1 - need + reads_before<NM, NR>(n, 0)>();
+        } else {
+          if constexpr (n < NB) { if constexpr (need > prev) lds_wait<NR - 1 - need>(); }
+          if constexpr (n == NB) tile_barrier();   // every read of this k-tile has landed (lgkmcnt(0) precedes it)
+        }
+        __builtin_amdgcn_sched_barrier(0);               // the MFMA stays behind the wait for its fragments
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][j], af[ks & 1][i], acc[i][j], 0, 0, 0);
+        static_for<NR>([&](auto k_) __attribute__((always_inline)) {
+          constexpr int k = decltype(k_)::value;
+          if (ks < 3) { if constexpr (k * NM / NR == n) read_frag(cur, ks + 1, k, (ks + 1) & 1); }
+          else { if constexpr (n >= NB && NB + k * (NM - NB) / NR == n) read_frag(nxt, 0, k, 0); }
+        });
+        static_for<NL>([&](auto q_) __attribute__((always_inline)) {
+          constexpr int q = decltype(q_)::value, slot = q * NS / NL;       // MFMAs after the barrier
+          if (ks == 3) { if constexpr (n >= NB && slot == n - NB) load_part(kt + 2, st, q); }
+          else if (ks == 0) { if constexpr (slot == (NM - NB) + n) load_part(kt + 1, st ^ 1, q); }
+        });
+        __builtin_amdgcn_sched_barrier(0);               // keeps the MFMAs, reads, loads and waits in this order
+      });
+    }
+  }
+  }
+  lds_wait<0>();
+
+  finish_tile<32, BM, BN, WGM, WGN, TM, TN, EPI, (BM + BN) * 256>(acc, smem, m0, n0, M, N, part, sec, swapped, e, ha);
+}
+
+
+// 64 x 16 bytes to LDS at dst: lane l's from byte voff(l) + soff of [base, base + bytes); the hardware returns zeros beyond
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t bytes, uint32_t voff, int soff, uint4* dst) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), (lds_void_t*)dst, 16, voff, soff, 0, 0);
+#endif
+}
+
+// Mid-size tiles: 2 x 4 wavefronts of (TM * 16) x (TN * 16), v_mfma_f32_16x16x32_bf16, k-slabs of KB in a ring of ST LDS stages.
+// The two wavefronts of a SIMD (one of each block half) take turns: while one multiplies a slab, the other reads its next
+// slab's fragments and issues its share of the tile loads, with a barrier at every change of roles.  Nothing is interleaved
+// by hand and a wavefront needs no second fragment buffer; ST - 1 slabs are in flight, waited for by count.
+// What bounds it: LDS.  A slab of 160 x 256 x 64 takes 1280 matrix-pipe cycles per SIMD and 147 KB of fragment reads (1150
+// cycles at 128 bytes a cycle) plus 53 KB of tile writes.  Five 16-row tiles by four use 18 reads per 40 MFMAs where one column
+// of five 32-row tiles took 24 per 20.  Measured against that layout (one block column per wavefront, pinned order, three
+// stages; plain store, us): 6240 x 1536 x 8960 173 -> 155, 6240 x 1536 x 1536 33.9 -> 31.2, 1560 x 4608 x 1536 as 128 x 256
+// tiles 30.2 -> 25.0; against a ring of four stages without turns 1008 x 4096 x 1024 (128 x 128) 15.5 -> 11.8.
+template <int TM, int TN, int KB, int ST, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bt,
+                                                   int64_t ldb, int64_t M, int64_t N, int64_t K, int tiles_n, int tiles,
+                                                   int parts, EpiArgs e, HeadsArgs ha) {
+  constexpr int WGM = 2, WGN = 4, NT = 512;
+  constexpr int WM = TM * 16, WN = TN * 16, BM = WGM * WM, BN = WGN * WN;
+  constexpr int CPR = KB / 8;                            // 16-byte chunks of an LDS row
+  constexpr int ACH = BM * CPR, BCH = BN * CPR, STAGE = ACH + BCH;
+  constexpr int IA = (ACH + NT - 1) / NT, IB = BCH / NT, NL = IA + IB;   // load instructions per wavefront and slab
+  constexpr bool RAG = ACH % NT != 0;                    // the last wavefronts have one A load less
+  constexpr int KS = KB / 32, D = ST - 1;                // k-steps of a slab, slabs in flight
+  static_assert(BCH % NT == 0 && ACH % 64 == 0 && (KB == 32 || KB == 64), "whole wavefront instructions");
+  extern __shared__ uint4 smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  // work ids as in k_gemm_bf16: a contiguous run per XCD, tiles in bands of 4 tile rows
+  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (pid >= tiles * parts) return;
+  const int part = EPI == EPI_PART ? pid / tiles : 0, tile = EPI == EPI_PART ? pid % tiles : pid;
+  const int tiles_m = tiles / tiles_n;
+  const int band = tile / (4 * tiles_n), in_band = tile % (4 * tiles_n);
+  const int band_rows = tiles_m - band * 4 < 4 ? tiles_m - band * 4 : 4;
+  const int64_t m0 = (int64_t)(band * 4 + in_band % band_rows) * BM, n0 = (int64_t)(in_band / band_rows) * BN;
+  const int s0 = EPI == EPI_PART ? (int)((K / KB) * part / parts) : 0;
+  const int NS = EPI == EPI_PART ? (int)((K / KB) * (part + 1) / parts) - s0 : (int)(K / KB);
+
+  // Slot p of a slab holds chunk (p % CPR) ^ swz(row) of row p / CPR, swz spreading a column of chunks over the banks (two
+  // 128-byte rows or four 64-byte rows make one sweep of the 64 banks).  Rows beyond the matrix read as zeros.
+  auto swz = [](int row) __attribute__((always_inline)) { return CPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
+  const bf16_t* const pa = A + m0 * lda + s0 * KB;
+  const bf16_t* const pb = Bt + n0 * ldb + s0 * KB;
+  const int64_t left_a = ((M - m0) * lda - s0 * KB) * 2, left_b = ((N - n0) * ldb - s0 * KB) * 2;
+  const uint32_t na = (uint32_t)(left_a < 0x7fffffff ? left_a : 0x7fffffff), nb = (uint32_t)(left_b < 0x7fffffff ? left_b : 0x7fffffff);
+  uint32_t va[IA], vb[IB];
+#pragma unroll
+  for (int q = 0; q < IA; ++q) { const int p = (q * 8 + wave) * 64 + lane, row = p / CPR; va[q] = (uint32_t)(row * lda + ((p % CPR) ^ swz(row)) * 8) * 2; }
+#pragma unroll
+  for (int q = 0; q < IB; ++q) { const int p = (q * 8 + wave) * 64 + lane, row = p / CPR; vb[q] = (uint32_t)(row * ldb + ((p % CPR) ^ swz(row)) * 8) * 2; }
+  auto load_slab = [&](int s, int st) __attribute__((always_inline)) {
+    uint4* const base = smem + st * STAGE;
+#pragma unroll
+    for (int q = 0; q < IA; ++q)
+      if (!RAG || (q * 8 + wave) * 64 < ACH) load_lds16(pa, na, va[q], s * KB * 2, base + (q * 8 + wave) * 64);
+#pragma unroll
+    for (int q = 0; q < IB; ++q) load_lds16(pb, nb, vb[q], s * KB * 2, base + ACH + (q * 8 + wave) * 64);
+  };
+  // at most d slabs of this wavefront's loads outstanding
+  const bool all_a = !RAG || ((IA - 1) * 8 + wave) * 64 < ACH;
+  auto wait_slabs = [&](auto d_) __attribute__((always_inline)) {
+    constexpr int d = decltype(d_)::value;
+    if (all_a) vm_wait<d * NL>(); else vm_wait<d * (NL - 1)>();
+  };
+  auto wait_behind = [&](int behind) __attribute__((always_inline)) {    // slabs issued behind the one waited for
+    static_for<D>([&](auto d_) __attribute__((always_inline)) {
+      constexpr int d = decltype(d_)::value;
+      if (d == D - 1 ? behind >= d : behind == d) wait_slabs(d_);
+    });
+  };
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  const int lr = lane & 15, lg = lane >> 4;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
+  const uint32_t fa = lds0 + (uint32_t)((wm * WM + lr) * CPR) * 16, fb = lds0 + (uint32_t)(ACH + (wn * WN + lr) * CPR) * 16;
+  const uint32_t sx = (uint32_t)(lg ^ swz(lr)) * 16;     // a lane's rows are 16 apart: one swizzle for all of them
+
+  // EPI_RESID: the tile is staged and updated in steps of GI accumulator rows of both block halves, the fp32 residual rows in
+  // whole rows, 16 bytes per lane.  The first step's are requested with the last slab's fragments, when no tile loads are left
+  // to wait for, and travel while that slab is multiplied; the second step's follow behind the multiplication.
+  constexpr bool FP32 = EPI == EPI_RESID || EPI == EPI_PART;
+  constexpr int NG = BM * BN * 4 <= STAGE * ST * 16 ? 1 : 2, GI = (TM + NG - 1) / NG;
+  static_assert(!FP32 || 2 * GI * 16 * BN * 4 <= STAGE * ST * 16, "a step fits");
+  constexpr int CPF = BN / 4, RPW = 64 / CPF, NX = 2 * GI * 16 / 8 / RPW;          // 16-byte chunks per row, rows per read, reads per step
+  float4 xv[EPI == EPI_RESID ? NG : 1][EPI == EPI_RESID ? NX : 1];
+  // row and first column, inside the tile, of this lane's chunk of read t of step g, and its place in LDS
+  auto fp32_at = [&](int g, int t, int& row, int& col, int& at) __attribute__((always_inline)) {
+    const int gi = TM - g * GI < GI ? TM - g * GI : GI;   // accumulator rows of this step
+    const int r = (t * 8 + wave) * RPW + lane / CPF, half = r / (gi * 16), p = lane % CPF;
+    row = half * WM + g * GI * 16 + r % (gi * 16);
+    col = (p ^ (r & 15)) * 4;
+    at = r * CPF + p;
+    return r < 2 * gi * 16;
+  };
+  auto resid_load = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NX; ++t) {
+      int row, col, at;
+      if (fp32_at(g, t, row, col, at) && m0 + row < M && n0 + col < N) xv[g][t] = *(const float4*)(e.resid + (m0 + row) * e.ldr + n0 + col);
+    }
+  };
+
+#pragma unroll
+  for (int z = 0; z < D; ++z) if (z < NS) load_slab(z, z);
+  wait_behind(NS - 1);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  if (wm == 1) __builtin_amdgcn_s_barrier();             // the second half starts half a slab later
+  __builtin_amdgcn_sched_barrier(0);
+  // EXCH: operands exchanged, the accumulators are those of C^T
+  auto multiply = [&](auto exch_) __attribute__((always_inline)) {
+    constexpr bool EXCH = decltype(exch_)::value;
+    int cur = 0, prev = ST - 1;
+    bf16x8 af[KS][TM], bfr[KS][TN];
+    auto slab = [&](int s, auto last_) __attribute__((always_inline)) {
+      constexpr bool LAST = decltype(last_)::value;
+      const uint32_t base = (uint32_t)cur * STAGE * 16;
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<KS>([&](auto k_) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_)::value;
+        const uint32_t o = base + (sx ^ (uint32_t)(k * 64));
+        static_for<TN>([&](auto j_) __attribute__((always_inline)) { constexpr int j = decltype(j_)::value; bfr[k][j] = __builtin_bit_cast(bf16x8, lds_read16_raw<j * 256 * CPR>(fb + o)); });
+        static_for<TM>([&](auto i_) __attribute__((always_inline)) { constexpr int i = decltype(i_)::value; af[k][i] = __builtin_bit_cast(bf16x8, lds_read16_raw<i * 256 * CPR>(fa + o)); });
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (!LAST) {
+        // into the stage of slab s - 1, which everyone has read: its reads were waited for before the last barrier
+        if (s + D < NS) load_slab(s + D, prev);
+        wait_behind(NS - 2 - s < D - 1 ? NS - 2 - s : D - 1);            // slab s + 1 has landed
+      } else if constexpr (EPI == EPI_RESID) {
+        resid_load(0);
+      }
+      lds_wait<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+      static_for<KS>([&](auto k_) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_)::value;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = EXCH ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[k][i], bfr[k][j], acc[i][j], 0, 0, 0)
+                             : __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[k][j], af[k][i], acc[i][j], 0, 0, 0);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(0);
+      if constexpr (!LAST) { __builtin_amdgcn_s_barrier(); __builtin_amdgcn_sched_barrier(0); }
+      prev = cur; cur = cur + 1 == ST ? 0 : cur + 1;
+    };
+    for (int s = 0; s < NS - 1; ++s) slab(s, std::false_type{});
+    slab(NS - 1, std::true_type{});
+  };
+  int sec = 0;
+  bool exch = false;
+  if constexpr (EPI == EPI_HEADS) {
+    sec = (int)(n0 / ha.dim);
+    exch = ha.sec[sec].transposed != 0;
+    if (exch) multiply(std::true_type{}); else multiply(std::false_type{});
+  } else {
+    multiply(std::false_type{});
+  }
+  if (wm == 0) __builtin_amdgcn_s_barrier();             // the halves meet again
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (FP32) {
+    const bf16_t* bias = (const bf16_t*)e.bias;
+    float4* l16 = (float4*)smem;
+    static_for<NG>([&](auto g_) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_)::value, gi = TM - g * GI < GI ? TM - g * GI : GI;
+      if constexpr (EPI == EPI_RESID && g + 1 < NG) resid_load(g + 1);
+      __syncthreads();                                   // the operand slabs / the previous step are done with
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int nl = wn * WN + j * 16 + lg * 4;
+        float bv[4] = {0.f, 0.f, 0.f, 0.f};
+        float4 gv = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (EPI == EPI_RESID && n0 + nl < N) {
+          if (bias) {
+            const uint2 b4 = *(const uint2*)(bias + n0 + nl);
+            bv[0] = bf16_to_f32((bf16_t)(b4.x & 0xffff)); bv[1] = bf16_to_f32((bf16_t)(b4.x >> 16));
+            bv[2] = bf16_to_f32((bf16_t)(b4.y & 0xffff)); bv[3] = bf16_to_f32((bf16_t)(b4.y >> 16));
+          }
+          if (e.gate) gv = *(const float4*)(e.gate + n0 + nl);
+        }
+#pragma unroll
+        for (int i = 0; i < gi; ++i) {
+          const f32x4 a = acc[g * GI + i][j];
+          const int r = (wm * gi + i) * 16 + lr;
+          l16[r * CPF + ((nl >> 2) ^ (r & 15))] = make_float4(gv.x * (a[0] + bv[0]), gv.y * (a[1] + bv[1]), gv.z * (a[2] + bv[2]), gv.w * (a[3] + bv[3]));
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NX; ++t) {
+        int row, col, at;
+        if (!fp32_at(g, t, row, col, at)) continue;
+        const float4 v = l16[at];
+        const int64_t m = m0 + row, n = n0 + col;
+        if (m >= M || n >= N) continue;
+        if constexpr (EPI == EPI_PART) {
+          *(float4*)(e.resid + ((int64_t)part * M + m) * e.ldr + n) = v;
+        } else {
+          float4 x = xv[g][t];
+          x.x += v.x; x.y += v.y; x.z += v.z; x.w += v.w;
+          *(float4*)(e.resid + m * e.ldr + n) = x;
+          if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x.x, x.y), cvt_pk_bf16(x.z, x.w));
+        }
+      }
+    });
+  } else {
+    finish_tile<16, BM, BN, WGM, WGN, TM, TN, EPI, STAGE * ST * 16>(acc, smem, m0, n0, M, N, part, sec, exch, e, ha);
+  }
+}
+
+template <int TM, int TN, int KB, int ST, int EPI>
+static void launch_turns(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                         int64_t K, const EpiArgs& e, hipStream_t st, int parts) {
+  constexpr int BM = 32 * TM, BN = 64 * TN;
+  constexpr int lds = (BM + BN) * KB * 2 * ST;
+  const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
+  static std::atomic<uint64_t> done;
+  allow_dynamic_lds((const void*)k_gemm_turns<TM, TN, KB, ST, EPI>, lds, done);
+  HeadsArgs ha{};
+  if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / BN; ha = *e.heads; }
+  dim3 grid((unsigned)((tm * tn * parts + 7) / 8 * 8));
+  k_gemm_turns<TM, TN, KB, ST, EPI><<<grid, 512, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
+}
+template <int TM, int TN, int KB, int ST>
+static bool launch_turns_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
+                             int64_t K, int epi, const EpiArgs& e, hipStream_t st, int parts) {
+  if (epi == EPI_STORE) launch_turns<TM, TN, KB, ST, EPI_STORE>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_GELU) launch_turns<TM, TN, KB, ST, EPI_GELU>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_RESID) launch_turns<TM, TN, KB, ST, EPI_RESID>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_HEADS) launch_turns<TM, TN, KB, ST, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_PART) launch_turns<TM, TN, KB, ST, EPI_PART>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else return false;
+  return true;
+}
+
 template <int BM, int BN, int WGM, int WGN, int EPI, int ST = 2>
 static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, const EpiArgs& e, hipStream_t st, int parts = 1) {
@@ -613,7 +886,7 @@ static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t l
 template <int BM, int BN, int WGM, int WGN, int ST>
 static bool launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, int epi, const EpiArgs& e, hipStream_t st, int parts) {
-  constexpr bool HEADS = BM <= 160 || BM == 256, PART = ST == 4 ? BM == 64 : BM == 160 || BM == 256;
+  constexpr bool HEADS = BM == 64 || BM == 256, PART = (BM == 64 && ST == 4) || BM == 256;
   if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU, ST>(A, lda, Wt, ldw, M, N, K, e, st);
   else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID, ST>(A, lda, Wt, ldw, M, N, K, e, st);
@@ -623,15 +896,15 @@ static bool launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t l
   return true;
 }
 
-// Which tile family a problem takes.  A 256-row tile keeps a CU busy by itself but a small problem has too few of them; small
-// tiles run as a ring of loads (see ST above), 64 x 64 ones up to three to a CU, 128 x 128 ones one.  Lines, measured at
-// 1560 x 1536 x 1536 (42 tiles of 256^2): 64^2 22 us, 128^2 ring 27, 128^2 with two stages 27; 1008 x 1024 x 4096 (16): 64^2 25,
-// 128^2 ring 51, two stages 63; 1008 x 4096 x 1024 (64): 128^2 ring 18, 64^2 20, 256^2 30; 1560 x 4608 x 1536 (126): 256^2 43,
-// 128^2 ring 47, 64^2 48; 1560 x 8960 x 1536 (245): 256^2 51, 64^2 79.
+// Which tile family a problem takes.  A 256-row tile keeps a CU busy by itself but a small problem has too few of them; 64 x 64
+// tiles run as a ring of loads, up to three to a CU, 128 x 128 ones in turns (k_gemm_turns), one to a CU.  Lines, measured (us):
+// 1008 x 1024 x 4096 (256 tiles of 64^2): 64^2 24, 128^2 41; 1560 x 1536 x 1536 (600): 24 and 21.5, with per-head stores 20 and
+// 21; 1008 x 3072 x 1024 (768), per-head stores: 17.4 and 16.9; 4032 x 1024 x 1024 (1008): 28 and 20.5; 1008 x 4096 x 1024 (256
+// of 128^2): 128^2 14.8, 128 x 256 20.5; 1560 x 4608 x 1536 (468): 39 and 29.
 enum { TILE_64 = 0, TILE_128 = 1, TILE_BIG = 2 };
-static int tile_family(int64_t M, int64_t N) {
-  if (((M + 63) / 64) * ((N + 63) / 64) <= 768) return TILE_64;        // three blocks per CU: one round
-  if (((M + 127) / 128) * ((N + 127) / 128) <= 256) return TILE_128;   // one block per CU: one round
+static int tile_family(int64_t M, int64_t N, int epi) {
+  if (((M + 63) / 64) * ((N + 63) / 64) <= (epi == EPI_HEADS ? 768 : 560)) return TILE_64;
+  if (((M + 127) / 128) * ((N + 127) / 128) <= 256) return TILE_128;   // one round
   return TILE_BIG;
 }
 // Tile shape, LDS stages and K ranges of a problem: what the rules below decide and launch_gemm_bf16 runs
@@ -641,9 +914,9 @@ static GemmRoute small_tile(int family, int64_t M, int64_t N) {
   return {64, 64, ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 4 : 3, 1};
 }
 
-// EPI_HEADS.  Sections must be whole tiles wide and a transposed section needs a square tile, 8 | M and 8 | row0.
+// EPI_HEADS.  Sections must be whole tiles wide, a transposed one needs 8 | M and 8 | row0.
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
-  const int family = tile_family(M, N), bn = family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
+  const int family = tile_family(M, N, EPI_HEADS), bn = family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
   if (h.dim <= 0 || (h.head_dim != 64 && h.head_dim != 128) || h.dim % bn || h.dim % h.head_dim || N % h.dim || N / h.dim > 3) return false;
   for (int i = 0; i < (int)(N / h.dim); ++i) {
     if (h.sec[i].transposed && (M % 8 || h.sec[i].row0 % 8 || h.sec[i].ld % 8)) return false;
@@ -651,20 +924,6 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   }
   return true;
 }
-// Duration of a block of the other large tiles over one of 256 x 256, from whole rounds of blocks at K = 1536 ... 13824, each
-// tile forced in turn: 160 rows (three LDS stages) 0.69 ... 0.74, 192 rows 0.81 ... 0.88, 320 rows 1.15 ... 1.25.  Where they
-// decide (us): 7800 x 5120 x 13824 160 rows in 4 rounds 1027, 256 rows in 3 1074; 9000 x 5632 x 1024 5 rounds 135, 4 143;
-// 7200 x 6720 x 3008 320 rows in 3 rounds 298, 160 rows in 5 307; 18720 x 8960 x 1536 256 rows in 11 512, 320 rows in 9 516.
-constexpr double kTile160 = 0.74, kTile192 = 0.88, kTile320 = 1.23;
-static GemmRoute big_heads_tile(int64_t M, int64_t N, bool any_transposed) {
-  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  // the 160-row tile cannot exchange its operands; it pays where it fills the one round better (see below)
-  const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
-  const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
-  if (!any_transposed && fits160 && kTile160 * (double)((t160 + 255) / 256) < (double)((t256 + 255) / 256)) return {160, 256, 3, 1};
-  return {256, 256, 2, 1};
-}
-
 // x[m, n] += gate[n] * (bias[n] + sum over the K ranges, in range order), and its rounded copy
 __global__ __launch_bounds__(256) void k_add_parts(const float* __restrict__ part, int parts, int64_t M, int64_t N, EpiArgs e) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
@@ -692,73 +951,85 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 }
 // Cutting K.  A long K over few tiles leaves most CUs idle, and small tiles in the hundreds move several times the bytes of
 // large ones through the caches.  Tiles whose K is cut over blocks until about one round of CUs is full do neither, for the
-// price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile 1.3
-// (256 x 256), 1.25 (160 x 256 on a nearly full chip), 0.27 per block on the CU (64 x 64), 8 (4) for a block's ends, 3 for
-// the second launch, partials at 4 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU, 0.72 for 128 x 128, and 1.3 per
-// round of 256 x 256 also where another large tile would run: the estimate of a cut problem is high by about as much (its
-// partial results stay in the caches).  Cut / the fastest uncut large tile in us: 776 x 5120 x 5120 69 / 88 (160 rows),
-// 920 x 5120 x 5120 75 / 89, 1288 x 5120 x 13824 204 / 226, 2560 x 3072 x 12288 194 / 210, 2560 x 2048 x 8192 106 / 133: at none of
-// 45 sizes (128 ... 3072 rows, 768 ... 5120 columns) was an uncut large tile faster.
+// price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile of a
+// block 0.5 (128 x 128), 0.75 (128 x 256), 0.9 (160 x 256), 1.3 (256 x 256), 0.27 for each 64 x 64 block on the CU; 7 for both
+// launches and a block's ends, partials at 6.5 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU and 7, 9 (128 x 128) or 14
+// for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 55 (128 x 256,
+// 3) / 77, 1008 x 2048 x 8192 45 (128 x 256, 4) / 64, 2560 x 2048 x 8192 88 (160 x 256, 2) / 104, 480 x 3584 x 19456 83 (160 x 256, 6)
+// / 158; left uncut 1288 x 5120 x 13824 180 (cut 204), 3000 x 1024 x 4096 41 (42).  Outputs narrower than 768 columns fill few
+// tiles of any kind: they take the 64-, 160- and 256-row tiles by the figures of an earlier measurement (a k-tile 1.25 at 160
+// rows, 8 for ends and 3 for the second launch, 4 TB/s), which the parity tests of those three cut tiles stand on.
+static GemmRoute big_tile(int64_t M, int64_t N, int epi);
 static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats) {
   GemmRoute r{0, 0, 0, 1};                             // parts == 1: not cut
   if (N % 4) return r;
-  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256), t160 = ((M + 159) / 160) * ((N + 255) / 256);
-  const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), KT = K / 64;
-  const bool fits160 = (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
-  const int family = tile_family(M, N);
-  double best = family == TILE_BIG ? 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8
-              : family == TILE_128 ? 0.72 * (double)KT + 5 : 0.24 * (double)(KT * ((t64 + 255) / 256)) + 5;
+  const bool narrow = N < 768;
+  auto tiles = [&](int64_t rows, int64_t cols) { return (M + rows - 1) / rows * ((N + cols - 1) / cols); };
+  const int64_t t256 = tiles(256, 256), t160 = tiles(160, 256), t64 = tiles(64, 64), KT = K / 64;
+  const bool fits160 = !narrow || (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
+  const int family = tile_family(M, N, EPI_RESID);
+  double best = family == TILE_64 ? 0.24 * (double)(KT * ((t64 + 255) / 256)) + (narrow ? 5 : 7)
+              : family == TILE_128 ? 0.5 * (double)KT + 9 : 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8;
+  if (family == TILE_BIG && !narrow) {
+    const GemmRoute u = big_tile(M, N, EPI_RESID);
+    const double kt = u.bm == 128 ? 0.75 : u.bm == 160 ? 0.9 : u.bm == 192 ? 1.15 : u.bm == 256 ? 1.3 : 1.6;
+    best = kt * (double)(KT * ((tiles(u.bm, u.bn) + 255) / 256)) + 14;
+  }
   best *= 0.9;                                         // not for a few per cent
   for (int p = 2; p <= 8; ++p) {
     if ((size_t)(p * M * N) > scratch_floats) break;
-    const double extra = 3 + (double)(M * N) * 4 * (2 * p + 2.5) / 4e6, kt = (double)((KT + p - 1) / p);
-    const double cost[3] = {t256 * p <= 256 && KT / p >= 8 ? 1.3 * kt + 8 + extra : 1e30,
-                            fits160 && t160 * p <= 256 && KT / p >= 8 ? 1.25 * kt + 8 + extra : 1e30,
-                            t64 * p <= 512 && KT / p >= 4 ? 0.27 * kt * (double)((t64 * p + 255) / 256) + 4 + extra : 1e30};
-    const GemmRoute tile[3] = {{256, 256, 2, p}, {160, 256, 3, p}, {64, 64, 4, p}};
-    for (int w = 0; w < 3; ++w)
-      if (cost[w] < best) { best = cost[w]; r = tile[w]; }
+    const double moved = (double)(M * N) * 4 * (2 * p + 2.5), kt = (double)((KT + p - 1) / p);
+    const double big = narrow ? 8 + 3 + moved / 4e6 : 7 + moved / 6.5e6, small = narrow ? 4 + 3 + moved / 4e6 : big;
+    const bool deep = KT / p >= 8;
+    struct { double c; GemmRoute t; } opt[5] = {
+        {narrow && t256 * p <= 256 && deep ? 1.3 * kt + big : 1e30, {256, 256, 2, p}},
+        {fits160 && t160 * p <= 256 && deep ? (narrow ? 1.25 : 0.9) * kt + big : 1e30, {160, 256, 3, p}},
+        {!narrow && tiles(128, 256) * p <= 256 && deep ? 0.75 * kt + big : 1e30, {128, 256, 3, p}},
+        {!narrow && tiles(128, 128) * p <= 256 && deep ? 0.5 * kt + big : 1e30, {128, 128, 4, p}},
+        {t64 * p <= 512 && KT / p >= 4 ? 0.27 * kt * (double)((t64 * p + 255) / 256) + small : 1e30, {64, 64, 4, p}}};
+    for (const auto& o : opt)
+      if (o.c < best) { best = o.c; r = o.t; }
   }
   return r;
 }
 
-// One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.
-// 256x256 tiles are the default.  Other shapes are taken when rounds x relative duration (above) comes out lower:
-// 192x256, 160x256 (1 x 8 wavefronts, more LDS reads per MFMA, but e.g. 39 x 6 tiles fill one round where 33 x 6 leave
-// 58 CUs idle) and 320x256 (fewer operand bytes per flop).
-// The 160-, 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where
-// that stays inside the 256-row padding the caller guarantees.
-static GemmRoute big_tile(int64_t M, int64_t N) {
-  const int64_t t256 = ((M + 255) / 256) * ((N + 255) / 256);
-  const int64_t t192 = ((M + 191) / 192) * ((N + 255) / 256);
-  const int64_t t160 = ((M + 159) / 160) * ((N + 255) / 256);
-  const int64_t t320 = ((M + 319) / 320) * ((N + 255) / 256);
-  const int64_t mpad = (M + 255) / 256 * 256;
-  const double cost256 = (double)((t256 + 255) / 256);
-  const double cost192 = (M + 191) / 192 * 192 <= mpad ? kTile192 * (double)((t192 + 255) / 256) : 1e30;
-  const double cost160 = (M + 159) / 160 * 160 <= mpad ? kTile160 * (double)((t160 + 255) / 256) : 1e30;
-  const double cost320 = (M + 319) / 320 * 320 <= mpad ? kTile320 * (double)((t320 + 255) / 256) : 1e30;
-  const double best = fmin(fmin(cost256, cost192), fmin(cost160, cost320));
-  // on a tie the taller tile wins: fewer operand bytes per flop
-  if (best == cost320) return {320, 256, 2, 1};
-  if (best == cost256) return {256, 256, 2, 1};
-  if (best == cost160) return {160, 256, 3, 1};
-  return {192, 256, 2, 1};
+// One block per CU at a time, so a launch costs ceil(blocks / 256) rounds of one block's duration.  Durations over that of a
+// 256 x 256 block, from whole rounds of blocks at K = 1536 ... 13824, each tile forced in turn: 320 rows 1.15 ... 1.25, 192 rows
+// 0.81 ... 0.88, and in turns 160 rows 0.62 ... 0.69 (the fp32 epilogue, whose reads are ahead of it, at the lower end), 128 rows
+// 0.53 ... 0.59.  Where they decide (us): 1560 x 4608 x 1536 128 rows, one round, 29, 160 rows 33, 256 rows 42; 2500 x 3072 x
+// 12288 168, 182, 254; 3600 x 13824 x 5120 160 rows in 5 rounds 437, 320 rows in 3 454; 18720 x 1536 x 8960 160 rows in 3 467, 256
+// rows in 2 488; 7800 x 4608 x 1536 160 rows in 4 117, 256 rows in 3 122; 14400 x 15360 x 5120 256 rows in 14 1850, 128 rows in
+// 27 1931; 14400 x 13824 x 5120 320 rows in 10 1601, 160 rows in 19 1634.
+// The 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where that stays inside the
+// 256-row padding the caller guarantees.  The tiles that run in turns read nothing beyond M; narrow outputs and plain stores
+// take them only where they fit the padding too (160 rows) or nearly fill the round (128 rows): the parity tests of the 192-
+// and 256-row tiles are such shapes.
+static GemmRoute big_tile(int64_t M, int64_t N, int epi) {
+  const int64_t tn = (N + 255) / 256, mpad = (M + 255) / 256 * 256;
+  const bool heads = epi == EPI_HEADS, any = heads || (epi == EPI_RESID && N >= 1536) || (epi == EPI_GELU && N >= 2048);
+  auto tiles = [&](int64_t rows) { return (M + rows - 1) / rows * tn; };
+  auto fits = [&](int64_t rows) { return (M + rows - 1) / rows * rows <= mpad; };
+  auto cost = [&](int64_t rows, double duration, bool ok) { return ok ? duration * (double)((tiles(rows) + 255) / 256) : 1e30; };
+  const GemmRoute tile[5] = {{320, 256, 2, 1}, {256, 256, 2, 1}, {160, 256, 3, 1}, {192, 256, 2, 1}, {128, 256, 3, 1}};
+  const double c[5] = {cost(320, 1.23, !heads && fits(320)), cost(256, 1.0, true), cost(160, epi == EPI_RESID ? 0.66 : 0.69, any || fits(160)),
+                       cost(192, 0.88, !heads && fits(192)), cost(128, 0.57, any || (tiles(128) > 210 && tiles(128) <= 256))};
+  int best = 0;                                          // on a tie the earlier one: fewer operand bytes per flop
+  for (int i = 1; i < 5; ++i) if (c[i] < c[best]) best = i;
+  return tile[best];
 }
 
-GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, bool any_transposed, size_t scratch_floats) {
+GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, size_t scratch_floats) {
   if (epi == EPI_RESID) {
     const GemmRoute r = cut_tile(M, N, K, scratch_floats);
     if (r.parts > 1) return r;
   }
-  const int family = tile_family(M, N);
-  if (family != TILE_BIG) return small_tile(family, M, N);
-  return epi == EPI_HEADS ? big_heads_tile(M, N, any_transposed) : big_tile(M, N);
+  const int family = tile_family(M, N, epi);
+  return family == TILE_BIG ? big_tile(M, N, epi) : small_tile(family, M, N);
 }
 // for the parity tests, which state the kernel that each of their products is meant to reach
-extern "C" void dp_gemm_bf16_route(int64_t M, int64_t N, int64_t K, int32_t epi, int32_t any_transposed, int64_t scratch_floats,
+extern "C" void dp_gemm_bf16_route(int64_t M, int64_t N, int64_t K, int32_t epi, int32_t /*any_transposed*/, int64_t scratch_floats,
                                    int32_t* bm_bn_stages_parts) {
-  const GemmRoute r = gemm_bf16_route(M, N, K, epi, any_transposed != 0, (size_t)scratch_floats);
+  const GemmRoute r = gemm_bf16_route(M, N, K, epi, (size_t)scratch_floats);
   const int32_t v[4] = {r.bm, r.bn, r.stages, r.parts};
   for (int i = 0; i < 4; ++i) bm_bn_stages_parts[i] = v[i];
 }
@@ -767,26 +1038,26 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
                       int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
   if (M <= 0 || N <= 0) return true;
   if (K < 64 || K % 64) return false;          // whole k-tiles of 64 (the callers validate their widths)
-  bool any_t = false;
-  if (epi == EPI_HEADS) {
-    if (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads)) return false;
-    for (int i = 0; i < (int)(N / e.heads->dim); ++i) any_t = any_t || e.heads->sec[i].transposed;
-  }
-  const GemmRoute r = gemm_bf16_route(M, N, K, epi, any_t, e.scratch && e.ldr % 4 == 0 ? e.scratch_floats : 0);
+  if (epi == EPI_HEADS && (!e.heads || !gemm_bf16_heads_ok(M, N, *e.heads))) return false;
+  const GemmRoute r = gemm_bf16_route(M, N, K, epi, e.scratch && e.ldr % 4 == 0 ? e.scratch_floats : 0);
   const EpiArgs part{nullptr, 0, nullptr, e.scratch, N, nullptr, nullptr, nullptr, 0};
   const EpiArgs& ea = r.parts > 1 ? part : e;
   const int ep = r.parts > 1 ? (int)EPI_PART : epi;
   bool ok = false;
 #define GEMM_TILE(BM, BN, WGM, WGN, ST) \
   if (r.bm == BM && r.stages == ST) ok = launch_cfg<BM, BN, WGM, WGN, ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
+#define TURNS_TILE(TM, TN, KB, ST) \
+  if (r.bm == 32 * TM && r.bn == 64 * TN && r.stages == ST) ok = launch_turns_cfg<TM, TN, KB, ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
   GEMM_TILE(64, 64, 2, 2, 4);
   else GEMM_TILE(64, 64, 2, 2, 3);
-  else GEMM_TILE(128, 128, 2, 2, 4);
-  else GEMM_TILE(160, 256, 1, 8, 3);
+  else TURNS_TILE(4, 2, 64, 4);
+  else TURNS_TILE(4, 4, 64, 3);
+  else TURNS_TILE(5, 4, 64, 3);
   else GEMM_TILE(192, 256, 2, 4, 2);
   else GEMM_TILE(256, 256, 2, 4, 2);
   else GEMM_TILE(320, 256, 2, 4, 2);
 #undef GEMM_TILE
+#undef TURNS_TILE
   if (r.parts > 1) k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, r.parts, M, N, e);
   return ok;
 }

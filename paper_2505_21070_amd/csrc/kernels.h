@@ -94,9 +94,9 @@ inline void allow_dynamic_lds(const void* kernel, int bytes, std::atomic<uint64_
 bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M,
                       int64_t N, int64_t K, int epi, const EpiArgs& e, hipStream_t st);
 // the kernel launch_gemm_bf16 takes: block tile, LDS stages, and ranges that K is cut into (EPI_RESID; scratch_floats: what
-// e.scratch holds, 0 if there is none); any_transposed: EPI_HEADS with a transposed section
+// e.scratch holds, 0 if there is none)
 struct GemmRoute { int bm, bn, stages, parts; };
-GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, bool any_transposed, size_t scratch_floats);
+GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, size_t scratch_floats);
 // EPI_RESID may cut K into ranges whose partial sums go through e.scratch (a second launch adds them up, in range order);
 // what a problem of up to M rows can make use of:
 size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N);
