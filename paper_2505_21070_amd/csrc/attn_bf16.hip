@@ -18,17 +18,19 @@
 // block whose row sums end up beyond 2^100 (or non-finite) is recomputed by the safe pass, the classical
 // online softmax that raises m whenever a tile exceeds it and rescales O^T.
 //
-// Work split: a block of 8 wavefronts owns QG * 32 queries of one head.  Two shapes are built.
+// Work split: a block of QG * KG wavefronts owns QG * 32 queries of one head.  Three shapes are built (launch_attn_bf16 has the
+// lines between them, and k_attn_few takes what is small).
 // QG = 4, KG = 2 (few queries or very few keys): wavefront w handles query tile w & 3 against key group
 // w >> 2 (first / second half of the key tiles); the two groups stream their own K / V^T tiles and are
 // merged through LDS at the end, which halves the length of a block.  QG = 8, KG = 1 (everything else,
 // self- and cross-attention at full size): all 8 wavefronts share every K / V^T tile, so a tile brought
-// into LDS serves 256 queries and the LDS fill traffic per query halves.  Tiles hold 64 keys, are double-buffered and are loaded
+// into LDS serves 256 queries and the LDS fill traffic per query halves.  QG = 4, KG = 1 (few keys): 4 wavefronts, two blocks
+// to a CU.  Tiles hold 64 keys, are double-buffered and are loaded
 // HBM -> LDS directly.  The two wavefronts of a SIMD are served oldest first rather than interleaved, so the
 // fast pass pins its issue order so that one wavefront alone keeps the matrix pipe busy: exponentials
 // between MFMAs, operand fragments read from LDS several MFMAs ahead with exact waits (see pass_fast).
 //
-// Grid: one block fits per compute unit, so a grid runs in rounds of 256 blocks.  The work ids that
+// Grid: one block of 8 wavefronts fits per compute unit, so a grid runs in rounds of 256 blocks (512 of 4 wavefronts).  The work ids that
 // would make up a last, partly filled round are instead cut into several key ranges each, one block per
 // range, which write unnormalised partial results (m, l, O) to a scratch buffer; k_attn_merge joins them.
 #include <type_traits>
@@ -61,8 +63,32 @@ template <int OFF> __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
   return __builtin_bit_cast(bf16x8, lds_read16_raw<OFF>(addr));
 }
 
+// The fragments of 32 queries from row q0 of a head: B operand, column = query lr, 8 head-dim values per lane
+template <int KS, int HD>
+__device__ __forceinline__ void load_queries(const bf16_t* __restrict__ qh, int64_t q0, int lr, int lg, int64_t S, const AttnQNorm& qn,
+                                             bf16x8 (&qf)[KS]) {
+  qh += (q0 + lr) * HD + lg * 8;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qh + ks * 16));
+  if (qn.ssq) {
+    // deferred RMSNorm of the queries: the row's sum of squares arrives as qn.np partial sums; the two lanes
+    // that share a query row add up the even and the odd ones
+    const int64_t row = q0 + lr < S ? q0 + lr : S - 1;
+    const float* pr = qn.ssq + row;
+    float sum = 0.f;
+#pragma unroll 4
+    for (int i = lg; i < qn.np; i += 2) sum += pr[i * qn.stride];
+    sum += __shfl_xor(sum, 32, 64);
+    const float r = rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * r);
+  }
+}
+
 template <int HD, int QG, int KG>
-__global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
+__global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
                                                   const bf16_t* __restrict__ k, int64_t k_head_stride,
                                                   int64_t k_row0, const bf16_t* __restrict__ vt,
                                                   int64_t vt_row_stride, int64_t S, int64_t L,
@@ -78,7 +104,6 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q,
   constexpr int GCH = NBUF * (KCH + VCH);    // chunks per key group: NBUF K tiles, NBUF V^T tiles
   constexpr int CK = KCH / (QG * 64), CV = VCH / (QG * 64);   // load instructions per wavefront and tile
   constexpr int QB = QG * 32;                // queries per block
-  static_assert(QG * KG == 8, "8 wavefronts");
   extern __shared__ uint4 smem[];            // KG * GCH chunks
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -115,28 +140,6 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q,
   const int n0 = KG == 2 ? (t1 - t0 + 1) / 2 : t1 - t0;   // tiles of group 0; also the trip count for everyone
   const int first = t0 + (kg ? n0 : 0), cnt = kg ? t1 - t0 - n0 : n0;
 
-  // Q fragments stay in registers: B operand, column = query, 8 head-dim values per lane
-  bf16x8 qf[KS];
-  {
-    const bf16_t* qh = q + (int64_t)head * q_head_stride + (q0 + lr) * HD + lg * 8;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qh + ks * 16));
-  }
-  if (qn.ssq) {
-    // deferred RMSNorm of the queries: the row's sum of squares arrives as qn.np partial sums; the two lanes
-    // that share a query row add up the even and the odd ones
-    const int64_t row = q0 + lr < S ? q0 + lr : S - 1;
-    const float* pr = qn.ssq + row;
-    float sum = 0.f;
-#pragma unroll 4
-    for (int i = lg; i < qn.np; i += 2) sum += pr[i * qn.stride];
-    sum += __shfl_xor(sum, 32, 64);
-    const float r = rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * r);
-  }
   const bf16_t* kh = k + (int64_t)head * k_head_stride + (k_row0 + (int64_t)first * 64) * HD;
   const bf16_t* vh = vt + (int64_t)head * HD * vt_row_stride + k_row0 + (int64_t)first * 64;
 
@@ -168,6 +171,13 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q,
 #pragma unroll
     for (int i = 0; i < CK + CV; ++i) load_part(tile, bufi, i);
   };
+
+  // the fast pass's first two tiles are requested ahead of the queries and their row sums: one trip to memory instead of two
+  if (cnt > 0) load_tile(cnt - 1, 0);
+  if (cnt > 1) load_tile(cnt - 2, 1);
+
+  bf16x8 qf[KS];
+  load_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qf);
 
   f32x16 oacc[DT], negm;
   float mrun, lsum;
@@ -313,10 +323,8 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q,
     for (int r = 0; r < 16; ++r) negm[r] = 0.f;
     mrun = 0.f; lsum = 0.f;
     // Step j of this pass works on tile cnt - 1 - j of the range (the sums do not care about the order), in
-    // buffer j % NBUF: the last tile of the range, the only one that can be ragged, comes first and is done
+    // buffer j % NBUF (the first two are on their way): the last tile of the range, the only one that can be ragged, comes first and is done
     // here in plain order with its keys at or beyond L masked; the pinned loop below then sees whole tiles only.
-    if (cnt > 0) load_tile(cnt - 1, 0);
-    if (cnt > 1) load_tile(cnt - 2, 1);
     tile_barrier();
     if (cnt > 0) {
       const int kvalid = (int)(L - (int64_t)(first + cnt - 1) * 64);   // >= 1; < 64 only in a ragged tile
@@ -526,6 +534,161 @@ __global__ __launch_bounds__(512) void k_attn_bf16(const bf16_t* __restrict__ q,
   }
 }
 
+// Few queries against few keys.  A block owns 32 queries of one head and its 8 wavefronts deal the key range out in tiles
+// of 32 keys (wavefront w: tiles w, w + 8, ...), each through its own piece of LDS and with its own online softmax; nobody
+// waits for anybody until the eight partial results are added up in LDS, in wavefront order.  What bounds it is latency: the
+// launch, one trip to memory, two short MFMA chains and the sum; k_attn_bf16 spends 4.5 us on its two groups' tile-by-tile
+// barriers, reference pass and merge around the tiles, and 1.5 us for every two tiles of 64 keys.  Measured (us, back to back;
+// queries x keys x heads): head_dim 128 216 x 360 x 2 11.9 -> 8.1, 216 x 40 x 2 8.6 -> 5.1, 500 x 700 x 4 15.7 -> 10.4; head_dim 64
+// 333 x 1000 x 12 13.2 -> 8.7, 1008 x 77 x 16 6.9 -> 5.8.
+template <int HD>
+__global__ __launch_bounds__(512, HD == 64 ? 4 : 2) void k_attn_few(const bf16_t* __restrict__ q, int64_t q_head_stride, const bf16_t* __restrict__ k,
+                                                 int64_t k_head_stride, int64_t k_row0, const bf16_t* __restrict__ vt,
+                                                 int64_t vt_row_stride, int64_t S, int64_t L, bf16_t* __restrict__ out,
+                                                 int64_t ldo, int qblocks, int n_work, AttnQNorm qn) {
+  constexpr int CR = HD / 8, KS = HD / 16, DT = HD / 32, QB = 32;
+  constexpr int KCH = 32 * CR, VCH = HD * 4;             // 16-byte chunks of a K tile (32 keys) and of a V^T tile
+  constexpr int OCH = QB * HD / 4;                       // of a partial result: fp32 [QB][HD]
+  constexpr int MINE = KCH + VCH > OCH ? KCH + VCH : OCH;
+  extern __shared__ uint4 smem[];                        // 8 * MINE chunks
+  __shared__ float2 ml[8][QB];                           // reference and row sum of each wavefront's part
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);   // contiguous per XCD
+  if (wid >= n_work) return;
+  const int head = wid / qblocks;
+  const int64_t q0 = (int64_t)(wid % qblocks) * QB;
+  const int NT = (int)((L + 31) / 32), parts = NT < 8 ? NT : 8;
+  uint4* const mine = smem + wave * MINE;
+
+  if (wave < parts) {
+    const bf16_t* kh = k + (int64_t)head * k_head_stride + k_row0 * HD;
+    const bf16_t* vh = vt + (int64_t)head * HD * vt_row_stride + k_row0;
+    // K slot p holds chunk (p % CR) ^ kswz(key) of key p / CR, V^T slot p chunk (p % 4) ^ ((row >> 2) & 3) of channel p / 4
+    auto load_tile = [&](int tile) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < KCH / 64; ++i) {
+        const int p = i * 64 + lane, row = p / CR;
+        __builtin_amdgcn_global_load_lds((glb_void_t*)(kh + ((int64_t)tile * 32 + row) * HD + ((p % CR) ^ kswz<CR>(row)) * 8),
+                                         (lds_void_t*)(mine + i * 64), 16, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < VCH / 64; ++i) {
+        const int p = i * 64 + lane, row = p >> 2;
+        __builtin_amdgcn_global_load_lds((glb_void_t*)(vh + row * vt_row_stride + (int64_t)tile * 32 + ((p & 3) ^ ((row >> 2) & 3)) * 8),
+                                         (lds_void_t*)(mine + KCH + i * 64), 16, 0, 0);
+      }
+    };
+    load_tile(wave);
+    bf16x8 qf[KS];
+    load_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qf);
+    f32x16 oacc[DT];
+    float m = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[d][r] = 0.f;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)mine;
+    // MFMA row lr of a K tile is key swap23(lr): a lane's packed probabilities are then eight consecutive keys
+    const int key = swap23(lr);
+    const uint32_t krow = lds0 + (uint32_t)(key * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(key)) * 16;
+    const uint32_t vrow = lds0 + (uint32_t)(KCH + lr * 4) * 16, vx = (uint32_t)(lg ^ ((lr >> 2) & 3)) * 16;
+    for (int t = wave; t < NT; t += 8) {
+      vm_wait<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      bf16x8 kf[KS], vf[2][DT];
+      static_for<KS>([&](auto i_) __attribute__((always_inline)) { constexpr int i = decltype(i_)::value; kf[i] = lds_read16<0>(krow + (kx ^ (uint32_t)(i * 32))); });
+      static_for<2 * DT>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int u = decltype(i_)::value / DT, d = decltype(i_)::value % DT;
+        vf[u][d] = lds_read16<d * 32 * 4 * 16>(vrow + (vx ^ (uint32_t)(u * 32)));
+      });
+      lds_wait<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      if (t + 8 < NT) load_tile(t + 8);                  // the tile is in registers: its LDS is free
+      const int valid = (int)(L - (int64_t)t * 32);      // >= 1; < 32 only in a ragged last tile
+      f32x16 s;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
+      // register r of lane group lg: key (r / 8) * 16 + lg * 8 + r % 8 of the tile
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        s[r] = (r >> 3) * 16 + lg * 8 + (r & 7) < valid ? s[r] : -INFINITY;
+        mx = fmaxf(mx, s[r]);
+      }
+      const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
+      const float al = __builtin_amdgcn_exp2f(m - mn);              // 2^-inf = 0 at the first tile
+      m = mn;
+      l *= al;
+      uint4 pf[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          w[j] = cvt_pk_bf16(__builtin_amdgcn_exp2f(s[u * 8 + 2 * j] - mn), __builtin_amdgcn_exp2f(s[u * 8 + 2 * j + 1] - mn));
+          l = add_pk_bf16(w[j], l);
+        }
+        pf[u] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[d][r] *= al;
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+          oacc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[u][d], __builtin_bit_cast(bf16x8, pf[u]), oacc[d], 0, 0, 0);
+    }
+    // partial results, unnormalised, fp32 [query][channel] in this wavefront's piece, 16-byte chunks XOR-swizzled with the query
+    float4* o4 = (float4*)mine;
+    constexpr int XO = HD / 4 - 1;
+    const float lt = l + __shfl_xor(l, 32, 64);
+    if (lg == 0) ml[wave][lr] = make_float2(m, lt);
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        o4[lr * (HD / 4) + ((d * 8 + g * 2 + lg) ^ (lr & XO))] = make_float4(oacc[d][g * 4], oacc[d][g * 4 + 1], oacc[d][g * 4 + 2], oacc[d][g * 4 + 3]);
+  }
+  __syncthreads();
+  constexpr int TPQ = 512 / QB, C4 = HD / 4 / TPQ;       // threads per query, 4-channel chunks per thread, TPQ chunks apart
+  const int ql = tid / TPQ, c0 = tid % TPQ;
+  if (q0 + ql >= S) return;
+  const float4* const o4 = (const float4*)smem + ql * (HD / 4);
+  const int x0 = ql & (HD / 4 - 1);
+  float mt = -INFINITY, lt = 0.f;
+  float4 o[C4];
+#pragma unroll
+  for (int c = 0; c < C4; ++c) o[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto sum = [&](auto n_) __attribute__((always_inline)) {               // n > 0: all reads in flight together
+    constexpr int n = decltype(n_)::value, U = n > 0 ? n : 1;
+    const int np = n > 0 ? n : parts;
+#pragma unroll U
+    for (int w = 0; w < np; ++w) mt = fmaxf(mt, ml[w][ql].x);
+#pragma unroll U
+    for (int w = 0; w < np; ++w) {
+      const float2 v = ml[w][ql];
+      const float f = __builtin_amdgcn_exp2f(v.x - mt);
+      lt += v.y * f;
+#pragma unroll
+      for (int c = 0; c < C4; ++c) {
+        const float4 x = o4[w * MINE + ((c0 + c * TPQ) ^ x0)];
+        o[c].x += x.x * f; o[c].y += x.y * f; o[c].z += x.z * f; o[c].w += x.w * f;
+      }
+    }
+  };
+  if (parts == 8) sum(std::integral_constant<int, 8>{}); else sum(std::integral_constant<int, 0>{});
+  const float inv = 1.f / lt;
+#pragma unroll
+  for (int c = 0; c < C4; ++c)
+    *(uint2*)(out + (q0 + ql) * ldo + (int64_t)head * HD + (c0 + c * TPQ) * 4) =
+        make_uint2(cvt_pk_bf16(o[c].x * inv, o[c].y * inv), cvt_pk_bf16(o[c].z * inv, o[c].w * inv));
+}
+
 // Combines the key ranges of the split work ids: O = sum_i 2^(m_i - m) O_i / sum_i 2^(m_i - m) l_i with
 // m = max_i m_i.  One thread per (query, 4 channels).  A block of 256 threads covers all channels of
 // 256 / (HD/4) consecutive queries (query index fastest), so that partials are read in whole 128-byte
@@ -570,14 +733,15 @@ static void launch_attn_cfg(const bf16_t* q, int64_t q_head_stride, const bf16_t
   constexpr int QB = QG * 32;
   constexpr int lds = KG * 2 * (64 * (HD / 8) + HD * 8) * 16;
   const int qblocks = (int)((S + QB - 1) / QB);
-  // One block fits per compute unit, so the grid runs in rounds of 256 blocks.  Whole rounds keep one
+  // One block (of 4 wavefronts: two) fits per compute unit, so the grid runs in rounds of SLOTS blocks.  Whole rounds keep one
   // block per work id; the work ids left over for the last round are cut into key ranges (at least 8
   // key tiles each) so that the round is both shorter and wider, and a merge kernel joins the ranges.
   const int W = qblocks * h, NKT = (int)((L + 63) / 64);
-  const int n_full = W / 256 * 256, n_tail = W - n_full;
+  constexpr int SLOTS = 256 * (8 / (QG * KG));
+  const int n_full = W / SLOTS * SLOTS, n_tail = W - n_full;
   int parts = 1;
   if (n_tail > 0 && scratch) {
-    parts = 256 / n_tail;
+    parts = SLOTS / n_tail;
     if (parts > 8) parts = 8;
     if (parts > NKT / 8) parts = NKT / 8;
     if (parts < 1) parts = 1;
@@ -585,11 +749,22 @@ static void launch_attn_cfg(const bf16_t* q, int64_t q_head_stride, const bf16_t
   dim3 grid((unsigned)(n_full + (n_tail * parts + 7) / 8 * 8));
   static std::atomic<uint64_t> done;
   allow_dynamic_lds((const void*)k_attn_bf16<HD, QG, KG>, lds, done);
-  k_attn_bf16<HD, QG, KG><<<grid, 512, lds, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, out, ldo, qblocks, n_full, n_tail, parts, scratch, qn);
+  k_attn_bf16<HD, QG, KG><<<grid, QG * KG * 64, lds, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, out, ldo, qblocks, n_full, n_tail, parts, scratch, qn);
   if (parts > 1) {
     constexpr int QPB = 256 / (HD / 4);                  // queries per merge block
     k_attn_merge<HD, QB><<<(unsigned)(n_tail * (QB / QPB)), 256, 0, st>>>(scratch, n_full, n_tail, parts, qblocks, S, out, ldo);
   }
+}
+
+template <int HD>
+static void launch_attn_few(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, int64_t k_head_stride, int64_t k_row0,
+                            const bf16_t* vt, int64_t vt_row_stride, int64_t S, int64_t L, int h, bf16_t* out, int64_t ldo,
+                            const AttnQNorm& qn, hipStream_t st) {
+  constexpr int QB = 32, tile = 2 * 32 * HD * 2, part = QB * HD * 4, lds = 8 * (tile > part ? tile : part);
+  const int qblocks = (int)((S + QB - 1) / QB), n = qblocks * h;
+  static std::atomic<uint64_t> done;
+  allow_dynamic_lds((const void*)k_attn_few<HD>, lds, done);
+  k_attn_few<HD><<<(unsigned)((n + 7) / 8 * 8), 512, lds, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, out, ldo, qblocks, n, qn);
 }
 
 void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, int64_t k_head_stride,
@@ -601,8 +776,24 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
   // still gives the grid half a round of blocks and the key range a few tiles; otherwise 128 queries per
   // block with the keys split over two groups, which halves the length of a block.
   const bool wide = L >= 256 && ((S + 255) / 256) * h >= 128;
+  // Few enough blocks of 32 queries for one round (one to a CU at head_dim 128, two at 64) and at most eight tiles to a
+  // wavefront: k_attn_few.  Beyond either line the other shapes are as fast (us): 1008 x 1680 x 16 heads of 64 (512 blocks) 17.9
+  // against 20.3, 1000 x 1900 x 8 heads of 128 (256) 19.9 and 24.2, 700 x 1000 x 12 of 128 (264) 24.0 and 20.6, 100 x 3000 x 8 of 128
+  // (32) 22.7 and 19.8.
+  const bool few = L <= 1920 && (S + 31) / 32 * h <= (d == 128 ? 256 : 512);
+  // Few keys: a block's start and end weigh as much as its tiles, so blocks of four wavefronts, two to a CU, fill each other's
+  // gaps.  Short key ranges, or up to 16 tiles where two rounds of such blocks are full (us): 6240 x 512 x 12 of 128 35.0 -> 31.5,
+  // 1560 x 512 x 12 of 128 15.2 -> 13.4, 3000 x 1000 x 24 of 128 54.4 -> 50.6, 8000 x 200 x 16 of 64 17.7 -> 16.5; not at 3000 x 512 x
+  // 16 of 64 (12.3 with 256 queries, 12.9) or 3000 x 1000 x 10 of 128 (22.9 with two groups, 34.2).
+  const bool pairs = (L <= 512 && (d == 128 || !wide)) || (L <= 1024 && (S + 127) / 128 * h > 512);
 #define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, scratch, qn, st
-  if (d == 128) { if (wide) launch_attn_cfg<128, 8, 1>(ATTN_ARGS); else launch_attn_cfg<128, 4, 2>(ATTN_ARGS); }
-  else { if (wide) launch_attn_cfg<64, 8, 1>(ATTN_ARGS); else launch_attn_cfg<64, 4, 2>(ATTN_ARGS); }
+  if (few) {
+    if (d == 128) launch_attn_few<128>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, qn, st);
+    else launch_attn_few<64>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, qn, st);
+  } else if (d == 128) {
+    if (pairs) launch_attn_cfg<128, 4, 1>(ATTN_ARGS); else if (wide) launch_attn_cfg<128, 8, 1>(ATTN_ARGS); else launch_attn_cfg<128, 4, 2>(ATTN_ARGS);
+  } else {
+    if (pairs) launch_attn_cfg<64, 4, 1>(ATTN_ARGS); else if (wide) launch_attn_cfg<64, 8, 1>(ATTN_ARGS); else launch_attn_cfg<64, 4, 2>(ATTN_ARGS);
+  }
 #undef ATTN_ARGS
 }

@@ -1,0 +1,44 @@
+"""The bf16 attention kernel's block shapes at the edges of their tiles: cross-attention against a float64 softmax over the very
+q, K, V that the kernel read (peeked from the library), at the text lengths and query counts where a shape can go wrong."""
+import numpy as np
+import pytest
+
+from harness import check
+from paper_2505_21070_amd import synth
+from test_gpu_stage import T_CUR, gpu_stage, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+FEW = [(2, 128, (2, 4, 1), n) for n in (1, 31, 32, 33, 255, 256, 257)]           # 8 queries: one to nine 32-key tiles
+CASES = FEW + [
+    (2, 64, (6, 12, 3), 40), (2, 64, (6, 12, 3), 300),                            # 216 queries, 2 and 10 tiles
+    (4, 128, (8, 10, 25), 1900),                                                  # 252 blocks of 32 queries, 60 tiles
+    (16, 64, (8, 9, 14), 70),                                                     # 512 blocks of 32
+    (8, 128, (8, 15, 10), 100), (8, 128, (8, 15, 10), 512),                       # 1200 queries: four wavefronts, two blocks to a CU
+    (16, 64, (8, 13, 10), 33), (16, 64, (8, 13, 10), 200),                        # 1040 queries
+    (16, 64, (8, 13, 40), 1024),                                                  # 4160: the last 16 blocks cut into key ranges
+    (8, 128, (8, 15, 10), 1100), (16, 64, (8, 13, 10), 1100),                     # two key groups
+]
+
+
+@pytest.mark.parametrize("peaked", [False, True], ids=["plain", "peaked"])
+@pytest.mark.parametrize("heads,hd,grid,text_len", CASES)
+def test_cross_attention_shapes(monkeypatch, heads, hd, grid, text_len, peaked):
+    """peaked: large q/k gains, so that logits of later keys exceed those of the first by more than a fixed reference can hold"""
+    monkeypatch.setitem(synth.CONFIGS, "shape", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=heads * hd, n_heads=heads, head_dim=hd, ffn_dim=128,
+                                                     text_len=text_len, text_dim=heads * hd, tok_h=grid[0], tok_w=grid[1],
+                                                     block_frames=grid[2], cache_frames=1))
+    cfg, w, text, blocks = synth.make_case("shape", seed=5, strong_gate=True)
+    if peaked:
+        for k in ("cgq", "cgk"):
+            w["layers"][0][k] = synth.round_to(w["layers"][0][k] * 12.0, "bf16")
+    g = gpu_stage(cfg, w, text, max_abs_frames=64)
+    g.forward(to_dev(blocks[1], cfg), cfg["block_frames"], 0, T_CUR)
+    q, k, v = (to_np(g.peek(n, 0)) for n in ("q", "text_k", "text_v"))            # q: already multiplied by log2(e)/sqrt(d)
+    ref = np.zeros_like(q)
+    for h in range(heads):
+        sl = slice(h * hd, (h + 1) * hd)
+        s2 = q[:, sl] @ k[:, sl].T
+        p = np.exp2(s2 - s2.max(1, keepdims=True))
+        ref[:, sl] = (p / p.sum(1, keepdims=True)) @ v[:, sl]
+    check("shape/cross_attn", to_np(g.peek("cross_attn", 0)), ref, "bf16")
