@@ -4,7 +4,8 @@
 // Block tile BM x BN x 64, WGM x WGN wavefronts, each owning a (BM/WGM) x (BN/WGN) sub-tile built from
 // v_mfma_f32_32x32x16_bf16.  k-tiles go HBM -> LDS directly (no staging registers, no LDS stores) into
 // two buffers: k-tile kt+1 is in flight while k-tile kt is multiplied (problems of few tiles take small tiles and a
-// ring of loads, see the ST > 2 loop; mid-size tiles run in turns, see k_gemm_turns; which takes what: tile_family, big_tile).  Operand fragments are
+// ring of loads, see k_gemm_ring and k_gemm_thin; mid-size tiles run in turns, see k_gemm_turns; which takes what: tile_family,
+// big_tile, cut_tile).  Operand fragments are
 // double-buffered in registers: those of k-step ks+1 are read from LDS while the MFMAs of k-step ks run.
 // The issue order of the main loop is pinned (see there): the two wavefronts of a SIMD are served oldest
 // first rather than interleaved, so each has to keep the matrix pipe busy on its own; tile loads go out
@@ -408,8 +409,7 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
   }
 }
 
-// ST: LDS stages.  Tiles of more than 128 rows run the pinned loop below (two stages), smaller ones a ring of ST > 2.
-template <int BM, int BN, int WGM, int WGN, int EPI, int ST>
+template <int BM, int BN, int WGM, int WGN, int EPI>
 __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __restrict__ A, int64_t lda,
                                                              const bf16_t* __restrict__ Bt, int64_t ldb,
                                                              int64_t M, int64_t N, int64_t K, int tiles_n,
@@ -526,51 +526,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
   // issued together right behind the barrier they fill the vector-memory queue, and a wavefront that waits
   // there to issue a load cannot issue the MFMAs behind it either.
   constexpr int NL = IA + IB, NS = (NM - NB) + NM;
-  if constexpr (ST > 2 && BM <= 128) {
-    // Ring of ST stages.  A small tile's k-tile is multiplied in a fraction of the time its loads travel, and a small
-    // problem has no second block to fill the gap, so ST - 1 k-tiles are in flight: tile kt is waited for by its place
-    // in the queue of vector loads (they arrive in order), not by an empty queue.  Behind the barrier every wavefront
-    // has tile kt, and all are done with tile kt - 1, whose stage the next loads go to.
-    static_assert(4 * NR <= 16, "one k-tile's fragment reads are counted in lgkmcnt");
-#pragma unroll
-    for (int z = 0; z < ST - 1; ++z)
-#pragma unroll
-      for (int q = 0; q < NL; ++q) load_part(z, z, q);
-    bf16x8 fr[4][NR];
-    int stage = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-      const int behind = KT - 1 - kt;                    // tiles behind this one that are (or were) still to come
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<ST - 1>([&](auto r_) __attribute__((always_inline)) {
-        constexpr int r = decltype(r_)::value;           // tiles in flight behind tile kt: min(ST - 2, behind)
-        if (r == ST - 2 ? behind >= r : behind == r) vm_wait<r * NL>();
-      });
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      const int nxt = stage == 0 ? ST - 1 : stage - 1;   // (kt + ST - 1) % ST
-#pragma unroll
-      for (int q = 0; q < NL; ++q) load_part(kt + ST - 1, nxt, q);
-      __builtin_amdgcn_sched_barrier(0);
-      const uint32_t base = (uint32_t)stage * STAGE * 16;
-      static_for<4 * NR>([&](auto i_) __attribute__((always_inline)) {
-        constexpr int ks = decltype(i_)::value / NR, f = decltype(i_)::value % NR;
-        fr[ks][f] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fbase[f] + (base + (swz ^ (uint32_t)(ks * 32)))));
-      });
-      static_for<4>([&](auto ks_) __attribute__((always_inline)) {
-        constexpr int ks = decltype(ks_)::value;
-        lds_wait<(3 - ks) * NR>();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[ks][1 + j], fr[ks][i == 0 ? 0 : TN + i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      stage = stage + 1 == ST ? 0 : stage + 1;
-    }
-  } else {
-  static_assert(ST == 2, "one k-tile in flight");
 #pragma unroll
   for (int q = 0; q < NL; ++q) load_part(0, 0, q);
   tile_barrier();
@@ -611,12 +566,476 @@ __global__ __launch_bounds__(WGM * WGN * 64) void k_gemm_bf16(const bf16_t* __re
       });
     }
   }
-  }
   lds_wait<0>();
 
   finish_tile<32, BM, BN, WGM, WGN, TM, TN, EPI, (BM + BN) * 256>(acc, smem, m0, n0, M, N, part, sec, swapped, e, ha);
 }
 
+
+// Small problems: 64 x 64 tiles, 2 x 2 wavefronts of 32 x 32, k-tiles of 64 in a ring of ST LDS stages.  A small tile's k-tile is
+// multiplied in a fraction of the time its loads travel, and a small problem has no second block to fill the gap, so ST - 1
+// k-tiles are in flight: tile kt is waited for by its place in the queue of vector loads (they arrive in order), not by an empty
+// queue.
+// What bounds it is latency: the launch, one trip to memory, a barrier, LDS reads and four dependent MFMAs per k-tile, and the
+// epilogue's own reads.  Those (bias, gate, residual rows, gains, rotations) are requested before anything else here and are there
+// when the sums are; against requesting them behind the main loop (us, back to back): 500 x 1024 x 1024 residual 10.1 -> 7.8, 1560 x
+// 512 x 512 residual 8.4 -> 6.2, 1008 x 1536 x 512 per-head stores 9.1 -> 8.4, 1008 x 1024 x 256 GELU 4.9 -> 4.3.  A second group of four
+// wavefronts with a ring of its own for every other k-tile changed nothing (20.2 -> 19.0 at K = 4096): a CU's operand path is busy.
+template <int ST, int EPI>
+__global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bt,
+                                                        int64_t ldb, int64_t M, int64_t N, int64_t K, int tiles_n, int tiles,
+                                                        int parts, EpiArgs e, HeadsArgs ha) {
+  constexpr int NL = 4, STAGE = 128 * 8;                 // loads per wavefront and k-tile, 16-byte chunks of a k-tile
+  extern __shared__ uint4 smem[];                        // ST stages
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+  // work ids as in k_gemm_bf16: a contiguous run per XCD, tiles in bands of 4 tile rows
+  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+  if (pid >= tiles * parts) return;
+  const int part = EPI == EPI_PART ? pid / tiles : 0, tile = EPI == EPI_PART ? pid % tiles : pid;
+  const int tiles_m = tiles / tiles_n;
+  const int band = tile / (4 * tiles_n), in_band = tile % (4 * tiles_n);
+  const int band_rows = tiles_m - band * 4 < 4 ? tiles_m - band * 4 : 4;
+  const int64_t m0 = (int64_t)(band * 4 + in_band % band_rows) * 64, n0 = (int64_t)(in_band / band_rows) * 64;
+  const int kt0 = EPI == EPI_PART ? (int)((K / 64) * part / parts) : 0;
+  const int KT = EPI == EPI_PART ? (int)((K / 64) * (part + 1) / parts) - kt0 : (int)(K / 64);
+  int sec = 0;
+  bool exch = false;
+  if constexpr (EPI == EPI_HEADS) { sec = (int)(n0 / ha.dim); exch = ha.sec[sec].transposed != 0; }
+
+  // the epilogue's operands; a thread's columns and rows are known now
+  const bf16_t* const bias = (const bf16_t*)e.bias;
+  uint2 b4[4] = {};
+  float4 gv[4], xv[4];
+  if constexpr (EPI != EPI_PART) {
+    if (bias) {
+      if (exch) { const int64_t n = n0 + wn * 32 + lr; b4[0].x = n < N ? (uint32_t)bias[n] : 0u; }
+      else
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { const int64_t n = n0 + wn * 32 + q * 8 + lg * 4; if (n < N) b4[q] = *(const uint2*)(bias + n); }
+    }
+  }
+  if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t n = n0 + wn * 32 + q * 8 + lg * 4;
+      gv[q] = e.gate && n < N ? *(const float4*)(e.gate + n) : make_float4(1.f, 1.f, 1.f, 1.f);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int row = (t * 256 + tid) >> 4, c = (tid & 15) ^ (row & 15);
+      if (m0 + row < M && n0 + c * 4 < N) xv[t] = *(const float4*)(e.resid + (m0 + row) * e.ldr + n0 + c * 4);
+    }
+  }
+  // EPI_HEADS: a thread takes columns c8 .. c8 + 7 and 32 more of them at c8 + 32 of row tid / 4
+  const int hrow = tid >> 2, c8 = (tid & 3) * 8;
+  const int64_t nsec = n0 - (int64_t)sec * ha.dim;       // first column of this tile inside its section
+  float4 hg[2][2], hc[2][2];
+  bool rotate = false, gains = false;
+  if constexpr (EPI == EPI_HEADS) {
+    rotate = !exch && ha.sec[sec].rope; gains = !exch && ha.sec[sec].gain;
+    const int half = ha.head_dim >> 1;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int n = (int)nsec + c8 + k * 32;
+      if (gains) { hg[k][0] = *(const float4*)(ha.sec[sec].gain + n); hg[k][1] = *(const float4*)(ha.sec[sec].gain + n + 4); }
+      if (rotate && m0 + hrow < M) {
+        const float4* t = (const float4*)(ha.cs + (m0 + hrow) * half + ((n & (ha.head_dim - 1)) >> 1));
+        hc[k][0] = t[0]; hc[k][1] = t[1];
+      }
+    }
+  }
+
+  // slot p of a tile holds chunk (p & 7) ^ ((row >> 1) & 7) of row p >> 3
+  const bf16_t *ga[2], *gb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int p = (wave * 2 + i) * 64 + lane, row = p >> 3, ch = (p & 7) ^ ((row >> 1) & 7);
+    ga[i] = A + (m0 + row) * lda + kt0 * 64 + ch * 8;
+    gb[i] = Bt + (n0 + row) * ldb + kt0 * 64 + ch * 8;
+  }
+  auto load_tile = [&](int s, int st) __attribute__((always_inline)) {
+    uint4* const base = smem + st * STAGE + wave * 128;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) __builtin_amdgcn_global_load_lds((glb_void_t*)(ga[i] + s * 64), (lds_void_t*)(base + i * 64), 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) __builtin_amdgcn_global_load_lds((glb_void_t*)(gb[i] + s * 64), (lds_void_t*)(base + 512 + i * 64), 16, 0, 0);
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
+  const uint32_t fa = lds0 + (uint32_t)(wm * 32 + lr) * 128, fb = lds0 + 8192 + (uint32_t)(wn * 32 + lr) * 128;
+  const uint32_t sx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+  __builtin_amdgcn_sched_barrier(0);                     // the epilogue's reads go first
+#pragma unroll
+  for (int z = 0; z < ST - 1; ++z) if (z < KT) load_tile(z, z);
+  auto multiply = [&](auto exch_) __attribute__((always_inline)) {
+    constexpr bool EXCH = decltype(exch_)::value;
+    int stage = 0;
+    for (int s = 0; s < KT; ++s) {
+      const int behind = KT - 1 - s;                     // tiles behind this one that are (or were) still to come
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<ST - 1>([&](auto r_) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_)::value;           // in flight behind tile s: min(ST - 2, behind)
+        if (r == ST - 2 ? behind >= r : behind == r) vm_wait<r * NL>();
+      });
+      __builtin_amdgcn_s_barrier();                      // tile s is there, and everyone is done with tile s - 1
+      __builtin_amdgcn_sched_barrier(0);
+      if (s + ST - 1 < KT) load_tile(s + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      const uint32_t base = (uint32_t)stage * STAGE * 16;
+      bf16x8 af[4], bfr[4];
+      static_for<4>([&](auto k_) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_)::value;
+        const uint32_t o = base + (sx ^ (uint32_t)(k * 32));
+        af[k] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fa + o));
+        bfr[k] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(fb + o));
+      });
+      static_for<4>([&](auto k_) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_)::value;
+        lds_wait<(3 - k) * 2>();
+        __builtin_amdgcn_sched_barrier(0);
+        // the weight rows are the A operand: a lane holds output row lr and four consecutive columns per register quad
+        acc = EXCH ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], bfr[k], acc, 0, 0, 0)
+                   : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[k], af[k], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      stage = stage + 1 == ST ? 0 : stage + 1;
+    }
+  };
+  if constexpr (EPI == EPI_HEADS) { if (exch) multiply(std::true_type{}); else multiply(std::false_type{}); }
+  else multiply(std::false_type{});
+
+  __syncthreads();                                       // the ring is free
+  auto bias4 = [&](int q, float (&bv)[4]) __attribute__((always_inline)) {
+    bv[0] = bf16_to_f32((bf16_t)(b4[q].x & 0xffff)); bv[1] = bf16_to_f32((bf16_t)(b4[q].x >> 16));
+    bv[2] = bf16_to_f32((bf16_t)(b4[q].y & 0xffff)); bv[3] = bf16_to_f32((bf16_t)(b4[q].y >> 16));
+  };
+  const int row_in = wm * 32 + lr;                       // this lane's row of the tile
+  if constexpr (EPI == EPI_RESID || EPI == EPI_PART) {
+    float4* const l16 = (float4*)smem;                   // 64 x 64 floats, 16-byte chunks XOR-swizzled with the row
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float bv[4];
+      bias4(q, bv);
+      const float4 g = EPI == EPI_RESID ? gv[q] : make_float4(1.f, 1.f, 1.f, 1.f);
+      l16[row_in * 16 + ((wn * 8 + q * 2 + lg) ^ (row_in & 15))] =
+          make_float4(g.x * (acc[q * 4] + bv[0]), g.y * (acc[q * 4 + 1] + bv[1]), g.z * (acc[q * 4 + 2] + bv[2]), g.w * (acc[q * 4 + 3] + bv[3]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int row = (t * 256 + tid) >> 4, c = (tid & 15) ^ (row & 15);
+      const int64_t m = m0 + row, n = n0 + c * 4;
+      if (m >= M || n >= N) continue;
+      const float4 v = l16[t * 256 + tid];
+      if constexpr (EPI == EPI_PART) {
+        *(float4*)(e.resid + ((int64_t)part * M + m) * e.ldr + n) = v;
+      } else {
+        float4 x = xv[t];
+        x.x += v.x; x.y += v.y; x.z += v.z; x.w += v.w;
+        *(float4*)(e.resid + m * e.ldr + n) = x;
+        if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x.x, x.y), cvt_pk_bf16(x.z, x.w));
+      }
+    }
+  } else {
+    uint2* const l8 = (uint2*)smem;                      // 64 x 64 bf16, 8-byte units XOR-swizzled with the row
+    float* const red = (float*)(smem + 512);             // EPI_HEADS: [row][wavefront column] sums of squares
+    if (EPI == EPI_HEADS && exch) {
+      // C^T: row = channel wn * 32 + lr, four consecutive output rows per quad
+      const int row = wn * 32 + lr;
+      const float bvr = bf16_to_f32((bf16_t)b4[0].x);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        l8[row * 16 + ((wm * 8 + q * 2 + lg) ^ (row & 15))] =
+            make_uint2(cvt_pk_bf16(acc[q * 4] + bvr, acc[q * 4 + 1] + bvr), cvt_pk_bf16(acc[q * 4 + 2] + bvr, acc[q * 4 + 3] + bvr));
+    } else {
+      float ss = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float bv[4], v[4];
+        bias4(q, bv);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          v[t] = acc[q * 4 + t] + bv[t];
+          ss += v[t] * v[t];
+          if (EPI == EPI_GELU) v[t] = gelu_tanh_fast(v[t]);
+        }
+        l8[row_in * 16 + ((wn * 8 + q * 2 + lg) ^ (row_in & 15))] = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+      }
+      if constexpr (EPI == EPI_HEADS) {
+        ss += __shfl_xor(ss, 32, 64);
+        if (lg == 0) red[row_in * 2 + wn] = ss;
+      }
+    }
+    __syncthreads();
+    // 16-byte chunk c of a staged row: units 2c and 2c + 1 lie in chunk c ^ ((row & 15) >> 1), exchanged for odd rows
+    auto chunk = [&](int row, int c) __attribute__((always_inline)) {
+      const uint4 d = smem[row * 8 + (c ^ ((row & 15) >> 1))];
+      return row & 1 ? make_uint4(d.z, d.w, d.x, d.y) : d;
+    };
+    if constexpr (EPI == EPI_HEADS) {
+      const HeadSection& sc = ha.sec[sec];
+      if (exch) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint4 d = chunk(hrow, (tid & 3) + k * 4);
+          const int64_t m = m0 + c8 + k * 32;
+          if (m < M) __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)sc.dst + (nsec + hrow) * sc.ld + sc.row0 + m));
+        }
+        return;
+      }
+      // one value per row and tile, tile-major so that rows are contiguous: ssq[tile in section][m]
+      if (sc.ssq && tid < 64 && m0 + tid < M) sc.ssq[(nsec >> 6) * ha.ssq_stride + m0 + tid] = red[tid * 2] + red[tid * 2 + 1];
+      const int64_t m = m0 + hrow;
+      if (m >= M) return;
+      const int hshift = ha.head_dim == 128 ? 7 : 6, hmask = ha.head_dim - 1;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int n = (int)nsec + c8 + k * 32;
+        uint4 d = chunk(hrow, (tid & 3) + k * 4);
+        if (rotate || gains) {
+          uint32_t w[4] = {d.x, d.y, d.z, d.w};
+          const float gs[8] = {hg[k][0].x, hg[k][0].y, hg[k][0].z, hg[k][0].w, hg[k][1].x, hg[k][1].y, hg[k][1].z, hg[k][1].w};
+          const float cs[8] = {hc[k][0].x, hc[k][0].y, hc[k][0].z, hc[k][0].w, hc[k][1].x, hc[k][1].y, hc[k][1].z, hc[k][1].w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            float a = bf16_to_f32((bf16_t)(w[u] & 0xffff)), b = bf16_to_f32((bf16_t)(w[u] >> 16));
+            if (gains) { a *= gs[2 * u]; b *= gs[2 * u + 1]; }
+            if (rotate) {
+              const float a2 = a * cs[2 * u] - b * cs[2 * u + 1], b2 = a * cs[2 * u + 1] + b * cs[2 * u];
+              a = a2; b = b2;
+            }
+            w[u] = cvt_pk_bf16(a, b);
+          }
+          d = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)sc.dst + (int64_t)(n >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (n & hmask)));
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int row = (t * 256 + tid) >> 3, c = tid & 7;
+        const uint4 d = chunk(row, c);
+        const int64_t m = m0 + row, n = n0 + c * 8;
+        if (m < M && n < N) __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)e.out + m * e.ldo + n));
+      }
+    }
+  }
+}
+
+template <int ST, int EPI>
+static void launch_ring(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                        const EpiArgs& e, hipStream_t st, int parts) {
+  constexpr int lds = 128 * 128 * ST;
+  const int tm = (int)((M + 63) / 64), tn = (int)((N + 63) / 64);
+  static std::atomic<uint64_t> done;
+  allow_dynamic_lds((const void*)k_gemm_ring<ST, EPI>, lds, done);
+  HeadsArgs ha{};
+  if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / 64; ha = *e.heads; }
+  k_gemm_ring<ST, EPI><<<(unsigned)((tm * tn * parts + 7) / 8 * 8), 256, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
+}
+template <int ST>
+static bool launch_ring_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                            int epi, const EpiArgs& e, hipStream_t st, int parts) {
+  if (epi == EPI_STORE) launch_ring<ST, EPI_STORE>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_GELU) launch_ring<ST, EPI_GELU>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_RESID) launch_ring<ST, EPI_RESID>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_HEADS) launch_ring<ST, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else if (epi == EPI_PART) launch_ring<ST, EPI_PART>(A, lda, Wt, ldw, M, N, K, e, st, parts);
+  else return false;
+  return true;
+}
+
+// The smallest problems: 32 x 64 tiles, and the k-tiles of 64 dealt to the eight wavefronts (wavefront w: tiles w, w + 8, ...), each
+// through its own piece of LDS, nobody waiting for anybody until the eight partial sums are added up in LDS, in wavefront order.
+// A CU reads operands at about 80 GB/s whatever the tile, so a 64 x 64 tile takes 0.2 us per k-tile however many are in flight;
+// where even these smaller tiles fill at most one round of CUs, 12 KB instead of 16 per k-tile and more CUs is what helps, and
+// up to eight k-tiles arrive together.  The epilogue's operands are requested first of all.  Measured (us, back to back,
+// k_gemm_ring -> this): 216 x 256 x 256 residual 4.2 -> 3.4, 500 x 512 x 512 5.5 -> 4.6, 500 x 1024 x 1024 7.8 -> 6.5, 216 x 256 x 1024
+// 7.5 -> 5.7, 216 x 1536 x 512 per-head stores 6.3 -> 5.8; beyond one round the ring is faster: 1008 x 1024 x 1024 (512 tiles) 8.6
+// against 10.4.
+template <int EPI>
+__global__ __launch_bounds__(512) void k_gemm_thin(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bt,
+                                                  int64_t ldb, int64_t M, int64_t N, int64_t K, int tiles_n, int tiles,
+                                                  EpiArgs e, HeadsArgs ha) {
+  constexpr int SLAB = 96 * 8;                           // 16-byte chunks of a k-tile: 32 rows of A, 64 of the weights
+  extern __shared__ uint4 smem[];                        // 8 * SLAB
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 31, lg = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pid = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);   // a contiguous run per XCD
+  if (pid >= tiles) return;
+  const int64_t m0 = (int64_t)(pid / tiles_n) * 32, n0 = (int64_t)(pid % tiles_n) * 64;
+  const int KT = (int)(K / 64), parts = KT < 8 ? KT : 8;
+  int sec = 0;
+  bool exch = false;                                     // operands exchanged: C^T
+  if constexpr (EPI == EPI_HEADS) { sec = (int)(n0 / ha.dim); exch = ha.sec[sec].transposed != 0; }
+  const int64_t nsec = n0 - (int64_t)sec * ha.dim;       // first column of this tile inside its section
+
+  // This thread's outputs: columns n .. n + 3 of row m, or (C^T) rows m .. m + 3 of channel n; and what they need
+  const int row = exch ? tid >> 3 : tid >> 4, c = exch ? tid & 7 : tid & 15;
+  const int64_t m = m0 + (exch ? c * 4 : row), n = n0 + (exch ? row : c * 4);
+  const bool here = m < M && n < N;
+  float bv[4] = {0.f, 0.f, 0.f, 0.f};
+  float4 x = {}, g = make_float4(1.f, 1.f, 1.f, 1.f), cs = {};
+  if (here) {
+    const bf16_t* const bias = (const bf16_t*)e.bias;
+    if (bias && exch) {
+      bv[0] = bv[1] = bv[2] = bv[3] = bf16_to_f32(bias[n]);
+    } else if (bias) {
+      const uint2 b4 = *(const uint2*)(bias + n);
+      bv[0] = bf16_to_f32((bf16_t)(b4.x & 0xffff)); bv[1] = bf16_to_f32((bf16_t)(b4.x >> 16));
+      bv[2] = bf16_to_f32((bf16_t)(b4.y & 0xffff)); bv[3] = bf16_to_f32((bf16_t)(b4.y >> 16));
+    }
+    if constexpr (EPI == EPI_RESID) {
+      x = *(const float4*)(e.resid + m * e.ldr + n);
+      if (e.gate) g = *(const float4*)(e.gate + n);
+    }
+    if constexpr (EPI == EPI_HEADS) {
+      const HeadSection& sc = ha.sec[sec];
+      const int ns = (int)nsec + c * 4;
+      if (!exch && sc.gain) g = *(const float4*)(sc.gain + ns);
+      if (!exch && sc.rope) cs = *(const float4*)(ha.cs + m * (ha.head_dim >> 1) + ((ns & (ha.head_dim - 1)) >> 1));
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  if (wave < parts) {
+    uint4* const mine = smem + wave * SLAB;
+    // slot p of a k-tile holds chunk (p & 7) ^ ((row >> 1) & 7) of row p >> 3; rows of A first.  Instruction i loads rows
+    // i * 8 .. i * 8 + 7, so a lane has two swizzles, for even and odd i.
+    const bf16_t *ga[2], *gb[2];
+    const int r8 = lane >> 3;
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const int at = wave * 64 + ((lane & 7) ^ (((o * 8 + r8) >> 1) & 7)) * 8;
+      ga[o] = A + (m0 + r8) * lda + at;
+      gb[o] = Bt + (n0 + r8) * ldb + at;
+    }
+    auto load = [&](int t) __attribute__((always_inline)) {             // k-tile wave + 8 t
+#pragma unroll
+      for (int i = 0; i < 4; ++i) __builtin_amdgcn_global_load_lds((glb_void_t*)(ga[i & 1] + i * 8 * lda + t * 512), (lds_void_t*)(mine + i * 64), 16, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) __builtin_amdgcn_global_load_lds((glb_void_t*)(gb[i & 1] + i * 8 * ldb + t * 512), (lds_void_t*)(mine + (4 + i) * 64), 16, 0, 0);
+    };
+    load(0);
+    f32x16 acc[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+    const uint32_t fa = (uint32_t)(uintptr_t)(lds_void_t*)mine + (uint32_t)lr * 128, sx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+    const int mt = (KT - wave + 7) / 8;
+    auto multiply = [&](auto exch_) __attribute__((always_inline)) {
+      constexpr bool EXCH = decltype(exch_)::value;
+      for (int t = 0; t < mt; ++t) {
+        vm_wait<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 af[4], bfr[4][2];
+        static_for<4>([&](auto k_) __attribute__((always_inline)) {
+          constexpr int k = decltype(k_)::value;
+          const uint32_t o = fa + (sx ^ (uint32_t)(k * 32));
+          af[k] = __builtin_bit_cast(bf16x8, lds_read16_raw<0>(o));
+          bfr[k][0] = __builtin_bit_cast(bf16x8, lds_read16_raw<32 * 128>(o));
+          bfr[k][1] = __builtin_bit_cast(bf16x8, lds_read16_raw<64 * 128>(o));
+        });
+        lds_wait<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (t + 1 < mt) load(t + 1);                     // this k-tile is in registers: its LDS is free
+        static_for<4>([&](auto k_) __attribute__((always_inline)) {
+          constexpr int k = decltype(k_)::value;
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc[b] = EXCH ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[k], bfr[k][b], acc[b], 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[k][b], af[k], acc[b], 0, 0, 0);
+        });
+      }
+      // 32 x 64 (C^T: 64 x 32) floats over this wavefront's own k-tile, 16-byte chunks XOR-swizzled with the row
+      float4* const l16 = (float4*)mine;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int at = EXCH ? (b * 32 + lr) * 8 + ((q * 2 + lg) ^ (lr & 7)) : lr * 16 + ((b * 8 + q * 2 + lg) ^ (lr & 15));
+          l16[at] = make_float4(acc[b][q * 4], acc[b][q * 4 + 1], acc[b][q * 4 + 2], acc[b][q * 4 + 3]);
+        }
+    };
+    if constexpr (EPI == EPI_HEADS) { if (exch) multiply(std::true_type{}); else multiply(std::false_type{}); }
+    else multiply(std::false_type{});
+  }
+  __syncthreads();
+  const float4* const l16 = (const float4*)smem + (exch ? row * 8 + (c ^ (row & 7)) : row * 16 + (c ^ (row & 15)));
+  float4 s = l16[0];
+  auto add = [&](int w) __attribute__((always_inline)) {
+    const float4 p = l16[w * SLAB];
+    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+  };
+  if (parts == 8) {
+#pragma unroll
+    for (int w = 1; w < 8; ++w) add(w);
+  } else {
+    for (int w = 1; w < parts; ++w) add(w);
+  }
+  float v[4] = {s.x + bv[0], s.y + bv[1], s.z + bv[2], s.w + bv[3]};
+  if constexpr (EPI == EPI_RESID) {
+    if (!here) return;
+    x.x += g.x * v[0]; x.y += g.y * v[1]; x.z += g.z * v[2]; x.w += g.w * v[3];
+    *(float4*)(e.resid + m * e.ldr + n) = x;
+    if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x.x, x.y), cvt_pk_bf16(x.z, x.w));
+  } else if constexpr (EPI == EPI_HEADS) {
+    const HeadSection& sc = ha.sec[sec];
+    if (exch) {
+      if (here) *(uint2*)((bf16_t*)sc.dst + (nsec + row) * sc.ld + sc.row0 + m) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+      return;
+    }
+    if (sc.ssq) {
+      // sum of squares over the tile's 64 columns: the 16 threads of a row
+      float ss = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+      if (c == 0 && m < M) sc.ssq[(nsec >> 6) * ha.ssq_stride + m] = ss;
+    }
+    if (!here) return;
+    v[0] *= g.x; v[1] *= g.y; v[2] *= g.z; v[3] *= g.w;
+    if (sc.rope) {
+      const float a0 = v[0] * cs.x - v[1] * cs.y, b0 = v[0] * cs.y + v[1] * cs.x;
+      const float a1 = v[2] * cs.z - v[3] * cs.w, b1 = v[2] * cs.w + v[3] * cs.z;
+      v[0] = a0; v[1] = b0; v[2] = a1; v[3] = b1;
+    }
+    const int ns = (int)nsec + c * 4, hshift = ha.head_dim == 128 ? 7 : 6;
+    *(uint2*)((bf16_t*)sc.dst + (int64_t)(ns >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (ns & (ha.head_dim - 1))) =
+        make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+  } else {
+    if (!here) return;
+    if (EPI == EPI_GELU) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = gelu_tanh_fast(v[t]);
+    }
+    *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+  }
+}
+
+template <int EPI>
+static void launch_thin(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                        const EpiArgs& e, hipStream_t st) {
+  constexpr int lds = 96 * 128 * 8;
+  const int tm = (int)((M + 31) / 32), tn = (int)((N + 63) / 64);
+  static std::atomic<uint64_t> done;
+  allow_dynamic_lds((const void*)k_gemm_thin<EPI>, lds, done);
+  HeadsArgs ha{};
+  if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / 64; ha = *e.heads; }
+  k_gemm_thin<EPI><<<(unsigned)((tm * tn + 7) / 8 * 8), 512, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, e, ha);
+}
+static bool launch_thin_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N, int64_t K,
+                            int epi, const EpiArgs& e, hipStream_t st) {
+  if (epi == EPI_STORE) launch_thin<EPI_STORE>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_GELU) launch_thin<EPI_GELU>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_RESID) launch_thin<EPI_RESID>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_HEADS) launch_thin<EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
+  else return false;
+  return true;
+}
 
 // 64 x 16 bytes to LDS at dst: lane l's from byte voff(l) + soff of [base, base + bytes); the hardware returns zeros beyond
 __device__ __forceinline__ void load_lds16(const void* base, uint32_t bytes, uint32_t voff, int soff, uint4* dst) {
@@ -869,29 +1288,29 @@ static bool launch_turns_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int
   return true;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int ST = 2>
+template <int BM, int BN, int WGM, int WGN, int EPI>
 static void launch_one(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, const EpiArgs& e, hipStream_t st, int parts = 1) {
   constexpr int NT = WGM * WGN * 64;
-  constexpr size_t lds = (size_t)(BM + BN) * 128 * ST;
+  constexpr size_t lds = (size_t)(BM + BN) * 256;        // two k-tiles
   const int tm = (int)((M + BM - 1) / BM), tn = (int)((N + BN - 1) / BN);
   static std::atomic<uint64_t> done;
-  allow_dynamic_lds((const void*)k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST>, (int)lds, done);
+  allow_dynamic_lds((const void*)k_gemm_bf16<BM, BN, WGM, WGN, EPI>, (int)lds, done);
   HeadsArgs ha{};
   if (EPI == EPI_HEADS) { e.heads->ssq_np = e.heads->dim / BN; ha = *e.heads; }
   dim3 grid((unsigned)((tm * tn * parts + 7) / 8 * 8));
-  k_gemm_bf16<BM, BN, WGM, WGN, EPI, ST><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
+  k_gemm_bf16<BM, BN, WGM, WGN, EPI><<<grid, NT, lds, st>>>(A, lda, Wt, ldw, M, N, K, tn, tm * tn, parts, e, ha);
 }
 // false: this tile shape has no such epilogue (the rules below never ask for it)
-template <int BM, int BN, int WGM, int WGN, int ST>
+template <int BM, int BN, int WGM, int WGN>
 static bool launch_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,
                        int64_t K, int epi, const EpiArgs& e, hipStream_t st, int parts) {
-  constexpr bool HEADS = BM == 64 || BM == 256, PART = (BM == 64 && ST == 4) || BM == 256;
-  if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE, ST>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU, ST>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID, ST>(A, lda, Wt, ldw, M, N, K, e, st);
-  else if (epi == EPI_HEADS && HEADS) { if constexpr (HEADS) launch_one<BM, BN, WGM, WGN, EPI_HEADS, ST>(A, lda, Wt, ldw, M, N, K, e, st); }
-  else if (epi == EPI_PART && PART) { if constexpr (PART) launch_one<BM, BN, WGM, WGN, EPI_PART, ST>(A, lda, Wt, ldw, M, N, K, e, st, parts); }
+  constexpr bool HEADS = BM == 256, PART = BM == 256;
+  if (epi == EPI_STORE) launch_one<BM, BN, WGM, WGN, EPI_STORE>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_GELU) launch_one<BM, BN, WGM, WGN, EPI_GELU>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_RESID) launch_one<BM, BN, WGM, WGN, EPI_RESID>(A, lda, Wt, ldw, M, N, K, e, st);
+  else if (epi == EPI_HEADS && HEADS) { if constexpr (HEADS) launch_one<BM, BN, WGM, WGN, EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st); }
+  else if (epi == EPI_PART && PART) { if constexpr (PART) launch_one<BM, BN, WGM, WGN, EPI_PART>(A, lda, Wt, ldw, M, N, K, e, st, parts); }
   else return false;
   return true;
 }
@@ -910,6 +1329,7 @@ static int tile_family(int64_t M, int64_t N, int epi) {
 // Tile shape, LDS stages and K ranges of a problem: what the rules below decide and launch_gemm_bf16 runs
 static GemmRoute small_tile(int family, int64_t M, int64_t N) {
   if (family == TILE_128) return {128, 128, 4, 1};
+  if ((M + 31) / 32 * ((N + 63) / 64) <= 256) return {32, 64, 1, 1};    // k_gemm_thin: one round
   // 64 KB of LDS (two blocks per CU) where two suffice, 48 KB where a third has to fit
   return {64, 64, ((M + 63) / 64) * ((N + 63) / 64) <= 512 ? 4 : 3, 1};
 }
@@ -953,8 +1373,8 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // large ones through the caches.  Tiles whose K is cut over blocks until about one round of CUs is full do neither, for the
 // price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile of a
 // block 0.5 (128 x 128), 0.75 (128 x 256), 0.9 (160 x 256), 1.3 (256 x 256), 0.27 for each 64 x 64 block on the CU; 7 for both
-// launches and a block's ends, partials at 6.5 TB/s; uncut 0.24 per k-tile and 64 x 64 block on the CU and 7, 9 (128 x 128) or 14
-// for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 55 (128 x 256,
+// launches and a block's ends, partials at 6.5 TB/s; uncut 0.185 per k-tile and 3.3 (32 x 64), 0.24 per k-tile and 64 x 64 block
+// on the CU and 5, 9 (128 x 128) or 14 for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 55 (128 x 256,
 // 3) / 77, 1008 x 2048 x 8192 45 (128 x 256, 4) / 64, 2560 x 2048 x 8192 88 (160 x 256, 2) / 104, 480 x 3584 x 19456 83 (160 x 256, 6)
 // / 158; left uncut 1288 x 5120 x 13824 180 (cut 204), 3000 x 1024 x 4096 41 (42).  Outputs narrower than 768 columns fill few
 // tiles of any kind: they take the 64-, 160- and 256-row tiles by the figures of an earlier measurement (a k-tile 1.25 at 160
@@ -968,7 +1388,7 @@ static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats
   const int64_t t256 = tiles(256, 256), t160 = tiles(160, 256), t64 = tiles(64, 64), KT = K / 64;
   const bool fits160 = !narrow || (M + 159) / 160 * 160 <= (M + 255) / 256 * 256;
   const int family = tile_family(M, N, EPI_RESID);
-  double best = family == TILE_64 ? 0.24 * (double)(KT * ((t64 + 255) / 256)) + (narrow ? 5 : 7)
+  double best = family == TILE_64 ? (tiles(32, 64) <= 256 ? 0.185 * (double)KT + 3.3 : 0.24 * (double)(KT * ((t64 + 255) / 256)) + 5)
               : family == TILE_128 ? 0.5 * (double)KT + 9 : 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8;
   if (family == TILE_BIG && !narrow) {
     const GemmRoute u = big_tile(M, N, EPI_RESID);
@@ -1044,18 +1464,22 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
   const EpiArgs& ea = r.parts > 1 ? part : e;
   const int ep = r.parts > 1 ? (int)EPI_PART : epi;
   bool ok = false;
-#define GEMM_TILE(BM, BN, WGM, WGN, ST) \
-  if (r.bm == BM && r.stages == ST) ok = launch_cfg<BM, BN, WGM, WGN, ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
+#define RING_TILE(ST) \
+  if (r.bm == 64 && r.stages == ST) ok = launch_ring_cfg<ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
+#define GEMM_TILE(BM, BN, WGM, WGN) \
+  if (r.bm == BM) ok = launch_cfg<BM, BN, WGM, WGN>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
 #define TURNS_TILE(TM, TN, KB, ST) \
   if (r.bm == 32 * TM && r.bn == 64 * TN && r.stages == ST) ok = launch_turns_cfg<TM, TN, KB, ST>(A, lda, Wt, ldw, M, N, K, ep, ea, st, r.parts)
-  GEMM_TILE(64, 64, 2, 2, 4);
-  else GEMM_TILE(64, 64, 2, 2, 3);
+  if (r.bm == 32) ok = launch_thin_cfg(A, lda, Wt, ldw, M, N, K, ep, ea, st);
+  else RING_TILE(4);
+  else RING_TILE(3);
   else TURNS_TILE(4, 2, 64, 4);
   else TURNS_TILE(4, 4, 64, 3);
   else TURNS_TILE(5, 4, 64, 3);
-  else GEMM_TILE(192, 256, 2, 4, 2);
-  else GEMM_TILE(256, 256, 2, 4, 2);
-  else GEMM_TILE(320, 256, 2, 4, 2);
+  else GEMM_TILE(192, 256, 2, 4);
+  else GEMM_TILE(256, 256, 2, 4);
+  else GEMM_TILE(320, 256, 2, 4);
+#undef RING_TILE
 #undef GEMM_TILE
 #undef TURNS_TILE
   if (r.parts > 1) k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, r.parts, M, N, e);
