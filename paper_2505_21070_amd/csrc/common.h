@@ -55,6 +55,14 @@ template <int C> __device__ __forceinline__ void vm_wait() {
   static_assert(C < 64, "vmcnt has six bits");
   __builtin_amdgcn_s_waitcnt(0x0F70 | (C & 15) | ((C >> 4) << 14));
 }
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void glb_void_t;
+// 64 x 16 bytes to LDS at dst: lane l's from byte voff(l) + soff of [base, base + bytes); the hardware returns zeros beyond
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t bytes, uint32_t voff, int soff, uint4* dst) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), (lds_void_t*)dst, 16, voff, soff, 0, 0);
+#endif
+}
 // 16 bytes at LDS byte address addr + OFF through inline assembly: the compiler neither moves it nor waits for
 // it; the caller does (lds_wait) before the first use of the result
 template <int OFF> __device__ __forceinline__ u32x4 lds_read16_raw(uint32_t addr) {

@@ -22,8 +22,6 @@
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) const void glb_void_t;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -1035,13 +1033,6 @@ static bool launch_thin_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int6
   else if (epi == EPI_HEADS) launch_thin<EPI_HEADS>(A, lda, Wt, ldw, M, N, K, e, st);
   else return false;
   return true;
-}
-
-// 64 x 16 bytes to LDS at dst: lane l's from byte voff(l) + soff of [base, base + bytes); the hardware returns zeros beyond
-__device__ __forceinline__ void load_lds16(const void* base, uint32_t bytes, uint32_t voff, int soff, uint4* dst) {
-#ifdef __HIP_DEVICE_COMPILE__
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), (lds_void_t*)dst, 16, voff, soff, 0, 0);
-#endif
 }
 
 // Mid-size tiles: 2 x 4 wavefronts of (TM * 16) x (TN * 16), v_mfma_f32_16x16x32_bf16, k-slabs of KB in a ring of ST LDS stages.
