@@ -40,7 +40,7 @@ struct LayerMem {
   float *gq, *gk, *cgq, *cgk, *ln3g, *ln3b;     // fp32 copies of the per-channel vectors
   void *kbuf, *vtbuf;                           // [h][Lpad][d], [h][d][Lpad]: rows / columns = key positions of the buffer
   void *tk, *tvt;                               // text keys [h][Ltpad][d], text values transposed [h][d][Ltpad]
-  void *tkq; float* cgqk;                       // heads_epi: text keys times the cross-attention query gains, and the gain product
+  void *tkq; float* cgqk;                       // bf16: text keys times the cross-attention query gains, and the gain product
   void *wqkv_t, *bqkv, *wo_t, *cwq_t, *cwo_t, *w1_t, *w2_t;   // bf16 path: weights as [out(pad 256), in]
 };
 
@@ -82,7 +82,7 @@ struct dp_stage {
                                                        // the residual GEMMs over cut K ranges
   // DP_BF16 with dim % 256 == 0: the q/k/v and cross-q projections write per head from their GEMM epilogues
   // (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
-  float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi; bool launch_ok = true;
+  float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi, cross_heads; bool launch_ok = true;
   // state
   // Key buffer geometry (rows of kbuf = columns of vtbuf, the same in every layer).  The last block's keys
   // sit at [blk0, blk0 + last_S); the feature cache is the range [cache0, cache0 + cache_len): the sub-range
@@ -170,7 +170,8 @@ static size_t carve(dp_stage* s, void* base) {
   const int64_t kmax = c.text_dim > D ? c.text_dim : D;
   const bool own = bf && c.weight_layout == DP_WEIGHTS_IN_OUT;   // the library keeps [out, in] copies of the matrices
   s->wtmp = own ? cv.take(rup(D, 256) * kmax * E) : nullptr;
-  s->heads_epi = bf && D % 256 == 0;
+  s->heads_epi = bf;                                  // which calls use it: gemm_bf16_heads_ok
+  s->cross_heads = bf && D % 256 == 0;                // until a forward says so (dp_stage_peek)
   s->ssq_np = (int)(D / 64);                          // most partial sums per row any tile shape produces
   s->qssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
   s->kssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
@@ -411,14 +412,6 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
   constexpr bool bf = sizeof(T) == 2;
   // the first LayerNorm reads x_in itself and leaves its fp32 copy in the residual stream, and the last GEMM writes
   // x_out next to its residual update, so neither end needs a conversion pass
-  // adaLN modulation: sinusoidal features -> two-layer MLP (SiLU) -> SiLU -> 6*dim head, plus each layer's table; the first
-  // launch also builds the block's rotation table
-  PROF(DP_PROF_MODULATION,
-       const RopeTokens rope{s->rt, frame0, c.tok_h, c.tok_w, S, s->rope_tok};
-       const GemvTable<T> table{(const T*)s->w.bm, s->mtab, s->mod, c.n_layers};
-       int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, s->heads_epi ? &rope : nullptr, st);
-       parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e2, nullptr, nullptr, st);
-       launch_gemv<T>(GemvIn{s->e2, parts, 0.f}, (const T*)s->w.bt2, (int)D, (const T*)s->w.wm, (int)(6 * D), nullptr, &table, nullptr, st));
   const int64_t kv_hs = s->Lpad * d;        // head stride of kbuf
   // where this block's keys go: directly before the cached range if it fits there, else directly after it
   // (dp_cache_update left the cache where one side has room for a maximal block)
@@ -428,6 +421,28 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     else { blk0 = s->cache0 + s->cache_len; key0 = s->cache0; }
   }
   s->blk0 = blk0;
+  // The fused projections store per head where the tile that their size takes divides dim; otherwise they store rows, and
+  // separate kernels normalise, rotate and transpose.
+  HeadsArgs qkv{}, cross{};
+  bool qkv_heads = false, cross_heads = false;
+  if (s->heads_epi) {
+    qkv.dim = cross.dim = (int)D; qkv.head_dim = cross.head_dim = d; qkv.cs = s->rope_tok; qkv.ssq_stride = cross.ssq_stride = s->Smax;
+    qkv.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 1, 0};
+    qkv.sec[1] = HeadSection{nullptr, kv_hs, blk0, nullptr, s->kssq, 1, 0};
+    qkv.sec[2] = HeadSection{nullptr, s->Lpad, blk0, nullptr, nullptr, 0, 1};
+    cross.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 0, 0};
+    qkv_heads = gemm_bf16_heads_ok(S, 3 * D, qkv);
+    cross_heads = gemm_bf16_heads_ok(S, D, cross);
+  }
+  s->cross_heads = cross_heads;
+  // adaLN modulation: sinusoidal features -> two-layer MLP (SiLU) -> SiLU -> 6*dim head, plus each layer's table; the first
+  // launch also builds the block's rotation table
+  PROF(DP_PROF_MODULATION,
+       const RopeTokens rope{s->rt, frame0, c.tok_h, c.tok_w, S, s->rope_tok};
+       const GemvTable<T> table{(const T*)s->w.bm, s->mtab, s->mod, c.n_layers};
+       int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, qkv_heads ? &rope : nullptr, st);
+       parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e2, nullptr, nullptr, st);
+       launch_gemv<T>(GemvIn{s->e2, parts, 0.f}, (const T*)s->w.bt2, (int)D, (const T*)s->w.wm, (int)(6 * D), nullptr, &table, nullptr, st));
   for (int l = 0; l < c.n_layers; ++l) {
     const dp_layer_weights& w = s->lw[(size_t)l]; LayerMem& m = s->lm[(size_t)l];
     const float* md = s->mod + (int64_t)l * 6 * D;
@@ -436,12 +451,11 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     PROF(DP_PROF_LN, launch_ln_modulate<T>(s->xres, l == 0 ? (const T*)x_in : nullptr, (T*)s->hbuf, S, (int)D,
                                            c.eps, sc1, sh1, 1, st));
     AttnQNorm qn{s->qssq, 0, s->Smax, 1.f / (float)D, c.eps, Path<T>::q_scale(d)};
-    if (s->heads_epi) {
-      HeadsArgs ha{};
-      ha.dim = (int)D; ha.head_dim = d; ha.cs = s->rope_tok; ha.ssq_stride = s->Smax;
-      ha.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, m.gq, s->qssq, 1, 0};
-      ha.sec[1] = HeadSection{m.kbuf, kv_hs, blk0, m.gk, s->kssq, 1, 0};
-      ha.sec[2] = HeadSection{m.vtbuf, s->Lpad, blk0, nullptr, nullptr, 0, 1};
+    if (qkv_heads) {
+      HeadsArgs ha = qkv;
+      ha.sec[0].gain = m.gq;
+      ha.sec[1].dst = m.kbuf; ha.sec[1].gain = m.gk;
+      ha.sec[2].dst = m.vtbuf;
       EpiArgs e = epi_store(nullptr, 0, m.bqkv);
       e.heads = &ha;
       PROF(DP_PROF_QKV_GEMM, s->launch_ok &= Path<T>::gemm(s->hbuf, D, nullptr, m.wqkv_t, S, 3 * D, D, EPI_HEADS, e, st));
@@ -465,16 +479,14 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     }
     PROF(DP_PROF_SELF_ATTN,
          Path<T>::attn(s->qbuf, s->Spad * d, m.kbuf, kv_hs, key0, m.vtbuf, s->Lpad, S,
-                       s->cache_len + S, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, s->heads_epi ? &qn : nullptr, st));
+                       s->cache_len + S, h, d, s->attn_o, D, s->attn_scratch, s->attn_scratch_floats, qkv_heads ? &qn : nullptr, st));
     if (s->tap_attn && l == c.n_layers - 1) launch_copy2d<T>((const T*)s->attn_o, 0, (T*)s->tap_attn, 0, 1, S * D, st);
     PROF(DP_PROF_OPROJ_GEMM, Path<T>::gemm(s->attn_o, D, w.wo, m.wo_t, S, D, D, EPI_RESID, epi_resid(s, w.bo, g1), st));
     if (s->tap_xself && l == c.n_layers - 1) launch_copy2d<float>(s->xres, 0, s->tap_xself, 0, 1, S * D, st);
     // --- cross-attention to the text tokens
     PROF(DP_PROF_LN, launch_ln_modulate<T>(s->xres, nullptr, (T*)s->hbuf, S, (int)D, c.eps, m.ln3g, m.ln3b, 0, st));
-    if (s->heads_epi) {
-      HeadsArgs ha{};
-      ha.dim = (int)D; ha.head_dim = d; ha.ssq_stride = s->Smax;
-      ha.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 0, 0};
+    if (cross_heads) {
+      HeadsArgs ha = cross;
       EpiArgs e = epi_store(nullptr, 0, w.cbq);
       e.heads = &ha;
       PROF(DP_PROF_CROSS_Q_GEMM, s->launch_ok &= Path<T>::gemm(s->hbuf, D, w.cwq, m.cwq_t, S, D, D, EPI_HEADS, e, st));
@@ -599,10 +611,10 @@ static int peek_typed(dp_stage* s, int what, int layer, float* dst, int64_t cap,
     case DP_PEEK_V: launch_gather_vt<T>((const T*)m.vtbuf, s->Lpad, s->blk0, n, h, d, dst, st); break;
     case DP_PEEK_CACHE_K: launch_gather_heads<T>((const T*)m.kbuf, s->Lpad * d, s->cache0, n, h, d, dst, st); break;
     case DP_PEEK_CACHE_V: launch_gather_vt<T>((const T*)m.vtbuf, s->Lpad, s->cache0, n, h, d, dst, st); break;
-    case DP_PEEK_TEXT_K: launch_gather_heads<T>((const T*)(s->heads_epi ? m.tkq : m.tk), s->Ltpad * d, 0, n, h, d, dst, st); break;
+    case DP_PEEK_TEXT_K: launch_gather_heads<T>((const T*)(s->cross_heads ? m.tkq : m.tk), s->Ltpad * d, 0, n, h, d, dst, st); break;
     case DP_PEEK_TEXT_V: launch_gather_vt<T>((const T*)m.tvt, s->Ltpad, 0, n, h, d, dst, st); break;
     case DP_PEEK_Q:
-      if (s->heads_epi) {
+      if (s->cross_heads) {
         const AttnQNorm qn{s->qssq, s->cross_np, s->Smax, 1.f / (float)D, c.eps, Path<T>::q_scale(d)};
         launch_gather_heads_qnorm((const bf16_t*)s->qbuf, s->Spad * d, n, h, d, qn, dst, st);
       } else {
