@@ -214,7 +214,10 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
 // Needs K % 32 == 0 and 16-byte steps everywhere.
 // Measured (us, k_gemm_f32 -> this): 1560 x 1536 x 8960 residual 461 -> 344 (80 rows), 1560 x 1536 x 1536 residual 89 -> 64 (80), q | k | v
 // of 1560 x 1536 241 -> 179 (112), 1560 x 8960 x 1536 GELU 438 -> 381 (112), 6240 x 8960 x 1536 1492 -> 1434 (112); with equal tiles
-// (64 x 64) 461 -> 406, 438 -> 391.
+// (64 x 64) 461 -> 406, 438 -> 391; these in one chain over K, 0 to 1 % faster than now.
+// The sum over K is taken in four runs of k-tiles that are added up in order, like the four chains of the 32 x 32 tiles: a layer
+// of 840 tokens x 1024 (FFN 4608) is 4.7e-7 from 64 bits on those, 7.0e-7 in one chain, 3.7e-7 this way; 1560 tokens x 1536
+// 1.3e-6 in one chain, 6.7e-7 this way.  Runs of 8 k-tiles: 2.8e-7 and 3.7e-7, but 5 and 2 % slower.
 template <int BM, int ST, int EPI>
 __global__ __launch_bounds__(256) void k_gemm_f32_ring(const float* __restrict__ A, int64_t lda, GemmF32W w, int64_t ldw,
                                                        int64_t M, int64_t N, int64_t K, int tiles_m, int tiles_n, int tiles, EpiArgs e) {
@@ -259,23 +262,23 @@ __global__ __launch_bounds__(256) void k_gemm_f32_ring(const float* __restrict__
       if (d == ST - 2 ? behind >= d : behind == d) { if (all_a) vm_wait<d * NL>(); else vm_wait<d * (NL - 1)>(); }
     });
   };
-  f32x4 acc[TM];
+  f32x4 acc[TM], sum[TM];                                // of the last run of k-tiles; of the runs before it
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[i][r] = 0.f;
+  for (int i = 0; i < TM; ++i) acc[i] = sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
   const uint32_t fa = lds0 + (uint32_t)lr * 128, xa = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
   const uint32_t fw = lds0 + (uint32_t)(ACH + lg * 4 * 16 + ((wave * 4 + (lr >> 2)) ^ (lg * 4))) * 16 + (uint32_t)(lr & 3) * 4;
 #pragma unroll
   for (int z = 0; z < ST - 1; ++z) if (z < KT) load_tile(z, z);
   int stage = 0;
-  for (int s = 0; s < KT; ++s) {
+  // k-tile s; LAST: one of the last ST - 1, behind which fewer or none have been requested
+  auto tile = [&](int s, auto last_) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last_)::value;
     __builtin_amdgcn_sched_barrier(0);
-    wait_behind(KT - 1 - s < ST - 2 ? KT - 1 - s : ST - 2);
+    wait_behind(LAST && KT - 1 - s < ST - 2 ? KT - 1 - s : ST - 2);
     __builtin_amdgcn_s_barrier();                        // tile s is there, and everyone is done with tile s - 1
     __builtin_amdgcn_sched_barrier(0);
-    if (s + ST - 1 < KT) load_tile(s + ST - 1, stage == 0 ? ST - 1 : stage - 1);
+    if constexpr (!LAST) load_tile(s + ST - 1, stage == 0 ? ST - 1 : stage - 1);
     __builtin_amdgcn_sched_barrier(0);
     const uint32_t base = (uint32_t)stage * STAGE * 16;
     f32x4 a[2][TM];
@@ -301,7 +304,20 @@ __global__ __launch_bounds__(256) void k_gemm_f32_ring(const float* __restrict__
       __builtin_amdgcn_sched_barrier(0);
     });
     stage = stage + 1 == ST ? 0 : stage + 1;
+  };
+  const int run = (KT + 3) >> 2, full = KT - (ST - 1);   // the last run takes the last tiles in
+  int s = 0;
+  while (s < full) {
+    const int end = s + run < full ? s + run : full;
+    for (; s < end; ++s) tile(s, std::false_type{});
+    if (s < full) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) { sum[i] += acc[i]; acc[i] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+    }
   }
+  for (; s < KT; ++s) tile(s, std::true_type{});
+#pragma unroll
+  for (int i = 0; i < TM; ++i) sum[i] += acc[i];
   // W was the A operand: a lane holds row lr of an accumulator tile and the four columns lg * 4 .. + 3
   const int64_t n = n0 + wave * 16 + lg * 4;
   if (n >= N) return;
@@ -316,7 +332,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32_ring(const float* __restrict__
   for (int i = 0; i < TM; ++i) {
     const int64_t m = m0 + i * 16 + lr;
     if (m >= M) continue;
-    float4 v = make_float4(acc[i][0] + bv.x, acc[i][1] + bv.y, acc[i][2] + bv.z, acc[i][3] + bv.w);
+    float4 v = make_float4(sum[i][0] + bv.x, sum[i][1] + bv.y, sum[i][2] + bv.z, sum[i][3] + bv.w);
     if (EPI == EPI_GELU) v = make_float4(gelu_tanh_f(v.x), gelu_tanh_f(v.y), gelu_tanh_f(v.z), gelu_tanh_f(v.w));
     if constexpr (EPI == EPI_RESID) {
       v = make_float4(x[i].x + gv.x * v.x, x[i].y + gv.y * v.y, x[i].z + gv.z * v.z, x[i].w + gv.w * v.w);
