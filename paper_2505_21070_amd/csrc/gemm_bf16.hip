@@ -82,9 +82,14 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
     constexpr int UPR = BN / 4, CPR = BN / 8, RPI = 64 / CPR;
     static_assert(BM * BN * 2 <= LB, "EPI_HEADS stages the whole tile at once");
     // [row][wavefront column]: sums of squares; behind the staged tile where there is room
-    constexpr bool RED_DYN = BM * BN * 2 + BM * WGN * 4 <= LB;
+    // Plain sections of 128-column tiles are staged in fp32, so that only the result is rounded, as by the separate kernels
+    // (staged in bf16, 64-column tiles left a layer of dim 1664 2.58e-3 from 64 bits, 2.50e-3 this way and by those, in
+    // the same time).  The wider tiles' fp32 rows do not all fit.
+    constexpr bool WIDE = BN == 128 && BM * BN * 4 + BM * WGN * 4 <= LB;
+    constexpr int SB = WIDE ? 4 : 2;
+    constexpr bool RED_DYN = BM * BN * SB + BM * WGN * 4 <= LB;
     __shared__ float red_static[RED_DYN ? 1 : BM * WGN];
-    float* const red = RED_DYN ? (float*)smem + BM * BN / 2 : red_static;
+    float* const red = RED_DYN ? (float*)smem + BM * BN * SB / 4 : red_static;
     const HeadSection sc = ha.sec[sec];
     const int64_t nsec = n0 - (int64_t)sec * ha.dim;     // first column of this tile inside its section
     const int hshift = ha.head_dim == 128 ? 7 : 6, hmask = ha.head_dim - 1;
@@ -158,10 +163,9 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
               v[t] = acc[i][j][q * 4 + t] + bv[t];
               ss[i] += v[t] * v[t];
             }
-            uint2 pk;
-            pk.x = cvt_pk_bf16(v[0], v[1]);
-            pk.y = cvt_pk_bf16(v[2], v[3]);
-            l8[row * UPR + ((nl >> 2) ^ (row & XM))] = pk;
+            const int u = row * UPR + ((nl >> 2) ^ (row & XM));
+            if constexpr (WIDE) ((float4*)smem)[u] = make_float4(v[0], v[1], v[2], v[3]);
+            else l8[u] = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
           }
         }
 #pragma unroll
@@ -211,6 +215,7 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
 #pragma unroll
     for (int it0 = 0; it0 < IT; it0 += G) {
       uint4 d[G][2];
+      float4 df[WIDE ? G : 1][2][2];
       float4 cs[G][2][2];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -218,6 +223,11 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
           const int row = wave * (BM / NW) + (it0 + g) * RP2 + lane / HC;
 #pragma unroll
           for (int k = 0; k < 2; ++k) {
+            if (WIDE && !swapped) {
+#pragma unroll
+              for (int u = 0; u < 2; ++u) df[WIDE ? g : 0][k][u] = ((const float4*)smem)[row * UPR + (((c8 >> 2) + k * (BN / 8) + u) ^ (row & XM))];
+              continue;
+            }
             d[g][k] = smem[row * CPR + (((c8 >> 3) + k * HC) ^ ((row & XM) >> 1))];
             if (row & 1) d[g][k] = make_uint4(d[g][k].z, d[g][k].w, d[g][k].x, d[g][k].y);
           }
@@ -244,14 +254,17 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
             } else if (m0 + row < M && col_ok[k]) {
               const int64_t m = m0 + row;
               uint4 dv = d[g][k];
-              if (scale) {
+              if (scale || WIDE) {
                 const uint32_t w[4] = {dv.x, dv.y, dv.z, dv.w};
+                const float4 f0 = df[WIDE ? g : 0][k][0], f1 = df[WIDE ? g : 0][k][1];
+                const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
                 const float4 c0 = cs[g][share ? 0 : k][0], c1 = cs[g][share ? 0 : k][1];
                 const float csv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
                 uint32_t o[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                  float a = bf16_to_f32((bf16_t)(w[u] & 0xffff)) * gg[k][2 * u], b = bf16_to_f32((bf16_t)(w[u] >> 16)) * gg[k][2 * u + 1];
+                  float a = (WIDE ? f[2 * u] : bf16_to_f32((bf16_t)(w[u] & 0xffff))) * gg[k][2 * u];
+                  float b = (WIDE ? f[2 * u + 1] : bf16_to_f32((bf16_t)(w[u] >> 16))) * gg[k][2 * u + 1];
                   if (rotate) {
                     const float a2 = a * csv[2 * u] - b * csv[2 * u + 1], b2 = a * csv[2 * u + 1] + b * csv[2 * u];
                     a = a2; b = b2;
@@ -739,7 +752,8 @@ __global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A,
     }
   } else {
     uint2* const l8 = (uint2*)smem;                      // 64 x 64 bf16, 8-byte units XOR-swizzled with the row
-    float* const red = (float*)(smem + 512);             // EPI_HEADS: [row][wavefront column] sums of squares
+    float4* const l16 = (float4*)smem;                   // EPI_HEADS, plain sections: 64 x 64 fp32, so that only the result is rounded
+    float* const red = (float*)(smem + 1024);            // EPI_HEADS: [row][wavefront column] sums of squares
     if (EPI == EPI_HEADS && exch) {
       // C^T: row = channel wn * 32 + lr, four consecutive output rows per quad
       const int row = wn * 32 + lr;
@@ -760,7 +774,9 @@ __global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A,
           ss += v[t] * v[t];
           if (EPI == EPI_GELU) v[t] = gelu_tanh_fast(v[t]);
         }
-        l8[row_in * 16 + ((wn * 8 + q * 2 + lg) ^ (row_in & 15))] = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
+        const int u = row_in * 16 + ((wn * 8 + q * 2 + lg) ^ (row_in & 15));
+        if constexpr (EPI == EPI_HEADS) l16[u] = make_float4(v[0], v[1], v[2], v[3]);
+        else l8[u] = make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
       }
       if constexpr (EPI == EPI_HEADS) {
         ss += __shfl_xor(ss, 32, 64);
@@ -792,23 +808,23 @@ __global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A,
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         const int n = (int)nsec + c8 + k * 32;
-        uint4 d = chunk(hrow, (tid & 3) + k * 4);
-        if (rotate || gains) {
-          uint32_t w[4] = {d.x, d.y, d.z, d.w};
-          const float gs[8] = {hg[k][0].x, hg[k][0].y, hg[k][0].z, hg[k][0].w, hg[k][1].x, hg[k][1].y, hg[k][1].z, hg[k][1].w};
-          const float cs[8] = {hc[k][0].x, hc[k][0].y, hc[k][0].z, hc[k][0].w, hc[k][1].x, hc[k][1].y, hc[k][1].z, hc[k][1].w};
+        const int unit = (tid & 3) * 2 + k * 8;
+        const float4 f0 = l16[hrow * 16 + (unit ^ (hrow & 15))], f1 = l16[hrow * 16 + ((unit + 1) ^ (hrow & 15))];
+        const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
+        const float gs[8] = {hg[k][0].x, hg[k][0].y, hg[k][0].z, hg[k][0].w, hg[k][1].x, hg[k][1].y, hg[k][1].z, hg[k][1].w};
+        const float cs[8] = {hc[k][0].x, hc[k][0].y, hc[k][0].z, hc[k][0].w, hc[k][1].x, hc[k][1].y, hc[k][1].z, hc[k][1].w};
+        uint32_t w[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            float a = bf16_to_f32((bf16_t)(w[u] & 0xffff)), b = bf16_to_f32((bf16_t)(w[u] >> 16));
-            if (gains) { a *= gs[2 * u]; b *= gs[2 * u + 1]; }
-            if (rotate) {
-              const float a2 = a * cs[2 * u] - b * cs[2 * u + 1], b2 = a * cs[2 * u + 1] + b * cs[2 * u];
-              a = a2; b = b2;
-            }
-            w[u] = cvt_pk_bf16(a, b);
+        for (int u = 0; u < 4; ++u) {
+          float a = f[2 * u], b = f[2 * u + 1];
+          if (gains) { a *= gs[2 * u]; b *= gs[2 * u + 1]; }
+          if (rotate) {
+            const float a2 = a * cs[2 * u] - b * cs[2 * u + 1], b2 = a * cs[2 * u + 1] + b * cs[2 * u];
+            a = a2; b = b2;
           }
-          d = make_uint4(w[0], w[1], w[2], w[3]);
+          w[u] = cvt_pk_bf16(a, b);
         }
+        const uint4 d = make_uint4(w[0], w[1], w[2], w[3]);
         __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)sc.dst + (int64_t)(n >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (n & hmask)));
       }
     } else {

@@ -80,8 +80,8 @@ struct dp_stage {
   void* tap_attn; float *tap_xself, *tap_xcross;
   float* attn_scratch; size_t attn_scratch_floats;   // partial results of attention over cut key ranges and of
                                                        // the residual GEMMs over cut K ranges
-  // DP_BF16 with dim % 256 == 0: the q/k/v and cross-q projections write per head from their GEMM epilogues
-  // (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
+  // DP_BF16, where the tile that a call's size takes divides dim: the q/k/v and cross-q projections write per head from
+  // their GEMM epilogues (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
   float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi, cross_heads; bool launch_ok = true;
   // state
   // Key buffer geometry (rows of kbuf = columns of vtbuf, the same in every layer).  The last block's keys

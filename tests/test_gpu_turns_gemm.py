@@ -12,6 +12,7 @@ SHAPES = {
     (768, 6, 128, 6144, 8, 47, 5): {"qkv": ("heads", 128, 256, 3), "ffn2": ("cut", 128, 256, 3)},         # 1880 rows
     (1024, 8, 128, 2048, 8, 75, 5): {"qkv": ("heads", 160, 256, 3)},                                       # 3000 rows
     (1536, 12, 128, 1536, 8, 113, 3): {"o": ("resid", 128, 256, 3)},                                       # 2712 rows
+    (640, 10, 64, 1280, 8, 53, 4): {"qkv": ("store", 128, 128, 4)},                                        # 1696 rows; the stage has it stored per head
     (768, 6, 128, 6144, 8, 59, 1): {"ffn2": ("cut", 128, 128, 4)},                                         # 472 rows
 }
 
