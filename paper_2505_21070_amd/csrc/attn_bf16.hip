@@ -617,7 +617,8 @@ __global__ __launch_bounds__(512, HD == 64 ? 4 : 2) void k_attn_few(const bf16_t
         mx = fmaxf(mx, s[r]);
       }
       const float mn = fmaxf(m, fmaxf(mx, __shfl_xor(mx, 32, 64)));
-      const float al = __builtin_amdgcn_exp2f(m - mn);              // 2^-inf = 0 at the first tile
+      const float ref = mn == -INFINITY ? 0.f : mn;      // nothing but scores of -inf so far: they weigh 0, not 2^(inf - inf)
+      const float al = __builtin_amdgcn_exp2f(m - ref);  // 2^-inf = 0 at the first tile
       m = mn;
       l *= al;
       uint4 pf[2];
@@ -626,7 +627,7 @@ __global__ __launch_bounds__(512, HD == 64 ? 4 : 2) void k_attn_few(const bf16_t
         uint32_t w[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          w[j] = cvt_pk_bf16(__builtin_amdgcn_exp2f(s[u * 8 + 2 * j] - mn), __builtin_amdgcn_exp2f(s[u * 8 + 2 * j + 1] - mn));
+          w[j] = cvt_pk_bf16(__builtin_amdgcn_exp2f(s[u * 8 + 2 * j] - ref), __builtin_amdgcn_exp2f(s[u * 8 + 2 * j + 1] - ref));
           l = add_pk_bf16(w[j], l);
         }
         pf[u] = make_uint4(w[0], w[1], w[2], w[3]);

@@ -42,3 +42,27 @@ def test_cross_attention_shapes(monkeypatch, heads, hd, grid, text_len, peaked):
         p = np.exp2(s2 - s2.max(1, keepdims=True))
         ref[:, sl] = (p / p.sum(1, keepdims=True)) @ v[:, sl]
     check("shape/cross_attn", to_np(g.peek("cross_attn", 0)), ref, "bf16")
+
+
+@pytest.mark.parametrize("heads,hd,grid,text_len,at", [(2, 128, (6, 12, 3), 33, slice(32, 33)), (2, 64, (6, 12, 3), 300, slice(64, 96))])
+def test_key_tiles_of_infinite_scores(monkeypatch, heads, hd, grid, text_len, at):
+    """A whole 32-key tile (a ragged one of one key; a full one) whose scores are -inf weighs nothing.  Keys `at` are infinite in one
+    channel, zero in the others' text rows; queries on its negative side are compared (the others' scores are +inf)."""
+    c, j, D = 5, 7, heads * hd
+    monkeypatch.setitem(synth.CONFIGS, "shape", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=D, n_heads=heads, head_dim=hd, ffn_dim=128,
+                                                     text_len=text_len, text_dim=D, tok_h=grid[0], tok_w=grid[1], block_frames=grid[2], cache_frames=1))
+    cfg, w, text, blocks = synth.make_case("shape", seed=6, strong_gate=True)
+    lw = w["layers"][0]
+    lw["cwk"][:, c] = 0.0
+    lw["cwk"][j, c], lw["cbk"][c], lw["cgk"][c], lw["cgq"][c] = 1.0, 0.0, 2.0 ** 125, 1.0
+    text[:, j] = 0.0
+    text[at, j] = 32.0
+    g = gpu_stage(cfg, w, text, max_abs_frames=64)
+    g.forward(to_dev(blocks[1], cfg), cfg["block_frames"], 0, T_CUR)
+    q, k, v, got = (to_np(g.peek(n, 0)) for n in ("q", "text_k", "text_v", "cross_attn"))
+    assert np.isinf(k[at, c]).all() and np.isfinite(np.delete(k, np.r_[at], 0)).all()
+    rows, sl = q[:, c] < 0, slice(0, hd)                                          # channel c is the first head's
+    s2 = q[rows, sl] @ k[:, sl].T
+    p = np.exp2(s2 - s2.max(1, keepdims=True))
+    assert rows.any() and (p[:, at] == 0).all()
+    check("shape/infinite", got[rows, sl], (p / p.sum(1, keepdims=True)) @ v[:, sl], "bf16")
