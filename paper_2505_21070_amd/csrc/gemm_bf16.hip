@@ -1342,9 +1342,13 @@ static GemmRoute small_tile(int family, int64_t M, int64_t N) {
 }
 
 // EPI_HEADS.  Sections must be whole tiles wide, a transposed one needs 8 | M and 8 | row0.
+static int heads_columns(int64_t M, int64_t N) {         // columns of the tile; grows with M
+  const int family = tile_family(M, N, EPI_HEADS);
+  return family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
+}
+bool gemm_bf16_heads_ever(int64_t M, int64_t N, int64_t dim) { return dim % heads_columns(M, N) == 0; }
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
-  const int family = tile_family(M, N, EPI_HEADS), bn = family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
-  if (h.dim <= 0 || (h.head_dim != 64 && h.head_dim != 128) || h.dim % bn || h.dim % h.head_dim || N % h.dim || N / h.dim > 3) return false;
+  if (h.dim <= 0 || (h.head_dim != 64 && h.head_dim != 128) || h.dim % heads_columns(M, N) || h.dim % h.head_dim || N % h.dim || N / h.dim > 3) return false;
   for (int i = 0; i < (int)(N / h.dim); ++i) {
     if (h.sec[i].transposed && (M % 8 || h.sec[i].row0 % 8 || h.sec[i].ld % 8)) return false;
     if (h.sec[i].ssq && h.ssq_stride < M) return false;

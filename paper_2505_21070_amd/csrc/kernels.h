@@ -102,6 +102,8 @@ GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, size_t scrat
 size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N);
 // whether launch_gemm_bf16(.., EPI_HEADS, ..) can take this problem; if not it launches nothing and returns false
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h);
+// whether it can for sections of `dim` columns and any number of rows from M on: false for M, false for all beyond
+bool gemm_bf16_heads_ever(int64_t M, int64_t N, int64_t dim);
 // ---- attn_bf16.hip : flash attention on MFMA, head_dim 64 or 128 ------------------------------
 // q must already be multiplied by log2(e)/sqrt(d) (attn_bf16_q_scale) and be readable for
 // roundup(S, 256) rows per head; k rows / vt columns readable (finite in vt) up to

@@ -40,7 +40,7 @@ struct LayerMem {
   float *gq, *gk, *cgq, *cgk, *ln3g, *ln3b;     // fp32 copies of the per-channel vectors
   void *kbuf, *vtbuf;                           // [h][Lpad][d], [h][d][Lpad]: rows / columns = key positions of the buffer
   void *tk, *tvt;                               // text keys [h][Ltpad][d], text values transposed [h][d][Ltpad]
-  void *tkq; float* cgqk;                       // bf16: text keys times the cross-attention query gains, and the gain product
+  void *tkq; float* cgqk;                       // any_cross_heads: text keys times the cross-attention query gains, and the gain product
   void *wqkv_t, *bqkv, *wo_t, *cwq_t, *cwo_t, *w1_t, *w2_t;   // bf16 path: weights as [out(pad 256), in]
 };
 
@@ -82,7 +82,9 @@ struct dp_stage {
                                                        // the residual GEMMs over cut K ranges
   // DP_BF16, where the tile that a call's size takes divides dim: the q/k/v and cross-q projections write per head from
   // their GEMM epilogues (gains and rotation applied there), leaving only the RMSNorm row scale, which arrives as partial sums
-  float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0; bool heads_epi, cross_heads; bool launch_ok = true;
+  float *qssq, *kssq; float2* rope_tok; int ssq_np, cross_np = 0;
+  bool any_qkv_heads, any_cross_heads;                 // some call of this stage does; without one, no memory for it
+  bool cross_heads; bool launch_ok = true;             // the last forward's cross-q projection did
   // state
   // Key buffer geometry (rows of kbuf = columns of vtbuf, the same in every layer).  The last block's keys
   // sit at [blk0, blk0 + last_S); the feature cache is the range [cache0, cache0 + cache_len): the sub-range
@@ -170,12 +172,13 @@ static size_t carve(dp_stage* s, void* base) {
   const int64_t kmax = c.text_dim > D ? c.text_dim : D;
   const bool own = bf && c.weight_layout == DP_WEIGHTS_IN_OUT;   // the library keeps [out, in] copies of the matrices
   s->wtmp = own ? cv.take(rup(D, 256) * kmax * E) : nullptr;
-  s->heads_epi = bf;                                  // which calls use it: gemm_bf16_heads_ok
+  s->any_qkv_heads = bf && gemm_bf16_heads_ever(s->tok, 3 * D, D);
+  s->any_cross_heads = bf && gemm_bf16_heads_ever(s->tok, D, D);
   s->cross_heads = bf && D % 256 == 0;                // until a forward says so (dp_stage_peek)
   s->ssq_np = (int)(D / 64);                          // most partial sums per row any tile shape produces
-  s->qssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
-  s->kssq = s->heads_epi ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
-  s->rope_tok = s->heads_epi ? (float2*)cv.take(s->Smax * (c.head_dim / 2) * 8) : nullptr;
+  s->qssq = s->any_cross_heads ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;   // q | k | v stores per head: so does cross-q
+  s->kssq = s->any_qkv_heads ? (float*)cv.take(s->Smax * s->ssq_np * 4) : nullptr;
+  s->rope_tok = s->any_qkv_heads ? (float2*)cv.take(s->Smax * (c.head_dim / 2) * 8) : nullptr;
   s->e1 = (float*)cv.take(GEMV_MAX_SLICES * D * 4); s->e2 = (float*)cv.take(GEMV_MAX_SLICES * D * 4);   // sliced vectors
   s->mtab = (float*)cv.take(L * 6 * D * 4);
   s->mod = (float*)cv.take(L * 6 * D * 4);
@@ -197,8 +200,8 @@ static size_t carve(dp_stage* s, void* base) {
     m.ln3g = (float*)cv.take(D * 4); m.ln3b = (float*)cv.take(D * 4);
     m.kbuf = cv.take(s->Lpad * D * E); m.vtbuf = cv.take(s->Lpad * D * E);
     m.tk = cv.take(s->Ltpad * D * E);
-    m.tkq = s->heads_epi ? cv.take(s->Ltpad * D * E) : nullptr;
-    m.cgqk = s->heads_epi ? (float*)cv.take(D * 4) : nullptr;
+    m.tkq = s->any_cross_heads ? cv.take(s->Ltpad * D * E) : nullptr;
+    m.cgqk = s->any_cross_heads ? (float*)cv.take(D * 4) : nullptr;
     m.tvt = cv.take(s->Ltpad * D * E);
   }
   const size_t zero_end = cv.off;      // everything up to here is zero-filled at init
@@ -330,7 +333,7 @@ static void init_typed(dp_stage* s, const void* text, hipStream_t st) {
     Path<T>::gemm(ctx, D, w.cwk, own ? s->wtmp : w.cwk, Lt, D, D, EPI_STORE, epi_store(s->raw, D, w.cbk), st);
     { const NormRopeJob<T> jk{0, m.cgk, 1.f, (T*)m.tk, s->Ltpad * d, 0, 0};
       launch_norm_rope<T>((const T*)s->raw, D, Lt, h, d, c.eps, &jk, 1, nullptr, 0, 1, 1, st); }
-    if (s->heads_epi) {
+    if (s->any_cross_heads) {
       // q.k with q = r (q_raw * cgq): the query gains move over to the keys, the row scale r to the attention kernel
       launch_mul_f32(m.cgk, m.cgq, m.cgqk, D, st);
       const NormRopeJob<T> jk{0, m.cgqk, 1.f, (T*)m.tkq, s->Ltpad * d, 0, 0};
@@ -425,13 +428,13 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
   // separate kernels normalise, rotate and transpose.
   HeadsArgs qkv{}, cross{};
   bool qkv_heads = false, cross_heads = false;
-  if (s->heads_epi) {
+  if (s->any_cross_heads) {
     qkv.dim = cross.dim = (int)D; qkv.head_dim = cross.head_dim = d; qkv.cs = s->rope_tok; qkv.ssq_stride = cross.ssq_stride = s->Smax;
     qkv.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 1, 0};
     qkv.sec[1] = HeadSection{nullptr, kv_hs, blk0, nullptr, s->kssq, 1, 0};
     qkv.sec[2] = HeadSection{nullptr, s->Lpad, blk0, nullptr, nullptr, 0, 1};
     cross.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 0, 0};
-    qkv_heads = gemm_bf16_heads_ok(S, 3 * D, qkv);
+    qkv_heads = s->any_qkv_heads && gemm_bf16_heads_ok(S, 3 * D, qkv);
     cross_heads = gemm_bf16_heads_ok(S, D, cross);
   }
   s->cross_heads = cross_heads;

@@ -87,6 +87,20 @@ def test_config_validation_without_gpu(B):
     B._lib.dp_stage_free(None)
 
 
+# dim, tokens of a frame, frames: copies of the text keys and values a layer keeps.  With a second copy of the keys (times the
+# query gains) only where some call's cross-q projection stores per head: widths that every tile divides; fewer tokens than
+# the large tiles take; not 1152 or 1408 in frames of 4096 and more (256-column tiles), nor 1088 in frames of 1088 (128)
+@pytest.mark.parametrize("dim,tok,frames,copies", [(1536, (30, 52), 4, 3), (1152, (8, 8), 4, 3), (1152, (8, 8), 64, 3), (1152, (64, 64), 1, 2),
+                                                   (1408, (64, 80), 3, 2), (1088, (32, 34), 2, 3), (1088, (48, 64), 2, 2)])
+def test_workspace_holds_second_text_keys_only_where_a_call_uses_them(B, dim, tok, frames, copies):
+    from paper_2505_21070_amd import synth
+    def nbytes(text_len):
+        cfg = synth.stage_config("tiny_bf16", n_layers=3, dim=dim, n_heads=dim // 64, text_len=text_len, text_dim=dim, tok_h=tok[0], tok_w=tok[1],
+                                 block_frames=frames, cache_frames=1)
+        return B.workspace_bytes(B.make_config(cfg))
+    assert nbytes(512) - nbytes(256) == 256 * dim * 2 * (3 + 3 * copies)          # text, two steps of its MLP, and the layers'
+
+
 @pytest.mark.parametrize("block_num,num_b,num_c", [(8, 4, 4), (5, 4, 2), (6, 8, 8), (7, 3, 6), (4, 5, 0), (4, 1, 2), (1, 4, 4)])
 @pytest.mark.parametrize("seed", [0, 3])
 def test_noise_assignment_matches_oracle(B, block_num, num_b, num_c, seed):
