@@ -169,10 +169,14 @@ def kv_bytes_per_layer(config):
 
 def _stream_handle(stream):
     """The hipStream_t a call runs on: the current device's current stream unless one is named.  Read as a number: building the
-    torch.cuda.Stream object takes 2.9 us, as long as a launch (an embedding of 544 tokens 9.3 -> 6.4 us a call)."""
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    torch.cuda.Stream object takes 2.9 us, as long as a launch (an embedding of 544 tokens 9.3 -> 6.4 us a call).  The two functions are
+    torch's own, not its interface: a build of it without them gets the object."""
+    if stream is None:
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
 class Stage:

@@ -87,6 +87,17 @@ def test_config_validation_without_gpu(B):
     B._lib.dp_stage_free(None)
 
 
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_private_functions(B, monkeypatch, missing):
+    import torch
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 40 + device)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("S", (), {"cuda_stream": 50}))
+    assert B._stream_handle(None) == 40 and B._stream_handle(torch.cuda.current_stream()) == 50
+    monkeypatch.delattr(torch._C, missing)
+    assert B._stream_handle(None) == 50
+
+
 # dim, tokens of a frame, frames: copies of the text keys and values a layer keeps.  With a second copy of the keys (times the
 # query gains) only where some call's cross-q projection stores per head: widths that every tile divides; fewer tokens than
 # the large tiles take; not 1152 or 1408 in frames of 4096 and more (256-column tiles), nor 1088 in frames of 1088 (128)
