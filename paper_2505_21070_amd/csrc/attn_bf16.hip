@@ -725,26 +725,55 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ pa
 // partial results of at most 256 blocks of at most 256 queries
 size_t attn_bf16_scratch_bytes(int d) { return (size_t)256 * (512 + 256 * (size_t)d) * sizeof(float); }
 
+static constexpr int attn_slots(int qb, int kg) { return 256 * (256 / (qb * kg)); }   // blocks that the chip holds at once
+// What a call takes: queries per block (32: k_attn_few), key groups, and key ranges that the work ids of the last round are cut into
+struct AttnRoute { int qb, kg, parts; };
+static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratch) {
+  // 256 queries per block share every K / V^T tile (half the LDS fill traffic per query) whenever that
+  // still gives the grid half a round of blocks and the key range a few tiles; otherwise 128 queries per
+  // block with the keys split over two groups, which halves the length of a block.
+  const bool wide = L >= 256 && ((S + 255) / 256) * h >= 128;
+  // Few enough blocks of 32 queries for one round (one to a CU at head_dim 128, two at 64) and at most eight tiles to a
+  // wavefront: k_attn_few.  Beyond either line the other shapes are as fast (us): 1008 x 1680 x 16 heads of 64 (512 blocks) 17.9
+  // against 20.3, 1000 x 1900 x 8 heads of 128 (256) 19.9 and 24.2, 700 x 1000 x 12 of 128 (264) 24.0 and 20.6, 100 x 3000 x 8 of 128
+  // (32) 22.7 and 19.8.
+  const bool few = L <= 1920 && (S + 31) / 32 * h <= (d == 128 ? 256 : 512);
+  // Few keys: a block's start and end weigh as much as its tiles, so blocks of four wavefronts, two to a CU, fill each other's
+  // gaps.  Short key ranges, or up to 16 tiles where two rounds of such blocks are full (us): 6240 x 512 x 12 of 128 35.0 -> 31.5,
+  // 1560 x 512 x 12 of 128 15.2 -> 13.4, 3000 x 1000 x 24 of 128 54.4 -> 50.6, 8000 x 200 x 16 of 64 17.7 -> 16.5; not at 3000 x 512 x
+  // 16 of 64 (12.3 with 256 queries, 12.9) or 3000 x 1000 x 10 of 128 (22.9 with two groups, 34.2).
+  const bool pairs = (L <= 512 && (d == 128 || !wide)) || (L <= 1024 && (S + 127) / 128 * h > 512);
+  AttnRoute r{32, 8, 1};
+  if (few) return r;
+  r.qb = !pairs && wide ? 256 : 128;
+  r.kg = pairs || wide ? 1 : 2;
+  // One block (of 4 wavefronts: two) fits per compute unit, so the grid runs in rounds of `slots` blocks.  Whole rounds keep one
+  // block per work id; the work ids left over for the last round are cut into key ranges (at least 8
+  // key tiles each) so that the round is both shorter and wider, and a merge kernel joins the ranges.
+  const int slots = attn_slots(r.qb, r.kg), W = (int)((S + r.qb - 1) / r.qb) * h, n_tail = W % slots, NKT = (int)((L + 63) / 64);
+  if (n_tail > 0 && scratch) {
+    r.parts = slots / n_tail;
+    if (r.parts > 8) r.parts = 8;
+    if (r.parts > NKT / 8) r.parts = NKT / 8;
+    if (r.parts < 1) r.parts = 1;
+  }
+  return r;
+}
+// for the tests, which state the kernel that each of their shapes is meant to reach
+extern "C" void dp_attn_bf16_route(int64_t S, int64_t L, int32_t h, int32_t d, int32_t* queries_groups_ranges) {
+  const AttnRoute r = attn_bf16_route(S, L, h, d, true);
+  const int32_t v[3] = {r.qb, r.kg, r.parts};
+  for (int i = 0; i < 3; ++i) queries_groups_ranges[i] = v[i];
+}
+
 template <int HD, int QG, int KG>
 static void launch_attn_cfg(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, int64_t k_head_stride,
                             int64_t k_row0, const bf16_t* vt, int64_t vt_row_stride, int64_t S, int64_t L,
-                            int h, bf16_t* out, int64_t ldo, float* scratch, const AttnQNorm& qn, hipStream_t st) {
+                            int h, bf16_t* out, int64_t ldo, float* scratch, int parts, const AttnQNorm& qn, hipStream_t st) {
   constexpr int QB = QG * 32;
   constexpr int lds = KG * 2 * (64 * (HD / 8) + HD * 8) * 16;
   const int qblocks = (int)((S + QB - 1) / QB);
-  // One block (of 4 wavefronts: two) fits per compute unit, so the grid runs in rounds of SLOTS blocks.  Whole rounds keep one
-  // block per work id; the work ids left over for the last round are cut into key ranges (at least 8
-  // key tiles each) so that the round is both shorter and wider, and a merge kernel joins the ranges.
-  const int W = qblocks * h, NKT = (int)((L + 63) / 64);
-  constexpr int SLOTS = 256 * (8 / (QG * KG));
-  const int n_full = W / SLOTS * SLOTS, n_tail = W - n_full;
-  int parts = 1;
-  if (n_tail > 0 && scratch) {
-    parts = SLOTS / n_tail;
-    if (parts > 8) parts = 8;
-    if (parts > NKT / 8) parts = NKT / 8;
-    if (parts < 1) parts = 1;
-  }
+  const int W = qblocks * h, n_tail = W % attn_slots(QB, KG), n_full = W - n_tail;
   dim3 grid((unsigned)(n_full + (n_tail * parts + 7) / 8 * 8));
   static std::atomic<uint64_t> done;
   allow_dynamic_lds((const void*)k_attn_bf16<HD, QG, KG>, lds, done);
@@ -771,28 +800,15 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
                       int h, int d, bf16_t* out, int64_t ldo, float* scratch, const AttnQNorm* qnorm, hipStream_t st) {
   if (S <= 0 || L <= 0) return;
   const AttnQNorm qn = qnorm ? *qnorm : AttnQNorm{nullptr, 0, 0, 0.f, 0.f, 0.f};
-  // 256 queries per block share every K / V^T tile (half the LDS fill traffic per query) whenever that
-  // still gives the grid half a round of blocks and the key range a few tiles; otherwise 128 queries per
-  // block with the keys split over two groups, which halves the length of a block.
-  const bool wide = L >= 256 && ((S + 255) / 256) * h >= 128;
-  // Few enough blocks of 32 queries for one round (one to a CU at head_dim 128, two at 64) and at most eight tiles to a
-  // wavefront: k_attn_few.  Beyond either line the other shapes are as fast (us): 1008 x 1680 x 16 heads of 64 (512 blocks) 17.9
-  // against 20.3, 1000 x 1900 x 8 heads of 128 (256) 19.9 and 24.2, 700 x 1000 x 12 of 128 (264) 24.0 and 20.6, 100 x 3000 x 8 of 128
-  // (32) 22.7 and 19.8.
-  const bool few = L <= 1920 && (S + 31) / 32 * h <= (d == 128 ? 256 : 512);
-  // Few keys: a block's start and end weigh as much as its tiles, so blocks of four wavefronts, two to a CU, fill each other's
-  // gaps.  Short key ranges, or up to 16 tiles where two rounds of such blocks are full (us): 6240 x 512 x 12 of 128 35.0 -> 31.5,
-  // 1560 x 512 x 12 of 128 15.2 -> 13.4, 3000 x 1000 x 24 of 128 54.4 -> 50.6, 8000 x 200 x 16 of 64 17.7 -> 16.5; not at 3000 x 512 x
-  // 16 of 64 (12.3 with 256 queries, 12.9) or 3000 x 1000 x 10 of 128 (22.9 with two groups, 34.2).
-  const bool pairs = (L <= 512 && (d == 128 || !wide)) || (L <= 1024 && (S + 127) / 128 * h > 512);
-#define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, scratch, qn, st
-  if (few) {
-    if (d == 128) launch_attn_few<128>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, qn, st);
-    else launch_attn_few<64>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo, qn, st);
-  } else if (d == 128) {
-    if (pairs) launch_attn_cfg<128, 4, 1>(ATTN_ARGS); else if (wide) launch_attn_cfg<128, 8, 1>(ATTN_ARGS); else launch_attn_cfg<128, 4, 2>(ATTN_ARGS);
-  } else {
-    if (pairs) launch_attn_cfg<64, 4, 1>(ATTN_ARGS); else if (wide) launch_attn_cfg<64, 8, 1>(ATTN_ARGS); else launch_attn_cfg<64, 4, 2>(ATTN_ARGS);
-  }
+  const AttnRoute r = attn_bf16_route(S, L, h, d, scratch != nullptr);
+#define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo
+#define ATTN_CASE(HD) do { \
+    if (r.qb == 32) launch_attn_few<HD>(ATTN_ARGS, qn, st); \
+    else if (r.qb == 256) launch_attn_cfg<HD, 8, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.kg == 1) launch_attn_cfg<HD, 4, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else launch_attn_cfg<HD, 4, 2>(ATTN_ARGS, scratch, r.parts, qn, st); \
+  } while (0)
+  if (d == 128) ATTN_CASE(128); else ATTN_CASE(64);
+#undef ATTN_CASE
 #undef ATTN_ARGS
 }

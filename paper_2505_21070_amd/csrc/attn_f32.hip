@@ -362,24 +362,13 @@ __global__ __launch_bounds__(256) void k_attn_f32_merge(const float* __restrict_
   *(f32x4*)(out + qi * ldo + (int64_t)head * HD + c4 * 4) = o * (1.f / l);
 }
 
-void launch_attn_f32(const float* q, int64_t q_head_stride, const float* k, int64_t k_head_stride,
-                     int64_t k_row0, const float* vt, int64_t vt_row_stride, int64_t S, int64_t L,
-                     int h, int d, float* out, int64_t ldo, float* scratch, size_t scratch_floats, hipStream_t st) {
-  if (S <= 0 || L <= 0) return;
-  const int lead = (int)(k_row0 & 3);
+// Key ranges of k_attn_f32_tiles (more than one: joined by the merge kernel), or 0: k_attn_f32.
+// A CU holds two blocks, the chip 512.  Four query tiles a block and whole key ranges if that fills the chip;
+// otherwise either four key groups per block (few keys, or so few queries that even a cut key range would not fill
+// it) or key ranges cut over blocks, as many as make the rounds of 512 blocks shortest.
+static int attn_f32_ranges(int64_t S, int64_t L, int lead, int h, int d, size_t scratch_floats) {
   const int64_t nkt = (L + lead + 31) / 32, b4 = (S + 127) / 128 * h;
-  const float scale = 1.0f / sqrtf((float)d);
-  // A CU holds two blocks, the chip 512.  Four query tiles a block and whole key ranges if that fills the chip;
-  // otherwise either four key groups per block (few keys, or so few queries that even a cut key range would not fill
-  // it) or key ranges cut over blocks, as many as make the rounds of 512 blocks shortest.
-  if (b4 < 512 && (nkt < 32 || b4 < 64)) {
-    const int qblocks = (int)((S + 31) / 32), blocks = qblocks * h;
-#define GROUPS_CASE(HD) k_attn_f32<HD><<<(unsigned)((blocks + 7) / 8 * 8), 256, 0, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, \
-    vt_row_stride, S, L, lead, out, ldo, scale, qblocks, blocks)
-    if (d == 64) GROUPS_CASE(64); else GROUPS_CASE(128);
-#undef GROUPS_CASE
-    return;
-  }
+  if (b4 < 512 && (nkt < 32 || b4 < 64)) return 0;
   int parts = 1;
   if (b4 < 1024) {
     double best = 1e30;
@@ -388,6 +377,28 @@ void launch_attn_f32(const float* q, int64_t q_head_stride, const float* k, int6
       const double cost = (double)((b4 * p + 511) / 512) / p + 0.01 * p;
       if (cost < best) { best = cost; parts = p; }
     }
+  }
+  return parts;
+}
+// for the tests, which state the kernel that each of their shapes is meant to reach
+extern "C" int32_t dp_attn_f32_ranges(int64_t S, int64_t L, int64_t k_row0, int32_t h, int32_t d, int64_t scratch_floats) {
+  return attn_f32_ranges(S, L, (int)(k_row0 & 3), h, d, (size_t)scratch_floats);
+}
+
+void launch_attn_f32(const float* q, int64_t q_head_stride, const float* k, int64_t k_head_stride,
+                     int64_t k_row0, const float* vt, int64_t vt_row_stride, int64_t S, int64_t L,
+                     int h, int d, float* out, int64_t ldo, float* scratch, size_t scratch_floats, hipStream_t st) {
+  if (S <= 0 || L <= 0) return;
+  const int lead = (int)(k_row0 & 3);
+  const float scale = 1.0f / sqrtf((float)d);
+  const int parts = attn_f32_ranges(S, L, lead, h, d, scratch_floats);
+  if (parts == 0) {
+    const int qblocks = (int)((S + 31) / 32), blocks = qblocks * h;
+#define GROUPS_CASE(HD) k_attn_f32<HD><<<(unsigned)((blocks + 7) / 8 * 8), 256, 0, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, \
+    vt_row_stride, S, L, lead, out, ldo, scale, qblocks, blocks)
+    if (d == 64) GROUPS_CASE(64); else GROUPS_CASE(128);
+#undef GROUPS_CASE
+    return;
   }
   const int qblocks = (int)((S + 127) / 128), blocks = qblocks * h * parts;
 #define TILES_CASE(HD) do { \

@@ -79,7 +79,7 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
     // accumulators; its channel gains and 3D rotation are applied on the way out of the staging tile, where
     // a lane holds 8 consecutive channels of one row, so that the table and gain reads are contiguous
     // across lanes.  A transposed section is C^T already.
-    constexpr int UPR = BN / 4, CPR = BN / 8, RPI = 64 / CPR;
+    constexpr int UPR = BN / 4, CPR = BN / 8;
     static_assert(BM * BN * 2 <= LB, "EPI_HEADS stages the whole tile at once");
     // [row][wavefront column]: sums of squares; behind the staged tile where there is room
     // Plain sections of 128-column tiles are staged in fp32, so that only the result is rounded, as by the separate kernels
@@ -1457,12 +1457,18 @@ GemmRoute gemm_bf16_route(int64_t M, int64_t N, int64_t K, int epi, size_t scrat
   const int family = tile_family(M, N, epi);
   return family == TILE_BIG ? big_tile(M, N, epi) : small_tile(family, M, N);
 }
-// for the parity tests, which state the kernel that each of their products is meant to reach
-extern "C" void dp_gemm_bf16_route(int64_t M, int64_t N, int64_t K, int32_t epi, int32_t /*any_transposed*/, int64_t scratch_floats,
-                                   int32_t* bm_bn_stages_parts) {
+// for the parity tests, which state the kernel that each of their products is meant to reach (the fifth argument has no
+// meaning any more: a tile of any shape stores transposed sections)
+extern "C" void dp_gemm_bf16_route(int64_t M, int64_t N, int64_t K, int32_t epi, int32_t, int64_t scratch_floats, int32_t* bm_bn_stages_parts) {
   const GemmRoute r = gemm_bf16_route(M, N, K, epi, (size_t)scratch_floats);
   const int32_t v[4] = {r.bm, r.bn, r.stages, r.parts};
   for (int i = 0; i < 4; ++i) bm_bn_stages_parts[i] = v[i];
+}
+// the same: whether a projection of M rows stores its N / dim sections per head, the third of them transposed
+extern "C" int32_t dp_gemm_bf16_heads(int64_t M, int64_t N, int32_t dim, int32_t head_dim) {
+  HeadsArgs h{};
+  h.dim = dim; h.head_dim = head_dim; h.sec[2].transposed = 1;
+  return gemm_bf16_heads_ok(M, N, h);
 }
 
 bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ldw, int64_t M, int64_t N,

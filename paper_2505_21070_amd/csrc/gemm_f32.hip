@@ -5,11 +5,10 @@
 // its packed forms, and lost more of it to LDS reads: 45 TFLOP/s).  An MFMA sums two k; a lane group lg of a wavefront
 // takes k = 8j + 4lg + t for the t-th of four MFMAs, so that the A operand of four is one 16-byte LDS read of a row and
 // the W operand one 4-byte read each.  k-tiles (32 deep, 64 where the wavefronts share out K) go through registers into one
-// of two LDS buffers, the loads of the next two in flight while one is multiplied (k_gemm_f32; widths in steps of 32 take
-// k_gemm_f32_ring).  Rows of As are the k-tile + 4 floats
+// of two LDS buffers, the loads of the next two in flight while one is multiplied (k_gemm_f32).  Rows of As are the k-tile + 4 floats
 // and rows of Ws BN + 8 apart: 16 rows x 16 bytes and the two lane groups' rows (4 apart) then fall on different banks.
-// 1560 x 1536 x 1536: 154 -> 88 us; 1560 x 8960 x 1536: 631 -> 391; 1560 x 1536 x 8960: 868 -> 462 (600 blocks: three on
-// some CUs, two on the others); q | k | v of 1560 x 1536: 492 in three launches -> 223 in one.
+// K in steps of 32 with rows in 16-byte steps, the usual case, goes through k_gemm_f32_ring (figures there) unless so few tiles are
+// to be had that the 32 x 32 ones of k_gemm_f32 are the faster ones (f32_rows).
 #include "kernels.h"
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -392,8 +391,16 @@ static int f32_rows(int64_t M, int64_t N, int64_t K, int n) {
   }
   return rows;
 }
-// for the tests, which state the kernel that each of their products is meant to reach
-extern "C" int32_t dp_gemm_f32_rows(int64_t M, int64_t N, int64_t K, int32_t n) { return K % 32 ? -1 : f32_rows(M, N, K, n); }
+// Tiles of k_gemm_f32 for what the ring does not take: K in other steps than 32, rows that do not start in 16-byte steps.  128 x 128,
+// two to a CU and half the operand bytes per flop, where they make at least two full rounds; 64 x 64, up to four to a CU; fewer
+// than one of those per CU: 32 x 32 with K dealt over the wavefronts.  The lines were measured at aligned sizes, before those
+// went to the ring (us): 1560 x 8960 x 1536 (910 of the large tiles) 64 x 64 391, 128 x 128 413; 1560 x 1536 x 8960 (156) 462 and 639;
+// 6240 x 8960 x 1536 (3430) 128 x 128 1432, 8 % less than 64 x 64; a stage of 128 tokens x 128 channels 32 x 32 148, 64 x 64 200, of
+// 300 x 768 210 and 301, of 750 x 768 340 and 379.
+static int f32_tile(int64_t M, int64_t N, int n) {
+  if ((M + 127) / 128 * ((N + 127) / 128) * n >= 1024) return 128;
+  return (M + 63) / 64 * ((N + 63) / 64) * n >= 256 ? 64 : 32;
+}
 
 void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw, int64_t M, int64_t N,
                      int64_t K, int epi, const EpiArgs& e, hipStream_t st) {
@@ -414,14 +421,18 @@ void launch_gemm_f32(const float* A, int64_t lda, const GemmF32W& w, int64_t ldw
     }
     return;
   }
-  // Widths in other steps: 64 x 64 tiles, up to four blocks to a CU, unless 128 x 128 ones (two to a CU, half the operand bytes per flop) make at
-  // least two full rounds.  64 x 64 against 128 x 128: 1560 x 8960 x 1536 (910 of the large ones) 391 against 413 us, 1560 x 1536
-  // x 8960 (156) 462 against 639; 6240 x 8960 x 1536 (3430) 1432 us = 120 TFLOP/s on 128 x 128 where 64 x 64 stay at 110.  Fewer than one 64 x 64 tile per CU:
-  // 32 x 32 tiles with K dealt over the wavefronts (whole passes: 128 tokens x 128 channels 200 -> 148 us, 300 x 768 301 -> 210,
-  // 750 x 768 379 -> 340)
-  const int64_t t128 = ((M + 127) / 128) * ((N + 127) / 128) * w.n;
-  if (t128 >= 1024)
-    launch_cfg<128, 128, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
-  else if (((M + 63) / 64) * ((N + 63) / 64) * w.n >= 256) launch_cfg<64, 64, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
-  else launch_cfg<32, 32, 1, 1, 4>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+  switch (f32_tile(M, N, w.n)) {
+    case 128: launch_cfg<128, 128, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st); break;
+    case 64: launch_cfg<64, 64, 2, 2, 1>(A, lda, w, ldw, M, N, K, epi, e, vec, st); break;
+    default: launch_cfg<32, 32, 1, 1, 4>(A, lda, w, ldw, M, N, K, epi, e, vec, st);
+  }
+}
+
+// For the tests, which state the kernel that each of their products is meant to reach: rows of the ring's tiles (-1: not the ring's
+// K, 0: its 32 x 32 tiles); the other products' tiles; and one product by itself.
+extern "C" int32_t dp_gemm_f32_rows(int64_t M, int64_t N, int64_t K, int32_t n) { return K % 32 ? -1 : f32_rows(M, N, K, n); }
+extern "C" int32_t dp_gemm_f32_tile(int64_t M, int64_t N, int32_t n) { return f32_tile(M, N, n); }
+extern "C" void dp_gemm_f32_run(const float* A, int64_t lda, const float* W, int64_t ldw, const float* bias, int64_t M, int64_t N, int64_t K,
+                                int32_t epi, float* out, int64_t ldo, float* resid, int64_t ldr, const float* gate, void* hip_stream) {
+  launch_gemm_f32(A, lda, GemmF32W{{W}, {bias}, 1}, ldw, M, N, K, epi, EpiArgs{out, ldo, nullptr, resid, ldr, gate}, (hipStream_t)hip_stream);
 }

@@ -37,12 +37,12 @@ CONFIGS = {
     # head_dim 64, with its work ids cut into two key ranges
     "wide64_bf16": dict(n_layers=1, dim=1024, n_heads=16, head_dim=64, ffn_dim=1024, text_len=32, text_dim=1024,
                         tok_h=16, tok_w=16, block_frames=8, cache_frames=2, dtype="bf16"),
-    # head_dim 128 with enough rows and columns for the GEMM's 256 x 256 tiles (72 of them in the fused
-    # q|k|v projection, whose epilogue writes per head) and the attention kernel's 256-query blocks
+    # head_dim 128 with enough rows and columns for the GEMM's 128 x 256 tiles in the fused q|k|v projection, whose
+    # epilogue writes per head, and the attention kernel's 128-query blocks with two key groups, cut into key ranges
     "wide128_bf16": dict(n_layers=1, dim=768, n_heads=6, head_dim=128, ffn_dim=1024, text_len=48, text_dim=768,
                          tok_h=16, tok_w=16, block_frames=8, cache_frames=2, dtype="bf16"),
-    # dim % 256 != 0, so q|k|v and the cross-attention query take the plain store epilogue and the separate
-    # norm / rotation / transpose kernels, at row counts that make the GEMM choose its large tile shapes:
+    # widths that the tile of a call this large does not divide, so q|k|v and the cross-attention query take the plain store
+    # epilogue and the separate norm / rotation / transpose kernels, at row counts that make the GEMM choose its large tiles:
     # 4032 rows of 1152 -> 192 x 256 tiles, 4096 rows -> 256 x 256 (more than 256 tiles of 128 x 128 in every
     # product, K too short to be cut); 4160 rows of 1408 -> 160 x 256, with 320 x 256 for q|k|v and the FFN's first
     # product (tests/test_gemm_routes.py holds them to it)
@@ -52,8 +52,8 @@ CONFIGS = {
                          tok_h=16, tok_w=32, block_frames=8, cache_frames=2, dtype="bf16"),
     "tile320_bf16": dict(n_layers=1, dim=1408, n_heads=11, head_dim=128, ffn_dim=3904, text_len=40, text_dim=1408,
                          tok_h=20, tok_w=26, block_frames=8, cache_frames=2, dtype="bf16"),
-    # few tokens, wide models: the widest register variants of the row kernels (LayerNorm, deferred key scale,
-    # norm + rotation); 6144 takes the per-head GEMM epilogue, 2176 = 17 x 128 the separate kernels
+    # few tokens, wide models: the wide register variants of the row kernels (LayerNorm, deferred key scale, the text keys'
+    # norm) behind the per-head GEMM epilogue
     "dim6144_bf16": dict(n_layers=1, dim=6144, n_heads=48, head_dim=128, ffn_dim=512, text_len=24, text_dim=6144,
                          tok_h=8, tok_w=8, block_frames=2, cache_frames=1, dtype="bf16"),
     "dim2176_bf16": dict(n_layers=1, dim=2176, n_heads=17, head_dim=128, ffn_dim=640, text_len=24, text_dim=2176,

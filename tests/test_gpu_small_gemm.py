@@ -1,9 +1,10 @@
-"""The bf16 GEMM's small tiles (a ring of loads through LDS) through the stage, against the CPU oracle: fewer k-tiles than
-ring stages, exactly as many, one more; rows and columns that fill no tile; the plain store, GELU, residual and per-head
-epilogues on each of the three rings (64 x 64 in four and in three stages, 128 x 128 in four); the residual product with K
-cut into ranges at each tile that does it.  tests/test_gemm_routes.py asserts that these shapes still reach those kernels."""
+"""The bf16 GEMM's tiles through the stage, against the CPU oracle: fewer k-tiles than a ring has stages, exactly as many, one
+more; rows and columns that fill no tile; the GELU, residual and per-head epilogues on each tile that has them, the plain
+store of the projections (separate norm and rotation kernels behind it) and of the text products; the residual product with K
+cut into ranges.  tests/test_gemm_routes.py asserts which kernels these shapes reach."""
 import pytest
 
+from harness import check, to_np
 from paper_2505_21070_amd import synth
 from test_gpu_stage import run_pair
 
@@ -25,6 +26,18 @@ SHAPES = [
     (256, 2, 128, 2048, 2, 4, 1),          # 8 rows, K cut into 8 ranges of 64 x 64 tiles
     (640, 5, 128, 6144, 24, 67, 1),        # 1608 rows, 7 ranges of 160 x 256 tiles
     (640, 5, 128, 8192, 24, 67, 1),        # 8 ranges of 256 x 256 tiles
+    # q | k | v as plain rows, normalised and rotated by separate kernels
+    (448, 7, 64, 448, 40, 60, 1),          # 2400 rows of 128 x 128 tiles, the narrowest rows
+    (1600, 25, 64, 1600, 8, 44, 2),        # 704 rows of 128 x 128 tiles, cross-q per head
+    (1664, 13, 128, 1664, 24, 35, 1),      # 840 rows of large tiles, cross-q per head; the only call size of its stage
+    (3136, 49, 64, 512, 8, 21, 2),         # 336 rows of 128 x 128 tiles, the widest rows
+    (1088, 17, 64, 1088, 47, 64, 1),       # 3008 rows, cross-q too on 128 x 128 tiles; a stage none of whose calls store per head
+]
+# the same with many text tokens, whose keys and values are plain stores
+TEXT_SHAPES = [
+    (1152, 9, 128, 1152, 8, 47, 2, 1000),  # 288 tiles of 64 x 64: two to a CU
+    (1152, 9, 128, 1152, 8, 47, 2, 1880),  # 540: three to a CU
+    (1408, 11, 128, 1408, 8, 47, 2, 1880), # 165 tiles of 128 x 128
 ]
 
 
@@ -33,3 +46,12 @@ def test_small_tiles(monkeypatch, dim, heads, hd, ffn, tok_h, tok_w, frames):
     monkeypatch.setitem(synth.CONFIGS, "ring", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=dim, n_heads=heads, head_dim=hd, ffn_dim=ffn,
                                                     text_dim=dim, tok_h=tok_h, tok_w=tok_w, block_frames=frames, cache_frames=1))
     run_pair("ring", 3, True, "later")
+
+
+@pytest.mark.parametrize("dim,heads,hd,ffn,tok_h,tok_w,frames,text_len", TEXT_SHAPES)
+def test_text_products(monkeypatch, dim, heads, hd, ffn, tok_h, tok_w, frames, text_len):
+    monkeypatch.setitem(synth.CONFIGS, "text", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=dim, n_heads=heads, head_dim=hd, ffn_dim=ffn,
+                                                    text_len=text_len, text_dim=dim, tok_h=tok_h, tok_w=tok_w, block_frames=frames,
+                                                    cache_frames=1))
+    g, o, _, _ = run_pair("text", 3, True, "later")
+    check("text/v", to_np(g.peek("text_v", 0)), o.text_v[0], "bf16")

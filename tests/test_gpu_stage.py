@@ -91,7 +91,7 @@ def test_small_bf16_stage(name, strong_gate):
 def test_every_gemm_tile_shape_and_epilogue(name):
     """Row counts and widths at which the GEMM picks its 192-, 256-, 160- and 320-row tiles (192, 256: the plain store,
     GELU and residual epilogues; 160: store and residual; 320: store and GELU; tests/test_gemm_routes.py asserts
-    it), with dim % 256 != 0 so that q/k normalisation, rotation and the V transposition run as separate kernels."""
+    it), of widths they do not divide, so that q/k normalisation, rotation and the V transposition run as separate kernels."""
     rep = {}
     run_pair(name, 0, True, "later", rep)
     print({k: f"{v['rel_l2']:.2e}" for k, v in rep.items() if "cache" not in k})
@@ -99,8 +99,8 @@ def test_every_gemm_tile_shape_and_epilogue(name):
 
 @pytest.mark.parametrize("name", ["dim6144_bf16", "dim2176_bf16", "dim2752_bf16"])
 def test_wide_and_odd_model_widths(name):
-    """Model widths that select the widest per-lane register variants of the row kernels, one with and one
-    without the per-head GEMM epilogue, and the modulation product's two-column form at its narrowest.  The
+    """Model widths that select wide per-lane register variants of the row kernels behind the per-head GEMM epilogue
+    (tests/test_gpu_small_gemm.py has widths behind plain stores), and the modulation product's two-column form at its narrowest.  The
     modulation rows are 32-bit sums of dim terms: at 6144 four chains per wavefront are 7.1e-8 from 64 bits (relative,
     2-norm), one chain is 1.07e-7, and the bound lies between."""
     rep = {}
@@ -323,7 +323,7 @@ def test_error_paths_leave_gpu_alone():
     assert rc == B.DP_EINVAL and not h.value      # null weights
 
 
-@pytest.mark.parametrize("name,over", [("small_bf16", {}),                      # 128-query blocks, one key tile
+@pytest.mark.parametrize("name,over", [("small_bf16", {}),                      # few queries: an online softmax from the start
                                        ("wide64_bf16", {"text_len": 320}),      # 256-query blocks, 5 key tiles
                                        ("wide64_bf16", {"text_len": 1100})])    # ... cut into two key ranges + merge
 def test_peaked_attention_takes_the_safe_pass(name, over):

@@ -3,7 +3,7 @@ and 128 x 256 tiles) through the stage, against the CPU oracle, at row counts th
 import pytest
 
 from paper_2505_21070_amd import synth
-from test_gemm_routes import products
+from test_gemm_routes import config, products
 from test_gpu_stage import run_pair
 
 # (dim, heads, head_dim, ffn, tok_h, tok_w, frames): {product: (epilogue, rows, columns, stages of the tile)}
@@ -12,14 +12,14 @@ SHAPES = {
     (768, 6, 128, 6144, 8, 47, 5): {"qkv": ("heads", 128, 256, 3), "ffn2": ("cut", 128, 256, 3)},         # 1880 rows
     (1024, 8, 128, 2048, 8, 75, 5): {"qkv": ("heads", 160, 256, 3)},                                       # 3000 rows
     (1536, 12, 128, 1536, 8, 113, 3): {"o": ("resid", 128, 256, 3)},                                       # 2712 rows
-    (640, 10, 64, 1280, 8, 53, 4): {"qkv": ("store", 128, 128, 4)},                                        # 1696 rows; the stage has it stored per head
+    (640, 10, 64, 1280, 8, 53, 4): {"qkv": ("heads", 128, 128, 4)},                                        # 1696 rows
     (768, 6, 128, 6144, 8, 59, 1): {"ffn2": ("cut", 128, 128, 4)},                                         # 472 rows
 }
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=str)
 def test_shapes_take_these_tiles(shape):
-    p = products(dict(dim=shape[0], ffn_dim=shape[3], tok_h=shape[4], tok_w=shape[5], block_frames=shape[6]))
+    p = products(config(*shape))
     assert {k: p[k] for k in SHAPES[shape]} == SHAPES[shape]
 
 

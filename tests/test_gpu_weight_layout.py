@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("small_bf16", dict(ffn_dim=768)),      # ragged token counts, head_dim 128, text MLP (text_dim != dim)
-    ("wide128_bf16", {}),                   # 256 x 256 GEMM tiles, per-head q|k|v epilogue, 256-query attention blocks
+    ("wide128_bf16", {}),                   # 128 x 256 GEMM tiles with the per-head q|k|v epilogue
     ("wide64_bf16", {}),                    # head_dim 64
 ]
 
