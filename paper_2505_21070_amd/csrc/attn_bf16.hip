@@ -18,7 +18,7 @@
 // block whose row sums end up beyond 2^100 (or non-finite) is recomputed by the safe pass, the classical
 // online softmax that raises m whenever a tile exceeds it and rescales O^T.
 //
-// Work split: a block of QG * KG wavefronts owns QG * 32 queries of one head.  Three shapes are built (launch_attn_bf16 has the
+// Work split: a block of QG * KG wavefronts owns QG * 32 queries of one head.  Three shapes are built (attn_bf16_route has the
 // lines between them, and k_attn_few takes what is small).
 // QG = 4, KG = 2 (few queries or very few keys): wavefront w handles query tile w & 3 against key group
 // w >> 2 (first / second half of the key tiles); the two groups stream their own K / V^T tiles and are

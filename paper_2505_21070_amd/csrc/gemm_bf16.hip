@@ -1059,7 +1059,9 @@ static bool launch_thin_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int6
 // cycles at 128 bytes a cycle) plus 53 KB of tile writes.  Five 16-row tiles by four use 18 reads per 40 MFMAs where one column
 // of five 32-row tiles took 24 per 20.  Measured against that layout (one block column per wavefront, pinned order, three
 // stages; plain store, us): 6240 x 1536 x 8960 173 -> 155, 6240 x 1536 x 1536 33.9 -> 31.2, 1560 x 4608 x 1536 as 128 x 256
-// tiles 30.2 -> 25.0; against a ring of four stages without turns 1008 x 4096 x 1024 (128 x 128) 15.5 -> 11.8.
+// tiles 30.2 -> 25.0; against a ring of four stages without turns 1008 x 4096 x 1024 (128 x 128) 15.5 -> 11.8.  Counted at 6240 x 1536 x
+// 8960 with the residual epilogue: matrix pipes busy 50 % of the cycles at 2.12 GHz, 57 % of those in which a CU has a block, where
+// that layout was busy 49 % at 1.91 GHz: what the saved LDS reads gave is clock.
 template <int TM, int TN, int KB, int ST, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bt,
                                                    int64_t ldb, int64_t M, int64_t N, int64_t K, int tiles_n, int tiles,
@@ -1387,9 +1389,10 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // launches and a block's ends, partials at 6.5 TB/s; uncut 0.185 per k-tile and 3.3 (32 x 64), 0.24 per k-tile and 64 x 64 block
 // on the CU and 5, 9 (128 x 128) or 14 for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 55 (128 x 256,
 // 3) / 77, 1008 x 2048 x 8192 45 (128 x 256, 4) / 64, 2560 x 2048 x 8192 88 (160 x 256, 2) / 104, 480 x 3584 x 19456 83 (160 x 256, 6)
-// / 158; left uncut 1288 x 5120 x 13824 180 (cut 204), 3000 x 1024 x 4096 41 (42).  Outputs narrower than 768 columns fill few
-// tiles of any kind: they take the 64-, 160- and 256-row tiles by the figures of an earlier measurement (a k-tile 1.25 at 160
-// rows, 8 for ends and 3 for the second launch, 4 TB/s), which the parity tests of those three cut tiles stand on.
+// / 158; left uncut 1288 x 5120 x 13824 180 (cut 204), 3000 x 1024 x 4096 41 (42).  Outputs narrower than 768 columns
+// are left on the 64-, 160- and 256-row tiles and on the figures of an earlier measurement (a k-tile 1.25 at 160
+// rows, 8 for ends and 3 for the second launch, 4 TB/s).  That line is no property of the tiles: the 128-row ones have not been
+// measured below it, and the parity tests of the cut 160- and 256-row tiles are shapes of that side.
 static GemmRoute big_tile(int64_t M, int64_t N, int epi);
 static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats) {
   GemmRoute r{0, 0, 0, 1};                             // parts == 1: not cut
@@ -1432,9 +1435,10 @@ static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats
 // rows in 2 488; 7800 x 4608 x 1536 160 rows in 4 117, 256 rows in 3 122; 14400 x 15360 x 5120 256 rows in 14 1850, 128 rows in
 // 27 1931; 14400 x 13824 x 5120 320 rows in 10 1601, 160 rows in 19 1634.
 // The 192- and 320-row tiles read rows beyond M up to their own multiple, so they are used only where that stays inside the
-// 256-row padding the caller guarantees.  The tiles that run in turns read nothing beyond M; narrow outputs and plain stores
-// take them only where they fit the padding too (160 rows) or nearly fill the round (128 rows): the parity tests of the 192-
-// and 256-row tiles are such shapes.
+// 256-row padding the caller guarantees.  The tiles that run in turns read nothing beyond M.  Narrow outputs and plain stores
+// take them only where they fit the padding too (160 rows) or nearly fill the round (128 rows).  Those lines are no property of the
+// tiles either: beyond them the tiles in turns have not been measured, and the parity tests of the 192- and 256-row tiles
+// are such shapes.
 static GemmRoute big_tile(int64_t M, int64_t N, int epi) {
   const int64_t tn = (N + 255) / 256, mpad = (M + 255) / 256 * 256;
   const bool heads = epi == EPI_HEADS, any = heads || (epi == EPI_RESID && N >= 1536) || (epi == EPI_GELU && N >= 2048);
