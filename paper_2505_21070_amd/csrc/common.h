@@ -102,6 +102,7 @@ struct HeadSection {
                            // the t-th run of dim / ssq_np columns of the section (one run per block tile), or null
   int rope;                // rotate channel pairs (2i, 2i+1) of each head by the row's entries of HeadsArgs::cs
   int transposed;          // written channel-major; such tiles are computed with the operands exchanged
+  float* wide;             // plain, tiles of 64 or 128 columns: fp32 [M][dim] written instead of dst, for a row scale to come, or null
 };
 struct HeadsArgs {
   HeadSection sec[3];

@@ -281,20 +281,26 @@ template void launch_norm_rope<bf16_t>(const bf16_t*, int64_t, int64_t, int, int
 
 // ---------------------------------------------------------------- deferred RMSNorm of head-major bf16 rows
 // k[head][row0 + s][:] *= rsqrt(sum_i ssq[i * stride + s] * inv_dim + eps) for every head: the row scale of an
-// RMSNorm whose gains and rotation a GEMM epilogue has applied already.  One wavefront per token.
-template <int VPL>
+// RMSNorm whose gains and rotation a GEMM epilogue has applied already.  One wavefront per token.  WIDE: the rows come as
+// fp32 from `wide`, so that the keys are rounded once; rounded before the rotation and behind it, as by k_norm_rope, their error
+// lies across the channel pairs, rounded twice behind it along the large channels, where queries that match a key weigh it most
+// (self-attention with 8 times the usual gains, dim 192: 4.43e-3 from 64 bits against 4.30e-3; once 4.06e-3).
+template <int VPL, bool WIDE>
 __global__ __launch_bounds__(256) void k_scale_rows(bf16_t* __restrict__ k, int64_t head_stride, int64_t row0, int64_t S,
-                                                    int h, int d, const float* __restrict__ ssq, int np,
-                                                    int64_t stride, float inv_dim, float eps) {
+                                                    int h, int d, const float* __restrict__ wide, const float* __restrict__ ssq,
+                                                    int np, int64_t stride, float inv_dim, float eps) {
   const int lane = threadIdx.x & 63;
   const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (s >= S) return;
   const int nvec = (h * d) >> 3;
-  uint4 raw[VPL];
+  uint4 raw[VPL][WIDE ? 2 : 1];
 #pragma unroll
   for (int i = 0; i < VPL; ++i) {
     const int c0 = (lane + i * 64) * 8;
-    if (lane + i * 64 < nvec) raw[i] = *(const uint4*)(k + (int64_t)(c0 / d) * head_stride + (row0 + s) * d + c0 % d);
+    if (lane + i * 64 >= nvec) continue;
+    const uint4* const p = WIDE ? (const uint4*)(wide + s * (h * d) + c0) : (const uint4*)(k + (int64_t)(c0 / d) * head_stride + (row0 + s) * d + c0 % d);
+    raw[i][0] = p[0];
+    if constexpr (WIDE) raw[i][1] = p[1];
   }
   float sum = 0.f;
   for (int i = lane; i < np; i += 64) sum += ssq[i * stride + s];
@@ -303,27 +309,36 @@ __global__ __launch_bounds__(256) void k_scale_rows(bf16_t* __restrict__ k, int6
   for (int i = 0; i < VPL; ++i) {
     const int c0 = (lane + i * 64) * 8;
     if (lane + i * 64 < nvec) {
-      const uint32_t w[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
       uint32_t o[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        o[e] = pack_bf16x2(bf16_to_f32((bf16_t)(w[e] & 0xffff)) * r, bf16_to_f32((bf16_t)(w[e] >> 16)) * r);
+      for (int e = 0; e < 4; ++e) {
+        if constexpr (WIDE) {
+          const uint4 v = raw[i][e >> 1];
+          o[e] = pack_bf16x2(__uint_as_float(e & 1 ? v.z : v.x) * r, __uint_as_float(e & 1 ? v.w : v.y) * r);
+        } else {
+          const uint4 v = raw[i][0];
+          const uint32_t w = e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
+          o[e] = pack_bf16x2(bf16_to_f32((bf16_t)(w & 0xffff)) * r, bf16_to_f32((bf16_t)(w >> 16)) * r);
+        }
+      }
       *(uint4*)(k + (int64_t)(c0 / d) * head_stride + (row0 + s) * d + c0 % d) = make_uint4(o[0], o[1], o[2], o[3]);
     }
   }
 }
-void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* ssq,
-                            int np, int64_t stride, float eps, hipStream_t st) {
+void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* wide,
+                            const float* ssq, int np, int64_t stride, float eps, hipStream_t st) {
   if (S <= 0) return;
   const int vpl = (h * d / 8 + 63) / 64;
   const float inv_dim = 1.f / (float)(h * d);
-#define SCALE_ROWS_CASE(V) k_scale_rows<V><<<cdiv(S, 4), 256, 0, st>>>(k, head_stride, row0, S, h, d, ssq, np, stride, inv_dim, eps)
+#define SCALE_ROWS(V, W) k_scale_rows<V, W><<<cdiv(S, 4), 256, 0, st>>>(k, head_stride, row0, S, h, d, wide, ssq, np, stride, inv_dim, eps)
+#define SCALE_ROWS_CASE(V) do { if (wide) SCALE_ROWS(V, true); else SCALE_ROWS(V, false); } while (0)
   if (vpl <= 1) SCALE_ROWS_CASE(1);
   else if (vpl <= 3) SCALE_ROWS_CASE(3);
   else if (vpl <= 6) SCALE_ROWS_CASE(6);
   else if (vpl <= 10) SCALE_ROWS_CASE(10);
   else SCALE_ROWS_CASE(16);
 #undef SCALE_ROWS_CASE
+#undef SCALE_ROWS
 }
 
 // ---------------------------------------------------------------- V -> V^T (per head [d][L])

@@ -260,7 +260,7 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
                 const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
                 const float4 c0 = cs[g][share ? 0 : k][0], c1 = cs[g][share ? 0 : k][1];
                 const float csv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-                uint32_t o[4];
+                float v[8];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                   float a = (WIDE ? f[2 * u] : bf16_to_f32((bf16_t)(w[u] & 0xffff))) * gg[k][2 * u];
@@ -269,9 +269,14 @@ __device__ __forceinline__ void finish_tile(typename Mfma<MF>::acc (&acc)[TM][TN
                     const float a2 = a * csv[2 * u] - b * csv[2 * u + 1], b2 = a * csv[2 * u + 1] + b * csv[2 * u];
                     a = a2; b = b2;
                   }
-                  o[u] = cvt_pk_bf16(a, b);
+                  v[2 * u] = a; v[2 * u + 1] = b;
                 }
-                dv = make_uint4(o[0], o[1], o[2], o[3]);
+                if (WIDE && sc.wide) {
+                  float4* const o = (float4*)(sc.wide + m * ha.dim + nn[k]);
+                  o[0] = make_float4(v[0], v[1], v[2], v[3]); o[1] = make_float4(v[4], v[5], v[6], v[7]);
+                  continue;
+                }
+                dv = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
               }
               // non-temporal like the other streamed outputs (same-box A/B, 14400 x 15360 x 5120: 1915 -> 1851 us)
               __builtin_nontemporal_store(u32x4{dv.x, dv.y, dv.z, dv.w}, (u32x4*)((bf16_t*)sc.dst + (int64_t)(nn[k] >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (nn[k] & hmask)));
@@ -813,7 +818,7 @@ __global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A,
         const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
         const float gs[8] = {hg[k][0].x, hg[k][0].y, hg[k][0].z, hg[k][0].w, hg[k][1].x, hg[k][1].y, hg[k][1].z, hg[k][1].w};
         const float cs[8] = {hc[k][0].x, hc[k][0].y, hc[k][0].z, hc[k][0].w, hc[k][1].x, hc[k][1].y, hc[k][1].z, hc[k][1].w};
-        uint32_t w[4];
+        float v[8];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           float a = f[2 * u], b = f[2 * u + 1];
@@ -822,9 +827,14 @@ __global__ __launch_bounds__(256) void k_gemm_ring(const bf16_t* __restrict__ A,
             const float a2 = a * cs[2 * u] - b * cs[2 * u + 1], b2 = a * cs[2 * u + 1] + b * cs[2 * u];
             a = a2; b = b2;
           }
-          w[u] = cvt_pk_bf16(a, b);
+          v[2 * u] = a; v[2 * u + 1] = b;
         }
-        const uint4 d = make_uint4(w[0], w[1], w[2], w[3]);
+        if (sc.wide) {
+          float4* const o = (float4*)(sc.wide + m * ha.dim + n);
+          o[0] = make_float4(v[0], v[1], v[2], v[3]); o[1] = make_float4(v[4], v[5], v[6], v[7]);
+          continue;
+        }
+        const uint4 d = make_uint4(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]), cvt_pk_bf16(v[4], v[5]), cvt_pk_bf16(v[6], v[7]));
         __builtin_nontemporal_store(u32x4{d.x, d.y, d.z, d.w}, (u32x4*)((bf16_t*)sc.dst + (int64_t)(n >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (n & hmask)));
       }
     } else {
@@ -1018,6 +1028,7 @@ __global__ __launch_bounds__(512) void k_gemm_thin(const bf16_t* __restrict__ A,
       v[0] = a0; v[1] = b0; v[2] = a1; v[3] = b1;
     }
     const int ns = (int)nsec + c * 4, hshift = ha.head_dim == 128 ? 7 : 6;
+    if (sc.wide) { *(float4*)(sc.wide + m * ha.dim + ns) = make_float4(v[0], v[1], v[2], v[3]); return; }
     *(uint2*)((bf16_t*)sc.dst + (int64_t)(ns >> hshift) * sc.ld + (sc.row0 + m) * ha.head_dim + (ns & (ha.head_dim - 1))) =
         make_uint2(cvt_pk_bf16(v[0], v[1]), cvt_pk_bf16(v[2], v[3]));
   } else {
@@ -1348,12 +1359,14 @@ static int heads_columns(int64_t M, int64_t N) {         // columns of the tile;
   const int family = tile_family(M, N, EPI_HEADS);
   return family == TILE_64 ? 64 : family == TILE_128 ? 128 : 256;
 }
+bool gemm_bf16_heads_wide(int64_t M, int64_t N) { return heads_columns(M, N) < 256; }
 bool gemm_bf16_heads_ever(int64_t M, int64_t N, int64_t dim) { return dim % heads_columns(M, N) == 0; }
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   if (h.dim <= 0 || (h.head_dim != 64 && h.head_dim != 128) || h.dim % heads_columns(M, N) || h.dim % h.head_dim || N % h.dim || N / h.dim > 3) return false;
   for (int i = 0; i < (int)(N / h.dim); ++i) {
     if (h.sec[i].transposed && (M % 8 || h.sec[i].row0 % 8 || h.sec[i].ld % 8)) return false;
     if (h.sec[i].ssq && h.ssq_stride < M) return false;
+    if (h.sec[i].wide && (h.sec[i].transposed || !gemm_bf16_heads_wide(M, N))) return false;
   }
   return true;
 }

@@ -23,9 +23,10 @@ void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float e
                       int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st);
 // cs[s][i] = rotation (cos, sin) of channel pair i < head_dim / 2 at token s < S of a block that starts at frame0
 struct RopeTokens { RopeTables rt; int frame0, tok_h, tok_w; int64_t S; float2* cs; };
-// k[head][row0 + s][:] *= rsqrt(sum_i ssq[i * stride + s] / (h * d) + eps), bf16 rows of d elements, in place
-void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* ssq,
-                            int np, int64_t stride, float eps, hipStream_t st);
+// k[head][row0 + s][:] = (wide ? wide[s][head * d ..] : k[head][row0 + s][:]) * rsqrt(sum_i ssq[i * stride + s] / (h * d) + eps),
+// bf16 rows of d elements; wide: fp32 [S][h * d]
+void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* wide,
+                            const float* ssq, int np, int64_t stride, float eps, hipStream_t st);
 // vt[head][c][col0 + s] = src[s, col + head*d + c]
 template <typename T>
 void launch_v_transpose(const T* src, int64_t ld, int col, int64_t S, int h, int d, T* vt,
@@ -104,6 +105,8 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N);
 bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h);
 // whether it can for sections of `dim` columns and any number of rows from M on: false for M, false for all beyond
 bool gemm_bf16_heads_ever(int64_t M, int64_t N, int64_t dim);
+// whether its plain sections can be had as fp32 rows (HeadSection::wide)
+bool gemm_bf16_heads_wide(int64_t M, int64_t N);
 // ---- attn_bf16.hip : flash attention on MFMA, head_dim 64 or 128 ------------------------------
 // q must already be multiplied by log2(e)/sqrt(d) (attn_bf16_q_scale) and be readable for
 // roundup(S, 256) rows per head; k rows / vt columns readable (finite in vt) up to

@@ -434,6 +434,7 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
     qkv.sec[1] = HeadSection{nullptr, kv_hs, blk0, nullptr, s->kssq, 1, 0};
     qkv.sec[2] = HeadSection{nullptr, s->Lpad, blk0, nullptr, nullptr, 0, 1};
     cross.sec[0] = HeadSection{s->qbuf, s->Spad * d, 0, nullptr, s->qssq, 0, 0};
+    if (gemm_bf16_heads_wide(S, 3 * D)) qkv.sec[1].wide = (float*)s->raw;        // [S][D] fp32: two thirds of it
     qkv_heads = s->any_qkv_heads && gemm_bf16_heads_ok(S, 3 * D, qkv);
     cross_heads = gemm_bf16_heads_ok(S, D, cross);
   }
@@ -463,7 +464,7 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
       e.heads = &ha;
       PROF(DP_PROF_QKV_GEMM, s->launch_ok &= Path<T>::gemm(s->hbuf, D, nullptr, m.wqkv_t, S, 3 * D, D, EPI_HEADS, e, st));
       qn.np = ha.ssq_np;
-      PROF(DP_PROF_NORM_ROPE, launch_scale_rows_bf16((bf16_t*)m.kbuf, kv_hs, blk0, S, h, d, s->kssq, ha.ssq_np, s->Smax, c.eps, st));
+      PROF(DP_PROF_NORM_ROPE, launch_scale_rows_bf16((bf16_t*)m.kbuf, kv_hs, blk0, S, h, d, ha.sec[1].wide, s->kssq, ha.ssq_np, s->Smax, c.eps, st));
     } else {
       if (bf) {
         PROF(DP_PROF_QKV_GEMM,

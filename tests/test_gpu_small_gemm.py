@@ -48,6 +48,19 @@ def test_small_tiles(monkeypatch, dim, heads, hd, ffn, tok_h, tok_w, frames):
     run_pair("ring", 3, True, "later")
 
 
+@pytest.mark.parametrize("dim,heads,hd,ffn,tok_h,tok_w,frames", [(128, 1, 128, 192, 3, 8, 3), (512, 4, 128, 1344, 8, 17, 9), (1024, 8, 128, 4096, 9, 16, 7),
+                                                                 (768, 6, 128, 2112, 16, 17, 5)])
+def test_keys_are_rounded_once(monkeypatch, dim, heads, hd, ffn, tok_h, tok_w, frames):
+    """Per-head stores of 64- and 128-column tiles (one shape for each) leave the keys unrounded until their row scale is
+    known.  A rounding to bf16 is 1.66e-3 (relative, root mean square, for evenly spread mantissas): with the LayerNorm's output
+    the first layer's keys are sqrt(2) of that from 64 bits, 2.35e-3, and would be sqrt(3), 2.87e-3, if rounded twice."""
+    monkeypatch.setitem(synth.CONFIGS, "keys", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=dim, n_heads=heads, head_dim=hd, ffn_dim=ffn,
+                                                    text_dim=dim, tok_h=tok_h, tok_w=tok_w, block_frames=frames, cache_frames=1))
+    rep = {}
+    run_pair("keys", 4, True, "later", rep)
+    assert rep["keys/k"]["rel_l2"] < 2.6e-3 and rep["keys/cache_k0"]["rel_l2"] < 2.6e-3
+
+
 @pytest.mark.parametrize("dim,heads,hd,ffn,tok_h,tok_w,frames,text_len", TEXT_SHAPES)
 def test_text_products(monkeypatch, dim, heads, hd, ffn, tok_h, tok_w, frames, text_len):
     monkeypatch.setitem(synth.CONFIGS, "text", dict(synth.CONFIGS["tiny_bf16"], n_layers=1, dim=dim, n_heads=heads, head_dim=hd, ffn_dim=ffn,
