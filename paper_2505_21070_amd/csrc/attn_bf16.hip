@@ -736,7 +736,9 @@ static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratc
   // Few enough blocks of 32 queries for one round (one to a CU at head_dim 128, two at 64) and at most eight tiles to a
   // wavefront: k_attn_few.  Beyond either line the other shapes are as fast (us): 1008 x 1680 x 16 heads of 64 (512 blocks) 17.9
   // against 20.3, 1000 x 1900 x 8 heads of 128 (256) 19.9 and 24.2, 700 x 1000 x 12 of 128 (264) 24.0 and 20.6, 100 x 3000 x 8 of 128
-  // (32) 22.7 and 19.8.
+  // (32) 22.7 and 19.8.  Inside a stage, with the queries' row sums to read, heads of 64 meet earlier: 1008 x 1680 x 16 22.3 against
+  // 21.6 (merge included), 1200 x 1600 x 12 21.1 and 20.8, 1200 x 1200 x 12 18.7 and 19.4, 672 x 1008 x 16 16.3 and 17.6; 1008 x 77 x 16
+  // 9.3 and 10.2.
   const bool few = L <= 1920 && (S + 31) / 32 * h <= (d == 128 ? 256 : 512);
   // Few keys: a block's start and end weigh as much as its tiles, so blocks of four wavefronts, two to a CU, fill each other's
   // gaps.  Short key ranges, or up to 16 tiles where two rounds of such blocks are full (us): 6240 x 512 x 12 of 128 35.0 -> 31.5,

@@ -1072,7 +1072,7 @@ static bool launch_thin_cfg(const bf16_t* A, int64_t lda, const bf16_t* Wt, int6
 // stages; plain store, us): 6240 x 1536 x 8960 173 -> 155, 6240 x 1536 x 1536 33.9 -> 31.2, 1560 x 4608 x 1536 as 128 x 256
 // tiles 30.2 -> 25.0; against a ring of four stages without turns 1008 x 4096 x 1024 (128 x 128) 15.5 -> 11.8.  Counted at 6240 x 1536 x
 // 8960 with the residual epilogue: matrix pipes busy 50 % of the cycles at 2.12 GHz, 57 % of those in which a CU has a block, where
-// that layout was busy 49 % at 1.91 GHz: what the saved LDS reads gave is clock.
+// that layout was busy 50 % at 1.93 GHz: what the saved LDS reads gave is clock.
 template <int TM, int TN, int KB, int ST, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ Bt,
                                                    int64_t ldb, int64_t M, int64_t N, int64_t K, int tiles_n, int tiles,
