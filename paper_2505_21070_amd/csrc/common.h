@@ -63,6 +63,25 @@ __device__ __forceinline__ void load_lds16(const void* base, uint32_t bytes, uin
   __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), (lds_void_t*)dst, 16, voff, soff, 0, 0);
 #endif
 }
+// a lane's 16 or 8 bytes at byte voff of [base, base + bytes): beyond, loads return zeros and stores are dropped
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x4 buffer_load16(const void* base, uint32_t bytes, uint32_t voff) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00020000), voff, 0, 0);
+#else
+  return u32x4{};
+#endif
+}
+__device__ __forceinline__ void buffer_store16(u32x4 v, void* base, uint32_t bytes, uint32_t voff) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000), voff, 0, 0);
+#endif
+}
+__device__ __forceinline__ void buffer_store8(u32x2 v, void* base, uint32_t bytes, uint32_t voff) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_buffer_store_b64(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000), voff, 0, 0);
+#endif
+}
 // 16 bytes at LDS byte address addr + OFF through inline assembly: the compiler neither moves it nor waits for
 // it; the caller does (lds_wait) before the first use of the result
 template <int OFF> __device__ __forceinline__ u32x4 lds_read16_raw(uint32_t addr) {

@@ -52,6 +52,9 @@ CONFIGS = {
                          tok_h=16, tok_w=32, block_frames=8, cache_frames=2, dtype="bf16"),
     "tile320_bf16": dict(n_layers=1, dim=1408, n_heads=11, head_dim=128, ffn_dim=3904, text_len=40, text_dim=1408,
                          tok_h=20, tok_w=26, block_frames=8, cache_frames=2, dtype="bf16"),
+    # 3848 rows of 4224: the residual products fill a round with 320 x 256 tiles and need two or three of any other
+    "tile320_resid_bf16": dict(n_layers=1, dim=4224, n_heads=33, head_dim=128, ffn_dim=256, text_len=16, text_dim=4224,
+                               tok_h=52, tok_w=74, block_frames=1, cache_frames=0, dtype="bf16"),
     # few tokens, wide models: the wide register variants of the row kernels (LayerNorm, deferred key scale, the text keys'
     # norm) behind the per-head GEMM epilogue
     "dim6144_bf16": dict(n_layers=1, dim=6144, n_heads=48, head_dim=128, ffn_dim=512, text_len=24, text_dim=6144,
