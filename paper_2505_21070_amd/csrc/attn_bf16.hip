@@ -12,25 +12,20 @@
 // Q arrives pre-multiplied by log2(e)/sqrt(head_dim), so scores are base-2 logits.  The softmax reference
 // m of a query is folded into the accumulator that the score MFMAs start from (-m instead of 0), so the
 // matrix cores hand back s - m and the vector unit only has to exponentiate.  Fast pass: m is fixed once,
-// to the query's maximum over the first 32 keys of its key group, and never raised, so O^T needs no
+// to the query's maximum over the first 32 keys of the tile it starts with, and never raised, so O^T needs no
 // rescaling and the loop body is straight-line code.  This is exact as long as nothing overflows: P (bf16)
 // and the fp32 sums have 8 exponent bits, so scores may exceed m by ~2^100 before anything is lost.  A
 // block whose row sums end up beyond 2^100 (or non-finite) is recomputed by the safe pass, the classical
 // online softmax that raises m whenever a tile exceeds it and rescales O^T.
 //
-// Work split: a block of QG * KG wavefronts owns QG * 32 queries of one head.  Three shapes are built (attn_bf16_route has the
-// lines between them, and k_attn_few takes what is small).
-// QG = 4, KG = 2 (few queries or very few keys): wavefront w handles query tile w & 3 against key group
-// w >> 2 (first / second half of the key tiles); the two groups stream their own K / V^T tiles and are
-// merged through LDS at the end, which halves the length of a block.  QG = 8, KG = 1 (everything else,
-// self- and cross-attention at full size): all 8 wavefronts share every K / V^T tile, so a tile brought
-// into LDS serves 256 queries and the LDS fill traffic per query halves.  QG = 4, KG = 1 (few keys): 4 wavefronts, two blocks
-// to a CU.  Tiles hold 64 keys, are double-buffered and are loaded
-// HBM -> LDS directly.  The two wavefronts of a SIMD are served oldest first rather than interleaved, so the
-// fast pass pins its issue order so that one wavefront alone keeps the matrix pipe busy: exponentials
-// between MFMAs, operand fragments read from LDS several MFMAs ahead with exact waits (see pass_fast).
+// Kernels (attn_bf16_route has the lines between them).  k_attn_turns: everything of some size, self- and cross-attention; a block of
+// eight wavefronts, the two of a SIMD taking turns at the matrix products and at the exponentials.  k_attn_bf16: few keys (blocks
+// of four wavefronts, two to a CU) and heads of 64 in less than a round of blocks; its wavefronts are served oldest first rather
+// than interleaved, so its fast pass pins its issue order so that one wavefront alone keeps the matrix pipe busy: exponentials
+// between MFMAs, operand fragments read from LDS several MFMAs ahead with exact waits (see pass_fast).  k_attn_few: what is small.
+// Tiles hold 64 keys (k_attn_few 32) and are loaded HBM -> LDS directly.
 //
-// Grid: one block of 8 wavefronts fits per compute unit, so a grid runs in rounds of 256 blocks (512 of 4 wavefronts).  The work ids that
+// Grid: one block of 8 wavefronts fits per compute unit, so a grid of them runs in rounds of 256 blocks (512 of 4 wavefronts).  The work ids that
 // would make up a last, partly filled round are instead cut into several key ranges each, one block per
 // range, which write unnormalised partial results (m, l, O) to a scratch buffer; k_attn_merge joins them.
 #include <type_traits>
@@ -40,6 +35,7 @@
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ uint32_t cvt_pk_bf16(float a, float b) {
@@ -85,8 +81,8 @@ __device__ __forceinline__ void load_queries(const bf16_t* __restrict__ qh, int6
   }
 }
 
-template <int HD, int QG, int KG>
-__global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
+template <int HD, int QG>
+__global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
                                                   const bf16_t* __restrict__ k, int64_t k_head_stride,
                                                   int64_t k_row0, const bf16_t* __restrict__ vt,
                                                   int64_t vt_row_stride, int64_t S, int64_t L,
@@ -98,15 +94,13 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
   constexpr int DT = HD / 32;                // 32-row tiles of O^T
   constexpr int KCH = 64 * CR;               // chunks in a K tile
   constexpr int VCH = HD * 8;                // chunks in a V^T tile
-  constexpr int NBUF = 2;                    // tile buffers per key group (a third one was measured: no gain)
-  constexpr int GCH = NBUF * (KCH + VCH);    // chunks per key group: NBUF K tiles, NBUF V^T tiles
+  constexpr int NBUF = 2;                    // tile buffers (a third one was measured: no gain)
   constexpr int CK = KCH / (QG * 64), CV = VCH / (QG * 64);   // load instructions per wavefront and tile
   constexpr int QB = QG * 32;                // queries per block
-  extern __shared__ uint4 smem[];            // KG * GCH chunks
+  extern __shared__ uint4 smem[];            // NBUF K tiles, NBUF V^T tiles
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int qt = wave % QG, kg = wave / QG;
+  const int qt = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lg = lane >> 5;
   // Blocks are dealt round-robin over the 8 XCDs, each with its own L2: give every XCD a contiguous run
   // of (head, query block) work ids so that the blocks streaming one head's K/V share an L2.  The first
@@ -131,15 +125,13 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
   }
   const int head = wid / qblocks;
   const int64_t q0 = (int64_t)(wid % qblocks) * QB + qt * 32;
-  uint4* const kbuf = smem + kg * GCH;
+  uint4* const kbuf = smem;
   uint4* const vbuf = kbuf + NBUF * KCH;
 
-  // this wavefront's share of the key tiles
-  const int n0 = KG == 2 ? (t1 - t0 + 1) / 2 : t1 - t0;   // tiles of group 0; also the trip count for everyone
-  const int first = t0 + (kg ? n0 : 0), cnt = kg ? t1 - t0 - n0 : n0;
+  const int cnt = t1 - t0;                   // key tiles
 
-  const bf16_t* kh = k + (int64_t)head * k_head_stride + (k_row0 + (int64_t)first * 64) * HD;
-  const bf16_t* vh = vt + (int64_t)head * HD * vt_row_stride + k_row0 + (int64_t)first * 64;
+  const bf16_t* kh = k + (int64_t)head * k_head_stride + (k_row0 + (int64_t)t0 * 64) * HD;
+  const bf16_t* vh = vt + (int64_t)head * HD * vt_row_stride + k_row0 + (int64_t)t0 * 64;
 
   // HBM -> LDS directly (no staging registers).  One wavefront instruction fills 64 consecutive
   // 16-byte LDS slots, slot = base + lane; each lane fetches the chunk that belongs in its slot:
@@ -204,7 +196,7 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
         const bf16x8 kf = __builtin_bit_cast(bf16x8, kbuf[row * CR + (ch ^ kswz<CR>(row))]);
         s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? negm : s0, 0, 0, 0);
       }
-      const int kv0 = (int)(L - (int64_t)first * 64);
+      const int kv0 = (int)(L - (int64_t)t0 * 64);
       float mx = -INFINITY;
 #pragma unroll
       for (int r = 0; r < 16; ++r)
@@ -214,14 +206,14 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
       for (int r = 0; r < 16; ++r) negm[r] = -mrun;
     }
 
-    for (int kt = 0; kt < n0; ++kt) {
+    for (int kt = 0; kt < cnt; ++kt) {
       if (kt < cnt) {
         // next tile into the other buffer (read last before the previous barrier); the tile past the
         // end is the last one again and never used
         load_tile(kt + NBUF - 1 < cnt ? kt + NBUF - 1 : cnt - 1, (kt + NBUF - 1) % NBUF);
         const uint4* kb = kbuf + (kt % NBUF) * KCH;
         const uint4* vb = vbuf + (kt % NBUF) * VCH;
-        const int kvalid = (int)(L - (int64_t)(first + kt) * 64);     // < 64 only in the ragged last tile
+        const int kvalid = (int)(L - (int64_t)(t0 + kt) * 64);     // < 64 only in the ragged last tile
 #pragma unroll
         for (int a = 0; a < 2; ++a) {                                  // two 32-key halves of the tile
           // S^T - m : 32 keys x 32 queries, accumulation started from -m
@@ -300,8 +292,8 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
   // This lane's row of a K tile (row lr of a 32-key half) and of a V^T tile (row lr of a 32-channel group) in
   // buffer 0, as LDS byte addresses; chunk c of the row sits at byte (c * 16) ^ swizzle, and c = ks*2 + lg or
   // (a*2+u)*2 + lg has lg as its lowest bit, so the lane-dependent part of the XOR is one constant per tile kind.
-  const uint32_t krow = lds0 + (uint32_t)(kg * GCH + lr * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(lr)) * 16;
-  const uint32_t vrow = lds0 + (uint32_t)(kg * GCH + NBUF * KCH + lr * 8) * 16, vx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+  const uint32_t krow = lds0 + (uint32_t)(lr * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(lr)) * 16;
+  const uint32_t vrow = lds0 + (uint32_t)(NBUF * KCH + lr * 8) * 16, vx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
   // operand fragment of MFMA i of a tile whose K / V^T buffers start kbo / vbo bytes behind buffer 0
   auto frag_read = [&](auto i_, uint32_t kbo, uint32_t vbo) __attribute__((always_inline)) {
     constexpr int i = decltype(i_)::value;
@@ -325,7 +317,7 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
     // here in plain order with its keys at or beyond L masked; the pinned loop below then sees whole tiles only.
     tile_barrier();
     if (cnt > 0) {
-      const int kvalid = (int)(L - (int64_t)(first + cnt - 1) * 64);   // >= 1; < 64 only in a ragged tile
+      const int kvalid = (int)(L - (int64_t)(t0 + cnt - 1) * 64);   // >= 1; < 64 only in a ragged tile
       // reference = maximum over the tile's first 32 keys (the valid ones of them).  Register r of lane group
       // lg is tile row a*32 + (r/4)*8 + lg*4 + r%4, which holds key swap23(row).
       f32x16 sv;
@@ -394,140 +386,500 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
       pw[a][pidx] = cvt_pk_bf16(__builtin_amdgcn_exp2f(sacc[a][2 * pidx]), __builtin_amdgcn_exp2f(sacc[a][2 * pidx + 1]));
       lsum = add_pk_bf16(pw[a][pidx], lsum);
     };
-    for (int j = 1; j < n0; ++j) {
-      if (j < cnt) {
-        const uint32_t kbo = (uint32_t)(j % NBUF) * KCH * 16, vbo = (uint32_t)(j % NBUF) * VCH * 16;
-        const uint32_t kbn = (uint32_t)((j + 1) % NBUF) * KCH * 16, vbn = (uint32_t)((j + 1) % NBUF) * VCH * 16;
-        static_for<NMF>([&](auto i_) __attribute__((always_inline)) {
-          constexpr int i = decltype(i_)::value;
-          if constexpr (i < NMF - PD) lds_wait<PD - 1>();               // fragment i has landed
-          __builtin_amdgcn_sched_barrier(0);                            // the MFMA stays behind the wait
-          if constexpr (i < KS) {
-            sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], qf[i], i == 0 ? negm : sacc[0], 0, 0, 0);
-          } else if constexpr (i < 2 * KS) {
-            sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], qf[i - KS], i == KS ? negm : sacc[1], 0, 0, 0);
+    for (int j = 1; j < cnt; ++j) {
+      const uint32_t kbo = (uint32_t)(j % NBUF) * KCH * 16, vbo = (uint32_t)(j % NBUF) * VCH * 16;
+      const uint32_t kbn = (uint32_t)((j + 1) % NBUF) * KCH * 16, vbn = (uint32_t)((j + 1) % NBUF) * VCH * 16;
+      static_for<NMF>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int i = decltype(i_)::value;
+        if constexpr (i < NMF - PD) lds_wait<PD - 1>();               // fragment i has landed
+        __builtin_amdgcn_sched_barrier(0);                            // the MFMA stays behind the wait
+        if constexpr (i < KS) {
+          sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], qf[i], i == 0 ? negm : sacc[0], 0, 0, 0);
+        } else if constexpr (i < 2 * KS) {
+          sacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], qf[i - KS], i == KS ? negm : sacc[1], 0, 0, 0);
 #pragma unroll
-            for (int e = 0; e < PPM; ++e) e_piece(0, (i - KS) * PPM + e);
-          } else {
-            constexpr int m = i - 2 * KS, a = m / (2 * DT), u = (m % (2 * DT)) / DT, dt = m % DT;
-            const uint4 pf = make_uint4(pw[a][u * 4], pw[a][u * 4 + 1], pw[a][u * 4 + 2], pw[a][u * 4 + 3]);
-            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], __builtin_bit_cast(bf16x8, pf), oacc[dt], 0, 0, 0);
-            if constexpr (a == 0) {
+          for (int e = 0; e < PPM; ++e) e_piece(0, (i - KS) * PPM + e);
+        } else {
+          constexpr int m = i - 2 * KS, a = m / (2 * DT), u = (m % (2 * DT)) / DT, dt = m % DT;
+          const uint4 pf = make_uint4(pw[a][u * 4], pw[a][u * 4 + 1], pw[a][u * 4 + 2], pw[a][u * 4 + 3]);
+          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[i % PD], __builtin_bit_cast(bf16x8, pf), oacc[dt], 0, 0, 0);
+          if constexpr (a == 0) {
 #pragma unroll
-              for (int e = 0; e < PPM; ++e) e_piece(1, m * PPM + e);
-            }
+            for (int e = 0; e < PPM; ++e) e_piece(1, m * PPM + e);
           }
-          // the two dependent S^T chains go first in the SIMD's issue arbitration (measured: 2 % over no hint)
-          if constexpr (i == 0) __builtin_amdgcn_s_setprio(1);
-          if constexpr (i == 2 * KS - 1) __builtin_amdgcn_s_setprio(0);
-          __builtin_amdgcn_sched_barrier(0);      // the read that reuses the MFMA's operand register stays behind it
-          if constexpr (i + PD < NMF) fr[i % PD] = frag_read(std::integral_constant<int, i + PD>{}, kbo, vbo);
-          if constexpr (i == NMF - PD - 1) {
-            lds_wait<0>();          // every fragment of this tile is in registers
-            tile_barrier();         // the next tile has landed and every wavefront is done reading this one
-          }
-          if constexpr (i >= NMF - PD) {
-            if (j + 2 < cnt) {
+        }
+        // the two dependent S^T chains go first in the SIMD's issue arbitration (measured: 2 % over no hint)
+        if constexpr (i == 0) __builtin_amdgcn_s_setprio(1);
+        if constexpr (i == 2 * KS - 1) __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);      // the read that reuses the MFMA's operand register stays behind it
+        if constexpr (i + PD < NMF) fr[i % PD] = frag_read(std::integral_constant<int, i + PD>{}, kbo, vbo);
+        if constexpr (i == NMF - PD - 1) {
+          lds_wait<0>();          // every fragment of this tile is in registers
+          tile_barrier();         // the next tile has landed and every wavefront is done reading this one
+        }
+        if constexpr (i >= NMF - PD) {
+          if (j + 2 < cnt) {
 #pragma unroll
-              for (int q = 0; q < CK + CV; ++q)
-                if (q * PD / (CK + CV) == i - (NMF - PD)) load_part(cnt - 3 - j, j % NBUF, q);
-            }
-            fr[i % PD] = frag_read(std::integral_constant<int, i + PD - NMF>{}, kbn, vbn);
+            for (int q = 0; q < CK + CV; ++q)
+              if (q * PD / (CK + CV) == i - (NMF - PD)) load_part(cnt - 3 - j, j % NBUF, q);
           }
-          __builtin_amdgcn_sched_barrier(0);                            // keeps this order
-        });
-      } else {
-        tile_barrier();
-      }
+          fr[i % PD] = frag_read(std::integral_constant<int, i + PD - NMF>{}, kbn, vbn);
+        }
+        __builtin_amdgcn_sched_barrier(0);                            // keeps this order
+      });
     }
     lds_wait<0>();
   };
 
   pass_fast();
-  const bool empty = cnt == 0;                          // this key group has no tile (a single-tile key range)
   float ltot = lsum + __shfl_xor(lsum, 32, 64);
-  if (__syncthreads_or(!empty && !(ltot <= 0x1p100f))) {  // overflow somewhere in the block: redo it safely
+  if (__syncthreads_or(!(ltot <= 0x1p100f))) {          // overflow somewhere in the block: redo it safely
     pass(std::true_type{});
     ltot = lsum + __shfl_xor(lsum, 32, 64);
   }
-
-  // merge the two key groups through LDS (tile buffers are free now): group 1 publishes m, l, O^T
-  float* xch = (float*)smem;                           // [qt][DT*16 + 2][64 lanes]
-  float* mine = xch + (size_t)qt * (DT * 16 + 2) * 64 + lane;
-  if constexpr (KG == 2) {
-    if (kg == 1) {
-      mine[0] = empty ? -INFINITY : mrun;
-      mine[64] = ltot;
+  if (slot >= 0) {
+    // one key range of a split work id: publish m, l and the unnormalised O^T for the merge kernel.
+    // Slot layout (floats): m[QB], l[QB], then O as [HD/4][QB queries][4 channels].
+    float* ps = partial + (size_t)slot * (2 * QB + QB * HD);
+    const int ql = qt * 32 + lr;
+    if (lg == 0) { ps[ql] = mrun; ps[QB + ql] = ltot; }
 #pragma unroll
-      for (int a = 0; a < DT; ++a)
+    for (int a = 0; a < DT; ++a)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mine[(2 + a * 16 + r) * 64] = oacc[a][r];
+      for (int g4 = 0; g4 < 4; ++g4) {
+        const float4 v = make_float4(oacc[a][g4 * 4 + 0], oacc[a][g4 * 4 + 1], oacc[a][g4 * 4 + 2], oacc[a][g4 * 4 + 3]);
+        *(float4*)(ps + 2 * QB + ((size_t)(a * 8 + g4 * 2 + lg) * QB + ql) * 4) = v;
+      }
+  } else {
+    // O[q][head*HD + c] = O^T[c][q]: a lane holds 4 consecutive channels per register quad.  The 32 x HD
+    // tile of this wavefront goes through LDS (the tile buffers are free; a wavefront only touches its own
+    // rows, and LDS serves a wavefront's accesses in order) so that global memory sees whole rows, 16
+    // bytes per lane.  8-byte units are XOR-swizzled with the row so that the column-wise writes spread
+    // over the banks.
+    const float inv = 1.f / ltot;
+    constexpr int UPR = HD / 4, CPR = HD / 8, RPI = 64 / CPR;      // units, 16-byte chunks per row; rows per read
+    uint2* stg = (uint2*)smem + qt * 32 * UPR;
+#pragma unroll
+    for (int a = 0; a < DT; ++a)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4) {
+        uint2 pk;
+        pk.x = cvt_pk_bf16(oacc[a][g4 * 4 + 0] * inv, oacc[a][g4 * 4 + 1] * inv);
+        pk.y = cvt_pk_bf16(oacc[a][g4 * 4 + 2] * inv, oacc[a][g4 * 4 + 3] * inv);
+        stg[lr * UPR + ((a * 8 + g4 * 2 + lg) ^ (lr & (UPR - 1)))] = pk;
+      }
+    const uint4* stg16 = (const uint4*)stg;
+#pragma unroll
+    for (int it = 0; it < 32 / RPI; ++it) {
+      const int row = it * RPI + lane / CPR, p = lane % CPR;
+      uint4 dv = stg16[row * CPR + p];
+      // units 2p and 2p+1 of the swizzled row are the halves of chunk p ^ (swizzle >> 1), exchanged for odd rows
+      if (row & 1) dv = make_uint4(dv.z, dv.w, dv.x, dv.y);
+      const int c = p ^ ((row & (UPR - 1)) >> 1);
+      if (q0 + row < S) *(uint4*)(out + (q0 + row) * ldo + (int64_t)head * HD + c * 8) = dv;
     }
+  }
+}
+
+// Eight wavefronts of 32 queries (two MFMA columns of 16), v_mfma_f32_16x16x32_bf16, key tiles of 64.  KG = 1: all share every
+// tile, a block has 256 queries and its halves are the wavefronts 0-3 and 4-7.  KG = 2: the halves have the same 128 queries
+// and one part of the keys each, with tiles of their own; they meet in LDS at the end, which halves the length of a block.
+// The two wavefronts of a SIMD (one of each half) take turns, with a barrier at every change: one multiplies, the scores of
+// tile j + 1 and the weighted sum of tile j back to back, and reads tile j's V^T fragments into the registers that the keys
+// leave; the other turns its scores of tile j + 1 into weights, reads tile j + 2's keys and requests tiles to come.  A turn of
+// products is 64 MFMAs of 16 cycles at head_dim 128, one of exponentials about 0.7 of that, so the matrix pipes see one
+// wavefront or the other all the time; the exponentials have no MFMA to wait for and nothing is interleaved by hand.
+// What bounds it: matrix pipes under the power limit.  Against a pinned order in which each wavefront mixed its own
+// exponentials between its MFMAs (32x32x16; us): 14400 x 21600 x 40 of 128 4978 -> 4487 (1.42 PFLOP/s), 6240 x 9360 x 12 305 -> 278,
+// 7800 x 7800 x 12 314 -> 287, 18720 x 24960 x 12 2250 -> 2026, 4096 x 1024 x 16 34.5 -> 32.7; heads of 64 6000 x 9000 x 16 210 -> 202,
+// 5000 x 7000 x 40 353 -> 329; two key groups 1560 x 3120 x 12 43.6 -> 40.8, 3000 x 4000 x 8 55.9 -> 50.6, 3000 x 1000 x 10 21.6 -> 21.1.
+// Tried: loads behind the exponentials (2 % slower), without s_setprio (0.4 %).
+template <int HD, int KG>
+__global__ __launch_bounds__(512) void k_attn_turns(const bf16_t* __restrict__ q, int64_t q_head_stride,
+                                                    const bf16_t* __restrict__ k, int64_t k_head_stride,
+                                                    int64_t k_row0, const bf16_t* __restrict__ vt,
+                                                    int64_t vt_row_stride, int64_t S, int64_t L,
+                                                    bf16_t* __restrict__ out, int64_t ldo, int qblocks,
+                                                    int n_full, int n_tail, int parts,
+                                                    float* __restrict__ partial, AttnQNorm qn) {
+  constexpr int CR = HD / 8;                 // 16-byte chunks per K row
+  constexpr int KS = HD / 32, DT = HD / 16;  // MFMA k-steps over the head dim, 16-channel tiles of O^T
+  constexpr int KCH = 64 * CR, VCH = HD * 8; // chunks in a K tile and in a V^T tile of 64 keys
+  constexpr int QG = 8 / KG, QB = QG * 32;   // wavefronts that share a tile; queries per block
+  constexpr int NST = KG == 1 ? 4 : 2;       // LDS stages of either, per key group
+  constexpr int CK = KCH / (QG * 64), CV = VCH / (QG * 64);   // load instructions per wavefront and tile
+  extern __shared__ uint4 smem[];            // per key group: NST K tiles, NST V^T tiles
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qt = wave % QG, kg = wave / QG;
+  // Work ids as in k_attn_bf16.
+  const int NKT = (int)((L + 63) / 64);
+  int wid, t0 = 0, t1 = NKT, slot = -1;
+  if ((int)blockIdx.x < n_full) {
+    wid = (int)(blockIdx.x & 7) * (n_full >> 3) + (int)(blockIdx.x >> 3);
+  } else {
+    const int local = (int)blockIdx.x - n_full, tail_grid = (int)gridDim.x - n_full;
+    const int pid = (local & 7) * (tail_grid >> 3) + (local >> 3);
+    if (pid >= n_tail * parts) return;
+    wid = n_full + pid / parts;
+    if (parts > 1) {
+      const int part = pid % parts;
+      t0 = (int)((int64_t)part * NKT / parts);
+      t1 = (int)((int64_t)(part + 1) * NKT / parts);
+      slot = pid;
+    }
+  }
+  // this wavefront's tiles: of two key groups the first has one more if they are odd
+  const int n0 = KG == 2 ? (t1 - t0 + 1) / 2 : t1 - t0;          // the trip count for everyone
+  const int cnt = kg ? t1 - t0 - n0 : n0;                        // >= 1
+  t0 += kg ? n0 : 0;
+  const int head = wid / qblocks;
+  const int64_t q0 = (int64_t)(wid % qblocks) * QB + qt * 32;
+  uint4* const kst = smem + kg * NST * (KCH + VCH);
+  uint4* const vst = kst + NST * KCH;
+  const bf16_t* const kh = k + (int64_t)head * k_head_stride + (k_row0 + (int64_t)t0 * 64) * HD;
+  const bf16_t* const vh = vt + (int64_t)head * HD * vt_row_stride + k_row0 + (int64_t)t0 * 64;
+
+  // K slot p of a tile holds chunk (p % CR) ^ kswz(row) of key keyat(row), row = p / CR; V^T slot p holds chunk
+  // (p % 8) ^ ((row >> 1) & 7) of channel row = p / 8.  Tile row u * 16 + g * 4 + r of a 32-key half holds key g * 8 + u * 4 + r, so
+  // that the accumulators a lane packs into one operand are eight consecutive keys.
+  auto keyat = [](int row) __attribute__((always_inline)) { return (row & 32) | ((row >> 2) & 3) * 8 | ((row >> 4) & 1) * 4 | (row & 3); };
+  // A wavefront's load instructions of a tile are QG * 64 slots apart: 16 keys (in rows of 8 or 16 chunks, tile rows 16 or 32
+  // apart) or 32 channels and more, so their swizzle is the same and what differs is uniform.
+  constexpr int KR = QG * 64 / CR, VR = QG * 8;
+  static_assert(KR % 16 == 0 && VR % 16 == 0, "one swizzle");
+  const int p0 = qt * 64 + lane;
+  const uint32_t koff = (uint32_t)(keyat(p0 / CR) * HD + ((p0 % CR) ^ kswz<CR>(p0 / CR)) * 8) * 2;
+  const uint32_t voff = (uint32_t)((p0 >> 3) * vt_row_stride + ((p0 & 7) ^ ((p0 >> 4) & 7)) * 8) * 2;
+  // tile j of the walk is tile cnt - 1 - j of the range: the last tile of the range, the only one that can be ragged, comes
+  // first; past the end the range's first tile is loaded again and never read
+  auto tile_of = [&](int j) __attribute__((always_inline)) { return j < cnt ? cnt - 1 - j : 0; };
+  auto load_k = [&](int j) __attribute__((always_inline)) {
+    const bf16_t* const base = kh + (int64_t)tile_of(j) * 64 * HD;
+#pragma unroll
+    for (int i = 0; i < CK; ++i) load_lds16(base, 0x7fffffff, koff, keyat(i * KR) * HD * 2, kst + (j % NST) * KCH + (i * QG + qt) * 64);
+  };
+  auto load_v = [&](int j) __attribute__((always_inline)) {
+    const bf16_t* const base = vh + (int64_t)tile_of(j) * 64;
+#pragma unroll
+    for (int i = 0; i < CV; ++i) load_lds16(base, 0xffffffff, voff, (int)((uint32_t)(i * VR * 2) * (uint32_t)vt_row_stride), vst + (j % NST) * VCH + (i * QG + qt) * 64);
+  };
+  // the fragments of this wavefront's 32 queries: B operand, column = query lr of a 16-query tile, 8 head-dim values per lane
+  bf16x8 qf[2][KS];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const bf16_t* const qh = q + (int64_t)head * q_head_stride + (q0 + t * 16 + lr) * HD + lg * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[t][ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qh + ks * 32));
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // the first keys travel with the queries and their row sums; what is needed later is requested behind them
+  load_k(0); load_k(1);
+  __builtin_amdgcn_sched_barrier(0);
+  if (qn.ssq) {
+    // deferred RMSNorm of the queries: the row's sum of squares arrives as qn.np partial sums; two of the four lanes of a query
+    // add up the even and two the odd ones, the order in which the other kernels and the test hook do it
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int64_t row = q0 + t * 16 + lr < S ? q0 + t * 16 + lr : S - 1;
+      const float* pr = qn.ssq + row;
+      float sum = 0.f;
+#pragma unroll 4
+      for (int i = lg & 1; i < qn.np; i += 2) sum += pr[i * qn.stride];
+      sum += __shfl_xor(sum, 16, 64);
+      const float r = rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[t][ks][e] = (__bf16)((float)qf[t][ks][e] * r);
+    }
+  }
+
+  __builtin_amdgcn_sched_barrier(0);
+  load_v(0);
+  if constexpr (KG == 1) { load_k(2); load_v(1); load_k(3); } else load_v(1);
+  __builtin_amdgcn_sched_barrier(0);
+
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
+  const uint32_t krow = lds0 + (uint32_t)(kg * NST * (KCH + VCH) + lr * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(lr)) * 16;
+  const uint32_t vrow = lds0 + (uint32_t)(kg * NST * (KCH + VCH) + NST * KCH + lr * 8) * 16, vx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+  bf16x8 kf[4][KS], vf[2][DT];
+  f32x4 o[DT][2], sc[4][2], negm[2];
+  uint4 pf[2][2];                            // P of a tile: [32-key half][query tile], packed
+  float lsum[2];
+  // 16-byte fragments of key tile j: keys kt * 16 .., head-dim values ks * 32 ..
+  auto read_k = [&](int j) __attribute__((always_inline)) {
+    const uint32_t b = krow + (uint32_t)(j % NST) * KCH * 16;
+    static_for<KS>([&](auto k_) __attribute__((always_inline)) {
+      constexpr int ks = decltype(k_)::value;
+      static_for<4>([&](auto t_) __attribute__((always_inline)) {
+        constexpr int t = decltype(t_)::value;
+        kf[t][ks] = lds_read16<t * 16 * CR * 16>(b + (kx ^ (uint32_t)(ks * 64)));
+      });
+    });
+  };
+  // four of the fragments of V^T tile j, in the order in which they are used
+  auto read_v4 = [&](int j, auto g_) __attribute__((always_inline)) {
+    constexpr int g = decltype(g_)::value;
+    const uint32_t b = vrow + (uint32_t)(j % NST) * VCH * 16;
+    static_for<4>([&](auto i_) __attribute__((always_inline)) {
+      constexpr int f = g * 4 + decltype(i_)::value, s = f / DT, d = f % DT;
+      vf[s][d] = lds_read16<d * 16 * 8 * 16>(b + (vx ^ (uint32_t)(s * 64)));
+    });
+  };
+  // this lane's key of accumulator register r of 16-key tile t
+  auto key_of = [&](int t, int r) __attribute__((always_inline)) { return (t >> 1) * 32 + lg * 8 + (t & 1) * 4 + r; };
+  // P = 2^(s - m) of the tile in sc, rounded to bf16 and packed; row sums from the rounded values
+  auto weigh = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4& v = sc[2 * s + (i >> 1)][t];
+          w[i] = cvt_pk_bf16(__builtin_amdgcn_exp2f(v[2 * (i & 1)]), __builtin_amdgcn_exp2f(v[2 * (i & 1) + 1]));
+          lsum[t] = add_pk_bf16(w[i], lsum[t]);
+        }
+        pf[s][t] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+  };
+  auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) o[d][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    lsum[0] = lsum[1] = 0.f;
+  };
+  auto scores = [&](bool from_zero) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          sc[kt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][ks], qf[t][ks], ks == 0 ? (from_zero ? f32x4{0.f, 0.f, 0.f, 0.f} : negm[t]) : sc[kt][t], 0, 0, 0);
+  };
+  // maximum of sc[kt][t] over kt0 <= kt < kt1 and the four lanes of a query
+  auto maximum = [&](int t, int kt1) __attribute__((always_inline)) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+      if (kt < kt1)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[kt][t][r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    return fmaxf(mx, __shfl_xor(mx, 32, 64));
+  };
+  auto mask = [&](int kvalid) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (key_of(kt, r) >= kvalid) { sc[kt][0][r] = -INFINITY; sc[kt][1][r] = -INFINITY; }
+  };
+
+  // Tile 0, in plain order: its scores, the reference of every query (its maximum over the tile's first 32 keys, the valid ones
+  // of them), its weights; and tile 1's keys
+  clear();
+  vm_wait<KG == 1 ? 2 * (CK + CV) : 2 * CV>();   // K tiles 0 and 1
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
+  read_k(0);
+  lds_wait<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  scores(true);
+  const int kvalid = (int)(L - (int64_t)(t0 + cnt - 1) * 64);    // of tile 0: >= 1, < 64 only if it is ragged
+  if (kvalid < 64) mask(kvalid);
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const float m = maximum(t, 2);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) negm[t][r] = -m;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) sc[kt][t] += negm[t];
+  }
+  weigh();
+  __builtin_amdgcn_sched_barrier(0);
+  read_k(1);
+  lds_wait<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();                           // K stage 0 is free
+  if constexpr (KG == 1) { load_v(2); load_k(4); } else load_k(2);
+  vm_wait<KG == 1 ? CK + CV : CK>();         // V tiles 0 and 1, and K tiles 2 and 3 of four stages
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  if (wave >= 4) __builtin_amdgcn_s_barrier();   // the second half starts half a turn later
+  __builtin_amdgcn_sched_barrier(0);
+  for (int j = 0; j < n0 - 1; ++j) {
+    if (KG == 2 && j >= cnt - 1) {           // this key group is a tile shorter: it only keeps step
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_s_barrier();
+      continue;
+    }
+    // scores of tile j + 1 and the weighted sum of tile j, whose V^T fragments take the place of the used keys
+    __builtin_amdgcn_s_setprio(1);
+    static_for<KS>([&](auto k_) __attribute__((always_inline)) {
+      constexpr int ks = decltype(k_)::value;
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          sc[kt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][ks], qf[t][ks], ks == 0 ? negm[t] : sc[kt][t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (ks > 0) read_v4(j, std::integral_constant<int, ks - 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    static_for<KS>([&](auto g_) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_)::value;
+      lds_wait<4 * (g == 0 ? KS - 2 : KS - 1 - g)>();
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<4>([&](auto i_) __attribute__((always_inline)) {
+        constexpr int f = g * 4 + decltype(i_)::value, s = f / DT, d = f % DT;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) o[d][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][d], __builtin_bit_cast(bf16x8, pf[s][t]), o[d][t], 0, 0, 0);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (g == 0) read_v4(j, std::integral_constant<int, KS - 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (KG == 2) vm_wait<0>();     // K tile j + 2, requested two turns ago
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    // the other half multiplies: tile j + 2's keys, tiles to come, weights of tile j + 1
+    read_k(j + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    // into stages that this group's wavefronts (one group: both halves) have read
+    if constexpr (KG == 1) { load_v(j + 3); load_k(j + 5); } else { load_v(j + 2); load_k(j + 3); }
+    __builtin_amdgcn_sched_barrier(0);
+    weigh();
+    if constexpr (KG == 1) vm_wait<CK + CV>();   // what was requested before this turn: V tile j + 2, K tile j + 4
+    lds_wait<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // the last tile's weighted sum
+  static_for<KS>([&](auto g_) __attribute__((always_inline)) { read_v4(cnt - 1, g_); });
+  lds_wait<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<2>([&](auto s_) __attribute__((always_inline)) {
+    constexpr int s = decltype(s_)::value;
+#pragma unroll
+    for (int d = 0; d < DT; ++d)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) o[d][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][d], __builtin_bit_cast(bf16x8, pf[s][t]), o[d][t], 0, 0, 0);
+  });
+  if (wave < 4) __builtin_amdgcn_s_barrier();    // the halves meet again
+  __builtin_amdgcn_sched_barrier(0);
+  tile_barrier();                            // nothing is in flight any more
+
+  auto total = [&](float v) __attribute__((always_inline)) { v += __shfl_xor(v, 16, 64); return v + __shfl_xor(v, 32, 64); };
+  float ltot[2] = {total(lsum[0]), total(lsum[1])};
+  if (__syncthreads_or(!(ltot[0] <= 0x1p100f) || !(ltot[1] <= 0x1p100f))) {
+    // overflow somewhere in the block: the classical online softmax, tile by tile
+    clear();
+#pragma unroll
+    for (int t = 0; t < 2; ++t) negm[t][0] = INFINITY;
+    for (int j = 0; j < n0; ++j) {
+      __syncthreads();
+      load_k(j); load_v(j);
+      tile_barrier();
+      if (KG == 2 && j >= cnt) continue;
+      read_k(j);
+      static_for<KS>([&](auto g_) __attribute__((always_inline)) { read_v4(j, g_); });
+      lds_wait<0>();
+      __builtin_amdgcn_sched_barrier(0);
+      scores(true);
+      if (j == 0 && kvalid < 64) mask(kvalid);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        // no key above -inf yet: any finite reference leaves zero weights
+        const float m = fmaxf(maximum(t, 4), -negm[t][0]), ref = m == -INFINITY ? 0.f : m;
+        const float alpha = __builtin_amdgcn_exp2f(-negm[t][0] - ref);
+        negm[t][0] = -m;
+        lsum[t] *= alpha;
+#pragma unroll
+        for (int d = 0; d < DT; ++d) o[d][t] *= alpha;
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) sc[kt][t] -= ref;
+      }
+      weigh();
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int d = 0; d < DT; ++d)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) o[d][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[s][d], __builtin_bit_cast(bf16x8, pf[s][t]), o[d][t], 0, 0, 0);
+    }
+    ltot[0] = total(lsum[0]); ltot[1] = total(lsum[1]);
     __syncthreads();
   }
-  if (kg == 0) {
-    float m = mrun, a0 = 1.f, a1 = 0.f, lall = ltot;
-    if constexpr (KG == 2) {
-      const float m1 = mine[0], l1 = mine[64];
-      const float m0 = empty ? -INFINITY : mrun;
-      m = fmaxf(m0, m1);
-      a0 = __builtin_amdgcn_exp2f(m0 - m); a1 = __builtin_amdgcn_exp2f(m1 - m);   // 2^-inf = 0
-      lall = ltot * a0 + l1 * a1;
+
+  float mrun[2] = {-negm[0][0], -negm[1][0]};
+  float4* const xch = (float4*)smem + (size_t)qt * (2 * DT + 1) * 64 + lane;     // [qt][2 * DT + 1][64 lanes]
+  if constexpr (KG == 2) {
+    // the two key groups meet in LDS: group 1 publishes m, l, O^T, and group 0 goes on with both
+    if (kg == 1) {
+      xch[0] = make_float4(mrun[0], mrun[1], ltot[0], ltot[1]);
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) xch[(1 + 2 * d + t) * 64] = make_float4(o[d][t][0], o[d][t][1], o[d][t][2], o[d][t][3]);
     }
-    // this lane's O^T value (register r of channel tile a) over both key groups, scaled by w0 / w1
-    auto both = [&](int a, int r, float w0, float w1) __attribute__((always_inline)) {
-      float v = oacc[a][r] * w0;
-      if constexpr (KG == 2) v += mine[(2 + a * 16 + r) * 64] * w1;
-      return v;
-    };
-    const int64_t qi = q0 + lr;
-    if (slot >= 0) {
-      // one key range of a split work id: publish m, l and the unnormalised O^T for the merge kernel.
-      // Slot layout (floats): m[QB], l[QB], then O as [HD/4][QB queries][4 channels].
-      float* ps = partial + (size_t)slot * (2 * QB + QB * HD);
-      const int ql = qt * 32 + lr;
-      if (lg == 0) { ps[ql] = m; ps[QB + ql] = lall; }
+    __syncthreads();
+    if (kg == 1) return;
+    const float4 ml = xch[0];
 #pragma unroll
-      for (int a = 0; a < DT; ++a)
+    for (int t = 0; t < 2; ++t) {
+      const float m1 = t ? ml.y : ml.x, l1 = t ? ml.w : ml.z, m = fmaxf(mrun[t], m1);
+      const float a0 = __builtin_amdgcn_exp2f(mrun[t] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+      mrun[t] = m;
+      ltot[t] = ltot[t] * a0 + l1 * a1;
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          float4 v;
-          v.x = both(a, g4 * 4 + 0, a0, a1);
-          v.y = both(a, g4 * 4 + 1, a0, a1);
-          v.z = both(a, g4 * 4 + 2, a0, a1);
-          v.w = both(a, g4 * 4 + 3, a0, a1);
-          *(float4*)(ps + 2 * QB + ((size_t)(a * 8 + g4 * 2 + lg) * QB + ql) * 4) = v;
-        }
-    } else {
-      // O[q][head*HD + c] = O^T[c][q]: a lane holds 4 consecutive channels per register quad.  The 32 x HD
-      // tile of this wavefront goes through LDS (the tile buffers are free; a wavefront only touches its own
-      // rows, and LDS serves a wavefront's accesses in order) so that global memory sees whole rows, 16
-      // bytes per lane.  8-byte units are XOR-swizzled with the row so that the column-wise writes spread
-      // over the banks.
-      const float inv = 1.f / lall;
-      const float w0 = a0 * inv, w1 = a1 * inv;
-      constexpr int UPR = HD / 4, CPR = HD / 8, RPI = 64 / CPR;      // units, 16-byte chunks per row; rows per read
-      constexpr int STG0 = KG == 2 ? QG * (DT * 16 + 2) * 64 * 4 / 16 : 0;    // behind the exchange area
-      uint2* stg = (uint2*)(smem + STG0) + qt * 32 * UPR;
-#pragma unroll
-      for (int a = 0; a < DT; ++a)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          uint2 pk;
-          pk.x = cvt_pk_bf16(both(a, g4 * 4 + 0, w0, w1), both(a, g4 * 4 + 1, w0, w1));
-          pk.y = cvt_pk_bf16(both(a, g4 * 4 + 2, w0, w1), both(a, g4 * 4 + 3, w0, w1));
-          stg[lr * UPR + ((a * 8 + g4 * 2 + lg) ^ (lr & (UPR - 1)))] = pk;
-        }
-      const uint4* stg16 = (const uint4*)stg;
-#pragma unroll
-      for (int it = 0; it < 32 / RPI; ++it) {
-        const int row = it * RPI + lane / CPR, p = lane % CPR;
-        uint4 dv = stg16[row * CPR + p];
-        // units 2p and 2p+1 of the swizzled row are the halves of chunk p ^ (swizzle >> 1), exchanged for odd rows
-        if (row & 1) dv = make_uint4(dv.z, dv.w, dv.x, dv.y);
-        const int c = p ^ ((row & (UPR - 1)) >> 1);
-        if (q0 + row < S) *(uint4*)(out + (q0 + row) * ldo + (int64_t)head * HD + c * 8) = dv;
+      for (int d = 0; d < DT; ++d) {
+        const float4 v = xch[(1 + 2 * d + t) * 64];
+        o[d][t] = o[d][t] * a0 + f32x4{v.x, v.y, v.z, v.w} * a1;
       }
+    }
+  }
+  if (slot >= 0) {
+    // one key range of a split work id: publish m, l and the unnormalised O^T for the merge kernel.
+    // Slot layout (floats): m[QB], l[QB], then O as [HD/4][QB queries][4 channels].
+    float* ps = partial + (size_t)slot * (2 * QB + QB * HD);
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int ql = qt * 32 + t * 16 + lr;
+      if (lg == 0) { ps[ql] = mrun[t]; ps[QB + ql] = ltot[t]; }
+#pragma unroll
+      for (int d = 0; d < DT; ++d) *(f32x4*)(ps + 2 * QB + ((size_t)(d * 4 + lg) * QB + ql) * 4) = o[d][t];
+    }
+  } else {
+    // O[q][head*HD + c] = O^T[c][q]: a lane holds 4 consecutive channels per accumulator tile.  The 32 x HD tile of this
+    // wavefront goes through LDS (a wavefront only touches its own rows, and LDS serves a wavefront's accesses in order) so that
+    // global memory sees whole rows, 16 bytes per lane.  8-byte units are XOR-swizzled with the row.
+    constexpr int UPR = HD / 4, CPR = HD / 8, RPI = 64 / CPR;      // units, 16-byte chunks per row; rows per read
+    constexpr int STG0 = KG == 2 ? QG * (2 * DT + 1) * 64 : 0;     // behind the exchange area
+    uint2* stg = (uint2*)(smem + STG0) + qt * 32 * UPR;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const float inv = 1.f / ltot[t];
+      const int row = t * 16 + lr;
+#pragma unroll
+      for (int d = 0; d < DT; ++d)
+        stg[row * UPR + ((d * 4 + lg) ^ (row & (UPR - 1)))] = make_uint2(cvt_pk_bf16(o[d][t][0] * inv, o[d][t][1] * inv), cvt_pk_bf16(o[d][t][2] * inv, o[d][t][3] * inv));
+    }
+    const uint4* stg16 = (const uint4*)stg;
+#pragma unroll
+    for (int it = 0; it < 32 / RPI; ++it) {
+      const int row = it * RPI + lane / CPR, p = lane % CPR;
+      uint4 dv = stg16[row * CPR + p];
+      // units 2p and 2p+1 of the swizzled row are the halves of chunk p ^ (swizzle >> 1), exchanged for odd rows
+      if (row & 1) dv = make_uint4(dv.z, dv.w, dv.x, dv.y);
+      const int c = p ^ ((row & (UPR - 1)) >> 1);
+      if (q0 + row < S) *(uint4*)(out + (q0 + row) * ldo + (int64_t)head * HD + c * 8) = dv;
     }
   }
 }
@@ -725,7 +1077,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ pa
 // partial results of at most 256 blocks of at most 256 queries
 size_t attn_bf16_scratch_bytes(int d) { return (size_t)256 * (512 + 256 * (size_t)d) * sizeof(float); }
 
-static constexpr int attn_slots(int qb, int kg) { return 256 * (256 / (qb * kg)); }   // blocks that the chip holds at once
+static constexpr int attn_slots(int qb, int kg) { return qb == 128 && kg < 2 ? 512 : 256; }   // blocks that the chip holds at once
 // What a call takes: queries per block (32: k_attn_few), key groups, and key ranges that the work ids of the last round are cut into
 struct AttnRoute { int qb, kg, parts; };
 static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratch) {
@@ -768,18 +1120,21 @@ extern "C" void dp_attn_bf16_route(int64_t S, int64_t L, int32_t h, int32_t d, i
   for (int i = 0; i < 3; ++i) queries_groups_ranges[i] = v[i];
 }
 
-template <int HD, int QG, int KG>
+// KG == 0: k_attn_bf16 with blocks of QB queries; else k_attn_turns
+template <int HD, int QB, int KG>
 static void launch_attn_cfg(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, int64_t k_head_stride,
                             int64_t k_row0, const bf16_t* vt, int64_t vt_row_stride, int64_t S, int64_t L,
                             int h, bf16_t* out, int64_t ldo, float* scratch, int parts, const AttnQNorm& qn, hipStream_t st) {
-  constexpr int QB = QG * 32;
-  constexpr int lds = KG * 2 * (64 * (HD / 8) + HD * 8) * 16;
+  constexpr int tile = (64 * (HD / 8) + HD * 8) * 16, lds = (KG ? 4 : 2) * tile, threads = KG ? 512 : QB * 2;
+  void (*const kernel)(const bf16_t*, int64_t, const bf16_t*, int64_t, int64_t, const bf16_t*, int64_t, int64_t, int64_t, bf16_t*, int64_t, int, int, int, int, float*, AttnQNorm) = [] {
+    if constexpr (KG) return &k_attn_turns<HD, KG>; else return &k_attn_bf16<HD, QB / 32>;
+  }();
   const int qblocks = (int)((S + QB - 1) / QB);
   const int W = qblocks * h, n_tail = W % attn_slots(QB, KG), n_full = W - n_tail;
   dim3 grid((unsigned)(n_full + (n_tail * parts + 7) / 8 * 8));
   static std::atomic<uint64_t> done;
-  allow_dynamic_lds((const void*)k_attn_bf16<HD, QG, KG>, lds, done);
-  k_attn_bf16<HD, QG, KG><<<grid, QG * KG * 64, lds, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, out, ldo, qblocks, n_full, n_tail, parts, scratch, qn);
+  allow_dynamic_lds((const void*)kernel, lds, done);
+  kernel<<<grid, threads, lds, st>>>(q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, out, ldo, qblocks, n_full, n_tail, parts, scratch, qn);
   if (parts > 1) {
     constexpr int QPB = 256 / (HD / 4);                  // queries per merge block
     k_attn_merge<HD, QB><<<(unsigned)(n_tail * (QB / QPB)), 256, 0, st>>>(scratch, n_full, n_tail, parts, qblocks, S, out, ldo);
@@ -803,12 +1158,17 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
   if (S <= 0 || L <= 0) return;
   const AttnQNorm qn = qnorm ? *qnorm : AttnQNorm{nullptr, 0, 0, 0.f, 0.f, 0.f};
   const AttnRoute r = attn_bf16_route(S, L, h, d, scratch != nullptr);
+  // Heads of 64 spend more of a tile on exponentials than on products, so a turn of the one is longer than of the other; it takes
+  // a full round of blocks and a few tiles to gain (us, k_attn_bf16 and k_attn_turns): 4096 x 1024 x 16 19.9 and 19.6, x 4096 66.5 and
+  // 63.2, 5000 x 7000 x 40 353 and 329; 3000 x 2000 x 14 29.1 and 30.9, 3000 x 8000 x 16 104.4 and 105.5, 4096 x 512 x 16 12.6 and 13.1
+  const bool turns = L >= 1024 && (S + 255) / 256 * h >= 256;
 #define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo
 #define ATTN_CASE(HD) do { \
     if (r.qb == 32) launch_attn_few<HD>(ATTN_ARGS, qn, st); \
-    else if (r.qb == 256) launch_attn_cfg<HD, 8, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
-    else if (r.kg == 1) launch_attn_cfg<HD, 4, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
-    else launch_attn_cfg<HD, 4, 2>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.qb == 256 && (HD == 128 || turns)) launch_attn_cfg<HD, 256, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.qb == 256) launch_attn_cfg<64, 256, 0>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.kg == 1) launch_attn_cfg<HD, 128, 0>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else launch_attn_cfg<HD, 128, 2>(ATTN_ARGS, scratch, r.parts, qn, st); \
   } while (0)
   if (d == 128) ATTN_CASE(128); else ATTN_CASE(64);
 #undef ATTN_CASE

@@ -1106,10 +1106,10 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // Cutting K.  A long K over few tiles leaves most CUs idle, and small tiles in the hundreds move several times the bytes of
 // large ones through the caches.  Tiles whose K is cut over blocks until about one round of CUs is full do neither, for the
 // price of one fp32 partial result per range, written and read once.  Costs in us per launch, from measurement: a k-tile of a
-// block 0.5 (128 x 128), 0.7 (128 x 256), 0.86 (160 x 256), 1.0 (192 x 256), 1.25 (256 x 256), 1.55 (320 x 256), 0.27 for each 64 x 64 block on the CU; 7 for both
+// block 0.5 (128 x 128), 0.75 (128 x 256), 0.86 (160 x 256), 1.0 (192 x 256), 1.25 (256 x 256), 1.55 (320 x 256), 0.27 for each 64 x 64 block on the CU; 7 for both
 // launches and a block's ends, partials at 6.5 TB/s; uncut 0.185 per k-tile and 3.3 (32 x 64), 0.24 per k-tile and 64 x 64 block
-// on the CU and 5, 9 (128 x 128) or 14 for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 52 (128 x 256,
-// 3) / 75, 1008 x 2048 x 8192 42 (128 x 256, 4) / 64, 2560 x 2048 x 8192 82 (160 x 256, 2) / 92; left uncut 1288 x 5120 x 13824 164.  Outputs narrower than 768 columns
+// on the CU and 5, 9 (128 x 128) or 14 for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 52 (160 x 256,
+// 4) / 75, 1008 x 2048 x 8192 42 (128 x 256, 4) / 64, 2560 x 2048 x 8192 82 (160 x 256, 2) / 92; left uncut 1288 x 5120 x 13824 164.  Outputs narrower than 768 columns
 // are left on the 64-, 160- and 256-row tiles and on the figures of an earlier measurement (a k-tile 1.25 at 160
 // rows, 8 for ends and 3 for the second launch, 4 TB/s).  That line is no property of the tiles: the 128-row ones have not been
 // measured below it, and the parity tests of the cut 160- and 256-row tiles are shapes of that side.
@@ -1126,7 +1126,7 @@ static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats
               : family == TILE_128 ? 0.5 * (double)KT + 9 : 1.3 * (double)(KT * ((t256 + 255) / 256)) + 8;
   if (family == TILE_BIG && !narrow) {
     const GemmRoute u = big_tile(M, N, EPI_RESID);
-    const double kt = u.bm == 128 ? 0.7 : u.bm == 160 ? 0.86 : u.bm == 192 ? 1.0 : u.bm == 256 ? 1.25 : 1.55;
+    const double kt = u.bm == 128 ? 0.75 : u.bm == 160 ? 0.86 : u.bm == 192 ? 1.0 : u.bm == 256 ? 1.25 : 1.55;
     best = kt * (double)(KT * ((tiles(u.bm, u.bn) + 255) / 256)) + 14;
   }
   best *= 0.9;                                         // not for a few per cent
@@ -1138,7 +1138,7 @@ static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats
     struct { double c; GemmRoute t; } opt[5] = {
         {narrow && t256 * p <= 256 && deep ? 1.3 * kt + big : 1e30, {256, 256, 2, p}},
         {fits160 && t160 * p <= 256 && deep ? (narrow ? 1.25 : 0.86) * kt + big : 1e30, {160, 256, 3, p}},
-        {!narrow && tiles(128, 256) * p <= 256 && deep ? 0.7 * kt + big : 1e30, {128, 256, 3, p}},
+        {!narrow && tiles(128, 256) * p <= 256 && deep ? 0.75 * kt + big : 1e30, {128, 256, 3, p}},
         {!narrow && tiles(128, 128) * p <= 256 && deep ? 0.5 * kt + big : 1e30, {128, 128, 4, p}},
         {t64 * p <= 512 && KT / p >= 4 ? 0.27 * kt * (double)((t64 * p + 255) / 256) + small : 1e30, {64, 64, 4, p}}};
     for (const auto& o : opt)
