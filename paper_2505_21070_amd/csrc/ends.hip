@@ -310,6 +310,221 @@ __global__ __launch_bounds__(512, 2) void k_head(const bf16_t* __restrict__ x, i
   }
 }
 
+// The output head where the modulation is not worth a product of its own (see head_streamed): the modulation moves into the
+// weights, W' = (1 + scale) W, rounded to bf16 once per call, and the statistics out of the product:
+//   out = rstd (x W' - mean sum_k W') + sum_k shift W + b
+// so the tokens stream through the MFMAs as they are, unrounded, and a row need not be held until its mean is known.
+// k_head_fold: W' in fragment order, and each 64 channels' share of the two sums over k (of W' as rounded, so that the mean
+// cancels) to pc[D / 64][2][P].
+__global__ __launch_bounds__(256) void k_head_fold(const float* __restrict__ e, int parts, const bf16_t* __restrict__ ebias,
+                                                   const float* __restrict__ mhead, int D, const uint4* __restrict__ wf, int P,
+                                                   uint4* __restrict__ wm, float* __restrict__ pc) {
+  __shared__ float mul[64], add[64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k0 = blockIdx.x * 64;
+  if (tid < 64) {
+    float v = bf16_to_f32(ebias[k0 + tid]);
+    for (int i = 0; i < parts; ++i) v += e[(int64_t)i * D + k0 + tid];
+    add[tid] = mhead[k0 + tid] + v;
+    mul[tid] = 1.f + (mhead[D + k0 + tid] + v);
+  }
+  __syncthreads();
+  const int ptiles = P >> 4;
+  for (int tile = wave; tile < ptiles; tile += 4) {
+    float c1 = 0.f, c2 = 0.f;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int64_t at = ((int64_t)(blockIdx.x * 2 + c) * ptiles + tile) * 64 + lane;
+      const uint4 w4 = wf[at];
+      const uint32_t w[4] = {w4.x, w4.y, w4.z, w4.w};
+      uint32_t r[4];
+      const int kl = c * 32 + (lane >> 4) * 8;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float a = __uint_as_float(w[i] << 16), b = __uint_as_float(w[i] & 0xffff0000u);
+        c2 += add[kl + 2 * i] * a; c2 += add[kl + 2 * i + 1] * b;
+        r[i] = cvt_pk(mul[kl + 2 * i] * a, mul[kl + 2 * i + 1] * b);
+        c1 += __uint_as_float(r[i] << 16); c1 += __uint_as_float(r[i] & 0xffff0000u);
+      }
+      wm[at] = make_uint4(r[0], r[1], r[2], r[3]);
+    }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) { c1 += __shfl_xor(c1, o, 64); c2 += __shfl_xor(c2, o, 64); }
+    if (lane < 16) {
+      pc[((int64_t)blockIdx.x * 2 + 0) * P + tile * 16 + lane] = c1;
+      pc[((int64_t)blockIdx.x * 2 + 1) * P + tile * 16 + lane] = c2;
+    }
+  }
+}
+// A block of 8 wavefronts owns TB = TG * RT * 16 tokens; wavefront w has RT * 16 of them and one of KH = 8 / TG shares of the
+// channels, dealt in slots of 32 (slot i * KH + w / TG in step i), and walks them in a ring of NS stages in LDS: its tokens'
+// values, in operand order, and a TG-th of the slot's weights, which the TG wavefronts of a share read; NS - 1 steps are in
+// flight, waited for by count.  (Into registers the compiler waits for all loads in flight at every branch.)  A step's
+// operands are read from LDS while the step before is multiplied and added up.  Statistics: a lane sums its values' distances
+// from the mean of its first eight, and their squares, so what cancels in the variance is no larger than the token's own
+// spread; the lanes of a token meet in LDS by their own means.  blockIdx.y: 64 of the 4C output values.
+// What bounds it: one pass over the tokens at 14400 x 5120 (147 MB in 28.6 us, 5.1 TB/s; k_head 57, which holds a block's rows in
+// registers and so loads and computes in turn); with fewer tokens the 40 to 160 steps of a block, latency each.  Reading the
+// operands of a step behind its own barrier: 54 instead of 53 us for the call; asking for all weights ahead: 56.
+template <int TG, int RT, int NS>
+__global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict__ x, int64_t S, int D, float eps,
+                                                 const uint4* __restrict__ wm, const float* __restrict__ pc,
+                                                 const bf16_t* __restrict__ bias, int P4, float* __restrict__ v_out, int tok, int tw,
+                                                 int C, int v_aligned) {
+  constexpr int KH = 8 / TG, TB = TG * RT * 16, P = NS - 1;        // shares of the channels, tokens, steps in flight
+  constexpr int NW = 4 / TG, NL = NW + RT;             // weight fragments and loads per wavefront and step
+  constexpr int STAGE = (KH * 4 + 8 * RT) * 64;        // 16-byte chunks: the shares' weights, the wavefronts' tokens
+  static_assert(4 % TG == 0 && NS * STAGE * 16 >= KH * TB * 68 * 4, "the partial products fit the ring");
+  __shared__ __align__(16) uint4 ring[NS * STAGE];     // afterwards the partial products
+  __shared__ float2 stat[KH * 4][TB];             // [share, lane quarter][token]: mean, sum of squares about it
+  __shared__ float cs[4][128], tm[TB], tr[TB];
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, lt = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tg = wave % TG, kh = wave / TG;
+  const int64_t s0 = (int64_t)blockIdx.x * TB;
+  const int chunks = D >> 5, ptiles = P4 >> 4, steps = (chunks + KH - 1) / KH;
+  const bf16_t* const xb = x + s0 * D;
+  const int rows = (int)(S - s0 < TB ? S - s0 : TB);
+  uint32_t xo[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int r = (tg * RT + t) * 16 + lt;
+    xo[t] = (uint32_t)((r < rows ? r : rows - 1) * D + q * 8) * 2;
+  }
+  uint4* const wst = ring + kh * 256;                  // of stage 0: this share's weights, this wavefront's tokens
+  uint4* const xst = ring + KH * 256 + wave * RT * 64;
+  auto load = [&](int i, int st) __attribute__((always_inline)) {
+    const int c = i * KH + kh < chunks ? i * KH + kh : chunks - 1;      // past the end the last one is loaded, and not used
+#pragma unroll
+    for (int f = 0; f < NW; ++f)
+      __builtin_amdgcn_global_load_lds((glb_void_t*)(wm + ((int64_t)c * ptiles + blockIdx.y * 4 + tg * NW + f) * 64 + lane), (lds_void_t*)(wst + st * STAGE + (tg * NW + f) * 64), 16, 0, 0);
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+      __builtin_amdgcn_global_load_lds((glb_void_t*)((const char*)(xb + c * 32) + xo[t]), (lds_void_t*)(xst + st * STAGE + t * 64), 16, 0, 0);
+  };
+  const uint32_t wl = (uint32_t)(uintptr_t)(lds_void_t*)wst + (uint32_t)lane * 16, xl = (uint32_t)(uintptr_t)(lds_void_t*)xst + (uint32_t)lane * 16;
+  f32x4 acc[RT][4];
+  float sh[RT], sd[RT], sq[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    sh[t] = sd[t] = sq[t] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  u32x4 xr[2][RT], w[2][4];
+  auto read = [&](int st, auto b_) __attribute__((always_inline)) {
+    constexpr int b = decltype(b_)::value;
+    const uint32_t o = (uint32_t)st * STAGE * 16;
+    static_for<RT>([&](auto t_) __attribute__((always_inline)) { constexpr int t = decltype(t_)::value; xr[b][t] = lds_read16_raw<t * 1024>(xl + o); });
+    static_for<4>([&](auto j_) __attribute__((always_inline)) { constexpr int j = decltype(j_)::value; w[b][j] = lds_read16_raw<j * 1024>(wl + o); });
+  };
+  auto elem = [&](const u32x4& v, int i) __attribute__((always_inline)) { return __uint_as_float((i & 1) ? (v[i >> 1] & 0xffff0000u) : (v[i >> 1] << 16)); };
+  auto add = [&](int i, auto b_) __attribute__((always_inline)) {
+    constexpr int b = decltype(b_)::value;
+    if (i == 0) {
+#pragma unroll
+      for (int t = 0; t < RT; ++t) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sh[t] += elem(xr[b][t], k);
+        sh[t] *= 0.125f;
+      }
+    }
+    if (i * KH + kh >= chunks) return;
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[b][j]), __builtin_bit_cast(bf16x8, xr[b][t]), acc[t][j], 0, 0, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float d = elem(xr[b][t], k) - sh[t];
+        sd[t] += d;
+        sq[t] += d * d;
+      }
+    }
+  };
+#pragma unroll
+  for (int z = 0; z < P; ++z) load(z, z);
+  int st = 0;
+  for (int i0 = 0; i0 < steps + 1; i0 += 2) {
+    static_for<2>([&](auto u_) __attribute__((always_inline)) {
+      constexpr int u = decltype(u_)::value;
+      const int i = i0 + u;
+      __builtin_amdgcn_sched_barrier(0);
+      if (i < steps) {
+        vm_wait<(P - 1) * NL>();                       // this step's loads have landed
+        __builtin_amdgcn_s_barrier();                  // everyone's have, and the stage of the step before is free
+        __builtin_amdgcn_sched_barrier(0);
+        load(i + P, st == 0 ? NS - 1 : st - 1);
+        read(st, u_);
+        __builtin_amdgcn_sched_barrier(0);
+        st = st + 1 == NS ? 0 : st + 1;
+      }
+      if (i > 0 && i <= steps) add(i - 1, std::integral_constant<int, u ^ 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      lds_wait<0>();
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  // values of share k that a lane has had
+  auto share = [&](int k) __attribute__((always_inline)) { return (float)(8 * ((chunks - k + KH - 1) / KH)); };
+  tile_barrier();                                      // nothing is in flight, everyone is done with the ring
+  float (*const part)[TB][68] = (float (*)[TB][68])ring;           // [share][token][64 values, padded]
+  {
+    const float cnt = share(kh);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+      const float m = cnt > 0.f ? sd[t] / cnt : 0.f;
+      const int tk = (tg * RT + t) * 16 + lt;
+      stat[kh * 4 + q][tk] = make_float2(sh[t] + m, sq[t] - sd[t] * m);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *(f32x4*)&part[kh][tk][j * 16 + q * 4] = acc[t][j];
+    }
+    // this block's 64 columns of both sums over k: four shares of the channels
+    float c = 0.f;
+    const float* pp = pc + (int64_t)((tid >> 6) & 1) * P4 + blockIdx.y * 64 + (tid & 63);
+#pragma unroll 4
+    for (int i = tid >> 7; i < D >> 6; i += 4) c += pp[(int64_t)i * 2 * P4];
+    cs[tid >> 7][tid & 127] = c;
+  }
+  __syncthreads();
+  if (tid < TB) {
+    float m = 0.f, v = 0.f;
+    for (int k = 0; k < KH; ++k) {
+      const float cnt = share(k);
+      for (int i = 0; i < 4; ++i) m += stat[k * 4 + i][tid].x * cnt;
+    }
+    m /= (float)D;
+    for (int k = 0; k < KH; ++k) {
+      const float cnt = share(k);
+      for (int i = 0; i < 4; ++i) {
+        const float2 a = stat[k * 4 + i][tid];
+        v += a.y + cnt * (a.x - m) * (a.x - m);
+      }
+    }
+    tm[tid] = m;
+    tr[tid] = rsqrtf(v / (float)D + eps);
+  }
+  __syncthreads();
+  for (int i = tid; i < TB * 16; i += 512) {           // four values of one token each
+    const int tk = i >> 4, r = (i & 15) * 4, o0 = blockIdx.y * 64 + r;
+    if (s0 + tk >= S) continue;
+    f32x4 v = *(const f32x4*)&part[0][tk][r];
+#pragma unroll
+    for (int k = 1; k < KH; ++k) v += *(const f32x4*)&part[k][tk][r];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float c1 = cs[0][r + k] + cs[1][r + k] + cs[2][r + k] + cs[3][r + k];
+      const float c2 = cs[0][64 + r + k] + cs[1][64 + r + k] + cs[2][64 + r + k] + cs[3][64 + r + k];
+      v[k] = tr[tk] * (v[k] - tm[tk] * c1) + c2 + bf16_to_f32(bias[o0 + k]);
+    }
+    float* o = v_out + patch_elem(s0 + tk, o0, tok, tw, C);         // consecutive channels of one pixel: C % 16 == 0
+    if (v_aligned) *(f32x4*)o = v;
+    else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) o[k] = v[k];
+    }
+  }
+}
+
 static const char* validate(const dp_ends_config* c) {
   if (!c) return "null config";
   if (c->dim < 1 || c->tok_h < 1 || c->tok_w < 1 || c->channels < 1 || c->max_frames < 1) return "non-positive size";
@@ -340,6 +555,9 @@ static bool embed_fused(const dp_ends_config& c, int64_t S) {
   return embed_frags(c) && (!embed_gemm(c) || S * c.dim * 4 * c.channels <= ((int64_t)1 << 30));
 }
 static bool head_fused(const dp_ends_config& c) { return embed_frags(c) && c.dim <= 5120; }
+// k_head_stream: where the timestep product is added up by a launch of its own in any case (launch_gemv: more than 2048 rows),
+// whose place k_head_fold takes, and both sets of fragments fit the repacked head matrix, whose rows are padded to 256.
+static bool head_streamed(const dp_ends_config& c) { return head_fused(c) && c.dim > 2048 && c.channels <= 32; }
 
 static size_t carve(dp_ends* s, void* base) {
   const dp_ends_config& c = s->cfg;
@@ -490,6 +708,24 @@ extern "C" int dp_embed_forward(dp_ends_t* s, const float* latent, void* x_out, 
   return DP_OK;
 }
 
+// e: the timestep product's slices, without its bias
+static void launch_head_streamed(dp_ends* s, const float* e, int parts, const void* x_in, float* v_out, int64_t S, hipStream_t st) {
+  const dp_ends_config& c = s->cfg;
+  const int va = ((uintptr_t)v_out & 15) == 0, P = (int)s->P;
+  uint4* const wm = (uint4*)s->w_head_t + (size_t)c.dim * P / 8;    // behind the fragments as packed
+  float* const pc = s->e1;                                          // the first product's slices have been read: D / 32 * P <= 8 D floats
+  k_head_fold<<<(unsigned)(c.dim / 64), 256, 0, st>>>(e, parts, (const bf16_t*)s->w.bt2, s->mhead, c.dim, (const uint4*)s->w_head_t, P, wm, pc);
+  // Tokens per block, by whole rounds of blocks (one to a CU) and what a round takes.  16 / 32 / 64 tokens in us (the whole call, of
+  // which 24 are the timestep's and k_head_fold): 3600 x 5120 38.4 / 42.0 / 51.2, 7200 x 5120 53.2 / 42.7 / 51.3, 14400 x 5120 80.9 /
+  // 60.7 / 53.2, 18720 x 4096 79.0 / 75.0 / 64.2, 6240 x 2112 31.7 / 25.7 / 29.9.
+  auto cost = [&](int tokens, int us) { return ((S + tokens - 1) / tokens * (P / 64) + 255) / 256 * us; };
+  const int64_t c16 = cost(16, 14), c32 = cost(32, 19), c64 = cost(64, 27);
+#define HEAD_CASE(TG, RT, NS) k_head_stream<TG, RT, NS><<<dim3((unsigned)((S + 16 * TG * RT - 1) / (16 * TG * RT)), (unsigned)(P / 64)), 512, 0, st>>>((const bf16_t*)x_in, S, c.dim, c.eps, \
+    wm, pc, (const bf16_t*)s->w.b_head, P, v_out, (int)s->tok, c.tok_w, c.channels, va)
+  if (c64 <= c32 && c64 <= c16) HEAD_CASE(2, 2, 4); else if (c32 <= c16) HEAD_CASE(2, 1, 5); else HEAD_CASE(1, 1, 3);
+#undef HEAD_CASE
+}
+
 static void launch_head(dp_ends* s, const void* x_in, float* v_out, int64_t S, hipStream_t st) {
   const dp_ends_config& c = s->cfg;
   const int ng = (c.dim / 64 + 7) / 8, xa = ((uintptr_t)x_in & 15) == 0, va = ((uintptr_t)v_out & 15) == 0;
@@ -514,15 +750,17 @@ static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int 
   const int64_t D = c.dim, S = s->tok * n_frames, n = S * s->P;
   // mod rows: shift, scale
   const GemvTable<T> table{(const T*)s->w.bt2, s->mhead, s->mod, 2};
-  const int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, nullptr, st);
-  launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e, &table, nullptr, st);
+  int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, nullptr, st);
+  const bool streamed = sizeof(T) == 2 && head_streamed(c) && ((uintptr_t)x_in & 15) == 0;
+  parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e, streamed ? nullptr : &table, nullptr, st);
   if constexpr (sizeof(T) == 2) {
     if (head_fused(c)) {
       if (overlap(x_in, (size_t)(S * D) * 2, v_out, (size_t)n * 4)) {
         launch_copy2d<bf16_t>((const bf16_t*)x_in, D, (bf16_t*)s->h, D, S, D, st);
         x_in = s->h;
       }
-      launch_head(s, x_in, v_out, S, st);
+      if (streamed) launch_head_streamed(s, s->e, parts, x_in, v_out, S, st);
+      else launch_head(s, x_in, v_out, S, st);
       return;
     }
   }

@@ -1,0 +1,27 @@
+"""The output head that streams its tokens (bf16, more than 2048 channels) at 16, 32 and 64 tokens per block, against the CPU oracle:
+channel counts that leave the shares uneven, last blocks of one and of all but one token, two groups of 64 output values, rows
+whose mean is far from zero (what cancels is the mean, in the statistics and in the product)."""
+import numpy as np
+import pytest
+import torch
+
+from harness import check, to_dev, to_np
+from test_gpu_ends_fused import setup
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("far", [False, True], ids=["plain", "far"])
+@pytest.mark.parametrize("dim,channels,tok_h,tok_w,frames", [
+    (2112, 16, 1, 1, 1), (2112, 32, 3, 16, 1), (2240, 16, 1, 4096, 1),     # 16 tokens a block: 1, 48 and 4096 of them
+    (2112, 16, 1, 4097, 1), (2304, 32, 1, 4095, 1), (2112, 16, 1, 8191, 1),   # 32: one token in the last block, one missing
+    (2112, 16, 1, 8193, 1), (2176, 32, 1, 8192, 2)])                       # 64
+def test_streamed_head(dim, channels, tok_h, tok_w, frames, far):
+    cfg, _, g, o, _, tokens = setup(dim, channels, tok_h, tok_w, frames)
+    if far:                                                                # rows at -60 .. 60, still of spread one
+        tokens = (tokens.float() + torch.linspace(-60, 60, tokens.shape[0])[:, None]).to(torch.bfloat16).float()
+    v = to_np(g.head(to_dev(tokens, cfg), 437.0, frames)).reshape(-1, channels)
+    ref = o.head(tokens.numpy().astype(np.float64), 437.0, frames).reshape(-1, channels)
+    check(f"{dim}/{channels}/{tok_w}/head", v, ref, "bf16")
+    # one rounding to bf16 (of the modulated weights; 2^-9 at most, 1.66e-3 in the mean square) per product, no other
+    assert np.linalg.norm(v - ref) / np.linalg.norm(ref) < 2.0 ** -9
