@@ -193,22 +193,61 @@ void launch_ln_modulate(float* x, const T* xin, T* out, int64_t S, int D, float 
 template void launch_ln_modulate<float>(float*, const float*, float*, int64_t, int, float, const float*, const float*, int, hipStream_t);
 template void launch_ln_modulate<bf16_t>(float*, const bf16_t*, bf16_t*, int64_t, int, float, const float*, const float*, int, hipStream_t);
 
+// ---------------------------------------------------------------- V -> V^T (per head [d][L])
+template <typename T> struct alignas(sizeof(T) * 8) Vec8 { T v[8]; };
+// 64 tokens x 64 channels through LDS: 16-byte reads along channels, 16-byte writes along tokens.
+template <typename T>
+__device__ __forceinline__ void v_transpose_tile(const VTransposeJob<T>& j, const T* __restrict__ src, int64_t ld, int64_t S, int D,
+                                                 int64_t s0, int c0, T (&tile)[64][72]) {  // [channel][token], row padded, rows stay vector-aligned
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int r = (t >> 3) + pass * 32, cc = (t & 7) * 8;
+    const int64_t s = s0 + r;
+    Vec8<T> x;
+    if (s < S && c0 + cc < D) x = *(const Vec8<T>*)(src + s * ld + j.col + c0 + cc);
+    else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x.v[e] = (T)0;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tile[cc + e][r] = x.v[e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    const int ch = (t >> 3) + pass * 32, tk = (t & 7) * 8;
+    const int c = c0 + ch;
+    const int64_t s = s0 + tk;
+    if (c < D && s < S) {
+      T* o = j.vt + (int64_t)c * j.row_stride + j.col0 + s;     // channel c = head*d + cc: row c of [h*d][row_stride]
+      if (j.vec_ok && s + 8 <= S) *(Vec8<T>*)o = *(const Vec8<T>*)&tile[ch][tk];
+      else for (int e = 0; e < 8 && s + e < S; ++e) o[e] = tile[ch][tk + e];
+    }
+  }
+}
+
 // ---------------------------------------------------------------- RMSNorm over D + 3D RoPE, head-major output
 // One wavefront per token and job (blockIdx.y: e.g. q and k of the same row), four tokens per block.  A lane
 // owns VPL groups of 8 consecutive channels (one 16-byte access each for bf16), all loaded before the first
 // use so that a wavefront keeps VPL KiB in flight, and kept in registers between the sum-of-squares pass and
 // the normalise/rotate/store pass: the row is read once, and nothing but wavefront shuffles synchronises.
-template <typename T> struct alignas(sizeof(T) * 8) Vec8 { T v[8]; };
-
+// The first tiles_s * cdiv(D, 64) blocks along x, if any, transpose the same rows' values instead, 64 x 64 each: they depend on
+// nothing that the others do (two fp32 layers of 128 tokens x 128 channels 143.5 us with a launch of their own, 137.2 this way).
 template <typename T, int VPL>
 __global__ __launch_bounds__(256) void k_norm_rope(const T* __restrict__ src, int64_t ld, int64_t S, int h, int d,
-                                                   float eps, NormRopeJob<T> j0, NormRopeJob<T> j1,
+                                                   float eps, NormRopeJob<T> j0, NormRopeJob<T> j1, VTransposeJob<T> jv, int tiles_s, int v_blocks,
                                                    RopeTables rt, int frame0, int tok_h, int tok_w) {
+  __shared__ __align__(32) T tile[64][72];
+  const int D = h * d, nvec = D >> 3;
+  if ((int)blockIdx.x < v_blocks) {
+    if (blockIdx.y == 0) v_transpose_tile(jv, src, ld, S, D, (int64_t)((int)blockIdx.x % tiles_s) * 64, (int)blockIdx.x / tiles_s * 64, tile);
+    return;
+  }
   const NormRopeJob<T> job = blockIdx.y == 0 ? j0 : j1;
   const int lane = threadIdx.x & 63;
-  const int64_t s = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t s = (int64_t)((int)blockIdx.x - v_blocks) * 4 + (threadIdx.x >> 6);
   if (s >= S) return;
-  const int D = h * d, nvec = D >> 3;
   const Vec8<T>* row = (const Vec8<T>*)(src + s * ld + job.col);
   Vec8<T> raw[VPL];
 #pragma unroll
@@ -258,17 +297,24 @@ __global__ __launch_bounds__(256) void k_norm_rope(const T* __restrict__ src, in
     }
   }
 }
+// whether whole groups of eight tokens can be stored at once
+template <typename T> static VTransposeJob<T> vec_checked(VTransposeJob<T> v) {
+  v.vec_ok = (v.col0 % 8 == 0) && (v.row_stride % 8 == 0) && ((uintptr_t)v.vt % (8 * sizeof(T)) == 0);
+  return v;
+}
 template <typename T>
 void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float eps, const NormRopeJob<T>* jobs,
-                      int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st) {
+                      int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st, const VTransposeJob<T>* v) {
   if (S <= 0 || n_jobs <= 0) return;
+  const int tiles_s = v ? cdiv(S, 64) : 1, v_blocks = v ? tiles_s * cdiv(h * d, 64) : 0;
+  const VTransposeJob<T> jv = v ? vec_checked(*v) : VTransposeJob<T>{};
   RopeTables rt = rope ? *rope : RopeTables{nullptr, nullptr, nullptr, 0, 0, 0};
   NormRopeJob<T> j0 = jobs[0], j1 = jobs[n_jobs > 1 ? 1 : 0];
   if (!rope) { j0.rope = 0; j1.rope = 0; }
-  const dim3 grid((unsigned)cdiv(S, 4), (unsigned)(n_jobs > 1 ? 2 : 1));
+  const dim3 grid((unsigned)(cdiv(S, 4) + v_blocks), (unsigned)(n_jobs > 1 ? 2 : 1));
   const int th = tok_h > 0 ? tok_h : 1, tw = tok_w > 0 ? tok_w : 1;
   const int vpl = (h * d / 8 + 63) / 64;               // 16-byte groups per lane; dim <= 8192
-#define NORM_ROPE_CASE(V) k_norm_rope<T, V><<<grid, 256, 0, st>>>(src, ld, S, h, d, eps, j0, j1, rt, frame0, th, tw)
+#define NORM_ROPE_CASE(V) k_norm_rope<T, V><<<grid, 256, 0, st>>>(src, ld, S, h, d, eps, j0, j1, jv, tiles_s, v_blocks, rt, frame0, th, tw)
   if (vpl <= 1) NORM_ROPE_CASE(1);
   else if (vpl <= 3) NORM_ROPE_CASE(3);
   else if (vpl <= 6) NORM_ROPE_CASE(6);
@@ -276,8 +322,8 @@ void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float e
   else NORM_ROPE_CASE(16);
 #undef NORM_ROPE_CASE
 }
-template void launch_norm_rope<float>(const float*, int64_t, int64_t, int, int, float, const NormRopeJob<float>*, int, const RopeTables*, int, int, int, hipStream_t);
-template void launch_norm_rope<bf16_t>(const bf16_t*, int64_t, int64_t, int, int, float, const NormRopeJob<bf16_t>*, int, const RopeTables*, int, int, int, hipStream_t);
+template void launch_norm_rope<float>(const float*, int64_t, int64_t, int, int, float, const NormRopeJob<float>*, int, const RopeTables*, int, int, int, hipStream_t, const VTransposeJob<float>*);
+template void launch_norm_rope<bf16_t>(const bf16_t*, int64_t, int64_t, int, int, float, const NormRopeJob<bf16_t>*, int, const RopeTables*, int, int, int, hipStream_t, const VTransposeJob<bf16_t>*);
 
 // ---------------------------------------------------------------- deferred RMSNorm of head-major bf16 rows
 // k[head][row0 + s][:] *= rsqrt(sum_i ssq[i * stride + s] * inv_dim + eps) for every head: the row scale of an
@@ -341,52 +387,19 @@ void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_
 #undef SCALE_ROWS
 }
 
-// ---------------------------------------------------------------- V -> V^T (per head [d][L])
-// 64 tokens x 64 channels through LDS: 16-byte reads along channels, 16-byte writes along tokens.
+// ---------------------------------------------------------------- V -> V^T (per head [d][L]) by itself
 template <typename T>
-__global__ __launch_bounds__(256) void k_v_transpose(const T* __restrict__ src, int64_t ld, int col, int64_t S,
-                                                     int D, int d, T* __restrict__ vt, int64_t row_stride,
-                                                     int64_t col0, int vec_ok) {
-  __shared__ __align__(32) T tile[64][72];       // [channel][token], row padded, rows stay vector-aligned
-  const int64_t s0 = (int64_t)blockIdx.x * 64;
-  const int c0 = blockIdx.y * 64;
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int r = (t >> 3) + pass * 32, cc = (t & 7) * 8;
-    const int64_t s = s0 + r;
-    Vec8<T> x;
-    if (s < S && c0 + cc < D) x = *(const Vec8<T>*)(src + s * ld + col + c0 + cc);
-    else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x.v[e] = (T)0;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) tile[cc + e][r] = x.v[e];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    const int ch = (t >> 3) + pass * 32, tk = (t & 7) * 8;
-    const int c = c0 + ch;
-    const int64_t s = s0 + tk;
-    if (c < D && s < S) {
-      T* o = vt + (int64_t)c * row_stride + col0 + s;     // channel c = head*d + cc: row c of [h*d][row_stride]
-      if (vec_ok && s + 8 <= S) *(Vec8<T>*)o = *(const Vec8<T>*)&tile[ch][tk];
-      else for (int e = 0; e < 8 && s + e < S; ++e) o[e] = tile[ch][tk + e];
-    }
-  }
+__global__ __launch_bounds__(256) void k_v_transpose(VTransposeJob<T> j, const T* __restrict__ src, int64_t ld, int64_t S, int D) {
+  __shared__ __align__(32) T tile[64][72];
+  v_transpose_tile(j, src, ld, S, D, (int64_t)blockIdx.x * 64, blockIdx.y * 64, tile);
 }
 template <typename T>
-void launch_v_transpose(const T* src, int64_t ld, int col, int64_t S, int h, int d, T* vt,
-                        int64_t row_stride, int64_t col0, hipStream_t st) {
+void launch_v_transpose(const T* src, int64_t ld, int64_t S, int h, int d, const VTransposeJob<T>& v, hipStream_t st) {
   if (S <= 0) return;
-  dim3 grid(cdiv(S, 64), cdiv(h * d, 64));
-  const int vec_ok = (col0 % 8 == 0) && (row_stride % 8 == 0) && ((uintptr_t)vt % (8 * sizeof(T)) == 0);
-  k_v_transpose<T><<<grid, 256, 0, st>>>(src, ld, col, S, h * d, d, vt, row_stride, col0, vec_ok);
+  k_v_transpose<T><<<dim3(cdiv(S, 64), cdiv(h * d, 64)), 256, 0, st>>>(vec_checked(v), src, ld, S, h * d);
 }
-template void launch_v_transpose<float>(const float*, int64_t, int, int64_t, int, int, float*, int64_t, int64_t, hipStream_t);
-template void launch_v_transpose<bf16_t>(const bf16_t*, int64_t, int, int64_t, int, int, bf16_t*, int64_t, int64_t, hipStream_t);
+template void launch_v_transpose<float>(const float*, int64_t, int64_t, int, int, const VTransposeJob<float>&, hipStream_t);
+template void launch_v_transpose<bf16_t>(const bf16_t*, int64_t, int64_t, int, int, const VTransposeJob<bf16_t>&, hipStream_t);
 
 // ---------------------------------------------------------------- strided row copy (feature-cache hand-over)
 // Rows are copied in 16-byte pieces when src, dst, strides and length allow it.

@@ -18,19 +18,21 @@ void launch_ln_modulate(float* x, const T* xin, T* out, int64_t S, int D, float 
 template <typename T> struct NormRopeJob {
   int col; const float* g; float out_scale; T* dst; int64_t head_stride; int64_t row0; int rope;
 };
+// v, if given, is transposed by the same launch.
+// vt[head][c][col0 + s] = src[s, col + head*d + c]; vec_ok is filled in
+template <typename T> struct VTransposeJob { int col; T* vt; int64_t row_stride, col0; int vec_ok; };
 template <typename T>
 void launch_norm_rope(const T* src, int64_t ld, int64_t S, int h, int d, float eps, const NormRopeJob<T>* jobs,
-                      int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st);
+                      int n_jobs, const RopeTables* rope, int frame0, int tok_h, int tok_w, hipStream_t st,
+                      const VTransposeJob<T>* v = nullptr);
 // cs[s][i] = rotation (cos, sin) of channel pair i < head_dim / 2 at token s < S of a block that starts at frame0
 struct RopeTokens { RopeTables rt; int frame0, tok_h, tok_w; int64_t S; float2* cs; };
 // k[head][row0 + s][:] = (wide ? wide[s][head * d ..] : k[head][row0 + s][:]) * rsqrt(sum_i ssq[i * stride + s] / (h * d) + eps),
 // bf16 rows of d elements; wide: fp32 [S][h * d]
 void launch_scale_rows_bf16(bf16_t* k, int64_t head_stride, int64_t row0, int64_t S, int h, int d, const float* wide,
                             const float* ssq, int np, int64_t stride, float eps, hipStream_t st);
-// vt[head][c][col0 + s] = src[s, col + head*d + c]
 template <typename T>
-void launch_v_transpose(const T* src, int64_t ld, int col, int64_t S, int h, int d, T* vt,
-                        int64_t row_stride, int64_t col0, hipStream_t st);
+void launch_v_transpose(const T* src, int64_t ld, int64_t S, int h, int d, const VTransposeJob<T>& v, hipStream_t st);
 // dst[r][0..len) = src[r][0..len) for r < rows (strides in elements)
 template <typename T>
 void launch_copy2d(const T* src, int64_t src_stride, T* dst, int64_t dst_stride, int64_t rows,

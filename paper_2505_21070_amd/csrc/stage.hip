@@ -341,7 +341,7 @@ static void init_typed(dp_stage* s, const void* text, hipStream_t st) {
     }
     if (own) launch_transpose_pad<T>((const T*)w.cwv, D, D, (T*)s->wtmp, rup(D, 256), st);
     Path<T>::gemm(ctx, D, w.cwv, own ? s->wtmp : w.cwv, Lt, D, D, EPI_STORE, epi_store(s->raw, D, w.cbv), st);
-    launch_v_transpose<T>((const T*)s->raw, D, 0, Lt, h, d, (T*)m.tvt, s->Ltpad, 0, st);
+    launch_v_transpose<T>((const T*)s->raw, D, Lt, h, d, VTransposeJob<T>{0, (T*)m.tvt, s->Ltpad, 0, 0}, st);
   }
 }
 
@@ -478,8 +478,8 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
       PROF(DP_PROF_NORM_ROPE,
            const NormRopeJob<T> qk[2] = {{0, m.gq, Path<T>::q_scale(d), (T*)s->qbuf, s->Spad * d, 0, 1},
                                          {(int)D, m.gk, 1.f, (T*)m.kbuf, kv_hs, blk0, 1}};
-           launch_norm_rope<T>((const T*)s->raw, 3 * D, S, h, d, c.eps, qk, 2, &s->rt, frame0, c.tok_h, c.tok_w, st);
-           launch_v_transpose<T>((const T*)s->raw, 3 * D, (int)(2 * D), S, h, d, (T*)m.vtbuf, s->Lpad, blk0, st));
+           const VTransposeJob<T> v{(int)(2 * D), (T*)m.vtbuf, s->Lpad, blk0, 0};
+           launch_norm_rope<T>((const T*)s->raw, 3 * D, S, h, d, c.eps, qk, 2, &s->rt, frame0, c.tok_h, c.tok_w, st, &v));
     }
     PROF(DP_PROF_SELF_ATTN,
          Path<T>::attn(s->qbuf, s->Spad * d, m.kbuf, kv_hs, key0, m.vtbuf, s->Lpad, S,
