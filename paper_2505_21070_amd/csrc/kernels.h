@@ -52,6 +52,9 @@ template <typename T> struct GemvTable { const T* bias; const float* mtab; float
 template <typename T>
 int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, float* y, const GemvTable<T>* table,
                 const RopeTokens* rope, hipStream_t st);
+// The first two of a chain: y = slices of SiLU(b1 + W1^T features(t)) times W2 [D, D] (returned count); mid: scratch as y
+template <typename T>
+int launch_gemv_pair(float t, const T* W1, const T* b1, int freq, const T* W2, int D, float* mid, float* y, const RopeTokens* rope, hipStream_t st);
 void launch_rope_table(float2* tab, int n_pos, int pairs, float theta, hipStream_t st);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // dst[s, head*d + c] (fp32) = src[head][row0 + s][c]

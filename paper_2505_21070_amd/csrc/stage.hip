@@ -444,8 +444,7 @@ static void forward_typed(dp_stage* s, const void* x_in, void* x_out, int n_fram
   PROF(DP_PROF_MODULATION,
        const RopeTokens rope{s->rt, frame0, c.tok_h, c.tok_w, S, s->rope_tok};
        const GemvTable<T> table{(const T*)s->w.bm, s->mtab, s->mod, c.n_layers};
-       int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, qkv_heads ? &rope : nullptr, st);
-       parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e2, nullptr, nullptr, st);
+       const int parts = launch_gemv_pair<T>(t, (const T*)s->w.wt1, (const T*)s->w.bt1, c.freq_dim, (const T*)s->w.wt2, (int)D, s->e1, s->e2, qkv_heads ? &rope : nullptr, st);
        launch_gemv<T>(GemvIn{s->e2, parts, 0.f}, (const T*)s->w.bt2, (int)D, (const T*)s->w.wm, (int)(6 * D), nullptr, &table, nullptr, st));
   for (int l = 0; l < c.n_layers; ++l) {
     const dp_layer_weights& w = s->lw[(size_t)l]; LayerMem& m = s->lm[(size_t)l];
