@@ -57,28 +57,44 @@ template <int OFF> __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
   return __builtin_bit_cast(bf16x8, lds_read16_raw<OFF>(addr));
 }
 
+// Deferred RMSNorm of the queries: a row's sum of squares arrives as qn.np partial sums; lanes of parity 0 and 1 add up the even and
+// the odd ones, in order.  The first PS of a lane are requested before anything else, so that they and what is requested behind
+// them are one trip to memory and none waits for what comes later; a wider model's are read when they are added up.
+struct QuerySums {
+  static constexpr int PS = 12;
+  float v[PS];
+  const float* p;
+  __device__ __forceinline__ void request(const AttnQNorm& qn, int64_t row, int64_t S, int parity) {
+    p = qn.ssq + (row < S ? row : S - 1);
+    if (!qn.ssq) return;
+#pragma unroll
+    for (int u = 0; u < PS; ++u) v[u] = p[(parity + 2 * u < qn.np ? parity + 2 * u : 0) * qn.stride];
+  }
+  // the factor of the row; O: distance to a lane of the other parity
+  template <int O> __device__ __forceinline__ float factor(const AttnQNorm& qn, int parity) const {
+    float sum = 0.f;
+#pragma unroll
+    for (int u = 0; u < PS; ++u) sum += parity + 2 * u < qn.np ? v[u] : 0.f;
+    for (int i = parity + 2 * PS; i < qn.np; i += 2) sum += p[i * qn.stride];
+    sum += __shfl_xor(sum, O, 64);
+    return rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
+  }
+};
+template <int KS> __device__ __forceinline__ void scale_queries(bf16x8 (&qf)[KS], float r) {
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * r);
+}
 // The fragments of 32 queries from row q0 of a head: B operand, column = query lr, 8 head-dim values per lane
 template <int KS, int HD>
-__device__ __forceinline__ void load_queries(const bf16_t* __restrict__ qh, int64_t q0, int lr, int lg, int64_t S, const AttnQNorm& qn,
-                                             bf16x8 (&qf)[KS]) {
+__device__ __forceinline__ void request_queries(const bf16_t* __restrict__ qh, int64_t q0, int lr, int lg, int64_t S, const AttnQNorm& qn,
+                                                QuerySums& qs, bf16x8 (&qf)[KS]) {
+  qs.request(qn, q0 + lr, S, lg);
   qh += (q0 + lr) * HD + lg * 8;
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qh + ks * 16));
-  if (qn.ssq) {
-    // deferred RMSNorm of the queries: the row's sum of squares arrives as qn.np partial sums; the two lanes
-    // that share a query row add up the even and the odd ones
-    const int64_t row = q0 + lr < S ? q0 + lr : S - 1;
-    const float* pr = qn.ssq + row;
-    float sum = 0.f;
-#pragma unroll 4
-    for (int i = lg; i < qn.np; i += 2) sum += pr[i * qn.stride];
-    sum += __shfl_xor(sum, 32, 64);
-    const float r = rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)((float)qf[ks][e] * r);
-  }
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 template <int HD, int QG>
@@ -162,12 +178,14 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
     for (int i = 0; i < CK + CV; ++i) load_part(tile, bufi, i);
   };
 
-  // the fast pass's first two tiles are requested ahead of the queries and their row sums: one trip to memory instead of two
+  // the queries' row sums, the queries and the fast pass's first two tiles: one trip to memory
+  bf16x8 qf[KS];
+  QuerySums qs;
+  request_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qs, qf);
   if (cnt > 0) load_tile(cnt - 1, 0);
   if (cnt > 1) load_tile(cnt - 2, 1);
-
-  bf16x8 qf[KS];
-  load_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qf);
+  __builtin_amdgcn_sched_barrier(0);
+  if (qn.ssq) scale_queries(qf, qs.factor<32>(qn, lg));
 
   f32x16 oacc[DT], negm;
   float mrun, lsum;
@@ -563,6 +581,10 @@ __global__ __launch_bounds__(512) void k_attn_turns(const bf16_t* __restrict__ q
 #pragma unroll
     for (int i = 0; i < CV; ++i) load_lds16(base, 0xffffffff, voff, (int)((uint32_t)(i * VR * 2) * (uint32_t)vt_row_stride), vst + (j % NST) * VCH + (i * QG + qt) * 64);
   };
+  // one trip to memory: the queries' row sums, the queries, the tiles in the order in which they are needed
+  QuerySums qs[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) qs[t].request(qn, q0 + t * 16 + lr, S, lg & 1);
   // the fragments of this wavefront's 32 queries: B operand, column = query lr of a 16-query tile, 8 head-dim values per lane
   bf16x8 qf[2][KS];
 #pragma unroll
@@ -572,31 +594,14 @@ __global__ __launch_bounds__(512) void k_attn_turns(const bf16_t* __restrict__ q
     for (int ks = 0; ks < KS; ++ks) qf[t][ks] = __builtin_bit_cast(bf16x8, *(const uint4*)(qh + ks * 32));
   }
   __builtin_amdgcn_sched_barrier(0);
-  // the first keys travel with the queries and their row sums; what is needed later is requested behind them
   load_k(0); load_k(1);
-  __builtin_amdgcn_sched_barrier(0);
-  if (qn.ssq) {
-    // deferred RMSNorm of the queries: the row's sum of squares arrives as qn.np partial sums; two of the four lanes of a query
-    // add up the even and two the odd ones, the order in which the other kernels and the test hook do it
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int64_t row = q0 + t * 16 + lr < S ? q0 + t * 16 + lr : S - 1;
-      const float* pr = qn.ssq + row;
-      float sum = 0.f;
-#pragma unroll 4
-      for (int i = lg & 1; i < qn.np; i += 2) sum += pr[i * qn.stride];
-      sum += __shfl_xor(sum, 16, 64);
-      const float r = rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) qf[t][ks][e] = (__bf16)((float)qf[t][ks][e] * r);
-    }
-  }
-
-  __builtin_amdgcn_sched_barrier(0);
   load_v(0);
   if constexpr (KG == 1) { load_k(2); load_v(1); load_k(3); } else load_v(1);
+  __builtin_amdgcn_sched_barrier(0);
+  if (qn.ssq) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) scale_queries(qf[t], qs[t].factor<16>(qn, lg & 1));
+  }
   __builtin_amdgcn_sched_barrier(0);
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;
@@ -929,9 +934,11 @@ __global__ __launch_bounds__(512, HD == 64 ? 4 : 2) void k_attn_few(const bf16_t
                                          (lds_void_t*)(mine + KCH + i * 64), 16, 0, 0);
       }
     };
-    load_tile(wave);
     bf16x8 qf[KS];
-    load_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qf);
+    QuerySums qs;
+    load_tile(wave);                                     // ahead: it is all that this wavefront may ever load
+    request_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qs, qf);
+    if (qn.ssq) scale_queries(qf, qs.factor<32>(qn, lg));
     f32x16 oacc[DT];
     float m = -INFINITY, l = 0.f;
 #pragma unroll
