@@ -88,47 +88,58 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {   // bytes % 4 ==
 // LayerNorm of a stage, which thereby also fills the fp32 residual stream).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-template <typename T, int NCH, int NW>
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t cvt_pk_bf16x2(float a, float b) {   // round to nearest even, in one instruction
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
+}
+// All of a row's loads are issued before the first use and the modulation's right behind them, in straight-line code (positions
+// beyond the row read its last one and count as zero): with the loads in branches, as a row's length would have it, the
+// compiler waited for each before the next.  In a stage (us each, with the launch gap): 1008 x 1024 8.3 -> 6.7, 1560 x 1536 10.5 -> 7.5, 6240 x
+// 1536 16.5 -> 15.9, 14400 x 5120 100.4 -> 92.0.
+template <typename T, int NCH, int NW, bool XIN>
 __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, const T* __restrict__ xin,
                                                      T* __restrict__ out, int64_t S, int D, float eps,
-                                                     const float* __restrict__ mul,
-                                                     const float* __restrict__ add, float plus) {
-  static_assert(NW == 1 || NW == 2 || NW == 4, "wavefronts per row");
-  constexpr int RPB = 4 / NW;                        // rows per block
+                                                     const float* __restrict__ mul, const float* __restrict__ add, float plus) {
+  constexpr int RPB = 4 / NW;                        // rows per block of 4 wavefronts
   __shared__ float red[2][4];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t row = (int64_t)blockIdx.x * RPB + w / NW;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t row0 = (int64_t)blockIdx.x * RPB + w / NW;
   const int part = (w % NW) * 64 + lane;             // this lane's float4 slot inside a run of NW * 64 slots
-  const bool live = row < S;                         // rows of a block end together only when NW > 1 shares them
+  const bool live = row0 < S;                        // rows of a block end together only when NW > 1 shares them
+  const int64_t row = live ? row0 : S - 1;
   const int nvec = D >> 2;
-  f32x4_t v[NCH];
-  float sum = 0.f;
-  if (live) {
-    f32x4_t* xr = (f32x4_t*)(x + row * D);
+  f32x4_t v[NCH], m[NCH], a[NCH];
+  auto at = [&](int i) __attribute__((always_inline)) { const int idx = i * (NW * 64) + part; return idx < nvec ? idx : nvec - 1; };
+  f32x4_t* const xr = (f32x4_t*)(x + row * D);
+  if constexpr (!XIN) {
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int idx = i * (NW * 64) + part;
-      if (idx < nvec) {
-        if (xin) {
-          if constexpr (sizeof(T) == 2) {
-            const u32x2_t wv = __builtin_nontemporal_load((const u32x2_t*)(xin + row * D) + idx);
-            v[i] = f32x4_t{bf16_to_f32((bf16_t)(wv.x & 0xffff)), bf16_to_f32((bf16_t)(wv.x >> 16)),
-                           bf16_to_f32((bf16_t)(wv.y & 0xffff)), bf16_to_f32((bf16_t)(wv.y >> 16))};
-          } else {
-            const T* p = xin + row * D + idx * 4;      // the caller's buffer may start anywhere
-            v[i] = f32x4_t{p[0], p[1], p[2], p[3]};
-          }
-          xr[idx] = v[i];
-        } else {
-          v[i] = __builtin_nontemporal_load(xr + idx);
-        }
-        sum += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-      }
-      else v[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int i = 0; i < NCH; ++i) v[i] = __builtin_nontemporal_load(xr + at(i));
+  } else if constexpr (sizeof(T) == 2) {
+    u32x2_t r[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) r[i] = __builtin_nontemporal_load((const u32x2_t*)(xin + row * D) + at(i));
+#pragma unroll
+    for (int i = 0; i < NCH; ++i)
+      v[i] = f32x4_t{__uint_as_float(r[i].x << 16), __uint_as_float(r[i].x & 0xffff0000u), __uint_as_float(r[i].y << 16), __uint_as_float(r[i].y & 0xffff0000u)};
   } else {
 #pragma unroll
-    for (int i = 0; i < NCH; ++i) v[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < NCH; ++i) {
+      const T* p = xin + row * D + at(i) * 4;        // the caller's buffer may start anywhere
+      v[i] = f32x4_t{p[0], p[1], p[2], p[3]};
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) m[i] = ((const f32x4_t*)mul)[at(i)];
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) a[i] = ((const f32x4_t*)add)[at(i)];
+  __builtin_amdgcn_sched_barrier(0);
+  float sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    const bool in = i * (NW * 64) + part < nvec;
+    if (XIN && in && live) xr[i * (NW * 64) + part] = v[i];
+    sum += in ? (v[i].x + v[i].y) + (v[i].z + v[i].w) : 0.f;
   }
   // sum over the row's NW wavefronts (consecutive wavefronts of the block), in wavefront order
   auto row_sum = [&](float part_sum, int slot) __attribute__((always_inline)) {
@@ -146,11 +157,8 @@ __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, cons
   float sq = 0.f;
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
-    const int idx = i * (NW * 64) + part;
-    if (idx < nvec) {
-      const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, d = v[i].w - mean;
-      sq += (a * a + b * b) + (c * c + d * d);
-    }
+    const float p = v[i].x - mean, q = v[i].y - mean, r = v[i].z - mean, t = v[i].w - mean;
+    sq += i * (NW * 64) + part < nvec ? (p * p + q * q) + (r * r + t * t) : 0.f;
   }
   const float rstd = rsqrtf(row_sum(sq, 1) / (float)D + eps);
   if (!live) return;
@@ -158,15 +166,13 @@ __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, cons
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int idx = i * (NW * 64) + part;
+    const float r0 = (v[i].x - mean) * rstd * (m[i].x + plus) + a[i].x;
+    const float r1 = (v[i].y - mean) * rstd * (m[i].y + plus) + a[i].y;
+    const float r2 = (v[i].z - mean) * rstd * (m[i].z + plus) + a[i].z;
+    const float r3 = (v[i].w - mean) * rstd * (m[i].w + plus) + a[i].w;
     if (idx < nvec) {
-      const float4 m = ((const float4*)mul)[idx];
-      const float4 a = ((const float4*)add)[idx];
-      const float r0 = (v[i].x - mean) * rstd * (m.x + plus) + a.x;
-      const float r1 = (v[i].y - mean) * rstd * (m.y + plus) + a.y;
-      const float r2 = (v[i].z - mean) * rstd * (m.z + plus) + a.z;
-      const float r3 = (v[i].w - mean) * rstd * (m.w + plus) + a.w;
       if constexpr (sizeof(T) == 2) {
-        u32x2_t pk; pk.x = pack_bf16x2(r0, r1); pk.y = pack_bf16x2(r2, r3);
+        u32x2_t pk; pk.x = cvt_pk_bf16x2(r0, r1); pk.y = cvt_pk_bf16x2(r2, r3);
         __builtin_nontemporal_store(pk, (u32x2_t*)orow + idx);
       } else {
         __builtin_nontemporal_store(f32x4_t{r0, r1, r2, r3}, (f32x4_t*)orow + idx);
@@ -179,7 +185,10 @@ void launch_ln_modulate(float* x, const T* xin, T* out, int64_t S, int D, float 
                         const float* add, int plus_one, hipStream_t st) {
   if (S <= 0) return;
   const float plus = plus_one ? 1.f : 0.f;
-#define LN_CASE(NCH, NW) k_ln_modulate<T, NCH, NW><<<cdiv(S, 4 / NW), 256, 0, st>>>(x, xin, out, S, D, eps, mul, add, plus)
+#define LN_CASE(NCH, NW) do { \
+    if (xin) k_ln_modulate<T, NCH, NW, true><<<cdiv(S, 4 / NW), 256, 0, st>>>(x, xin, out, S, D, eps, mul, add, plus); \
+    else k_ln_modulate<T, NCH, NW, false><<<cdiv(S, 4 / NW), 256, 0, st>>>(x, xin, out, S, D, eps, mul, add, plus); \
+  } while (0)
   if (D <= 256) LN_CASE(1, 1);
   else if (D <= 1536) LN_CASE(6, 1);
   else if (D <= 2048) LN_CASE(8, 1);
