@@ -88,11 +88,6 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {   // bytes % 4 ==
 // LayerNorm of a stage, which thereby also fills the fp32 residual stream).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t cvt_pk_bf16x2(float a, float b) {   // round to nearest even, in one instruction
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
-}
 // All of a row's loads are issued before the first use and the modulation's right behind them, in straight-line code (positions
 // beyond the row read its last one and count as zero): with the loads in branches, as a row's length would have it, the
 // compiler waited for each before the next.  In a stage (us each, with the launch gap): 1008 x 1024 8.3 -> 6.7, 1560 x 1536 10.5 -> 7.5, 6240 x
@@ -172,7 +167,7 @@ __global__ __launch_bounds__(256) void k_ln_modulate(float* __restrict__ x, cons
     const float r3 = (v[i].w - mean) * rstd * (m[i].w + plus) + a[i].w;
     if (idx < nvec) {
       if constexpr (sizeof(T) == 2) {
-        u32x2_t pk; pk.x = cvt_pk_bf16x2(r0, r1); pk.y = cvt_pk_bf16x2(r2, r3);
+        u32x2_t pk; pk.x = pack_bf16x2(r0, r1); pk.y = pack_bf16x2(r2, r3);
         __builtin_nontemporal_store(pk, (u32x2_t*)orow + idx);
       } else {
         __builtin_nontemporal_store(f32x4_t{r0, r1, r2, r3}, (f32x4_t*)orow + idx);
@@ -243,6 +238,9 @@ __device__ __forceinline__ void v_transpose_tile(const VTransposeJob<T>& j, cons
 // the normalise/rotate/store pass: the row is read once, and nothing but wavefront shuffles synchronises.
 // The first tiles_s * cdiv(D, 64) blocks along x, if any, transpose the same rows' values instead, 64 x 64 each: they depend on
 // nothing that the others do (two fp32 layers of 128 tokens x 128 channels 143.5 us with a launch of their own, 137.2 this way).
+// Loads are straight-line (lanes beyond the row read its last group), and up to 1536 channels the gains and rotations are requested
+// with the row: in branches, or behind the sum of squares, the compiler waited for each.  Beyond, their registers would halve
+// the wavefronts in flight.  In a stage (us each, with the launch gap): 6240 x 1536 13.0 -> 11.2, 1560 x 1536 7.2 -> 6.6.
 template <typename T, int VPL>
 __global__ __launch_bounds__(256) void k_norm_rope(const T* __restrict__ src, int64_t ld, int64_t S, int h, int d,
                                                    float eps, NormRopeJob<T> j0, NormRopeJob<T> j1, VTransposeJob<T> jv, int tiles_s, int v_blocks,
@@ -258,52 +256,64 @@ __global__ __launch_bounds__(256) void k_norm_rope(const T* __restrict__ src, in
   const int64_t s = (int64_t)((int)blockIdx.x - v_blocks) * 4 + (threadIdx.x >> 6);
   if (s >= S) return;
   const Vec8<T>* row = (const Vec8<T>*)(src + s * ld + job.col);
+  auto at = [&](int i) __attribute__((always_inline)) { return lane + i * 64 < nvec ? lane + i * 64 : nvec - 1; };
   Vec8<T> raw[VPL];
 #pragma unroll
-  for (int i = 0; i < VPL; ++i) {
-    const int vi = lane + i * 64;
-    if (vi < nvec) raw[i] = row[vi];
+  for (int i = 0; i < VPL; ++i) raw[i] = row[at(i)];
+  const int tok = tok_h * tok_w;
+  const int f = frame0 + (int)(s / tok), rem = (int)(s % tok);
+  const int y = rem / tok_w, x = rem % tok_w;
+  // gains and rotations of group i: requested with the row where the registers allow it (a trip to memory each otherwise)
+  constexpr int G = VPL <= 3 ? VPL : 1;
+  float4 gg[G][2];
+  float2 cs[G][4];
+  auto request = [&](int i) __attribute__((always_inline)) {
+    const int c0 = at(i) * 8, p0 = (c0 % d) >> 1;        // first channel, its pair in the head
+    gg[i % G][0] = *(const float4*)(job.g + c0); gg[i % G][1] = *(const float4*)(job.g + c0 + 4);
+    if (job.rope) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int pi = p0 + e;
+        const float2* const t = pi < rt.c_f ? rt.f + (int64_t)f * rt.c_f + pi : pi < rt.c_f + rt.c_h ? rt.y + y * rt.c_h + (pi - rt.c_f) : rt.x + x * rt.c_w + (pi - rt.c_f - rt.c_h);
+        cs[i % G][e] = *t;
+      }
+    }
+  };
+  if constexpr (G == VPL) {
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) request(i);
   }
+  __builtin_amdgcn_sched_barrier(0);
   float v[VPL][8];
   float sq = 0.f;
 #pragma unroll
   for (int i = 0; i < VPL; ++i) {
-    const int vi = lane + i * 64;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      v[i][e] = vi < nvec ? Elem<T>::ld(&raw[i].v[e]) : 0.f;
+      v[i][e] = lane + i * 64 < nvec ? Elem<T>::ld(&raw[i].v[e]) : 0.f;
       sq += v[i][e] * v[i][e];
     }
   }
   const float r = rsqrtf(wave_sum(sq) / (float)D + eps) * job.out_scale;
-  const int tok = tok_h * tok_w;
-  const int f = frame0 + (int)(s / tok), rem = (int)(s % tok);
-  const int y = rem / tok_w, x = rem % tok_w;
 #pragma unroll
   for (int i = 0; i < VPL; ++i) {
     const int vi = lane + i * 64;
-    if (vi < nvec) {
-      const int c0 = vi * 8, head = c0 / d, p0 = (c0 % d) >> 1;        // first channel, its head, first pair in the head
-      const float4 g0 = *(const float4*)(job.g + c0), g1 = *(const float4*)(job.g + c0 + 4);
-      const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-      Vec8<T> o;
+    if constexpr (G != VPL) request(i);
+    const int c0 = vi * 8, head = c0 / d;
+    const float gs[8] = {gg[i % G][0].x, gg[i % G][0].y, gg[i % G][0].z, gg[i % G][0].w, gg[i % G][1].x, gg[i % G][1].y, gg[i % G][1].z, gg[i % G][1].w};
+    Vec8<T> o;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float a = v[i][2 * e] * r * gg[2 * e], b = v[i][2 * e + 1] * r * gg[2 * e + 1];
-        if (job.rope) {
-          const int pi = p0 + e;
-          float2 cs;
-          if (pi < rt.c_f) cs = rt.f[(int64_t)f * rt.c_f + pi];
-          else if (pi < rt.c_f + rt.c_h) cs = rt.y[y * rt.c_h + (pi - rt.c_f)];
-          else cs = rt.x[x * rt.c_w + (pi - rt.c_f - rt.c_h)];
-          const float a2 = a * cs.x - b * cs.y, b2 = a * cs.y + b * cs.x;
-          a = a2; b = b2;
-        }
-        Elem<T>::st(&o.v[2 * e], a);
-        Elem<T>::st(&o.v[2 * e + 1], b);
+    for (int e = 0; e < 4; ++e) {
+      float a = v[i][2 * e] * r * gs[2 * e], b = v[i][2 * e + 1] * r * gs[2 * e + 1];
+      if (job.rope) {
+        const float2 c = cs[i % G][e];
+        const float a2 = a * c.x - b * c.y, b2 = a * c.y + b * c.x;
+        a = a2; b = b2;
       }
-      *(Vec8<T>*)(job.dst + (int64_t)head * job.head_stride + (job.row0 + s) * d + (c0 % d)) = o;
+      Elem<T>::st(&o.v[2 * e], a);
+      Elem<T>::st(&o.v[2 * e + 1], b);
     }
+    if (vi < nvec) *(Vec8<T>*)(job.dst + (int64_t)head * job.head_stride + (job.row0 + s) * d + (c0 % d)) = o;
   }
 }
 // whether whole groups of eight tokens can be stored at once
@@ -481,7 +491,7 @@ template void launch_transpose_pad<bf16_t>(const bf16_t*, int64_t, int64_t, bf16
 // slices in order.  A product is either sliced over blocks, partial results left for the consumer to add up, or whole: a
 // block takes all slices of its columns and adds its result to the L rows of a table.
 // 5120 x 30720: 315 MB in 78 us = 4.0 TB/s, what a read-only pass reaches here; more rows in flight do not change it.
-// The chain (features, three products, table, rotation table) is three launches: 128-wide model 28 -> 13 us, 1536-wide
+// The chain (features, three products, table, rotation table) is three launches (k_gemv_pair: two): 128-wide model 28 -> 13 us, 1536-wide
 // 39 -> 29 us under the profiler, which counts a launch as 4.6 us; 1 us each otherwise.
 template <typename T> struct GemvArgs {
   GemvIn in;
