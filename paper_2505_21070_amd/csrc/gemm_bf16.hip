@@ -1078,26 +1078,30 @@ bool gemm_bf16_heads_ok(int64_t M, int64_t N, const HeadsArgs& h) {
   }
   return true;
 }
-// x[m, n] += gate[n] * (bias[n] + sum over the K ranges, in range order), and its rounded copy
-__global__ __launch_bounds__(256) void k_add_parts(const float* __restrict__ part, int parts, int64_t M, int64_t N, EpiArgs e) {
+// x[m, n] += gate[n] * (bias[n] + sum over the K ranges, in range order), and its rounded copy.  P ranges, all requested before
+// the first is added: one trip to memory, not one each (product and sum, 1560 x 1536 x 8960 in 4 ranges in a stage, 57.9 -> 56.5 us).
+template <int P>
+__global__ __launch_bounds__(256) void k_add_parts(const float* __restrict__ part, int64_t M, int64_t N, EpiArgs e) {
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= M * N) return;
   const int64_t m = i / N, n = i % N;
-  float4 s = *(const float4*)(part + i);
-  for (int p = 1; p < parts; ++p) {
-    const float4 v = *(const float4*)(part + (int64_t)p * M * N + i);
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
-  if (e.bias) {
-    const uint2 b = *(const uint2*)((const bf16_t*)e.bias + n);
-    s.x += bf16_to_f32((bf16_t)(b.x & 0xffff)); s.y += bf16_to_f32((bf16_t)(b.x >> 16));
-    s.z += bf16_to_f32((bf16_t)(b.y & 0xffff)); s.w += bf16_to_f32((bf16_t)(b.y >> 16));
-  }
-  float4 x = *(const float4*)(e.resid + m * e.ldr + n);
-  const float4 g = e.gate ? *(const float4*)(e.gate + n) : make_float4(1.f, 1.f, 1.f, 1.f);
-  x.x += g.x * s.x; x.y += g.y * s.y; x.z += g.z * s.z; x.w += g.w * s.w;
-  *(float4*)(e.resid + m * e.ldr + n) = x;
-  if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x.x, x.y), cvt_pk_bf16(x.z, x.w));
+  f32x4 v[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) v[p] = *(const f32x4*)(part + (int64_t)p * M * N + i);
+  f32x4 x = *(const f32x4*)(e.resid + m * e.ldr + n);
+  const f32x4 g = e.gate ? *(const f32x4*)(e.gate + n) : f32x4{1.f, 1.f, 1.f, 1.f};
+  const uint2 b = e.bias ? *(const uint2*)((const bf16_t*)e.bias + n) : make_uint2(0, 0);
+#pragma unroll
+  for (int p = 1; p < P; ++p) v[0] += v[p];
+  v[0] += f32x4{__uint_as_float(b.x << 16), __uint_as_float(b.x & 0xffff0000u), __uint_as_float(b.y << 16), __uint_as_float(b.y & 0xffff0000u)};
+  x += g * v[0];
+  *(f32x4*)(e.resid + m * e.ldr + n) = x;
+  if (e.out) *(uint2*)((bf16_t*)e.out + m * e.ldo + n) = make_uint2(cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3]));
+}
+template <int P>
+static void launch_add_parts(int parts, int64_t M, int64_t N, const EpiArgs& e, hipStream_t st) {   // P <= parts <= 8
+  if constexpr (P < 8) if (parts > P) return launch_add_parts<P + 1>(parts, M, N, e, st);
+  k_add_parts<P><<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, M, N, e);
 }
 size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
   const size_t most = (size_t)256 * 256 * 256 * 4, need = (size_t)(8 * M * N * 4);      // one round of 256 x 256 tiles
@@ -1218,6 +1222,6 @@ bool launch_gemm_bf16(const bf16_t* A, int64_t lda, const bf16_t* Wt, int64_t ld
   else TURNS_TILE(10, 4);
 #undef RING_TILE
 #undef TURNS_TILE
-  if (r.parts > 1) k_add_parts<<<(unsigned)((M * N / 4 + 255) / 256), 256, 0, st>>>(e.scratch, r.parts, M, N, e);
+  if (r.parts > 1) launch_add_parts<2>(r.parts, M, N, e, st);
   return ok;
 }
