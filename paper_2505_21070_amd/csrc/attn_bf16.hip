@@ -190,10 +190,9 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
   f32x16 oacc[DT], negm;
   float mrun, lsum;
 
-  // One pass over this wavefront's key tiles.  SAFE = false: fixed reference (see the file header).
-  // SAFE = true: classical online softmax, reference raised per 32-key half tile, O^T rescaled.
-  auto pass = [&](auto safe_tag) __attribute__((always_inline)) {
-    constexpr bool SAFE = decltype(safe_tag)::value;
+  // Safe pass over this wavefront's key tiles: classical online softmax, reference raised per 32-key half tile, O^T rescaled.
+  // Scores of -inf weigh 0 and set no reference: until a query has another (fresh) its reference is 0, and -inf afterwards.
+  auto pass_safe = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int a = 0; a < DT; ++a)
 #pragma unroll
@@ -201,100 +200,77 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
 #pragma unroll
     for (int r = 0; r < 16; ++r) negm[r] = 0.f;
     mrun = 0.f; lsum = 0.f;
-    bool fresh = true;                                  // SAFE: no key seen yet, mrun is a placeholder
+    bool fresh = true;
 
     if (cnt > 0) load_tile(0, 0);
     tile_barrier();
-    if (!SAFE && cnt > 0) {
-      // reference = maximum over the first 32 keys (all valid: a group's first tile starts below L)
-      f32x16 s0;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int row = lr, ch = ks * 2 + lg;
-        const bf16x8 kf = __builtin_bit_cast(bf16x8, kbuf[row * CR + (ch ^ kswz<CR>(row))]);
-        s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? negm : s0, 0, 0, 0);
-      }
-      const int kv0 = (int)(L - (int64_t)t0 * 64);
-      float mx = -INFINITY;
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (swap23((r >> 2) * 8 + lg * 4 + (r & 3)) < kv0) mx = fmaxf(mx, s0[r]);
-      mrun = fmaxf(mx, __shfl_xor(mx, 32, 64));
-#pragma unroll
-      for (int r = 0; r < 16; ++r) negm[r] = -mrun;
-    }
-
     for (int kt = 0; kt < cnt; ++kt) {
-      if (kt < cnt) {
-        // next tile into the other buffer (read last before the previous barrier); the tile past the
-        // end is the last one again and never used
-        load_tile(kt + NBUF - 1 < cnt ? kt + NBUF - 1 : cnt - 1, (kt + NBUF - 1) % NBUF);
-        const uint4* kb = kbuf + (kt % NBUF) * KCH;
-        const uint4* vb = vbuf + (kt % NBUF) * VCH;
-        const int kvalid = (int)(L - (int64_t)(t0 + kt) * 64);     // < 64 only in the ragged last tile
+      // next tile into the other buffer (read last before the previous barrier); the tile past the
+      // end is the last one again and never used
+      load_tile(kt + NBUF - 1 < cnt ? kt + NBUF - 1 : cnt - 1, (kt + NBUF - 1) % NBUF);
+      const uint4* kb = kbuf + (kt % NBUF) * KCH;
+      const uint4* vb = vbuf + (kt % NBUF) * VCH;
+      const int kvalid = (int)(L - (int64_t)(t0 + kt) * 64);     // < 64 only in the ragged last tile
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {                                  // two 32-key halves of the tile
-          // S^T - m : 32 keys x 32 queries, accumulation started from -m
-          f32x16 sacc;
+      for (int a = 0; a < 2; ++a) {                                  // two 32-key halves of the tile
+        // S^T - m : 32 keys x 32 queries, accumulation started from -m
+        f32x16 sacc;
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            const int row = a * 32 + lr, ch = ks * 2 + lg;
-            const bf16x8 kf = __builtin_bit_cast(bf16x8, kb[row * CR + (ch ^ kswz<CR>(row))]);
-            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? negm : sacc, 0, 0, 0);
+        for (int ks = 0; ks < KS; ++ks) {
+          const int row = a * 32 + lr, ch = ks * 2 + lg;
+          const bf16x8 kf = __builtin_bit_cast(bf16x8, kb[row * CR + (ch ^ kswz<CR>(row))]);
+          sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], ks == 0 ? negm : sacc, 0, 0, 0);
+        }
+        // register r, lane group lg, is tile row a*32 + (r/4)*8 + lg*4 + (r%4), which holds key
+        // swap23(row); keys at or beyond L get -inf
+        if (kvalid < 64) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (swap23(a * 32 + (r >> 2) * 8 + lg * 4 + (r & 3)) >= kvalid) sacc[r] = -INFINITY;
+        }
+        float mx = sacc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));                    // maximum of this half relative to m
+        const bool none = mx == -INFINITY;
+        const float up = none ? 0.f : fresh ? mx : fmaxf(mx, 0.f);
+        const float alpha = fresh ? 0.f : __builtin_amdgcn_exp2f(-up);
+        mrun += up;
+        lsum *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { sacc[r] -= up; negm[r] = -mrun; }
+        fresh = fresh && none;
+        // P = 2^(s - m), packed to bf16 as the B operand of O^T += V^T P^T; row sums from the rounded values
+        uint4 pf[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          uint32_t w[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            w[j] = cvt_pk_bf16(__builtin_amdgcn_exp2f(sacc[u * 8 + 2 * j]), __builtin_amdgcn_exp2f(sacc[u * 8 + 2 * j + 1]));
+            lsum = add_pk_bf16(w[j], lsum);
           }
-          // register r, lane group lg, is tile row a*32 + (r/4)*8 + lg*4 + (r%4), which holds key
-          // swap23(row); keys at or beyond L get -inf
-          if (kvalid < 64) {
+          pf[u] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        // O^T += V^T * P^T : k-step u covers keys [a*32 + 16u, +16), lane group lg the lower/upper 8
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (swap23(a * 32 + (r >> 2) * 8 + lg * 4 + (r & 3)) >= kvalid) sacc[r] = -INFINITY;
-          }
-          if constexpr (SAFE) {
-            float mx = sacc[0];
+        for (int u = 0; u < 2; ++u) {
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));                    // maximum of this half relative to m
-            const float up = fresh ? mx : fmaxf(mx, 0.f);
-            const float alpha = fresh ? 0.f : __builtin_amdgcn_exp2f(-up);
-            mrun += up;
-            lsum *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) oacc[dt][r] *= alpha;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) { sacc[r] -= up; negm[r] = -mrun; }
-            fresh = false;
-          }
-          // P = 2^(s - m), packed to bf16 as the B operand of O^T += V^T P^T; row sums from the rounded values
-          uint4 pf[2];
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            uint32_t w[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              w[j] = cvt_pk_bf16(__builtin_amdgcn_exp2f(sacc[u * 8 + 2 * j]), __builtin_amdgcn_exp2f(sacc[u * 8 + 2 * j + 1]));
-              lsum = add_pk_bf16(w[j], lsum);
-            }
-            pf[u] = make_uint4(w[0], w[1], w[2], w[3]);
-          }
-          // O^T += V^T * P^T : k-step u covers keys [a*32 + 16u, +16), lane group lg the lower/upper 8
-#pragma unroll
-          for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-              const int row = dt * 32 + lr, ch = (a * 2 + u) * 2 + lg;
-              const bf16x8 vf = __builtin_bit_cast(bf16x8, vb[row * 8 + (ch ^ ((row >> 1) & 7))]);
-              oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pf[u]), oacc[dt], 0, 0, 0);
-            }
+          for (int dt = 0; dt < DT; ++dt) {
+            const int row = dt * 32 + lr, ch = (a * 2 + u) * 2 + lg;
+            const bf16x8 vf = __builtin_bit_cast(bf16x8, vb[row * 8 + (ch ^ ((row >> 1) & 7))]);
+            oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, __builtin_bit_cast(bf16x8, pf[u]), oacc[dt], 0, 0, 0);
           }
         }
       }
       tile_barrier();       // the next tile has landed and every wavefront is done with this one
     }
-    return fresh;
+    if (fresh) mrun = -INFINITY;
   };
-
 
   // Fast pass (fixed reference).  Per tile a wavefront issues NMF MFMAs in the order S^T of the first 32-key
   // half, S^T of the second half, O^T += V^T P^T of the first half, then of the second; the exponentials of
@@ -452,7 +428,7 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
   pass_fast();
   float ltot = lsum + __shfl_xor(lsum, 32, 64);
   if (__syncthreads_or(!(ltot <= 0x1p100f))) {          // overflow somewhere in the block: redo it safely
-    pass(std::true_type{});
+    pass_safe();
     ltot = lsum + __shfl_xor(lsum, 32, 64);
   }
   if (slot >= 0) {
@@ -840,7 +816,8 @@ __global__ __launch_bounds__(512) void k_attn_turns(const bf16_t* __restrict__ q
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const float m1 = t ? ml.y : ml.x, l1 = t ? ml.w : ml.z, m = fmaxf(mrun[t], m1);
-      const float a0 = __builtin_amdgcn_exp2f(mrun[t] - m), a1 = __builtin_amdgcn_exp2f(m1 - m);
+      const float ref = m == -INFINITY ? 0.f : m;          // a range of nothing but -inf: l and O stay 0
+      const float a0 = __builtin_amdgcn_exp2f(mrun[t] - ref), a1 = __builtin_amdgcn_exp2f(m1 - ref);
       mrun[t] = m;
       ltot[t] = ltot[t] * a0 + l1 * a1;
 #pragma unroll

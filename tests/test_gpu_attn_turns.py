@@ -74,3 +74,33 @@ def test_tiles_of_infinite_scores(monkeypatch, heads, hd, grid, text_len, at):
     p = softmax2(q[rows, sl] @ k[:, sl].T)
     assert rows.any() and (p[:, at] == 0).all()
     check("turns/infinite", got[rows, sl], p @ v[:, sl], "bf16")
+
+
+# heads, head_dim, token grid, text tokens, keys at -inf, head that has them: (queries of a block, key groups, key ranges of the last
+# round's blocks)
+RANGES = [((8, 128, (8, 15, 10), 1100, np.r_[0:576], 0), (128, 2, 2)),         # all keys of a range, in both key groups
+          ((16, 64, (8, 13, 40), 1024, np.r_[0:512], 15), (128, 1, 2)),        # the same in blocks of four wavefronts; a head of the last round
+          ((8, 128, (8, 15, 10), 512, np.r_[0:32, 448:480], 0), (128, 1, 1)),  # the keys that the one and the other pass start with
+          ((16, 64, (8, 15, 17), 600, np.r_[0:32, 576:600], 0), (256, 1, 1))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case,taken", RANGES)
+def test_ranges_of_infinite_scores(monkeypatch, case, taken):
+    """A whole key range of a cut work id whose scores are -inf weighs nothing, nor do such scores where both passes start (the fixed
+    reference fails there, and the online softmax has none yet).  Keys and queries as in the test above."""
+    heads, hd, grid, text_len, at, head = case
+    assert route(grid[0] * grid[1] * grid[2], text_len, heads, hd) == taken
+    c, j = head * hd + 5, 7
+    cfg, w, text, blocks = layer(monkeypatch, heads, hd, grid, text_len, 6)
+    lw = w["layers"][0]
+    lw["cwk"][:, c] = 0.0
+    lw["cwk"][j, c], lw["cbk"][c], lw["cgk"][c], lw["cgq"][c] = 1.0, 0.0, 2.0 ** 125, 1.0
+    text[:, j] = 0.0
+    text[at, j] = 32.0
+    q, k, v, got = operands(cfg, w, text, blocks)
+    assert np.isinf(k[at, c]).all() and np.isfinite(np.delete(k, at, 0)).all()
+    rows, sl = q[:, c] < 0, slice(head * hd, (head + 1) * hd)
+    p = softmax2(q[rows, sl] @ k[:, sl].T)
+    assert rows.any() and (p[:, at] == 0).all()
+    check("turns/infinite", got[rows, sl], p @ v[:, sl], "bf16")
