@@ -1141,7 +1141,10 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
                       int h, int d, bf16_t* out, int64_t ldo, float* scratch, const AttnQNorm* qnorm, hipStream_t st) {
   if (S <= 0 || L <= 0) return;
   const AttnQNorm qn = qnorm ? *qnorm : AttnQNorm{nullptr, 0, 0, 0.f, 0.f, 0.f};
-  const AttnRoute r = attn_bf16_route(S, L, h, d, scratch != nullptr);
+  AttnRoute r = attn_bf16_route(S, L, h, d, scratch != nullptr);
+  // The larger blocks reach a head's rows of V^T by 32-bit offsets from its first: signed, in elements, or unsigned, in bytes.  Key
+  // buffers too long for that (2^24 positions of 128 channels, whatever this call reads of them) take the kernel that has 64.
+  if ((int64_t)d * vt_row_stride > (int64_t)1 << 31) r = AttnRoute{32, 8, 1};
   // Heads of 64 spend more of a tile on exponentials than on products, so a turn of the one is longer than of the other; it takes
   // a full round of blocks and a few tiles to gain (us, k_attn_bf16 and k_attn_turns): 4096 x 1024 x 16 19.9 and 19.6, x 4096 66.5 and
   // 63.2, 5000 x 7000 x 40 353 and 329; 3000 x 2000 x 14 29.1 and 30.9, 3000 x 8000 x 16 104.4 and 105.5, 4096 x 512 x 16 12.6 and 13.1
