@@ -421,33 +421,37 @@ template void launch_v_transpose<float>(const float*, int64_t, int64_t, int, int
 template void launch_v_transpose<bf16_t>(const bf16_t*, int64_t, int64_t, int, int, const VTransposeJob<bf16_t>&, hipStream_t);
 
 // ---------------------------------------------------------------- strided row copy (feature-cache hand-over)
-// Rows are copied in 16-byte pieces when src, dst, strides and length allow it.
+// Rows are copied in 16-byte pieces when dst, its stride and the length allow it; those of a src that starts anywhere are loads that
+// claim an element's alignment (14400 x 5120 bf16 off a 16-byte boundary, the output head's tokens: 154 us by elements, 60 this way).
+template <typename T> struct Piece16 { T v[16 / sizeof(T)]; };
 template <typename T, typename V>
 __global__ void k_copy2d(const T* __restrict__ src, int64_t src_stride, T* __restrict__ dst,
                          int64_t dst_stride, int64_t len_v) {
+  typedef std::conditional_t<sizeof(V) == 16, uint4, V> W;
   const V* s = (const V*)(src + (int64_t)blockIdx.y * src_stride);
-  V* d = (V*)(dst + (int64_t)blockIdx.y * dst_stride);
+  W* d = (W*)(dst + (int64_t)blockIdx.y * dst_stride);
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < len_v; i += stride) d[i] = s[i];
+  for (; i < len_v; i += stride) d[i] = __builtin_bit_cast(W, s[i]);
 }
 template <typename T>
 void launch_copy2d(const T* src, int64_t src_stride, T* dst, int64_t dst_stride, int64_t rows,
                    int64_t len, hipStream_t st) {
   if (rows <= 0 || len <= 0) return;
-  const int per = 16 / (int)sizeof(T);
-  const bool vec = ((uintptr_t)src % 16 == 0) && ((uintptr_t)dst % 16 == 0) && (src_stride % per == 0) &&
-                   (dst_stride % per == 0) && (len % per == 0);
+  if (src_stride == len && dst_stride == len) { len *= rows; src_stride = dst_stride = len; rows = 1; }
+  const int per = 16 / (int)sizeof(T), most = rows == 1 ? 8192 : 64;         // blocks to a row
+  const bool vec = ((uintptr_t)dst % 16 == 0) && (dst_stride % per == 0) && (len % per == 0);
+  const bool src16 = ((uintptr_t)src % 16 == 0) && (src_stride % per == 0);
   // rows can exceed the grid.y limit only for absurd shapes; split defensively
   for (int64_t r0 = 0; r0 < rows; r0 += 32768) {
     const int64_t nr = rows - r0 < 32768 ? rows - r0 : 32768;
     if (vec) {
       const int64_t lv = len / per;
-      int gx = cdiv(lv, 256); if (gx > 64) gx = 64;
-      k_copy2d<T, uint4><<<dim3(gx, (unsigned)nr), 256, 0, st>>>(src + r0 * src_stride, src_stride,
-                                                                 dst + r0 * dst_stride, dst_stride, lv);
+      int gx = cdiv(lv, 256); if (gx > most) gx = most;
+      if (src16) k_copy2d<T, uint4><<<dim3(gx, (unsigned)nr), 256, 0, st>>>(src + r0 * src_stride, src_stride, dst + r0 * dst_stride, dst_stride, lv);
+      else k_copy2d<T, Piece16<T>><<<dim3(gx, (unsigned)nr), 256, 0, st>>>(src + r0 * src_stride, src_stride, dst + r0 * dst_stride, dst_stride, lv);
     } else {
-      int gx = cdiv(len, 256); if (gx > 64) gx = 64;
+      int gx = cdiv(len, 256); if (gx > most) gx = most;
       k_copy2d<T, T><<<dim3(gx, (unsigned)nr), 256, 0, st>>>(src + r0 * src_stride, src_stride,
                                                              dst + r0 * dst_stride, dst_stride, len);
     }

@@ -751,11 +751,12 @@ static void head_typed(dp_ends* s, const void* x_in, float t, float* v_out, int 
   // mod rows: shift, scale
   const GemvTable<T> table{(const T*)s->w.bt2, s->mhead, s->mod, 2};
   int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, c.freq_dim, (const T*)s->w.wt1, (int)D, s->e1, nullptr, nullptr, st);
-  const bool streamed = sizeof(T) == 2 && head_streamed(c) && ((uintptr_t)x_in & 15) == 0;
+  const bool streamed = sizeof(T) == 2 && head_streamed(c);
   parts = launch_gemv<T>(GemvIn{s->e1, parts, 0.f}, (const T*)s->w.bt1, (int)D, (const T*)s->w.wt2, (int)D, s->e, streamed ? nullptr : &table, nullptr, st);
   if constexpr (sizeof(T) == 2) {
     if (head_fused(c)) {
-      if (overlap(x_in, (size_t)(S * D) * 2, v_out, (size_t)n * 4)) {
+      // k_head_stream loads 16 bytes at once: tokens that start elsewhere are copied too, so that their bits do not depend on where they lie
+      if (overlap(x_in, (size_t)(S * D) * 2, v_out, (size_t)n * 4) || (streamed && ((uintptr_t)x_in & 15))) {
         launch_copy2d<bf16_t>((const bf16_t*)x_in, D, (bf16_t*)s->h, D, S, D, st);
         x_in = s->h;
       }

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from harness import check, to_dev, to_np
+from paper_2505_21070_amd import binding as B
 from test_gpu_ends_fused import setup
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +26,17 @@ def test_streamed_head(dim, channels, tok_h, tok_w, frames, far):
     check(f"{dim}/{channels}/{tok_w}/head", v, ref, "bf16")
     # one rounding to bf16 (of the modulated weights; 2^-9 at most, 1.66e-3 in the mean square) per product, no other
     assert np.linalg.norm(v - ref) / np.linalg.norm(ref) < 2.0 ** -9
+
+
+@pytest.mark.parametrize("channels,frames", [(16, 1), (32, 3)])
+def test_tokens_off_a_16_byte_boundary(channels, frames):
+    """One arithmetic serves every pointer: the same bits wherever the tokens start, from the handle and from the static call."""
+    cfg, _, g, _, _, tokens = setup(2112, channels, 5, 16, frames)
+    x = to_dev(tokens, cfg)
+    buf = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+    buf[1:] = x.reshape(-1)
+    ref = g.head(x, 437.0, frames)
+    assert torch.equal(g.head(buf[1:].view(x.shape), 437.0, frames), ref)
+    out = torch.full_like(ref, float("nan"))
+    B.head_forward_static(cfg, g._keep, channels, buf[1:].view(x.shape), 437.0, frames, out)
+    assert torch.equal(out, ref)
