@@ -355,10 +355,12 @@ __global__ __launch_bounds__(256) void k_head_fold(const float* __restrict__ e, 
     }
   }
 }
-// A block of 8 wavefronts owns TB = TG * RT * 16 tokens; wavefront w has RT * 16 of them and one of KH = 8 / TG shares of the
-// channels, dealt in slots of 32 (slot i * KH + w / TG in step i), and walks them in a ring of NS stages in LDS: its tokens'
-// values, in operand order, and a TG-th of the slot's weights, which the TG wavefronts of a share read; NS - 1 steps are in
-// flight, waited for by count.  (Into registers the compiler waits for all loads in flight at every branch.)  A step's
+// A block of 8 wavefronts owns TB = TG * RT * 16 tokens.  The channels are dealt in slots of 32 to eight shares (slot n to share
+// n % 8), and KH = 8 / TG wavefronts walk them for the same tokens: wavefront w has RT * 16 tokens and the shares w / TG + KH z, z <
+// TG (slot i * KH + w / TG in step i), in a ring of NS stages in LDS: its tokens' values, in operand order, and a TG-th of the
+// slot's weights, which TG wavefronts read; NS - 1 steps are in flight, waited for by count.  Every share has its own accumulators
+// and statistics, which are joined in one order (k and k + 4 first), so that a token's result does not depend on TG, and so not on how
+// many tokens the call has.  (Into registers the compiler waits for all loads in flight at every branch.)  A step's
 // operands are read from LDS while the step before is multiplied and added up.  Statistics: a lane sums its values' distances
 // from the mean of its first eight, and their squares, so what cancels in the variance is no larger than the token's own
 // spread; the lanes of a token meet in LDS by their own means.  blockIdx.y: 64 of the 4C output values.
@@ -370,12 +372,12 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
                                                  const uint4* __restrict__ wm, const float* __restrict__ pc,
                                                  const bf16_t* __restrict__ bias, int P4, float* __restrict__ v_out, int tok, int tw,
                                                  int C, int v_aligned) {
-  constexpr int KH = 8 / TG, TB = TG * RT * 16, P = NS - 1;        // shares of the channels, tokens, steps in flight
+  constexpr int KH = 8 / TG, TB = TG * RT * 16, P = NS - 1;        // wavefronts that share tokens, tokens, steps in flight
   constexpr int NW = 4 / TG, NL = NW + RT;             // weight fragments and loads per wavefront and step
-  constexpr int STAGE = (KH * 4 + 8 * RT) * 64;        // 16-byte chunks: the shares' weights, the wavefronts' tokens
-  static_assert(4 % TG == 0 && NS * STAGE * 16 >= KH * TB * 68 * 4, "the partial products fit the ring");
+  constexpr int STAGE = (KH * 4 + 8 * RT) * 64;        // 16-byte chunks: the slots' weights, the wavefronts' tokens
+  static_assert((TG == 1 || TG == 2) && NS * STAGE * 16 >= KH * TB * 68 * 4, "the partial products fit the ring");
   __shared__ __align__(16) uint4 ring[NS * STAGE];     // afterwards the partial products
-  __shared__ float2 stat[KH * 4][TB];             // [share, lane quarter][token]: mean, sum of squares about it
+  __shared__ float2 stat[8 * 4][TB];                   // [share, lane quarter][token]: mean, sum of squares about it
   __shared__ float cs[4][128], tm[TB], tr[TB];
   const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, lt = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), tg = wave % TG, kh = wave / TG;
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
     const int r = (tg * RT + t) * 16 + lt;
     xo[t] = (uint32_t)((r < rows ? r : rows - 1) * D + q * 8) * 2;
   }
-  uint4* const wst = ring + kh * 256;                  // of stage 0: this share's weights, this wavefront's tokens
+  uint4* const wst = ring + kh * 256;                  // of stage 0: this slot's weights, this wavefront's tokens
   uint4* const xst = ring + KH * 256 + wave * RT * 64;
   auto load = [&](int i, int st) __attribute__((always_inline)) {
     const int c = i * KH + kh < chunks ? i * KH + kh : chunks - 1;      // past the end the last one is loaded, and not used
@@ -401,14 +403,16 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
       __builtin_amdgcn_global_load_lds((glb_void_t*)((const char*)(xb + c * 32) + xo[t]), (lds_void_t*)(xst + st * STAGE + t * 64), 16, 0, 0);
   };
   const uint32_t wl = (uint32_t)(uintptr_t)(lds_void_t*)wst + (uint32_t)lane * 16, xl = (uint32_t)(uintptr_t)(lds_void_t*)xst + (uint32_t)lane * 16;
-  f32x4 acc[RT][4];
-  float sh[RT], sd[RT], sq[RT];
+  f32x4 acc[TG][RT][4];
+  float sh[TG][RT], sd[TG][RT], sq[TG][RT];
 #pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    sh[t] = sd[t] = sq[t] = 0.f;
+  for (int z = 0; z < TG; ++z)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
+    for (int t = 0; t < RT; ++t) {
+      sh[z][t] = sd[z][t] = sq[z][t] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[z][t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   u32x4 xr[2][RT], w[2][4];
   auto read = [&](int st, auto b_) __attribute__((always_inline)) {
     constexpr int b = decltype(b_)::value;
@@ -418,13 +422,13 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
   };
   auto elem = [&](const u32x4& v, int i) __attribute__((always_inline)) { return __uint_as_float((i & 1) ? (v[i >> 1] & 0xffff0000u) : (v[i >> 1] << 16)); };
   auto add = [&](int i, auto b_) __attribute__((always_inline)) {
-    constexpr int b = decltype(b_)::value;
-    if (i == 0) {
+    constexpr int b = decltype(b_)::value, z = b % TG;                // b: parity of i
+    if (i < TG) {
 #pragma unroll
       for (int t = 0; t < RT; ++t) {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) sh[t] += elem(xr[b][t], k);
-        sh[t] *= 0.125f;
+        for (int k = 0; k < 8; ++k) sh[z][t] += elem(xr[b][t], k);
+        sh[z][t] *= 0.125f;
       }
     }
     if (i * KH + kh >= chunks) return;
@@ -432,12 +436,12 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
     for (int t = 0; t < RT; ++t) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[b][j]), __builtin_bit_cast(bf16x8, xr[b][t]), acc[t][j], 0, 0, 0);
+        acc[z][t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[b][j]), __builtin_bit_cast(bf16x8, xr[b][t]), acc[z][t][j], 0, 0, 0);
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const float d = elem(xr[b][t], k) - sh[t];
-        sd[t] += d;
-        sq[t] += d * d;
+        const float d = elem(xr[b][t], k) - sh[z][t];
+        sd[z][t] += d;
+        sq[z][t] += d * d;
       }
     }
   };
@@ -465,18 +469,20 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
     });
   }
   // values of share k that a lane has had
-  auto share = [&](int k) __attribute__((always_inline)) { return (float)(8 * ((chunks - k + KH - 1) / KH)); };
+  auto share = [&](int k) __attribute__((always_inline)) { return (float)(8 * ((chunks - k + 7) / 8)); };
   tile_barrier();                                      // nothing is in flight, everyone is done with the ring
-  float (*const part)[TB][68] = (float (*)[TB][68])ring;           // [share][token][64 values, padded]
+  float (*const part)[TB][68] = (float (*)[TB][68])ring;           // [wavefront of the token][token][64 values, padded]
   {
-    const float cnt = share(kh);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      const float m = cnt > 0.f ? sd[t] / cnt : 0.f;
       const int tk = (tg * RT + t) * 16 + lt;
-      stat[kh * 4 + q][tk] = make_float2(sh[t] + m, sq[t] - sd[t] * m);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) *(f32x4*)&part[kh][tk][j * 16 + q * 4] = acc[t][j];
+      for (int z = 0; z < TG; ++z) {
+        const float m = sd[z][t] / share(z * KH + kh);
+        stat[(z * KH + kh) * 4 + q][tk] = make_float2(sh[z][t] + m, sq[z][t] - sd[z][t] * m);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *(f32x4*)&part[kh][tk][j * 16 + q * 4] = TG == 1 ? acc[0][t][j] : acc[0][t][j] + acc[TG - 1][t][j];
     }
     // this block's 64 columns of both sums over k: four shares of the channels
     float c = 0.f;
@@ -488,12 +494,12 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
   __syncthreads();
   if (tid < TB) {
     float m = 0.f, v = 0.f;
-    for (int k = 0; k < KH; ++k) {
+    for (int k = 0; k < 8; ++k) {
       const float cnt = share(k);
       for (int i = 0; i < 4; ++i) m += stat[k * 4 + i][tid].x * cnt;
     }
     m /= (float)D;
-    for (int k = 0; k < KH; ++k) {
+    for (int k = 0; k < 8; ++k) {
       const float cnt = share(k);
       for (int i = 0; i < 4; ++i) {
         const float2 a = stat[k * 4 + i][tid];
@@ -507,9 +513,12 @@ __global__ __launch_bounds__(512, 2) void k_head_stream(const bf16_t* __restrict
   for (int i = tid; i < TB * 16; i += 512) {           // four values of one token each
     const int tk = i >> 4, r = (i & 15) * 4, o0 = blockIdx.y * 64 + r;
     if (s0 + tk >= S) continue;
-    f32x4 v = *(const f32x4*)&part[0][tk][r];
+    auto pair = [&](int k) __attribute__((always_inline)) {
+      return TG == 1 ? *(const f32x4*)&part[k][tk][r] + *(const f32x4*)&part[KH - 4 + k][tk][r] : *(const f32x4*)&part[k][tk][r];
+    };
+    f32x4 v = pair(0);
 #pragma unroll
-    for (int k = 1; k < KH; ++k) v += *(const f32x4*)&part[k][tk][r];
+    for (int k = 1; k < 4; ++k) v += pair(k);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float c1 = cs[0][r + k] + cs[1][r + k] + cs[2][r + k] + cs[3][r + k];

@@ -40,3 +40,13 @@ def test_tokens_off_a_16_byte_boundary(channels, frames):
     out = torch.full_like(ref, float("nan"))
     B.head_forward_static(cfg, g._keep, channels, buf[1:].view(x.shape), 437.0, frames, out)
     assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("dim,channels,n", [(2112, 16, 8193), (2112, 32, 8193), (5120, 16, 8200)])
+def test_a_token_does_not_depend_on_the_others(dim, channels, n):
+    """A whole call and the same tokens fed in parts, at 64, 32 and 16 tokens a block: the same bits."""
+    cfg, _, g, _, _, tokens = setup(dim, channels, 1, 1, n)
+    x = to_dev(tokens, cfg)
+    whole = g.head(x, 437.0, n)
+    for first, count in ((0, 4097 if channels == 16 else 2049), (5, 1000), (n - 1, 1)):
+        assert torch.equal(g.head(x[first:first + count], 437.0, count), whole[first:first + count])
