@@ -18,12 +18,13 @@
 // block whose row sums end up beyond 2^100 (or non-finite) is recomputed by the safe pass, the classical
 // online softmax that raises m whenever a tile exceeds it and rescales O^T.
 //
-// Kernels (attn_bf16_route has the lines between them).  k_attn_turns: everything of some size, self- and cross-attention; a block of
-// eight wavefronts, the two of a SIMD taking turns at the matrix products and at the exponentials.  k_attn_bf16: few keys (blocks
-// of four wavefronts, two to a CU) and heads of 64 in less than a round of blocks; its wavefronts are served oldest first rather
-// than interleaved, so its fast pass pins its issue order so that one wavefront alone keeps the matrix pipe busy: exponentials
-// between MFMAs, operand fragments read from LDS several MFMAs ahead with exact waits (see pass_fast).  k_attn_few: what is small.
-// Tiles hold 64 keys (k_attn_few 32) and are loaded HBM -> LDS directly.
+// Kernels (attn_bf16_route and attn_bf16_turns have the lines between them).  k_attn_turns: many keys, self- and cross-attention; a
+// block of eight wavefronts, the two of a SIMD taking turns at the matrix products and at the exponentials.  k_attn_bf16: fewer keys,
+// and heads of 64 but for the largest; its wavefronts are served oldest first rather than interleaved, so its fast pass pins its
+// issue order so that one wavefront alone keeps the matrix pipe busy: exponentials between MFMAs, operand fragments read from LDS
+// several MFMAs ahead with exact waits (see pass_fast).  Both: 256 queries a block, or 128 with the keys split over two groups of four
+// wavefronts, which halves the length of a block; k_attn_bf16 also four wavefronts and 128 queries, two blocks to a CU.  k_attn_few:
+// what is small.  Tiles hold 64 keys (k_attn_few 32) and are loaded HBM -> LDS directly.
 //
 // Grid: one block of 8 wavefronts fits per compute unit, so a grid of them runs in rounds of 256 blocks (512 of 4 wavefronts).  The work ids that
 // would make up a last, partly filled round are instead cut into several key ranges each, one block per
@@ -97,8 +98,8 @@ __device__ __forceinline__ void request_queries(const bf16_t* __restrict__ qh, i
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int HD, int QG>
-__global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
+template <int HD, int QG, int KG>
+__global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __restrict__ q, int64_t q_head_stride,
                                                   const bf16_t* __restrict__ k, int64_t k_head_stride,
                                                   int64_t k_row0, const bf16_t* __restrict__ vt,
                                                   int64_t vt_row_stride, int64_t S, int64_t L,
@@ -110,13 +111,14 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
   constexpr int DT = HD / 32;                // 32-row tiles of O^T
   constexpr int KCH = 64 * CR;               // chunks in a K tile
   constexpr int VCH = HD * 8;                // chunks in a V^T tile
-  constexpr int NBUF = 2;                    // tile buffers (a third one was measured: no gain)
+  constexpr int NBUF = 2;                    // tile buffers per key group (a third one was measured: no gain)
+  constexpr int GCH = NBUF * (KCH + VCH);    // chunks per key group
   constexpr int CK = KCH / (QG * 64), CV = VCH / (QG * 64);   // load instructions per wavefront and tile
   constexpr int QB = QG * 32;                // queries per block
-  extern __shared__ uint4 smem[];            // NBUF K tiles, NBUF V^T tiles
+  extern __shared__ uint4 smem[];            // per key group: NBUF K tiles, NBUF V^T tiles
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int qt = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), qt = wave % QG, kg = wave / QG;
   const int lr = lane & 31, lg = lane >> 5;
   // Blocks are dealt round-robin over the 8 XCDs, each with its own L2: give every XCD a contiguous run
   // of (head, query block) work ids so that the blocks streaming one head's K/V share an L2.  The first
@@ -141,10 +143,13 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
   }
   const int head = wid / qblocks;
   const int64_t q0 = (int64_t)(wid % qblocks) * QB + qt * 32;
-  uint4* const kbuf = smem;
+  uint4* const kbuf = smem + kg * GCH;
   uint4* const vbuf = kbuf + NBUF * KCH;
 
-  const int cnt = t1 - t0;                   // key tiles
+  // this wavefront's key tiles: of two key groups the first has one more if they are odd
+  const int n0 = KG == 2 ? (t1 - t0 + 1) / 2 : t1 - t0;          // the trip count for everyone
+  const int cnt = kg ? t1 - t0 - n0 : n0;
+  t0 += kg ? n0 : 0;
 
   const bf16_t* kh = k + (int64_t)head * k_head_stride + (k_row0 + (int64_t)t0 * 64) * HD;
   const bf16_t* vh = vt + (int64_t)head * HD * vt_row_stride + k_row0 + (int64_t)t0 * 64;
@@ -178,13 +183,21 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
     for (int i = 0; i < CK + CV; ++i) load_part(tile, bufi, i);
   };
 
-  // the queries' row sums, the queries and the fast pass's first two tiles: one trip to memory
+  // The queries' row sums, the queries and the fast pass's first two tiles: one trip to memory.  Which goes first decides how the
+  // wavefronts of a SIMD stand to each other from then on, and that 2 to 4 % of the whole: 256 queries of heads of 128 want the
+  // tiles first (in a stage, queries first / tiles first in us: 3000 x 2000 x 14 60.2 / 58.2, 6240 x 6240 x 12 235 / 225), heads of
+  // 64 (4096 x 4096 x 16 76.3 / 78.8) and two key groups (1560 x 2500 x 12 46.1 / 47.0) the queries, four wavefronts either.
+  constexpr bool TILES_FIRST = HD == 128 && QG == 8;
   bf16x8 qf[KS];
   QuerySums qs;
+  auto request_tiles = [&]() __attribute__((always_inline)) {
+    if (cnt > 0) load_tile(cnt - 1, 0);
+    if (cnt > 1) load_tile(cnt - 2, 1);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (TILES_FIRST) request_tiles();
   request_queries<KS, HD>(q + (int64_t)head * q_head_stride, q0, lr, lg, S, qn, qs, qf);
-  if (cnt > 0) load_tile(cnt - 1, 0);
-  if (cnt > 1) load_tile(cnt - 2, 1);
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!TILES_FIRST) request_tiles();
   if (qn.ssq) scale_queries(qf, qs.factor<32>(qn, lg));
 
   f32x16 oacc[DT], negm;
@@ -204,7 +217,8 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
 
     if (cnt > 0) load_tile(0, 0);
     tile_barrier();
-    for (int kt = 0; kt < cnt; ++kt) {
+    for (int kt = 0; kt < n0; ++kt) {
+      if (KG == 2 && kt >= cnt) { tile_barrier(); continue; }    // this key group is a tile shorter: it only keeps step
       // next tile into the other buffer (read last before the previous barrier); the tile past the
       // end is the last one again and never used
       load_tile(kt + NBUF - 1 < cnt ? kt + NBUF - 1 : cnt - 1, (kt + NBUF - 1) % NBUF);
@@ -286,8 +300,8 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
   // This lane's row of a K tile (row lr of a 32-key half) and of a V^T tile (row lr of a 32-channel group) in
   // buffer 0, as LDS byte addresses; chunk c of the row sits at byte (c * 16) ^ swizzle, and c = ks*2 + lg or
   // (a*2+u)*2 + lg has lg as its lowest bit, so the lane-dependent part of the XOR is one constant per tile kind.
-  const uint32_t krow = lds0 + (uint32_t)(lr * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(lr)) * 16;
-  const uint32_t vrow = lds0 + (uint32_t)(NBUF * KCH + lr * 8) * 16, vx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
+  const uint32_t krow = lds0 + (uint32_t)(kg * GCH + lr * CR) * 16, kx = (uint32_t)(lg ^ kswz<CR>(lr)) * 16;
+  const uint32_t vrow = lds0 + (uint32_t)(kg * GCH + NBUF * KCH + lr * 8) * 16, vx = (uint32_t)(lg ^ ((lr >> 1) & 7)) * 16;
   // operand fragment of MFMA i of a tile whose K / V^T buffers start kbo / vbo bytes behind buffer 0
   auto frag_read = [&](auto i_, uint32_t kbo, uint32_t vbo) __attribute__((always_inline)) {
     constexpr int i = decltype(i_)::value;
@@ -380,7 +394,8 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
       pw[a][pidx] = cvt_pk_bf16(__builtin_amdgcn_exp2f(sacc[a][2 * pidx]), __builtin_amdgcn_exp2f(sacc[a][2 * pidx + 1]));
       lsum = add_pk_bf16(pw[a][pidx], lsum);
     };
-    for (int j = 1; j < cnt; ++j) {
+    for (int j = 1; j < n0; ++j) {
+      if (KG == 2 && j >= cnt) { tile_barrier(); continue; }
       const uint32_t kbo = (uint32_t)(j % NBUF) * KCH * 16, vbo = (uint32_t)(j % NBUF) * VCH * 16;
       const uint32_t kbn = (uint32_t)((j + 1) % NBUF) * KCH * 16, vbn = (uint32_t)((j + 1) % NBUF) * VCH * 16;
       static_for<NMF>([&](auto i_) __attribute__((always_inline)) {
@@ -431,6 +446,28 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
     pass_safe();
     ltot = lsum + __shfl_xor(lsum, 32, 64);
   }
+  if constexpr (KG == 2) {
+    // the two key groups meet in LDS: group 1 publishes m, l, O^T, and group 0 goes on with both
+    float* const xch = (float*)smem + (size_t)qt * (DT * 16 + 2) * 64 + lane;    // [qt][DT * 16 + 2][64 lanes]
+    if (kg == 1) {
+      xch[0] = mrun; xch[64] = ltot;
+#pragma unroll
+      for (int a = 0; a < DT; ++a)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) xch[(2 + a * 16 + r) * 64] = oacc[a][r];
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const float m1 = xch[0], l1 = xch[64], m = fmaxf(mrun, m1);
+    const float ref = m == -INFINITY ? 0.f : m;          // a range of nothing but -inf: l and O stay 0
+    const float a0 = __builtin_amdgcn_exp2f(mrun - ref), a1 = __builtin_amdgcn_exp2f(m1 - ref);
+    mrun = m;
+    ltot = ltot * a0 + l1 * a1;
+#pragma unroll
+    for (int a = 0; a < DT; ++a)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[a][r] = oacc[a][r] * a0 + xch[(2 + a * 16 + r) * 64] * a1;
+  }
   if (slot >= 0) {
     // one key range of a split work id: publish m, l and the unnormalised O^T for the merge kernel.
     // Slot layout (floats): m[QB], l[QB], then O as [HD/4][QB queries][4 channels].
@@ -452,7 +489,8 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
     // over the banks.
     const float inv = 1.f / ltot;
     constexpr int UPR = HD / 4, CPR = HD / 8, RPI = 64 / CPR;      // units, 16-byte chunks per row; rows per read
-    uint2* stg = (uint2*)smem + qt * 32 * UPR;
+    constexpr int STG0 = KG == 2 ? QG * (DT * 16 + 2) * 64 / 4 : 0;    // behind the exchange area
+    uint2* stg = (uint2*)(smem + STG0) + qt * 32 * UPR;
 #pragma unroll
     for (int a = 0; a < DT; ++a)
 #pragma unroll
@@ -486,7 +524,8 @@ __global__ __launch_bounds__(QG * 64, 2) void k_attn_bf16(const bf16_t* __restri
 // What bounds it: matrix pipes under the power limit.  Against a pinned order in which each wavefront mixed its own
 // exponentials between its MFMAs (32x32x16; us): 14400 x 21600 x 40 of 128 4978 -> 4487 (1.42 PFLOP/s), 6240 x 9360 x 12 305 -> 278,
 // 7800 x 7800 x 12 314 -> 287, 18720 x 24960 x 12 2250 -> 2026, 4096 x 1024 x 16 34.5 -> 32.7; heads of 64 6000 x 9000 x 16 210 -> 202,
-// 5000 x 7000 x 40 353 -> 329; two key groups 1560 x 3120 x 12 43.6 -> 40.8, 3000 x 4000 x 8 55.9 -> 50.6, 3000 x 1000 x 10 21.6 -> 21.1.
+// 5000 x 7000 x 40 353 -> 329; two key groups 1560 x 3120 x 12 43.6 -> 40.8, 3000 x 4000 x 8 55.9 -> 50.6.  Back to back and alone, that is: in
+// a stage and with few keys it is the other way round (attn_bf16_turns).  <128, 2> spills 8 registers outside its loop.
 // Tried: loads behind the exponentials (2 % slower), without s_setprio (0.4 %).
 template <int HD, int KG>
 __global__ __launch_bounds__(512) void k_attn_turns(const bf16_t* __restrict__ q, int64_t q_head_stride,
@@ -1097,21 +1136,42 @@ static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratc
   }
   return r;
 }
+// Whether blocks of eight wavefronts are k_attn_turns or k_attn_bf16.  Turns gain a few per cent of every tile and cost 1 to 3 us at a
+// block's ends (the first tile in plain order, the halves half a turn apart, twice the tiles requested before the first product), so
+// they take many tiles, and many blocks, whose ends overlap others' tiles only where there is more than a round.  Both inside a
+// stage, on one card, k_attn_bf16 / k_attn_turns in us, queries x keys x heads:
+//   heads of 128, 256 queries, less than a round of blocks: 2048 x 520 x 16 25.3 / 26.9, 1304 x 2000 x 24 57.7 / 59.0, 2560 x 3000 x 20 84.9 / 88.4,
+//     x 5000 136.4 / 134.1, 2048 x 4000 x 16 76.4 / 76.6, x 6000 103.0 / 100.8; at least one: 4096 x 1100 x 16 46.3 / 46.7, x 2000 69.4 / 69.2,
+//     x 2500 84.1 / 83.2, x 4500 137.8 / 134.4, 9000 x 1500 x 12 97.1 / 97.7, x 3000 169.4 / 167.3, x 9000 465 / 459, 6240 x 9360 x 12 327 / 321
+//   heads of 128, two key groups: 1560 x 520 x 12 20.3 / 23.0, x 1000 25.9 / 27.8, x 2200 41.0 / 41.6, x 2500 45.3 / 44.9, x 4500 70.1 / 67.5; 3000
+//     x 1500 x 10 35.5 / 35.9, x 2000 42.6 / 42.2, x 3000 57.0 / 55.2; in two key ranges 2000 x 2500 x 8 38.4 / 38.8, x 3500 45.3 / 45.1,
+//     1304 x 3000 x 8 37.6 / 38.2, x 4500 47.3 / 47.1; in four 1000 x 2800 x 8 31.6 / 32.2
+//   heads of 64, which spend more of a tile on exponentials than on products, so that a turn of the one is longer than of the other: 2040 x
+//     2040 x 32 43.4 / 44.3, 4096 x 9000 x 16 156 / 157, 6240 x 6240 x 12 137 / 140, 9000 x 13000 x 8 257 / 253; two rounds and more 5000 x 1500 x
+//     40 112 / 113, x 2500 165 / 163, 8000 x 8000 x 64 1042 / 1020; two key groups 2000 x 1500 x 12 22.2 / 23.1, 3000 x 9000 x 10 82.0 / 85.3
+static bool attn_bf16_turns(const AttnRoute& r, int64_t S, int64_t L, int h, int d) {
+  const int64_t tiles = (L + 63) / 64, blocks = (S + r.qb - 1) / r.qb * h;
+  if (d == 64) return r.qb == 256 && blocks >= 256 && tiles >= (blocks >= 512 ? 40 : 200);
+  if (r.qb == 256) return tiles >= (blocks >= 256 ? 36 : 80);
+  return r.kg == 2 && tiles >= (r.parts > 1 ? 32 * r.parts : blocks >= 192 ? 32 : 38);
+}
 // for the tests, which state the kernel that each of their shapes is meant to reach
 extern "C" void dp_attn_bf16_route(int64_t S, int64_t L, int32_t h, int32_t d, int32_t* queries_groups_ranges) {
   const AttnRoute r = attn_bf16_route(S, L, h, d, true);
   const int32_t v[3] = {r.qb, r.kg, r.parts};
   for (int i = 0; i < 3; ++i) queries_groups_ranges[i] = v[i];
 }
+extern "C" int dp_attn_bf16_turns(int64_t S, int64_t L, int32_t h, int32_t d) {
+  return attn_bf16_turns(attn_bf16_route(S, L, h, d, true), S, L, h, d);
+}
 
-// KG == 0: k_attn_bf16 with blocks of QB queries; else k_attn_turns
-template <int HD, int QB, int KG>
+template <int HD, int QB, int KG, bool TURNS>
 static void launch_attn_cfg(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, int64_t k_head_stride,
                             int64_t k_row0, const bf16_t* vt, int64_t vt_row_stride, int64_t S, int64_t L,
                             int h, bf16_t* out, int64_t ldo, float* scratch, int parts, const AttnQNorm& qn, hipStream_t st) {
-  constexpr int tile = (64 * (HD / 8) + HD * 8) * 16, lds = (KG ? 4 : 2) * tile, threads = KG ? 512 : QB * 2;
+  constexpr int tile = (64 * (HD / 8) + HD * 8) * 16, lds = (TURNS ? 4 : 2 * KG) * tile, threads = QB * KG * 2;
   void (*const kernel)(const bf16_t*, int64_t, const bf16_t*, int64_t, int64_t, const bf16_t*, int64_t, int64_t, int64_t, bf16_t*, int64_t, int, int, int, int, float*, AttnQNorm) = [] {
-    if constexpr (KG) return &k_attn_turns<HD, KG>; else return &k_attn_bf16<HD, QB / 32>;
+    if constexpr (TURNS) return &k_attn_turns<HD, KG>; else return &k_attn_bf16<HD, QB / 32, KG>;
   }();
   const int qblocks = (int)((S + QB - 1) / QB);
   const int W = qblocks * h, n_tail = W % attn_slots(QB, KG), n_full = W - n_tail;
@@ -1145,17 +1205,15 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
   // The larger blocks reach a head's rows of V^T by 32-bit offsets from its first: signed, in elements, or unsigned, in bytes.  Key
   // buffers too long for that (2^24 positions of 128 channels, whatever this call reads of them) take the kernel that has 64.
   if ((int64_t)d * vt_row_stride > (int64_t)1 << 31) r = AttnRoute{32, 8, 1};
-  // Heads of 64 spend more of a tile on exponentials than on products, so a turn of the one is longer than of the other; it takes
-  // a full round of blocks and a few tiles to gain (us, k_attn_bf16 and k_attn_turns): 4096 x 1024 x 16 19.9 and 19.6, x 4096 66.5 and
-  // 63.2, 5000 x 7000 x 40 353 and 329; 3000 x 2000 x 14 29.1 and 30.9, 3000 x 8000 x 16 104.4 and 105.5, 4096 x 512 x 16 12.6 and 13.1
-  const bool turns = L >= 1024 && (S + 255) / 256 * h >= 256;
+  const bool turns = attn_bf16_turns(r, S, L, h, d);
 #define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo
 #define ATTN_CASE(HD) do { \
     if (r.qb == 32) launch_attn_few<HD>(ATTN_ARGS, qn, st); \
-    else if (r.qb == 256 && (HD == 128 || turns)) launch_attn_cfg<HD, 256, 1>(ATTN_ARGS, scratch, r.parts, qn, st); \
-    else if (r.qb == 256) launch_attn_cfg<64, 256, 0>(ATTN_ARGS, scratch, r.parts, qn, st); \
-    else if (r.kg == 1) launch_attn_cfg<HD, 128, 0>(ATTN_ARGS, scratch, r.parts, qn, st); \
-    else launch_attn_cfg<HD, 128, 2>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.qb == 256 && turns) launch_attn_cfg<HD, 256, 1, true>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.qb == 256) launch_attn_cfg<HD, 256, 1, false>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.kg == 1) launch_attn_cfg<HD, 128, 1, false>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (HD == 128 && turns) launch_attn_cfg<128, 128, 2, true>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else launch_attn_cfg<HD, 128, 2, false>(ATTN_ARGS, scratch, r.parts, qn, st); \
   } while (0)
   if (d == 128) ATTN_CASE(128); else ATTN_CASE(64);
 #undef ATTN_CASE

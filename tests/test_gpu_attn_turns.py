@@ -1,11 +1,14 @@
-"""The bf16 attention kernel whose wavefronts take turns, at the edges of its tiles: cross-attention against a float64 softmax over the
+"""The bf16 attention kernel whose wavefronts take turns (many keys) and the one with a pinned order (fewer), in blocks of eight
+wavefronts at the edges of their tiles: cross-attention against a float64 softmax over the
 very q, K, V that the kernel read, with one and with two key groups, whole and with key ranges that are merged; last tiles of one
 key, one short of a tile and a whole one; queries that fill no block; overflow of the fixed reference; tiles of -inf scores."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
 from harness import check
-from paper_2505_21070_amd import synth
+from paper_2505_21070_amd import binding, synth
 from test_gpu_attn_shapes import route
 from test_gpu_stage import T_CUR, gpu_stage, to_dev, to_np
 
@@ -15,6 +18,16 @@ CASES.update({(16, 128, (8, 15, 17), n): (256, 1, 2) for n in (1025, 1088)})    
 CASES.update({(32, 64, (8, 15, 17), n): (256, 1, 1) for n in (1025, 1087, 1088)})  # 256 blocks
 CASES.update({(8, 128, (8, 15, 10), n): (128, 2, 1) for n in (513, 576, 639, 640)})         # 1200 queries: 5 + 4 and 5 + 5 tiles
 CASES.update({(16, 64, (8, 13, 10), n): (128, 2, 1) for n in (1025, 1151, 1152)})  # 1040 queries: 9 + 8, 9 + 9
+# with enough keys for turns
+TURNS = {(32, 128, (8, 15, 17), n): (256, 1, 1) for n in (2241, 2304)}             # 2040 queries: 256 blocks, 36 tiles
+TURNS.update({(16, 128, (8, 15, 17), n): (256, 1, 2) for n in (5057, 5119, 5184)}) # 128 blocks: 80 and 81 tiles, 40 and 41 in a range
+TURNS.update({(13, 128, (8, 15, 10), n): (128, 2, 1) for n in (2369, 2432, 2495, 2496)})    # 1200 queries: 19 + 19 and 20 + 19 tiles
+TURNS.update({(10, 128, (8, 163, 1), n): (128, 2, 2) for n in (4033, 4160)})       # 1304 queries: 64 and 65 tiles, 16 + 16 and 17 + 16 in a range
+TURNS.update({(64, 64, (8, 15, 17), n): (256, 1, 1) for n in (2497,)})             # 512 blocks, 40 tiles
+CASES.update(TURNS)
+
+_turns = binding._lib.dp_attn_bf16_turns
+_turns.argtypes, _turns.restype = [C.c_int64] * 2 + [C.c_int32] * 2, C.c_int
 
 
 def layer(monkeypatch, heads, hd, grid, text_len, seed):
@@ -37,7 +50,9 @@ def softmax2(s2):
 
 @pytest.mark.parametrize("heads,hd,grid,text_len", CASES)
 def test_shapes_take_this_kernel(heads, hd, grid, text_len):
-    assert route(grid[0] * grid[1] * grid[2], text_len, heads, hd) == CASES[heads, hd, grid, text_len]
+    S = grid[0] * grid[1] * grid[2]
+    assert route(S, text_len, heads, hd) == CASES[heads, hd, grid, text_len]
+    assert bool(_turns(S, text_len, heads, hd)) == ((heads, hd, grid, text_len) in TURNS)
 
 
 @pytest.mark.gpu
@@ -81,7 +96,11 @@ def test_tiles_of_infinite_scores(monkeypatch, heads, hd, grid, text_len, at):
 RANGES = [((8, 128, (8, 15, 10), 1100, np.r_[0:576], 0), (128, 2, 2)),         # all keys of a range, in both key groups
           ((16, 64, (8, 13, 40), 1024, np.r_[0:512], 15), (128, 1, 2)),        # the same in blocks of four wavefronts; a head of the last round
           ((8, 128, (8, 15, 10), 512, np.r_[0:32, 448:480], 0), (128, 1, 1)),  # the keys that the one and the other pass start with
-          ((16, 64, (8, 15, 17), 600, np.r_[0:32, 576:600], 0), (256, 1, 1))]
+          ((16, 64, (8, 15, 17), 600, np.r_[0:32, 576:600], 0), (256, 1, 1)),
+          ((8, 128, (8, 15, 10), 640, np.r_[0:32, 288:352, 608:640], 0), (128, 2, 1)),
+          ((16, 128, (8, 15, 17), 5184, np.r_[0:2560], 0), (256, 1, 2)),       # in turns: a whole range,
+          ((10, 128, (8, 163, 1), 4096, np.r_[0:2048], 0), (128, 2, 2)),       # both groups of one,
+          ((13, 128, (8, 15, 10), 2496, np.r_[0:32, 1248:1312, 2432:2464], 0), (128, 2, 1))]     # where each group and pass starts
 
 
 @pytest.mark.gpu
