@@ -9,7 +9,7 @@
 // chunks over all banks.
 //
 // 16-bit outputs are staged through LDS so that global memory is written in whole rows, 16 bytes per lane; the fp32 residual
-// update takes 64 bytes of a row per four lanes as the accumulators lie.  EPI_HEADS stores per attention head (q | k | v
+// update too in tiles of 128 and 160 rows, in the taller ones it takes 64 bytes of a row per four lanes as the accumulators lie.  EPI_HEADS stores per attention head (q | k | v
 // sections: channel gains, 3D rotation, transposed V, row sums of squares for a deferred RMSNorm).
 #include "kernels.h"
 
@@ -849,12 +849,20 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
   // Rows and columns beyond the matrix lie beyond the buffer: they read as zeros and are not written.
   constexpr bool FP32 = EPI == EPI_RESID || EPI == EPI_PART;
   constexpr int XP = 2 * PH;
-  u32x4 xv[XP][TN];
+  // Tiles of 128 and 160 rows by 256 columns, which run in about one round of blocks, all update the residual stream at the same time:
+  // theirs goes through LDS, GI accumulator rows of both block halves a step, so that memory sees whole rows, and the first step's
+  // residual rows are requested ahead of the last multiplication (in a stage, as it lies / staged in us: 3648 x 1600 x 1600 36.7 / 34.3,
+  // 1760 x 2560 x 2560 50.3 / 47.7, 1400 x 3968 x 3968 66.5 / 63.8, 1560 x 3072 x 3072 51.9 / 49.2; 160 rows
+  // 16704 x 256 x 256 20.0 / 17.0, 4288 x 1216 x 5824 97.3 / 91.5).  The taller ones spread over rounds and update it as it lies.
+  constexpr bool STAGED = FP32 && TN == 4 && TM <= 5;
+  constexpr int NG = 2 * TM * 16 * BN * 4 <= G::LDS ? 1 : 2, GI = (TM + NG - 1) / NG, NX = GI * 4;   // steps, rows in a step, reads of a row per wavefront
+  static_assert(!STAGED || (BN == 256 && 2 * GI * 16 * BN * 4 <= G::LDS), "a step fits, a read is a row");
+  u32x4 xv[STAGED ? NG : XP][STAGED ? NX : TN];
   float* const px = FP32 ? e.resid + ((int64_t)part * M + m0) * e.ldr + n0 : nullptr;
   const int64_t left_x = ((M - m0) * e.ldr - n0) * 4;
   const uint32_t nx = (uint32_t)(left_x < 0x7fffffff ? left_x : 0x7fffffff), xrow = (uint32_t)e.ldr * 64;
   uint32_t vx[TN];
-  if constexpr (FP32) {
+  if constexpr (FP32 && !STAGED) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int n = wn * WN + j * 16 + lg * 4;
@@ -864,6 +872,23 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
   auto resid_load = [&](int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) xv[i % XP][j] = buffer_load16(px, nx, vx[j] + i * xrow);
+  };
+  // STAGED, read t of step g: row of the step, row of the tile; a lane's four columns lie XOR-swizzled with the former
+  auto step_row = [&](int g, int t, int& row) __attribute__((always_inline)) {
+    const int gi = TM - g * GI < GI ? TM - g * GI : GI, r = t * 8 + wave;
+    row = r / (gi * 16) * WM + g * GI * 16 + r % (gi * 16);
+    return r;
+  };
+  auto step_at = [&](int g, int t, int64_t ld, int size, uint32_t& at) __attribute__((always_inline)) {   // byte of that place in a matrix
+    int row;
+    const int r = step_row(g, t, row), col = (lane ^ (r & 15)) * 4;
+    at = n0 + col < N ? (uint32_t)(row * ld + col) * size : 0x7fffffffu;
+  };
+  auto step_reads = [](int g) constexpr { return (TM - g * GI < GI ? TM - g * GI : GI) * 4; };
+  auto step_load = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NX; ++t)
+      if (t < step_reads(g)) { uint32_t at; step_at(g, t, e.ldr, 4, at); xv[g][t] = buffer_load16(px, nx, at); }
   };
 
   // A wavefront's queue of loads: in slab s's turn A(s + DA), B(s + DB), and before slab 0's the turns -D .. -1 with what exists
@@ -904,6 +929,7 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
           // them, and those reads were waited for before the last barrier.
           if constexpr (R >= DA) load_a(s + DA, ca == 0 ? SA - 1 : ca - 1);
           if constexpr (R >= DB) load_b(s + DB, cb == 0 ? SB - 1 : cb - 1);
+          if constexpr (EPI == EPI_RESID && STAGED && R == 0) step_load(0);
         }
         // what was requested behind A(s + 1) and behind B(s + 1); the first half reads the second one's share of B(s + 1) right
         // after this turn of the second half's, so that is waited for before the multiplication, the rest behind it
@@ -932,7 +958,7 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
             for (int j = 0; j < TN; ++j)
               acc[i][j] = EXCH ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[k][i], bfr[k][j], acc[i][j], 0, 0, 0)
                                : __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[k][j], af[k][i], acc[i][j], 0, 0, 0);
-          if constexpr (EPI == EPI_RESID && R == 0 && PH == 2 && k == 0) {
+          if constexpr (EPI == EPI_RESID && !STAGED && R == 0 && PH == 2 && k == 0) {
             __builtin_amdgcn_sched_barrier(0);
             resid_load(0); resid_load(1);
             __builtin_amdgcn_sched_barrier(0);
@@ -966,7 +992,53 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
   }
   if (wm == 0) __builtin_amdgcn_s_barrier();             // the halves meet again
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (EPI == EPI_PART) {
+  if constexpr (STAGED) {
+    const bf16_t* bias = (const bf16_t*)e.bias;
+    float4* const l16 = (float4*)smem;
+    bf16_t* const po = (bf16_t*)e.out + m0 * e.ldo + n0;
+    const int64_t left_o = ((M - m0) * e.ldo - n0) * 2;
+    const uint32_t no = (uint32_t)(left_o < 0x7fffffff ? left_o : 0x7fffffff);
+    static_for<NG>([&](auto g_) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_)::value, gi = TM - g * GI < GI ? TM - g * GI : GI;
+      if constexpr (EPI == EPI_RESID && g > 0) step_load(g);
+      __syncthreads();                                   // the operand slabs / the previous step are done with
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int nl = wn * WN + j * 16 + lg * 4;
+        float b[4] = {0.f, 0.f, 0.f, 0.f};
+        float4 gv = make_float4(1.f, 1.f, 1.f, 1.f);
+        if (EPI == EPI_RESID && n0 + nl < N) {
+          if (bias) {
+            const uint2 b4 = *(const uint2*)(bias + n0 + nl);
+            b[0] = bf16_to_f32((bf16_t)(b4.x & 0xffff)); b[1] = bf16_to_f32((bf16_t)(b4.x >> 16));
+            b[2] = bf16_to_f32((bf16_t)(b4.y & 0xffff)); b[3] = bf16_to_f32((bf16_t)(b4.y >> 16));
+          }
+          if (e.gate) gv = *(const float4*)(e.gate + n0 + nl);
+        }
+#pragma unroll
+        for (int i = 0; i < gi; ++i) {
+          const f32x4 a = acc[g * GI + i][j];
+          const int r = (wm * gi + i) * 16 + lr;
+          l16[r * 64 + ((nl >> 2) ^ (r & 15))] = make_float4(gv.x * (a[0] + b[0]), gv.y * (a[1] + b[1]), gv.z * (a[2] + b[2]), gv.w * (a[3] + b[3]));
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < gi * 4; ++t) {
+        int row;
+        const float4 v = l16[step_row(g, t, row) * 64 + lane];
+        f32x4 x = {v.x, v.y, v.z, v.w};
+        uint32_t at;
+        if constexpr (EPI == EPI_RESID) x += __builtin_bit_cast(f32x4, xv[g][t]);
+        step_at(g, t, e.ldr, 4, at);
+        buffer_store16(__builtin_bit_cast(u32x4, x), px, nx, at);
+        if (EPI == EPI_RESID && e.out) {
+          step_at(g, t, e.ldo, 2, at);
+          buffer_store8(u32x2{cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3])}, po, no, at);
+        }
+      }
+    });
+  } else if constexpr (EPI == EPI_PART) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -997,6 +1069,7 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
     const uint32_t no = (uint32_t)(left_o < 0x7fffffff ? left_o : 0x7fffffff);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      u32x2 r[TN];
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const f32x4 a = acc[i][j];
@@ -1004,10 +1077,18 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
         x[0] += gv[j].x * (a[0] + bv[j][0]); x[1] += gv[j].y * (a[1] + bv[j][1]);
         x[2] += gv[j].z * (a[2] + bv[j][2]); x[3] += gv[j].w * (a[3] + bv[j][3]);
         buffer_store16(__builtin_bit_cast(u32x4, x), px, nx, vx[j] + i * xrow);
-        if (e.out) {
-          const int n = wn * WN + j * 16 + lg * 4;
+        r[j] = u32x2{cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3])};
+      }
+      if (e.out) {
+#pragma unroll
+        for (int j = 0; j < TN; j += 2) {
+          // two column tiles at once: lanes of even lg take eight columns of the first, of odd lg of the second, so that four
+          // lanes write 64 bytes of a row and not 32
+          const auto lo = __builtin_amdgcn_permlane16_swap(r[j].x, r[j + 1].x, false, false);
+          const auto hi = __builtin_amdgcn_permlane16_swap(r[j].y, r[j + 1].y, false, false);
+          const int n = wn * WN + (j + (lg & 1)) * 16 + (lg >> 1) * 8;
           const uint32_t o = n0 + n < N ? (uint32_t)((wm * WM + i * 16 + lr) * e.ldo + n) * 2 : 0x7fffffffu;
-          buffer_store8(u32x2{cvt_pk_bf16(x[0], x[1]), cvt_pk_bf16(x[2], x[3])}, po, no, o);
+          buffer_store16(u32x4{lo[0], hi[0], lo[1], hi[1]}, po, no, o);
         }
       }
       if (i + XP < TM) resid_load(i + XP);
