@@ -60,7 +60,8 @@ template <int OFF> __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) {
 
 // Deferred RMSNorm of the queries: a row's sum of squares arrives as qn.np partial sums; lanes of parity 0 and 1 add up the even and
 // the odd ones, in order.  The first PS of a lane are requested before anything else, so that they and what is requested behind
-// them are one trip to memory and none waits for what comes later; a wider model's are read when they are added up.
+// them are one trip to memory and none waits for what comes later; more of them (wide models on 64-column tiles) are read PS at a
+// time when they are added up (480 queries x 75 keys x 28 heads of 128, 56 partial sums, in a stage: one at a time 15.9 us, 13.0 this way).
 struct QuerySums {
   static constexpr int PS = 12;
   float v[PS];
@@ -76,7 +77,13 @@ struct QuerySums {
     float sum = 0.f;
 #pragma unroll
     for (int u = 0; u < PS; ++u) sum += parity + 2 * u < qn.np ? v[u] : 0.f;
-    for (int i = parity + 2 * PS; i < qn.np; i += 2) sum += p[i * qn.stride];
+    for (int i0 = parity + 2 * PS; i0 < qn.np; i0 += 2 * PS) {
+      float w[PS];
+#pragma unroll
+      for (int u = 0; u < PS; ++u) w[u] = p[(i0 + 2 * u < qn.np ? i0 + 2 * u : 0) * qn.stride];
+#pragma unroll
+      for (int u = 0; u < PS; ++u) sum += i0 + 2 * u < qn.np ? w[u] : 0.f;
+    }
     sum += __shfl_xor(sum, O, 64);
     return rsqrtf(sum * qn.inv_dim + qn.eps) * qn.scale;
   }
