@@ -639,7 +639,7 @@ __global__ __launch_bounds__(1024, SINUS ? 4 : 8) void k_gemv(GemvArgs<T> a, Rop
       for (int l = 0; l < a.L; ++l) a.mod[(int64_t)l * a.N + n0 + tid] = a.mtab[(int64_t)l * a.N + n0 + tid] + y;
   }
 }
-// The first two products of a chain in one launch, for 256 features and up to 2048 channels: a block makes the piece of the
+// The first two products of a chain in one launch, for 256 features and less than 2048 channels: a block makes the piece of the
 // first product that its slice of the second one reads (at most 256 columns; all blocks of a slice make it, from L2), while the
 // second one's weights are on their way.  Sums in the order of the two launches, so with their bits.
 // What bounds it: latency, four trips to memory instead of six and a launch less; the whole chain of a stage at 256 channels 14.8 ->
@@ -766,8 +766,10 @@ int launch_gemv(const GemvIn& in, const T* xbias, int K, const T* W, int N, floa
 template <typename T>
 int launch_gemv_pair(float t, const T* W1, const T* b1, int freq, const T* W2, int D, float* mid, float* y, const RopeTokens* rope, hipStream_t st) {
   // by the two launches where the features are other than 256, or so many channels that each block's share of the first product
-  // is more than a latency (the first product's four slices, whose order is kept, are those of up to 5440 columns)
-  if (freq != 256 || D > 2048) {
+  // is more than a latency (the first product's four slices, whose order is kept, are those of up to 5440 columns).  The whole chain
+  // in a stage, one launch / two in us: 1536 channels 21.8 / 22.9 (640 tokens), 26.2 / 26.6 (8000), 1984 27.6 / 28.0, 33.4 / 34.1, 2048 28.1 /
+  // 27.1, 34.9 / 34.3
+  if (freq != 256 || D >= 2048) {
     const int parts = launch_gemv<T>(GemvIn{nullptr, 0, t}, (const T*)nullptr, freq, W1, D, mid, nullptr, rope, st);
     return launch_gemv<T>(GemvIn{mid, parts, 0.f}, b1, D, W2, D, y, nullptr, nullptr, st);
   }
