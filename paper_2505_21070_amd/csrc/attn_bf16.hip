@@ -19,8 +19,8 @@
 // online softmax that raises m whenever a tile exceeds it and rescales O^T.
 //
 // Kernels (attn_bf16_route and attn_bf16_turns have the lines between them).  k_attn_turns: many keys, self- and cross-attention; a
-// block of eight wavefronts, the two of a SIMD taking turns at the matrix products and at the exponentials.  k_attn_bf16: fewer keys,
-// and heads of 64 but for the largest; its wavefronts are served oldest first rather than interleaved, so its fast pass pins its
+// block of eight wavefronts, the two of a SIMD taking turns at the matrix products and at the exponentials (heads of 128).  k_attn_bf16: fewer keys,
+// and heads of 64; its wavefronts are served oldest first rather than interleaved, so its fast pass pins its
 // issue order so that one wavefront alone keeps the matrix pipe busy: exponentials between MFMAs, operand fragments read from LDS
 // several MFMAs ahead with exact waits (see pass_fast).  Both: 256 queries a block, or 128 with the keys split over two groups of four
 // wavefronts, which halves the length of a block; k_attn_bf16 also four wavefronts and 128 queries, two blocks to a CU.  k_attn_few:
@@ -191,10 +191,10 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
   };
 
   // The queries' row sums, the queries and the fast pass's first two tiles: one trip to memory.  Which goes first decides how the
-  // wavefronts of a SIMD stand to each other from then on, and that 2 to 4 % of the whole: 256 queries of heads of 128 want the
-  // tiles first (in a stage, queries first / tiles first in us: 3000 x 2000 x 14 60.2 / 58.2, 6240 x 6240 x 12 235 / 225), heads of
-  // 64 (4096 x 4096 x 16 76.3 / 78.8) and two key groups (1560 x 2500 x 12 46.1 / 47.0) the queries, four wavefronts either.
-  constexpr bool TILES_FIRST = HD == 128 && QG == 8;
+  // wavefronts of a SIMD stand to each other from then on, and that some per cent of the whole: eight wavefronts on the same tiles
+  // want the tiles first (in a stage, queries first / tiles first in us: of 128 3000 x 2000 x 14 60.2 / 58.2, 6240 x 6240 x 12 235 / 225; of 64
+  // 3648 x 3648 x 38 159 / 154), two key groups the queries (1560 x 2500 x 12 of 128 46.1 / 47.0), four wavefronts either.
+  constexpr bool TILES_FIRST = QG == 8;
   bf16x8 qf[KS];
   QuerySums qs;
   auto request_tiles = [&]() __attribute__((always_inline)) {
@@ -402,7 +402,9 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
       lsum = add_pk_bf16(pw[a][pidx], lsum);
     };
     for (int j = 1; j < n0; ++j) {
-      if (KG == 2 && j >= cnt) { tile_barrier(); continue; }
+      // a key group that is a tile shorter only keeps step.  With one group that is never so, but heads of 64 run 2 % faster with the
+      // branch, by which the compiler lays out the loop, and heads of 128 2 % slower.
+      if ((KG == 2 || (HD == 64 && QG == 8)) && j >= cnt) { tile_barrier(); continue; }
       const uint32_t kbo = (uint32_t)(j % NBUF) * KCH * 16, vbo = (uint32_t)(j % NBUF) * VCH * 16;
       const uint32_t kbn = (uint32_t)((j + 1) % NBUF) * KCH * 16, vbn = (uint32_t)((j + 1) % NBUF) * VCH * 16;
       static_for<NMF>([&](auto i_) __attribute__((always_inline)) {
@@ -530,8 +532,7 @@ __global__ __launch_bounds__(QG * KG * 64, 2) void k_attn_bf16(const bf16_t* __r
 // wavefront or the other all the time; the exponentials have no MFMA to wait for and nothing is interleaved by hand.
 // What bounds it: matrix pipes under the power limit.  Against a pinned order in which each wavefront mixed its own
 // exponentials between its MFMAs (32x32x16; us): 14400 x 21600 x 40 of 128 4978 -> 4487 (1.42 PFLOP/s), 6240 x 9360 x 12 305 -> 278,
-// 7800 x 7800 x 12 314 -> 287, 18720 x 24960 x 12 2250 -> 2026, 4096 x 1024 x 16 34.5 -> 32.7; heads of 64 6000 x 9000 x 16 210 -> 202,
-// 5000 x 7000 x 40 353 -> 329; two key groups 1560 x 3120 x 12 43.6 -> 40.8, 3000 x 4000 x 8 55.9 -> 50.6.  Back to back and alone, that is: in
+// 7800 x 7800 x 12 314 -> 287, 18720 x 24960 x 12 2250 -> 2026; two key groups 1560 x 3120 x 12 43.6 -> 40.8, 3000 x 4000 x 8 55.9 -> 50.6.  Back to back and alone, that is: in
 // a stage and with few keys it is the other way round (attn_bf16_turns).  <128, 2> spills 8 registers outside its loop.
 // Tried: loads behind the exponentials (2 % slower), without s_setprio (0.4 %).
 template <int HD, int KG>
@@ -1146,19 +1147,19 @@ static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratc
 // Whether blocks of eight wavefronts are k_attn_turns or k_attn_bf16.  Turns gain a few per cent of every tile and cost 1 to 3 us at a
 // block's ends (the first tile in plain order, the halves half a turn apart, twice the tiles requested before the first product), so
 // they take many tiles, and many blocks, whose ends overlap others' tiles only where there is more than a round.  Both inside a
-// stage, on one card, k_attn_bf16 / k_attn_turns in us, queries x keys x heads:
-//   heads of 128, 256 queries, less than a round of blocks: 2048 x 520 x 16 25.3 / 26.9, 1304 x 2000 x 24 57.7 / 59.0, 2560 x 3000 x 20 84.9 / 88.4,
+// stage, on one card, k_attn_bf16 / k_attn_turns in us, queries x keys x heads of 128:
+//   256 queries, less than a round of blocks: 2048 x 520 x 16 25.3 / 26.9, 1304 x 2000 x 24 57.7 / 59.0, 2560 x 3000 x 20 84.9 / 88.4,
 //     x 5000 136.4 / 134.1, 2048 x 4000 x 16 76.4 / 76.6, x 6000 103.0 / 100.8; at least one: 4096 x 1100 x 16 46.3 / 46.7, x 2000 69.4 / 69.2,
 //     x 2500 84.1 / 83.2, x 4500 137.8 / 134.4, 9000 x 1500 x 12 97.1 / 97.7, x 3000 169.4 / 167.3, x 9000 465 / 459, 6240 x 9360 x 12 327 / 321
-//   heads of 128, two key groups: 1560 x 520 x 12 20.3 / 23.0, x 1000 25.9 / 27.8, x 2200 41.0 / 41.6, x 2500 45.3 / 44.9, x 4500 70.1 / 67.5; 3000
+//   two key groups: 1560 x 520 x 12 20.3 / 23.0, x 1000 25.9 / 27.8, x 2200 41.0 / 41.6, x 2500 45.3 / 44.9, x 4500 70.1 / 67.5; 3000
 //     x 1500 x 10 35.5 / 35.9, x 2000 42.6 / 42.2, x 3000 57.0 / 55.2; in two key ranges 2000 x 2500 x 8 38.4 / 38.8, x 3500 45.3 / 45.1,
 //     1304 x 3000 x 8 37.6 / 38.2, x 4500 47.3 / 47.1; in four 1000 x 2800 x 8 31.6 / 32.2
-//   heads of 64, which spend more of a tile on exponentials than on products, so that a turn of the one is longer than of the other: 2040 x
-//     2040 x 32 43.4 / 44.3, 4096 x 9000 x 16 156 / 157, 6240 x 6240 x 12 137 / 140, 9000 x 13000 x 8 257 / 253; two rounds and more 5000 x 1500 x
-//     40 112 / 113, x 2500 165 / 163, 8000 x 8000 x 64 1042 / 1020; two key groups 2000 x 1500 x 12 22.2 / 23.1, 3000 x 9000 x 10 82.0 / 85.3
+// Heads of 64 spend more of a tile on exponentials than on products, so a turn of the one is longer than of the other, and nothing is
+// gained at any size: 2040 x 2040 x 32 43.4 / 44.3, 4096 x 9000 x 16 155 / 159, 14400 x 14400 x 16 889 / 910, 8000 x 20000 x 64 2514 / 2563; two key
+// groups 2000 x 1500 x 12 22.2 / 23.1, 3000 x 9000 x 10 82.0 / 85.3.
 static bool attn_bf16_turns(const AttnRoute& r, int64_t S, int64_t L, int h, int d) {
   const int64_t tiles = (L + 63) / 64, blocks = (S + r.qb - 1) / r.qb * h;
-  if (d == 64) return r.qb == 256 && blocks >= 256 && tiles >= (blocks >= 512 ? 40 : 200);
+  if (d == 64) return false;
   if (r.qb == 256) return tiles >= (blocks >= 256 ? 36 : 80);
   return r.kg == 2 && tiles >= (r.parts > 1 ? 32 * r.parts : blocks >= 192 ? 32 : 38);
 }
@@ -1216,7 +1217,7 @@ void launch_attn_bf16(const bf16_t* q, int64_t q_head_stride, const bf16_t* k, i
 #define ATTN_ARGS q, q_head_stride, k, k_head_stride, k_row0, vt, vt_row_stride, S, L, h, out, ldo
 #define ATTN_CASE(HD) do { \
     if (r.qb == 32) launch_attn_few<HD>(ATTN_ARGS, qn, st); \
-    else if (r.qb == 256 && turns) launch_attn_cfg<HD, 256, 1, true>(ATTN_ARGS, scratch, r.parts, qn, st); \
+    else if (r.qb == 256 && HD == 128 && turns) launch_attn_cfg<128, 256, 1, true>(ATTN_ARGS, scratch, r.parts, qn, st); \
     else if (r.qb == 256) launch_attn_cfg<HD, 256, 1, false>(ATTN_ARGS, scratch, r.parts, qn, st); \
     else if (r.kg == 1) launch_attn_cfg<HD, 128, 1, false>(ATTN_ARGS, scratch, r.parts, qn, st); \
     else if (HD == 128 && turns) launch_attn_cfg<128, 128, 2, true>(ATTN_ARGS, scratch, r.parts, qn, st); \

@@ -1,4 +1,4 @@
-"""The bf16 attention kernel whose wavefronts take turns (many keys) and the one with a pinned order (fewer), in blocks of eight
+"""The bf16 attention kernel whose wavefronts take turns (many keys, heads of 128) and the one with a pinned order, in blocks of eight
 wavefronts at the edges of their tiles: cross-attention against a float64 softmax over the
 very q, K, V that the kernel read, with one and with two key groups, whole and with key ranges that are merged; last tiles of one
 key, one short of a tile and a whole one; queries that fill no block; overflow of the fixed reference; tiles of -inf scores."""
@@ -23,7 +23,6 @@ TURNS = {(32, 128, (8, 15, 17), n): (256, 1, 1) for n in (2241, 2304)}          
 TURNS.update({(16, 128, (8, 15, 17), n): (256, 1, 2) for n in (5057, 5119, 5184)}) # 128 blocks: 80 and 81 tiles, 40 and 41 in a range
 TURNS.update({(13, 128, (8, 15, 10), n): (128, 2, 1) for n in (2369, 2432, 2495, 2496)})    # 1200 queries: 19 + 19 and 20 + 19 tiles
 TURNS.update({(10, 128, (8, 163, 1), n): (128, 2, 2) for n in (4033, 4160)})       # 1304 queries: 64 and 65 tiles, 16 + 16 and 17 + 16 in a range
-TURNS.update({(64, 64, (8, 15, 17), n): (256, 1, 1) for n in (2497,)})             # 512 blocks, 40 tiles
 CASES.update(TURNS)
 
 _turns = binding._lib.dp_attn_bf16_turns
