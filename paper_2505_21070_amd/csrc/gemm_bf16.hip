@@ -849,14 +849,15 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
   // Rows and columns beyond the matrix lie beyond the buffer: they read as zeros and are not written.
   constexpr bool FP32 = EPI == EPI_RESID || EPI == EPI_PART;
   constexpr int XP = 2 * PH;
-  // Tiles of 128 and 160 rows by 256 columns, which run in about one round of blocks, all update the residual stream at the same time:
+  // Tiles of 128 and 160 rows, which run in about one round of blocks, all update the residual stream at the same time:
   // theirs goes through LDS, GI accumulator rows of both block halves a step, so that memory sees whole rows, and the first step's
   // residual rows are requested ahead of the last multiplication (in a stage, as it lies / staged in us: 3648 x 1600 x 1600 36.7 / 34.3,
   // 1760 x 2560 x 2560 50.3 / 47.7, 1400 x 3968 x 3968 66.5 / 63.8, 1560 x 3072 x 3072 51.9 / 49.2; 160 rows
-  // 16704 x 256 x 256 20.0 / 17.0, 4288 x 1216 x 5824 97.3 / 91.5).  The taller ones spread over rounds and update it as it lies.
-  constexpr bool STAGED = FP32 && TN == 4 && TM <= 5;
-  constexpr int NG = 2 * TM * 16 * BN * 4 <= G::LDS ? 1 : 2, GI = (TM + NG - 1) / NG, NX = GI * 4;   // steps, rows in a step, reads of a row per wavefront
-  static_assert(!STAGED || (BN == 256 && 2 * GI * 16 * BN * 4 <= G::LDS), "a step fits, a read is a row");
+  // 16704 x 256 x 256 20.0 / 17.0, 4288 x 1216 x 5824 97.3 / 91.5; 128 x 128 13568 x 256 x 256 13.4 / 12.5).  The taller ones spread over rounds and update it as it lies.
+  constexpr bool STAGED = FP32 && TM <= 5;
+  constexpr int CPF = BN / 4, RPW = 64 / CPF;            // 16-byte chunks of a row, rows of a wavefront's read
+  constexpr int NG = 2 * TM * 16 * BN * 4 <= G::LDS ? 1 : 2, GI = (TM + NG - 1) / NG, NX = GI * 4 / RPW;   // steps, rows in a step, reads per wavefront
+  static_assert(!STAGED || 2 * GI * 16 * BN * 4 <= G::LDS, "a step fits");
   u32x4 xv[STAGED ? NG : XP][STAGED ? NX : TN];
   float* const px = FP32 ? e.resid + ((int64_t)part * M + m0) * e.ldr + n0 : nullptr;
   const int64_t left_x = ((M - m0) * e.ldr - n0) * 4;
@@ -875,16 +876,16 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
   };
   // STAGED, read t of step g: row of the step, row of the tile; a lane's four columns lie XOR-swizzled with the former
   auto step_row = [&](int g, int t, int& row) __attribute__((always_inline)) {
-    const int gi = TM - g * GI < GI ? TM - g * GI : GI, r = t * 8 + wave;
+    const int gi = TM - g * GI < GI ? TM - g * GI : GI, r = (t * 8 + wave) * RPW + lane / CPF;
     row = r / (gi * 16) * WM + g * GI * 16 + r % (gi * 16);
     return r;
   };
   auto step_at = [&](int g, int t, int64_t ld, int size, uint32_t& at) __attribute__((always_inline)) {   // byte of that place in a matrix
     int row;
-    const int r = step_row(g, t, row), col = (lane ^ (r & 15)) * 4;
+    const int r = step_row(g, t, row), col = ((lane % CPF) ^ (r & 15)) * 4;
     at = n0 + col < N ? (uint32_t)(row * ld + col) * size : 0x7fffffffu;
   };
-  auto step_reads = [](int g) constexpr { return (TM - g * GI < GI ? TM - g * GI : GI) * 4; };
+  auto step_reads = [](int g) constexpr { return (TM - g * GI < GI ? TM - g * GI : GI) * 4 / RPW; };
   auto step_load = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < NX; ++t)
@@ -1019,14 +1020,14 @@ __global__ __launch_bounds__(512) void k_gemm_turns(const bf16_t* __restrict__ A
         for (int i = 0; i < gi; ++i) {
           const f32x4 a = acc[g * GI + i][j];
           const int r = (wm * gi + i) * 16 + lr;
-          l16[r * 64 + ((nl >> 2) ^ (r & 15))] = make_float4(gv.x * (a[0] + b[0]), gv.y * (a[1] + b[1]), gv.z * (a[2] + b[2]), gv.w * (a[3] + b[3]));
+          l16[r * CPF + ((nl >> 2) ^ (r & 15))] = make_float4(gv.x * (a[0] + b[0]), gv.y * (a[1] + b[1]), gv.z * (a[2] + b[2]), gv.w * (a[3] + b[3]));
         }
       }
       __syncthreads();
 #pragma unroll
-      for (int t = 0; t < gi * 4; ++t) {
+      for (int t = 0; t < step_reads(g); ++t) {
         int row;
-        const float4 v = l16[step_row(g, t, row) * 64 + lane];
+        const float4 v = l16[step_row(g, t, row) * CPF + lane % CPF];
         f32x4 x = {v.x, v.y, v.z, v.w};
         uint32_t at;
         if constexpr (EPI == EPI_RESID) x += __builtin_bit_cast(f32x4, xv[g][t]);
