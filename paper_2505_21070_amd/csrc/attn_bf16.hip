@@ -69,8 +69,15 @@ struct QuerySums {
   __device__ __forceinline__ void request(const AttnQNorm& qn, int64_t row, int64_t S, int parity) {
     p = qn.ssq + (row < S ? row : S - 1);
     if (!qn.ssq) return;
+    static_for<3>([&](auto g_) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_)::value * 4;
 #pragma unroll
-    for (int u = 0; u < PS; ++u) v[u] = p[(parity + 2 * u < qn.np ? parity + 2 * u : 0) * qn.stride];
+      for (int u = g; u < g + 4; ++u) v[u] = 0.f;
+      if (2 * g < qn.np) {                               // no loads that few sums do not need: every wavefront of a block makes them
+#pragma unroll
+        for (int u = g; u < g + 4; ++u) v[u] = p[(parity + 2 * u < qn.np ? parity + 2 * u : 0) * qn.stride];
+      }
+    });
   }
   // the factor of the row; O: distance to a lane of the other parity
   template <int O> __device__ __forceinline__ float factor(const AttnQNorm& qn, int parity) const {
@@ -1149,7 +1156,8 @@ static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratc
 // they take many tiles, and many blocks, whose ends overlap others' tiles only where there is more than a round.  Both inside a
 // stage, on one card, k_attn_bf16 / k_attn_turns in us, queries x keys x heads of 128:
 //   256 queries, less than a round of blocks: 2048 x 520 x 16 25.3 / 26.9, 1304 x 2000 x 24 57.7 / 59.0, 2560 x 3000 x 20 84.9 / 88.4,
-//     x 5000 136.4 / 134.1, 2048 x 4000 x 16 76.4 / 76.6, x 6000 103.0 / 100.8; at least one: 4096 x 1100 x 16 46.3 / 46.7, x 2000 69.4 / 69.2,
+//     x 5000 136.4 / 134.1, 2048 x 4000 x 16 (in two key ranges) 76.4 / 76.6, x 6000 103.0 / 100.8, but 3000 x 7600 x 14 183.0 / 184.7, 5504 x
+//     8256 x 6 184 / 189: on a chip that is far from full the pinned order has clock to spare; at least one round: 4096 x 1100 x 16 46.3 / 46.7, x 2000 69.4 / 69.2,
 //     x 2500 84.1 / 83.2, x 4500 137.8 / 134.4, 9000 x 1500 x 12 97.1 / 97.7, x 3000 169.4 / 167.3, x 9000 465 / 459, 6240 x 9360 x 12 327 / 321
 //   two key groups: 1560 x 520 x 12 20.3 / 23.0, x 1000 25.9 / 27.8, x 2200 41.0 / 41.6, x 2500 45.3 / 44.9, x 4500 70.1 / 67.5; 3000
 //     x 1500 x 10 35.5 / 35.9, x 2000 42.6 / 42.2, x 3000 57.0 / 55.2; in two key ranges 2000 x 2500 x 8 38.4 / 38.8, x 3500 45.3 / 45.1,
@@ -1160,7 +1168,7 @@ static AttnRoute attn_bf16_route(int64_t S, int64_t L, int h, int d, bool scratc
 static bool attn_bf16_turns(const AttnRoute& r, int64_t S, int64_t L, int h, int d) {
   const int64_t tiles = (L + 63) / 64, blocks = (S + r.qb - 1) / r.qb * h;
   if (d == 64) return false;
-  if (r.qb == 256) return tiles >= (blocks >= 256 ? 36 : 80);
+  if (r.qb == 256) return blocks >= 256 ? tiles >= 36 : blocks * r.parts >= 192 && tiles >= 80;
   return r.kg == 2 && tiles >= (r.parts > 1 ? 32 * r.parts : blocks >= 192 ? 32 : 38);
 }
 // for the tests, which state the kernel that each of their shapes is meant to reach
