@@ -50,3 +50,42 @@ def test_a_token_does_not_depend_on_the_others(dim, channels, n):
     whole = g.head(x, 437.0, n)
     for first, count in ((0, 4097 if channels == 16 else 2049), (5, 1000), (n - 1, 1)):
         assert torch.equal(g.head(x[first:first + count], 437.0, count), whole[first:first + count])
+
+
+@pytest.mark.parametrize("channels", [16, 32])
+def test_static_call_gives_the_handle_s_bits(channels):
+    """The static array holds the modulated weights behind the packed ones and their sums in the first product's place: a large call,
+    a smaller one and the large one again, each as the handle has it."""
+    cfg, _, g, _, _, tokens = setup(2112, channels, 1, 1, 4100)
+    x = to_dev(tokens, cfg)
+    for n, t in ((4100, 437.0), (33, 812.0), (4100, 437.0)):
+        ref = g.head(x[:n], t, n)
+        out = torch.full_like(ref, float("nan"))
+        B.head_forward_static(cfg, g._keep, channels, x[:n], t, n, out)
+        assert torch.equal(out, ref)
+
+
+@pytest.mark.parametrize("channels", [16, 32])
+def test_streamed_output_may_overlap_the_tokens(channels):
+    """An output that shares memory with the tokens, at more blocks than are resident at once: the values of one that does not."""
+    n, dim = 16384, 2112
+    cfg, _, g, _, _, tokens = setup(dim, channels, 1, 1, n)
+    x = to_dev(tokens, cfg)
+    want = g.head(x, 437.0, n)
+    size, out_size = x.numel() * 2, want.numel() * 4
+    for off in (-(out_size // 2), 0, size // 2):             # bytes of the output against the tokens
+        buf = torch.zeros(size + 2 * out_size, dtype=torch.uint8, device="cuda")
+        src = buf[out_size:out_size + size].view(torch.bfloat16).view(x.shape)
+        src.copy_(x)
+        out = buf[out_size + off:2 * out_size + off].view(torch.float32).view(want.shape)
+        B._check(B._lib.dp_head_forward(g._h, src.data_ptr(), 437.0, out.data_ptr(), n, torch.cuda.current_stream().cuda_stream), "overlap")
+        assert torch.equal(out, want), off
+
+
+@pytest.mark.parametrize("dim,channels,n", [(3136, 64, 5), (3136, 64, 4099), (5120, 48, 17), (5120, 48, 4097)])
+def test_wide_heads_of_more_channels(dim, channels, n):
+    """More than 32 latent channels stay with the kernel that holds a token in registers: eight and ten groups of channels a
+    wavefront, 16 and 32 tokens a block."""
+    cfg, _, g, o, _, tokens = setup(dim, channels, 1, 1, n)
+    check(f"{dim}/{channels}/{n}/head", to_np(g.head(to_dev(tokens, cfg), 437.0, n)).reshape(-1, channels),
+          o.head(tokens.numpy().astype(np.float64), 437.0, n).reshape(-1, channels), "bf16")
