@@ -18,7 +18,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // One key tile's scores s (S^T, masked) of a lane's query against the running maximum m and this lane's share l of the sum:
-// s becomes the probabilities, o is rescaled where some query's maximum rose (the first tile: alpha = 0).
+// s becomes the probabilities, o is rescaled where some query's maximum rose (the first tile: alpha = 0).  Scores of -inf weigh 0 also
+// where a query has had no others yet (m still -inf).
 template <int GN>
 __device__ __forceinline__ void softmax_tile(f32x16& s, f32x16 (&o)[GN], float& m, float& l) {
   float mx = s[0];
@@ -27,7 +28,7 @@ __device__ __forceinline__ void softmax_tile(f32x16& s, f32x16 (&o)[GN], float& 
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const float mnew = fmaxf(m, mx);
   if (__any(mnew > m)) {
-    const float alpha = expf(m - mnew);
+    const float alpha = expf(m - (mnew == -INFINITY ? 0.f : mnew));
     l *= alpha;
 #pragma unroll
     for (int a = 0; a < GN; ++a)
@@ -35,9 +36,10 @@ __device__ __forceinline__ void softmax_tile(f32x16& s, f32x16 (&o)[GN], float& 
       for (int r = 0; r < 16; ++r) o[a][r] *= alpha;
     m = mnew;
   }
+  const float ref = m == -INFINITY ? 0.f : m;
   float ps = 0.f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { s[r] = expf(s[r] - m); ps += s[r]; }
+  for (int r = 0; r < 16; ++r) { s[r] = expf(s[r] - ref); ps += s[r]; }
   l += ps;
 }
 // scores of keys outside [lo, hi) of the tile
