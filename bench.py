@@ -28,8 +28,8 @@ PEAK_HBM_GBS = 8000.0         # HBM3E, published
 # it was measured on: `src` names the source file and `sha` the first 16 hex digits of its SHA-256 at the time of
 # the profile.  With any other source (or no entry) the bench prints null instead of a stale figure.
 MEASURED_TRAFFIC = {
-    ("wan14b_stage", "self_attn"): {"bytes": 1.5597e+09, "src": "attn_bf16.hip", "sha": "50a7136db63aa49d"},
-    ("wan1p3b_stage", "self_attn"): {"bytes": 2.2939e+08, "src": "attn_bf16.hip", "sha": "50a7136db63aa49d"},
+    ("wan14b_stage", "self_attn"): {"bytes": 1.5597e+09, "src": "attn_bf16.hip", "sha": "127015ddf1d18d56"},
+    ("wan1p3b_stage", "self_attn"): {"bytes": 2.2941e+08, "src": "attn_bf16.hip", "sha": "127015ddf1d18d56"},
 }
 
 

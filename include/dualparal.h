@@ -267,7 +267,7 @@ int dp_noise_gather(const void* pool, int32_t pool_frames, int64_t frame_bytes, 
  * [n_frames*tok_h*tok_w, dim] in the configured storage type.  Like a stage, the handle owns no device
  * memory: the caller provides the workspace (dp_ends_workspace_bytes, 256-byte aligned) and keeps the
  * weights alive.  Calls are asynchronous on hip_stream.  x_out may share memory with latent and v_out with x_in,
- * in any position; an overlapping call may cost a copy of its input.  DP_BF16 needs dim % 64 == 0 and
+ * in any position; an overlapping call, or bf16 tokens off a 16-byte boundary, may cost a copy of the input.  DP_BF16 needs dim % 64 == 0 and
  * 4 * channels % 64 == 0.
  * Errors: DP_EINVAL (null pointer, sizes outside the configured limits, NaN timestep), DP_ENOMEM
  * (workspace too small), DP_EHIP.

@@ -69,7 +69,7 @@ struct QuerySums {
   __device__ __forceinline__ void request(const AttnQNorm& qn, int64_t row, int64_t S, int parity) {
     p = qn.ssq + (row < S ? row : S - 1);
     if (!qn.ssq) return;
-    static_for<3>([&](auto g_) __attribute__((always_inline)) {
+    static_for<PS / 4>([&](auto g_) __attribute__((always_inline)) {
       constexpr int g = decltype(g_)::value * 4;
 #pragma unroll
       for (int u = g; u < g + 4; ++u) v[u] = 0.f;

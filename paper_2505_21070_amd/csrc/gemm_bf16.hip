@@ -1196,8 +1196,8 @@ size_t gemm_bf16_scratch_bytes(int64_t M, int64_t N) {
 // launches and a block's ends, partials at 6.5 TB/s; uncut 0.185 per k-tile and 3.3 (32 x 64), 0.24 per k-tile and 64 x 64 block
 // on the CU and 5, 9 (128 x 128) or 14 for launch and ends.  Cut / best uncut in us: 500 x 1536 x 8960 27.9 (128 x 128, 5 ranges) / 43, 1560 x 1536 x 8960 52 (160 x 256,
 // 4) / 75, 1008 x 2048 x 8192 42 (128 x 256, 4) / 64, 2560 x 2048 x 8192 82 (160 x 256, 2) / 92; left uncut 1288 x 5120 x 13824 164.  Outputs narrower than 768 columns
-// are left on the 64-, 160- and 256-row tiles and on the figures of an earlier measurement (a k-tile 1.25 at 160
-// rows, 8 for ends and 3 for the second launch, 4 TB/s).  That line is no property of the tiles: the 128-row ones have not been
+// are left on the 64-, 160- and 256-row tiles and on figures that were measured before the
+// loop in turns (a k-tile 1.25 at 160 rows, 8 for ends and 3 for the second launch, 4 TB/s) and not again.  That line is no property of the tiles: the 128-row ones have not been
 // measured below it, and the parity tests of the cut 160- and 256-row tiles are shapes of that side.
 static GemmRoute big_tile(int64_t M, int64_t N, int epi);
 static GemmRoute cut_tile(int64_t M, int64_t N, int64_t K, size_t scratch_floats) {
